@@ -1,15 +1,45 @@
 // fp32 windowed attention forward: the accuracy path (1e-5 against the fp64 oracle).
-// One 64-lane wave per (batch, head, query patch).  Lane (n, g4) = query column n of
-// the patch, head-dim slice [16*g4, 16*g4+16).  It walks the same per-patch steps
-// and lane masks as the bf16 MFMA kernel, reading K and V rows straight from global
-// memory, with a scalar online softmax (Section 2 of the paper: softmax over the
-// kept keys only).
+// Section 2 of the paper: softmax over the kept keys only.  fp32 operands, products, sums and
+// exponentials throughout.
+//
+// One workgroup = four waves = one query patch of one (batch, head); wave w takes the patch's
+// 32-key steps w, w + 4, ... (the plan's steps and lane masks, as the bf16 kernels walk them) and
+// the four partial results are merged through LDS at the end.  The products run on
+// v_mfma_f32_16x16x4_f32, straight from global memory: nothing of K or V is shared between the
+// waves of a workgroup, and the operand order can be chosen so that every load is a 16-byte piece
+// of a row and no value has to move between lanes:
+//   S^T = K Q^T   contraction slice (j, e) of the head dimension is {16 j + 4 g4 + e : g4 = 0..3},
+//                 so lane (n, g4) = (lane % 16, lane / 16) loads floats 16 j + 4 g4 .. + 3 of row n
+//                 (four lanes cover 64 contiguous bytes); it receives the scores of query n
+//                 with the four keys 4 g4 + i of a tile;
+//   O^T += V^T P^T  contraction slice i is the keys {4 g4 + i}: the B operand is the lane's own
+//                 probability, and row n of dimension tile dt is dimension 4 n + dt, so one
+//                 16-byte load of V's row feeds all four tiles (sixteen lanes cover a row).
+//
+// Bound: a step is 64 MFMAs of 32 cycles (2048 cycles of a SIMD's matrix pipe) against 16 KB of
+// gathered rows; four waves per patch, because the accuracy workloads have few patches (57 per
+// (batch, head) at 680 tokens) and the longest one would otherwise be a chain of eleven steps.
+// 680 tokens, 32 (batch, head) pairs, radius 2: 30 us a call (one wave per patch with scalar dot
+// products and a shuffle per key: 233 us); the matrix pipe's share is 8 us, the rest is the chain
+// descriptor -> tokens -> rows -> MFMAs of two rounds of workgroups.
 #include "attn_bf16_common.h"
 
 namespace lv {
 
-__global__ __launch_bounds__(64) void k_attn_f32(AttnArgs a, int n_waves) {
-  const int wv = blockIdx.x % n_waves, bh = blockIdx.x / n_waves;
+namespace {
+
+constexpr int kF32Waves = 4;            // waves per patch
+constexpr float kF32Floor = -3.402823466e+38f;   // softmax reference of a query without a kept key so far
+
+}  // namespace
+
+__global__ __launch_bounds__(kF32Waves * 64) void k_attn_f32(AttnArgs a, int n_waves) {
+  __shared__ __align__(16) f32x4 part_o[kF32Waves][4][64];
+  __shared__ float part_m[kF32Waves][16], part_l[kF32Waves][16];
+  // workgroup i runs on XCD i % 8: all patches of one (batch, head) share one L2
+  const int seq = blockIdx.x >> 3;
+  const int bh = (seq / n_waves) * 8 + (int)(blockIdx.x & 7), wv = seq % n_waves;
+  if (bh >= a.B * a.H) return;
   if (!plan_usable(a.hdr)) return;
   const int b = bh / a.H, h = bh % a.H;
   const WaveDesc wd = a.waves[wv + (a.head_map ? a.head_map[h] * n_waves : 0)];   // the head group's patches
@@ -17,61 +47,119 @@ __global__ __launch_bounds__(64) void k_attn_f32(AttnArgs a, int n_waves) {
   const bool shared = a.cfg_share && a.cfg_share[h * a.n_scales + wd.kq];
   if (shared && b >= a.B / 2) return;
 
-  const int lane = threadIdx.x, n = lane % 16, g4 = lane / 16;
-  const int dy = n / 4, dx = n % 4;
+  const int lane = threadIdx.x & 63, n = lane & 15, g4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int dy = n >> 2, dx = n & 3;
   const int qrow = ((wd.valid >> n) & 1u) ? checked_index(a.hdr, wd.q_base + dy * wd.sk + dx, a.q_len) : -1;
 
+  const char* Kp = (const char*)((const float*)a.k + b * a.ks[0] + h * a.ks[1]);
+  const char* Vp = (const char*)((const float*)a.v + b * a.ks[0] + h * a.ks[1]);
+  const unsigned row_bytes = (unsigned)a.ks[2] * 4u;   // (24 bits, and a slab spans < 2 GiB: checked by the API)
+
+  f32x4 qv[4], O[4];
   const float* Q = (const float*)a.q + b * a.qs[0] + h * a.qs[1];
-  const float* Kp = (const float*)a.k + b * a.ks[0] + h * a.ks[1];
-  const float* Vp = (const float*)a.v + b * a.ks[0] + h * a.ks[1];
-
-  float qv[16], acc[16];
-  for (int d = 0; d < 16; ++d) {
-    qv[d] = qrow >= 0 ? Q[qrow * a.qs[2] + 16 * g4 + d] : 0.f;
-    acc[d] = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    qv[j] = f32x4{0.f, 0.f, 0.f, 0.f}; O[j] = qv[j];
+    if (qrow >= 0) qv[j] = *(const f32x4*)(Q + qrow * a.qs[2] + 16 * j + 4 * g4);
   }
-  float m = -INFINITY, l = 0.f;
+  float m = kF32Floor, l = 0.f;          // softmax reference of query n (the same in its four lanes), this lane's row sum
 
-  for (int s = 0; s < wd.n_steps; ++s) {
-    const int64_t S = (int64_t)wd.step_begin + s;
-    for (int i = 0; i < kStepKeys; ++i) {
-      int tok = a.step_tok[S * kStepKeys + i];
-      if (tok < 0) continue;                      // padding key (uniform over the wave)
-      tok = checked_index(a.hdr, tok, a.kv_len);
-      const float* kr = Kp + tok * a.ks[2] + 16 * g4;
-      float dot = 0.f;
-      for (int d = 0; d < 16; ++d) dot = fmaf(qv[d], kr[d], dot);
-      dot += __shfl_xor(dot, 16);
-      dot += __shfl_xor(dot, 32);
-      const int r = i % 16;
-      const bool keep = a.step_mask[S * 8 + 4 * (i / 16) + r % 4] >> ((r / 4) * 16 + n) & 1;
-      if (keep) {
-        const float z = dot * a.sm_scale;
-        const float m_new = fmaxf(m, z);
-        const float alpha = expf(m - m_new);      // exp(-inf) = 0 on the first kept key
-        const float p = expf(z - m_new);
-        const float* vr = Vp + tok * a.ks[2] + 16 * g4;
-        l = l * alpha + p;
-        for (int d = 0; d < 16; ++d) acc[d] = fmaf(p, vr[d], acc[d] * alpha);
-        m = m_new;
-      }
+  const int64_t S0 = wd.step_begin;
+  const int n_steps = wd.n_steps;
+  // the tokens of this lane's K rows (keys n and 16 + n) and V rows (keys 16 t + 4 g4 + i) of a step
+  struct Tokens { int k[2]; int4 v[2]; };
+  auto load_tokens = [&](int s) {
+    const int32_t* t = a.step_tok + (S0 + min(s, n_steps - 1)) * kStepKeys;
+    return Tokens{{t[n], t[16 + n]}, {*(const int4*)(t + 4 * g4), *(const int4*)(t + 16 + 4 * g4)}};
+  };
+  Tokens tok = load_tokens(wave);
+  for (int s = wave; s < n_steps; s += kF32Waves) {
+    // (padding keys carry token -1; they read the row of the step's first key, which every step has)
+    const int first = __builtin_amdgcn_readfirstlane(tok.k[0]);
+    auto row = [&](int t) -> unsigned {
+      return __umul24((unsigned)checked_index(a.hdr, t < 0 ? first : t, a.kv_len), row_bytes);
+    };
+    f32x4 kf[2][4], vf[2][4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const unsigned o = row(tok.k[t]) + 16u * (unsigned)g4;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) kf[t][j] = *(const f32x4*)(Kp + (o + 64u * j));
     }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int vt[4] = {tok.v[t].x, tok.v[t].y, tok.v[t].z, tok.v[t].w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) vf[t][i] = *(const f32x4*)(Vp + (row(vt[i]) + 16u * (unsigned)n));
+    }
+    const const_u64_ptr mk = (const_u64_ptr)(a.step_mask + (S0 + s) * 8);
+    uint64_t keep[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) keep[e] = mk[e];
+    tok = load_tokens(s + kF32Waves);
+
+    f32x4 S[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) S[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t][j][e], qv[j][e], S[t], 0, 0, 0);
+
+    float z[8], mx = kF32Floor;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      z[e] = mask_select(S[e >> 2][e & 3] * a.sm_scale, keep[e]);
+      mx = fmaxf(mx, z[e]);
+    }
+    const float m_new = fmaxf(m, max_across_rows(mx));
+    if (__builtin_amdgcn_ballot_w64(m_new > m) != 0) {
+      const float alpha = expf(m - m_new);
+      l *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt) O[dt] *= alpha;
+      m = m_new;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { z[e] = expf(z[e] - m); l += z[e]; }      // (masked: exp(-inf) = 0)
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+        O[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[e >> 2][e & 3][dt], z[e], O[dt], 0, 0, 0);
+  }
+
+  // ---- merge the four waves: wave w forms the head dimensions 16 g4 + 4 w .. + 3 of query n ----
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) part_o[wave][i][lane] = f32x4{O[0][i], O[1][i], O[2][i], O[3][i]};
+  if (g4 == 0) { part_m[wave][n] = m; part_l[wave][n] = l; }
+  __syncthreads();
+  float m_all = part_m[0][n];
+#pragma unroll
+  for (int w = 1; w < kF32Waves; ++w) m_all = fmaxf(m_all, part_m[w][n]);
+  float sum = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < kF32Waves; ++w) {
+    const float f = expf(part_m[w][n] - m_all);
+    sum = fmaf(part_l[w][n], f, sum);
+    acc += part_o[w][wave][lane] * f;
   }
   if (qrow < 0) return;
-  const float inv = 1.f / l;
-  float* O = (float*)a.o + b * a.os[0] + h * a.os[1] + qrow * a.os[2] + 16 * g4;
-  for (int d = 0; d < 16; ++d) O[d] = acc[d] * inv;
-  if (shared) {
-    float* O2 = O + (a.B / 2) * a.os[0];
-    for (int d = 0; d < 16; ++d) O2[d] = acc[d] * inv;
-  }
+  acc *= 1.f / sum;
+  float* o = (float*)a.o + b * a.os[0] + h * a.os[1] + qrow * a.os[2] + 16 * g4 + 4 * wave;
+  *(f32x4*)o = acc;
+  if (shared) *(f32x4*)(o + (a.B / 2) * a.os[0]) = acc;
 }
 
 litevar_status launch_attn_f32(const litevar_plan* pl, const AttnArgs& a, hipStream_t st) {
   const int64_t n_waves = (int64_t)pl->n_groups * pl->waves_per_group;
-  const int64_t blocks = n_waves * a.B * a.H;
+  const int64_t blocks = n_waves * (((int64_t)a.B * a.H + 7) / 8 * 8);
   if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large for the fp32 path");
-  hipLaunchKernelGGL(k_attn_f32, dim3((unsigned)blocks), dim3(64), 0, st, a, (int)n_waves);
+  hipLaunchKernelGGL(k_attn_f32, dim3((unsigned)blocks), dim3(kF32Waves * 64), 0, st, a, (int)n_waves);
   return hip_check(hipGetLastError(), "fp32 attention launch");
 }
 
