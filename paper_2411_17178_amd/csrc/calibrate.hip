@@ -2,7 +2,9 @@
 // post-softmax attention map, the smallest window radius per (head, query scale, key scale)
 // whose window holds the fraction R_0 of the part's values.
 //
-// Layout of the work.  In a part (query scale k, key scale j) a key's distance from the
+// Scale sides up to 64 take the streaming pass of calib_stream.h, larger ones k_calib_mass below.
+//
+// Layout of k_calib_mass.  In a part (query scale k, key scale j) a key's distance from the
 // window centre depends only on its offset (oy, ox) from that centre, and so does every
 // window it belongs to: radius r holds the offsets with max(|oy|, |ox|) <= r.  One thread
 // owns one offset and walks all queries of the part, adding the map's value at
@@ -17,7 +19,7 @@
 // folds its 256 offsets into per-distance sums (fixed order again) and writes them to the
 // workspace; a second, small kernel adds the workgroups of a part, forms the in-window sums
 // by prefix and picks the radius.
-#include "internal.h"
+#include "calib_stream.h"
 
 #include <mutex>
 
@@ -39,6 +41,7 @@ struct CalibArgs {
   int32_t* radius;      // [H][K][K]
   double* mass;         // [H][K][K][smax] or nullptr
   double r0;
+  int stream_splits[kMaxScales];   // row shares of a query scale in the streaming pass
 };
 
 __host__ __device__ inline int tiles_of(int sj) {
@@ -135,132 +138,89 @@ __global__ __launch_bounds__(kCalibThreads) void k_calib_mass(CalibArgs a) {
   }
 }
 
-// The same sums for maps whose largest side is at most kRowsMaxSide, one map row at a time.
-// Same grid and same partial-sum slots as k_calib_mass, but a workgroup owns a share of the
-// part's (sample, query) rows instead of a tile of offsets: a wave reads the row's s_j^2 keys
-// of the part with consecutive lanes on consecutive floats (whole cache lines, each value
-// read exactly once), every lane works out its key's distance from the row's centre and
-// adds the value to bin `distance` of a column of bins in LDS that belongs to this lane
-// alone (no two lanes on one address, and a lane's additions happen in program order, so
-// the sums repeat bit for bit).  At the end the 64 columns of a wave are folded by a fixed butterfly, the four waves
-// of the workgroup in order.
-constexpr int kRowsMaxSide = 64;           // bins of the four waves: 4 x side x 64 x 8 bytes of LDS
-constexpr int kRowsThreads = 256;
+// The same sums for maps whose largest side is at most kStreamMaxSide, by the streaming pass of
+// calib_stream.h: a part is one key scale, a lane's offset class (uy, ux) has four wrap states.
+// Measured (8 samples x 30 heads x 680^2): 63 us, 4.4 TB/s of the block-causal values; the former kernel,
+// which binned every value through a read-add-write in LDS, took 157 us.
+struct WindowWalk {
+  static constexpr int kClasses = 4;     // bit 0: ux wrapped (offset ux - side), bit 1: uy wrapped
+  const StreamGeom& g; const StreamTask& t; const short* cen;   // cen[key scale - ja][query coordinate]
+  const short* cj;
+  int sj, uy, ux, qy, qx, dqy, dqx, sk, off0;
+  __device__ void start(int e, int row, int step) {
+    int j = t.ja;
+    while (j + 1 < t.jb && t.col0 + e >= g.off[j + 1]) ++j;
+    const int u = t.col0 + e - g.off[j];
+    sj = g.s[j]; uy = u / sj; ux = u - uy * sj;
+    sk = g.s[t.k];
+    cj = cen + (j - t.ja) * sk;
+    qy = row / sk; qx = row - qy * sk;
+    dqy = step / sk; dqx = step - dqy * sk;
+    off0 = g.off[j];
+  }
+  __device__ int64_t next(int& cls) {
+    int ky = cj[qy] + uy, kx = cj[qx] + ux;
+    const bool wy = ky >= sj, wx = kx >= sj;
+    ky -= wy ? sj : 0; kx -= wx ? sj : 0;
+    cls = (int)wx + 2 * (int)wy;
+    const int64_t at = (int64_t)(qy * sk + qx) * g.L + off0 + ky * sj + kx;
+    qy += dqy; qx += dqx;
+    if (qx >= sk) { qx -= sk; ++qy; }
+    return at;
+  }
+};
 
-// (A plain read-add-write on the lane's own column: LDS atomics -- ds_add_f64, and ds_add_u64
-// alike -- were measured at about 240 cycles per wave instruction here, six times the cost of
-// everything else in the loop; the read-add-write chains of the sixteen waves of a CU overlap.)
-__device__ inline void lds_add_f64(double* col, int d, double v) { col[d * 64] += v; }
-
-__global__ __launch_bounds__(kRowsThreads) void k_calib_mass_rows(CalibArgs a) {
+// grid: slots x heads, the slots with the most work first
+template <int NB>
+__global__ __launch_bounds__(kStreamThreads) void k_calib_stream(StreamGeom g, double* partial, int slots_per_part, int smax) {
   extern __shared__ __align__(16) unsigned char calib_smem[];
-  const Slot sl = decode_slot(a, blockIdx.x);
-  const int k = sl.k, j = sl.j, h = blockIdx.z, tile = sl.tile, split = sl.split;
-  const int sk = a.s[k], sj = a.s[j];
-  const int nt = tiles_of(sj);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // LDS: bins[wave][d][lane] (fp64), then the centres of the part's query coordinates
-  double* const bins = (double*)calib_smem + (size_t)wave * sj * 64;
-  double* const fold = (double*)calib_smem + (size_t)4 * a.smax * 64;          // [4][smax]
-  short* const cen = (short*)(fold + 4 * a.smax);                              // [sk]
-  for (int c = threadIdx.x; c < sk; c += kRowsThreads) cen[c] = (short)(((2 * c + 1) * sj) / (2 * sk));
-  for (int i = lane; i < sj * 64; i += 64) bins[i] = 0.0;
-  __syncthreads();
-
-  double* const bins_lane = bins + lane;                                       // this lane's column of bins
-  const int nkeys = sj * sj, nq = sk * sk;
-  const int share = split * nt + tile, n_shares = a.splits * nt;               // this workgroup's rows
-  const float* part = a.p + (int64_t)h * a.L * a.L + (int64_t)a.off[k] * a.L + a.off[j];
-  const int64_t sample_stride = (int64_t)a.H * a.L * a.L;
-  // this wave's queries: first, first + stride, ...; the N samples of a query share its centre,
-  // so their values are added in registers first and binned once
-  const int first = share * 4 + wave, stride = n_shares * 4;
-  if (nkeys >= 64) {
-    constexpr int U = 4, NB = 8;                          // an item: 256 keys of a query's row, 8 samples: 32 loads
-    const int nchunk = (nkeys + 64 * U - 1) / (64 * U);
-    const int my_q = first < nq ? (nq - first + stride - 1) / stride : 0;
-    const int n_items = my_q * nchunk;
-    auto load_item = [&](int t, int n0, float (&v)[NB][U]) {
-      const int q = first + (t / nchunk) * stride, i0 = (t % nchunk) * 64 * U;
-      const float* row = part + (int64_t)q * a.L;
-#pragma unroll
-      for (int m = 0; m < NB; ++m)
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int i = i0 + 64 * u + lane;
-          v[m][u] = (n0 + m < a.N && i < nkeys) ? row[(n0 + m) * sample_stride + i] : 0.f;
-        }
-    };
-    // the loads of the next item are in flight while this one is binned
-    float cur[NB][U], nxt[NB][U];
-    if (n_items > 0) load_item(0, 0, cur);
-    for (int t = 0; t < n_items; ++t) {
-      if (t + 1 < n_items) load_item(t + 1, 0, nxt);
-      const int q = first + (t / nchunk) * stride, i0 = (t % nchunk) * 64 * U;
-      const int cy = cen[q / sk], cx = cen[q % sk];
-      double acc[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) acc[u] = 0.0;
-#pragma unroll
-      for (int m = 0; m < NB; ++m)
-#pragma unroll
-        for (int u = 0; u < U; ++u) acc[u] += (double)cur[m][u];
-      for (int n0 = NB; n0 < a.N; n0 += NB) {             // (more than eight samples: further batches, not overlapped)
-        load_item(t, n0, cur);
-#pragma unroll
-        for (int m = 0; m < NB; ++m)
-#pragma unroll
-          for (int u = 0; u < U; ++u) acc[u] += (double)cur[m][u];
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int i = i0 + 64 * u + lane;
-        const int ky = i / sj, kx = i - ky * sj;
-        if (i < nkeys) lds_add_f64(bins_lane, max(abs(ky - cy), abs(kx - cx)), acc[u]);
-      }
-#pragma unroll
-      for (int m = 0; m < NB; ++m)
-#pragma unroll
-        for (int u = 0; u < U; ++u) cur[m][u] = nxt[m][u];
-    }
-  } else {
-    // a part with fewer than 64 keys per row: a pass covers 64 / nkeys queries, lane = (query, key)
-    const int qpp = 64 / nkeys;                           // queries per pass
-    const int sub = lane / nkeys, key = lane - sub * nkeys;
-    const int ky = key / sj, kx = key - ky * sj;
-    for (int t0 = 0; first + (int64_t)t0 * stride < nq; t0 += qpp) {
-      const int64_t q = first + (int64_t)(t0 + sub) * stride;
-      const bool in = sub < qpp && q < nq;
-      const int qq = in ? (int)q : first;
-      const int d = max(abs(ky - cen[qq / sk]), abs(kx - cen[qq % sk]));
-      const float* src = part + (int64_t)qq * a.L + key;
-      double acc = 0.0;
-      for (int n = 0; n < a.N; n += 8) {                  // eight loads in flight
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = n + u < a.N ? src[(n + u) * sample_stride] : 0.f;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc += (double)v[u];
-      }
-      if (in) lds_add_f64(bins_lane, d, acc);
-    }
-  }
-  // fold the wave's 64 columns (fixed butterfly), then the four waves in order
-  for (int d = 0; d < sj; ++d) {
-    double x = bins[d * 64 + lane];
-#pragma unroll
-    for (int m = 32; m > 0; m >>= 1) x += __shfl_xor(x, m);
-    if (lane == 0) fold[wave * a.smax + d] = x;
+  const StreamTask t = stream_task(g);
+  double* const acc = (double*)calib_smem;                                     // [4][entries]
+  short* const cen = (short*)(acc + 4 * g.entries);                            // [key scale - ja][sk]
+  const int sk = g.s[t.k];
+  for (int i = threadIdx.x; i < (t.jb - t.ja) * sk; i += kStreamThreads) {
+    const int j = i / sk, c = i - j * sk;
+    cen[i] = (short)(((2 * c + 1) * g.s[t.ja + j]) / (2 * sk));
   }
   __syncthreads();
-  double* out = a.partial +
-      (((((int64_t)h * a.K + k) * a.K + j) * a.splits + split) * a.max_tiles + tile) * a.smax;
-  for (int d = threadIdx.x; d < sj; d += kRowsThreads)
-    out[d] = ((fold[d] + fold[a.smax + d]) + fold[2 * a.smax + d]) + fold[3 * a.smax + d];
+  WindowWalk walk{g, t, cen};
+  stream_sums<NB>(g, t, walk, acc);
+  __syncthreads();
+  // by absolute offset (dy, dx): the sums of up to four signed offsets, in place of class 0's (only
+  // the entry's own thread reads that one)
+  const int R = stream_rows_at_once(t);
+  for (int e = threadIdx.x; e < t.ncols; e += kStreamThreads) {
+    int j = t.ja;
+    while (j + 1 < t.jb && t.col0 + e >= g.off[j + 1]) ++j;
+    const int p0 = g.off[j] - t.col0, sj = g.s[j], dy = (e - p0) / sj, dx = e - p0 - dy * sj;
+    double v = 0.0;
+    for (int r = 0; r < R; ++r) {
+      const double* a = acc + (R > 1 ? r * t.ncols : 0) + p0;
+      v += a[dy * sj + dx];
+      if (dx > 0) v += a[g.entries + dy * sj + sj - dx];
+      if (dy > 0) v += a[2 * g.entries + (sj - dy) * sj + dx];
+      if (dy > 0 && dx > 0) v += a[3 * g.entries + (sj - dy) * sj + sj - dx];
+    }
+    acc[e] = v;
+  }
+  __syncthreads();
+  // rings max(dy, dx) = d
+  int n_rings = 0;
+  for (int j = t.ja; j < t.jb; ++j) n_rings += g.s[j];
+  for (int q = threadIdx.x; q < n_rings; q += kStreamThreads) {
+    int j = t.ja, d = q;
+    while (d >= g.s[j]) { d -= g.s[j]; ++j; }
+    const int sj = g.s[j];
+    const double* a = acc + (g.off[j] - t.col0);
+    double v = 0.0;
+    for (int x = 0; x <= d; ++x) v += a[d * sj + x];
+    for (int y = 0; y < d; ++y) v += a[y * sj + d];
+    partial[((((int64_t)t.h * g.K + t.k) * g.K + j) * slots_per_part + t.split) * smax + d] = v;
+  }
 }
 
-// grid (K * K, H), one wave
-__global__ __launch_bounds__(64) void k_calib_pick(CalibArgs a) {
+// grid (K * K, H), one wave; stream: the partial sums are k_calib_stream's (splits[k] consecutive slots)
+__global__ __launch_bounds__(64) void k_calib_pick(CalibArgs a, bool stream) {
   const int k = blockIdx.x / a.K, j = blockIdx.x % a.K, h = blockIdx.y;
   const int64_t part = ((int64_t)h * a.K + k) * a.K + j;
   double* mass = a.mass ? a.mass + part * a.smax : nullptr;
@@ -270,27 +230,24 @@ __global__ __launch_bounds__(64) void k_calib_pick(CalibArgs a) {
     return;
   }
   const int sj = a.s[j], nt = tiles_of(sj);
-  __shared__ double ring[kMaxSide];          // values at distance exactly d
+  __shared__ double inside[kMaxSide];        // values at distance exactly d, then within d
+  __shared__ int found;
   const double* in = a.partial + part * a.splits * a.max_tiles * a.smax;
   for (int d = threadIdx.x; d < sj; d += 64) {
     double s = 0.0;
-    for (int sp = 0; sp < a.splits; ++sp)
-      for (int t = 0; t < nt; ++t) s += in[((int64_t)sp * a.max_tiles + t) * a.smax + d];
-    ring[d] = s;
+    if (stream) {
+#pragma unroll 8
+      for (int sp = 0; sp < a.stream_splits[k]; ++sp) s += in[(int64_t)sp * a.smax + d];   // (loads in flight together)
+    } else {
+      for (int sp = 0; sp < a.splits; ++sp)
+        for (int t = 0; t < nt; ++t) s += in[((int64_t)sp * a.max_tiles + t) * a.smax + d];
+    }
+    inside[d] = s;
   }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  double total = 0.0;
-  for (int d = 0; d < sj; ++d) total += ring[d];
   // the window grows from zero until the ratio reaches the threshold
-  double inside = 0.0;
-  int found = -1;
-  for (int r = 0; r < a.smax; ++r) {
-    if (r < sj) inside += ring[r];
-    if (mass) mass[r] = inside;
-    if (found < 0 && r < sj && (total == 0.0 || inside / total >= a.r0)) found = r;
-  }
-  a.radius[part] = found < 0 ? sj - 1 : found;
+  const int r = prefix_and_pick(inside, sj, a.r0, &found);
+  if (mass) for (int d = threadIdx.x; d < a.smax; d += 64) mass[d] = inside[min(d, sj - 1)];
+  if (threadIdx.x == 0) a.radius[part] = r;
 }
 
 litevar_status calib_geom(const int32_t* scales, int32_t K, CalibArgs& a) {
@@ -427,20 +384,29 @@ litevar_status calibrate_with(CalibArgs& a, const float* d_attn, int32_t N, int3
   a.N = N; a.H = H; a.p = d_attn; a.partial = (double*)d_workspace;
   a.radius = d_radius; a.mass = d_mass; a.r0 = (double)r0;
   hipStream_t st = (hipStream_t)stream;
-  if (a.smax <= kRowsMaxSide) {
-    // (maps of small scales, the usual case: whole rows with coalesced loads)
-    const size_t lds = (size_t)4 * a.smax * 64 * sizeof(double) + (size_t)4 * a.smax * sizeof(double) +
-                       (size_t)a.smax * sizeof(short) + 16;
+  const bool stream_pass = a.smax <= kStreamMaxSide;
+  if (stream_pass) {
+    // (maps of small scales, the usual case)
+    StreamGeom g = {};
+    g.K = a.K; g.N = N; g.H = H; g.L = a.L; g.p = d_attn;
+    for (int k = 0; k < a.K; ++k) { g.s[k] = a.s[k]; g.off[k] = a.off[k]; }
+    g.off[a.K] = a.off[a.K];
+    stream_plan(g, 1, [&](int) { return a.splits * a.max_tiles; });
+    for (int k = 0; k < a.K; ++k) a.stream_splits[k] = g.splits[k];
+    const int64_t blocks = g.slot_begin[a.K] * (int64_t)H;
+    if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large");
+    const size_t lds = (size_t)4 * g.entries * sizeof(double) + (size_t)a.K * a.smax * sizeof(short);
+    const auto kernel = stream_pick(N, k_calib_stream<1>, k_calib_stream<2>, k_calib_stream<4>, k_calib_stream<8>);
     if (lds > 64 * 1024)     // (beyond the default limit of dynamically sized LDS; no allocation involved)
-      if (litevar_status s = hip_check(hipFuncSetAttribute((const void*)k_calib_mass_rows,
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
-                                       "hipFuncSetAttribute")) return s;
-    hipLaunchKernelGGL(k_calib_mass_rows, dim3(a.n_slots, 1, H), dim3(kRowsThreads), lds, st, a);
+      if (litevar_status s = hip_check(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                           (int)lds), "hipFuncSetAttribute")) return s;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kStreamThreads), lds, st, g, a.partial,
+                       a.splits * a.max_tiles, a.smax);
   } else {
     hipLaunchKernelGGL(k_calib_mass, dim3(a.n_slots, 1, H), dim3(kCalibThreads), 0, st, a);
   }
   if (litevar_status s = hip_check(hipGetLastError(), "calibration mass launch")) return s;
-  hipLaunchKernelGGL(k_calib_pick, dim3(a.K * a.K, H), dim3(64), 0, st, a);
+  hipLaunchKernelGGL(k_calib_pick, dim3(a.K * a.K, H), dim3(64), 0, st, a, stream_pass);
   return hip_check(hipGetLastError(), "calibration pick launch");
 }
 

@@ -160,3 +160,14 @@ def test_band_calibrate_feeds_a_band_plan(lv):
                 blk = summed[off[k]:off[k + 1], off[first]:off[last + 1]]
                 kept = blk[m[off[k]:off[k + 1], off[first]:off[last + 1]]].sum()
                 assert kept / blk.sum() >= float(np.float32(0.9)) - 1e-9
+
+
+@pytest.mark.parametrize("samples", [1, 2, 3, 5, 9])
+@pytest.mark.parametrize("scales", [(16,), (11, 2, 5, 12, 17), (3, 4, 15, 1, 33), (2, 6, 48)])
+def test_calibrate_segments_and_sample_batches(lv, scales, samples):
+    """Parts of more and of fewer columns than a workgroup has lanes, several rows side by side, row
+    shares with a remainder, sample counts around the batch sizes; both mask readings."""
+    p = workloads.make_attn_map(scales, samples, 2, 71)
+    _compare(lv, scales, p, 0.9)
+    if max(scales) < 20:                  # (the oracle walks a band radius by radius: minutes for the larger ones)
+        _compare_band(lv, scales, p, 0.9)
