@@ -54,8 +54,8 @@ struct Geom {
   short rad[kMaxScales][kMaxScales];   // radii of ONE head group, [query scale][key scale]
                                        // (Section 2, step (3): one window size per scale and
                                        // part); < 0: dense part.  The host sizes one head
-                                       // group at a time; on the device only the kernel that
-                                       // writes the tables reads this field.
+                                       // group at a time; the device kernels read tables in
+                                       // the blob and never this field.
   int grp_off[kMaxScales + 1];  // groups are ordered by DESCENDING query scale:
                                 // slot i holds scale qe-1-i; grp_off is its prefix sum
 };
@@ -117,17 +117,18 @@ LV_HD unsigned ring_swizzle(unsigned slot) { return (slot ^ (slot >> 3)) & 7u; }
 // coordinate c of scale k: centre = floor((2c+1) s_j / (2 s_k)), radius r, clipped.
 struct Interval { int lo, hi; };   // empty when hi < lo
 
-LV_HD Interval win_interval(const Geom& g, int k, int j, int c) {
-  const int sj = g.s[j];
+LV_HD Interval window_interval(int sk, int sj, int c, int rad) {
   Interval iv;
-  const int rad = g.rad[k][j];
-  if (j < g.n_sink || rad < 0) { iv.lo = 0; iv.hi = sj - 1; return iv; }
+  if (rad < 0) { iv.lo = 0; iv.hi = sj - 1; return iv; }
   // (sides are at most kMaxSide = 1024, so the product fits 32 bits: a 64-bit division would
   // cost an order of magnitude more on the device)
-  const int ctr = (int)((unsigned)((2 * c + 1) * sj) / (unsigned)(2 * g.s[k]));
+  const int ctr = (int)((unsigned)((2 * c + 1) * sj) / (unsigned)(2 * sk));
   iv.lo = ctr - rad < 0 ? 0 : ctr - rad;
   iv.hi = ctr + rad > sj - 1 ? sj - 1 : ctr + rad;
   return iv;
+}
+LV_HD Interval win_interval(const Geom& g, int k, int j, int c) {
+  return window_interval(g.s[k], g.s[j], c, j < g.n_sink ? -1 : g.rad[k][j]);
 }
 
 // Where the builder takes its intervals from: the arithmetic above (host sizing, and the

@@ -1,7 +1,8 @@
 // Plan construction: host-side validation and sizing, device-side builder kernels
-// (window table, work-list count -> scan -> fill) and the parity exports.
+// (tables, work-list count -> scan -> fill) and the parity exports.
 #include "internal.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -247,32 +248,42 @@ static BlobPtrs blob_ptrs(void* blob, const uint64_t* off) {
 
 struct Caps { int64_t n_steps, n_union, n_phase_entries, retained_pairs; uint64_t bytes; };
 
-// K1, once per head group (g.rad holds that group's radii): the radius table
-// rad[hg][k][j] (-1: dense part) and, in window mode, the window table
-// win[hg][k][j][c] = inclusive [lo, hi]; (-1,-1) where undefined.  Every other builder
-// kernel reads these tables and never the radii of the descriptor.
-__global__ void k_tables(Geom g, int hg, int16_t* win, int16_t* rad) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx < g.K * g.K) {
-    const int j = idx % g.K, k = idx / g.K;
-    rad[(size_t)hg * g.K * g.K + idx] = j > k ? (int16_t)0 : (j < g.n_sink ? (int16_t)-1 : g.rad[k][j]);
+// K1: the radius tables rad[hg][k][j] (-1: dense part), in window mode the window tables
+// win[hg][k][j][c] = inclusive [lo, hi] ((-1,-1) where undefined), and the head map.  Every other
+// builder kernel reads these tables and never the radii of the descriptor.
+// The radii travel as kernel arguments (no copy that a caller's stream would have to order), the
+// lower triangles of as many head groups as fit the 4 KiB argument block: 33 of ten scales, 3 of
+// thirty-two.  Thirty distinct tables of ten scales take 3.9 us in one launch; a launch per table
+// took 30 x 3.1 us on the GPU.
+constexpr int kTableRadii = 1840;
+struct TablesArg {
+  int K, mode, n_sink, smax, hg0, n_hg, n_heads;   // head groups [hg0, hg0 + n_hg); n_heads < 0: no head map in this launch
+  uint16_t s[kMaxScales];
+  uint8_t head_group[kMaxHeads];
+  int16_t rad[kTableRadii];                        // [hg - hg0][k (k + 1) / 2 + j]
+};
+static_assert(sizeof(TablesArg) + 3 * sizeof(void*) <= 4096, "kernel argument block");
+
+// grid (entries of a head group's window table / 256, head groups of the launch)
+__global__ __launch_bounds__(256) void k_tables(TablesArg a, int16_t* win, int16_t* rad, int32_t* head_map) {
+  const int idx = blockIdx.x * 256 + threadIdx.x, hg = a.hg0 + blockIdx.y;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && a.n_heads >= 0)
+    head_map[threadIdx.x] = (int)threadIdx.x < a.n_heads ? a.head_group[threadIdx.x] : 0;
+  const int16_t* r = a.rad + blockIdx.y * (a.K * (a.K + 1) / 2);
+  if (idx < a.K * a.K) {
+    const int k = idx / a.K, j = idx - k * a.K;
+    rad[(size_t)hg * a.K * a.K + idx] = j > k ? (int16_t)0 : j < a.n_sink ? (int16_t)-1 : r[k * (k + 1) / 2 + j];
   }
-  if (g.mode != kModeWindow) return;
-  const int total = g.K * g.K * g.smax;
+  if (a.mode != kModeWindow) return;
+  const int total = a.K * a.K * a.smax;
   if (idx >= total) return;
-  const int c = idx % g.smax, j = (idx / g.smax) % g.K, k = idx / (g.smax * g.K);
+  const int c = idx % a.smax, kj = idx / a.smax, k = kj / a.K, j = kj - k * a.K;
   Interval iv = {-1, -1};
-  if (j <= k && c < g.s[k]) iv = win_interval(g, k, j, c);
+  if (j <= k && c < a.s[k]) iv = window_interval(a.s[k], a.s[j], c, j < a.n_sink ? -1 : r[k * (k + 1) / 2 + j]);
   int16_t* out = win + ((size_t)hg * total + idx) * 2;
   out[0] = (int16_t)iv.lo; out[1] = (int16_t)iv.hi;
 }
-
-struct HeadMapArg { uint8_t group[kMaxHeads]; };
-
-__global__ void k_head_map(HeadMapArg m, int n_heads, int32_t* out) {
-  const int i = threadIdx.x;
-  if (i < kMaxHeads) out[i] = i < n_heads ? m.group[i] : 0;
-}
+static_assert(kMaxHeads == 256, "one thread per head");
 
 // value of `v` in lane `lane`, for a lane index that is the same in every lane of the wave:
 // v_readlane_b32, where __shfl would go through the LDS crossbar
@@ -361,6 +372,8 @@ __device__ int wave_walk_patch(const Geom& g, const TableWin& win, const TableRa
   // v_readlane.
   constexpr int kRounds = kMaxScales / 4;
   Interval pre[kRounds];
+  // (likewise the key scales' sides and offsets, one per lane)
+  const int my_side = g.s[min(lane, g.K - 1)], my_off = g.off[min(lane, g.K - 1)];
   {
     const int sk = g.s[e.k];
     const int role = lane & 15;
@@ -394,7 +407,7 @@ __device__ int wave_walk_patch(const Geom& g, const TableWin& win, const TableRa
     pb.ylo = rw[0].lo; pb.yhi = lane_value(mine_iv.hi, l0 + p.ny - 1);
     pb.xlo = cw[0].lo; pb.xhi = lane_value(mine_iv.hi, l0 + 4 + p.nx - 1);
     const int gw = gb.xhi - gb.xlo + 1;
-    const int sj = g.s[j], offj = g.off[j];
+    const int sj = lane_value(my_side, j), offj = lane_value(my_off, j);
     // lanes of a pass in key order: RP rows of the patch's box (W columns each) when the box
     // is narrower than a wave, else 64 columns of one row
     const int W = pb.xhi - pb.xlo + 1;
@@ -509,11 +522,12 @@ __global__ __launch_bounds__(64) void k_count(Geom g, BlobPtrs p) {
 }
 
 // K2b: exclusive scans over groups (union keys, phase entries) and patches (steps) by one
-// 1024-thread block: per-thread partial sums over a contiguous slice of groups, a block-wide
-// scan of the partials (Hillis-Steele in LDS), then the slice is revisited
+// 1024-thread block: per-thread partial sums over a contiguous slice of groups, a scan of the
+// partials inside each wave, then over the waves' totals, then the slice is revisited.
+// (60 groups of 8 patches: 5.5 us; 8.1 us with ten rounds through LDS)
 __global__ __launch_bounds__(1024) void k_scan(Geom g, BlobPtrs p, Caps caps) {
-  __shared__ int64_t part[2][4][1024];
-  const int t = threadIdx.x;
+  __shared__ int64_t wave_total[4][16];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int n_all = g.n_groups * g.n_hg;
   const int per = (n_all + 1023) / 1024;
   const int g0 = t * per < n_all ? t * per : n_all;
@@ -521,19 +535,25 @@ __global__ __launch_bounds__(1024) void k_scan(Geom g, BlobPtrs p, Caps caps) {
   int64_t v[4] = {0, 0, 0, 0};                          // steps, union keys, phase entries, pairs
   for (int grp = g0; grp < g1; ++grp) {
     v[1] += (int64_t)p.groups[grp].n_phases * g.C; v[2] += (int64_t)p.groups[grp].n_phases * g.NW;
+#pragma unroll 4
     for (int w = 0; w < g.NW; ++w) { v[0] += p.waves[grp * g.NW + w].n_steps; v[3] += p.waves[grp * g.NW + w].pairs; }
   }
-  int cur = 0;
+  int64_t sum[4];                                       // inclusive
 #pragma unroll
-  for (int i = 0; i < 4; ++i) part[0][i][t] = v[i];
-  __syncthreads();
-  for (int d = 1; d < 1024; d <<= 1) {                  // inclusive scan
+  for (int i = 0; i < 4; ++i) {
+    sum[i] = v[i];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) part[cur ^ 1][i][t] = part[cur][i][t] + (t >= d ? part[cur][i][t - d] : 0);
-    cur ^= 1;
-    __syncthreads();
+    for (int d = 1; d < 64; d <<= 1) {
+      const int64_t below = __shfl_up(sum[i], d);
+      if (lane >= d) sum[i] += below;
+    }
+    if (lane == 63) wave_total[i][wave] = sum[i];
   }
-  int64_t steps = part[cur][0][t] - v[0], uni = part[cur][1][t] - v[1], phe = part[cur][2][t] - v[2];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    for (int w = 0; w < wave; ++w) sum[i] += wave_total[i][w];
+  int64_t steps = sum[0] - v[0], uni = sum[1] - v[1], phe = sum[2] - v[2];
   for (int grp = g0; grp < g1; ++grp) {
     GroupDesc& gd = p.groups[grp];
     gd.union_base = (int32_t)uni; gd.phase_base = (int32_t)phe;
@@ -548,18 +568,16 @@ __global__ __launch_bounds__(1024) void k_scan(Geom g, BlobPtrs p, Caps caps) {
     memset(&h, 0, sizeof h);
     h.magic = kMagic; h.blob_bytes = caps.bytes;
     h.n_groups = n_all; h.n_waves = n_all * g.NW;
-    h.n_steps = part[cur][0][t]; h.n_union = part[cur][1][t]; h.n_phase_entries = part[cur][2][t];
-    h.retained_pairs = part[cur][3][t];
+    h.n_steps = sum[0]; h.n_union = sum[1]; h.n_phase_entries = sum[2];
+    h.retained_pairs = sum[3];
     h.error = (h.n_steps != caps.n_steps || h.n_union != caps.n_union ||
                h.n_phase_entries != caps.n_phase_entries || h.retained_pairs != caps.retained_pairs) ? kErrBuilder : kErrNone;
     *p.hdr = h;
   }
 }
 
-// K2c: the group's key list (token indices), padded to whole chunks with its last key
-__global__ void k_fill_union(Geom g, BlobPtrs p, Caps caps) {
-  const int G = blockIdx.x;
-  if (p.hdr->error) return;
+// the group's key list (token indices), padded to whole chunks with its last key; one wave
+__device__ void fill_union(const Geom& g, const BlobPtrs& p, const Caps& caps, int G) {
   const GroupTables t = group_tables(g, p, G);
   const GroupDesc gd = p.groups[G];
   const GroupExtent e = group_extent(g, gd.k, gd.gy, gd.gx);
@@ -602,9 +620,16 @@ __global__ void k_fill_union(Geom g, BlobPtrs p, Caps caps) {
 struct StepBuf { uint32_t slot[kStepKeys]; int32_t tok[kStepKeys]; uint32_t qmask[kStepKeys]; };
 
 struct FillSink {
-  uint2* addr; uint64_t* mask; int32_t* toks; int32_t* phase_cnt;
+  uint2* addr; uint64_t* mask; int32_t* toks; int32_t* phase_end;
   StepBuf* buf;
   int R, logC, lane;
+  int chunk = 0;                       // chunk of the last closed step: phase_end is written up to it
+  int end0 = 0, end2 = 0;              // steps that end in chunk 0, in chunks 0 to 2
+  // steps close in the order of their chunks, so the cumulative counts of the chunks that a step
+  // skips are final when it closes: no counter is read back
+  __device__ void fill_ends(int from, int to, int steps) {
+    for (int i = from + lane; i < to; i += 64) phase_end[i] = steps;
+  }
   __device__ static uint32_t k_off(uint32_t slot, int g4) {
     return slot * kRingRowBytes + (((2u * g4) ^ ring_swizzle(slot)) << 4);
   }
@@ -633,40 +658,39 @@ struct FillSink {
     }
     if (lane < 8) mask[(int64_t)step * 8 + lane] = mine;
     if (lane < kStepKeys) toks[(int64_t)step * kStepKeys + lane] = lane < n_keys ? buf->tok[lane] : -1;
-    if (lane == 0) phase_cnt[last_upos >> logC] += 1;
+    const int c = last_upos >> logC;
+    if (c > chunk) { fill_ends(chunk, c, step); chunk = c; }
+    if (c == 0) end0 = step + 1;
+    if (c <= 2) end2 = step + 1;
     __syncthreads();                                   // the buffer may be refilled
   }
 };
 
-// K2d: one wave per (group, patch): steps (ring addresses, lane masks, tokens) and the
-// cumulative number of steps that are runnable after each phase
-__global__ __launch_bounds__(64) void k_fill_steps(Geom g, BlobPtrs p, Caps caps) {
+// K2c: one wave per (group, patch): steps (ring addresses, lane masks, tokens) and the
+// cumulative number of steps that are runnable after each phase; then one wave per group: its
+// key list (in the same launch: neither needs the other).  Bound: the serial walk of one wave.
+// 480 patches of 30 head groups: 27 us, 35 us as two launches with counters that were read back.
+__global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int n_waves) {
   __shared__ StepBuf buf;
   const int idx = blockIdx.x, lane = threadIdx.x;
   if (p.hdr->error) return;
+  if (idx >= n_waves) { fill_union(g, p, caps, idx - n_waves); return; }
   const int G = idx / g.NW, w = idx % g.NW;
   const GroupTables t = group_tables(g, p, G);
   const GroupDesc gd = p.groups[G];
   const WaveDesc wd = p.waves[idx];
   if ((int64_t)wd.step_begin + wd.n_steps > caps.n_steps ||
       (int64_t)gd.phase_base + (int64_t)gd.n_phases * g.NW > caps.n_phase_entries) return;
-  int32_t* pe = p.phase_end + gd.phase_base + (int64_t)w * gd.n_phases;
-  for (int i = lane; i < gd.n_phases; i += 64) pe[i] = 0;
-  __syncthreads();
   const GroupExtent e = group_extent(g, gd.k, gd.gy, gd.gx);
   FillSink sink;
   sink.addr = p.step_addr + (int64_t)wd.step_begin * 64;
   sink.mask = p.step_mask + (int64_t)wd.step_begin * 8;
   sink.toks = p.step_tok + (int64_t)wd.step_begin * kStepKeys;
-  sink.phase_cnt = pe; sink.buf = &buf; sink.R = g.R; sink.logC = g.logC; sink.lane = lane;
-  wave_walk_patch(g, t.win, t.rad, e, patch_extent(g, gd.k, gd.gy, gd.gx, w), sink, lane);
-  __syncthreads();
-  if (lane == 0) {
-    int acc = 0;
-    for (int i = 0; i < gd.n_phases; ++i) { acc += pe[i]; pe[i] = acc; }
-    const int i1 = gd.n_phases - 1 < 2 ? gd.n_phases - 1 : 2;
-    p.waves[idx].first_ends = (uint32_t)pe[0] | ((uint32_t)pe[i1] << 16);   // (a patch has at most 65535 steps)
-  }
+  sink.phase_end = p.phase_end + gd.phase_base + (int64_t)w * gd.n_phases;
+  sink.buf = &buf; sink.R = g.R; sink.logC = g.logC; sink.lane = lane;
+  const int ns = wave_walk_patch(g, t.win, t.rad, e, patch_extent(g, gd.k, gd.gy, gd.gx, w), sink, lane);
+  sink.fill_ends(sink.chunk, gd.n_phases, ns);
+  if (lane == 0) p.waves[idx].first_ends = (uint32_t)sink.end0 | ((uint32_t)sink.end2 << 16);   // (a patch has at most 65535 steps)
 }
 
 litevar_status build_plan(PlanSpec& sp, const PlanSizes& z, void* d_blob, hipStream_t st) {
@@ -674,20 +698,24 @@ litevar_status build_plan(PlanSpec& sp, const PlanSizes& z, void* d_blob, hipStr
   const BlobPtrs p = blob_ptrs(d_blob, z.off);
   Caps caps{z.n_steps, z.n_union, z.n_phase_entries, z.retained_pairs, z.bytes};
   const int ntab = g.mode == kModeWindow ? g.K * g.K * g.smax : g.K * g.K;
-  for (int hg = 0; hg < g.n_hg; ++hg) {
-    sp.load_head_group(hg);
-    hipLaunchKernelGGL(k_tables, dim3((ntab + 255) / 256), dim3(256), 0, st, g, hg, p.win, p.rad);
+  const int tri = g.K * (g.K + 1) / 2, per_launch = kTableRadii / tri;
+  TablesArg ta;
+  ta.K = g.K; ta.mode = g.mode; ta.n_sink = g.n_sink; ta.smax = g.smax;
+  for (int k = 0; k < g.K; ++k) ta.s[k] = (uint16_t)g.s[k];
+  memcpy(ta.head_group, sp.head_group, sizeof ta.head_group);
+  for (int hg0 = 0; hg0 < g.n_hg; hg0 += per_launch) {
+    ta.hg0 = hg0; ta.n_hg = std::min(per_launch, g.n_hg - hg0); ta.n_heads = hg0 == 0 ? sp.n_heads : -1;
+    int at = 0;
+    for (int hg = hg0; hg < hg0 + ta.n_hg; ++hg)
+      for (int k = 0; k < g.K; ++k)
+        for (int j = 0; j <= k; ++j) ta.rad[at++] = sp.rad_all[((size_t)hg * g.K + k) * g.K + j];
+    hipLaunchKernelGGL(k_tables, dim3((ntab + 255) / 256, ta.n_hg), dim3(256), 0, st, ta, p.win, p.rad, p.head_map);
   }
-  sp.load_head_group(0);
-  HeadMapArg hm;
-  memcpy(hm.group, sp.head_group, sizeof hm.group);
-  hipLaunchKernelGGL(k_head_map, dim3(1), dim3(kMaxHeads), 0, st, hm, sp.n_heads, p.head_map);
   const int n_all = g.n_groups * g.n_hg;
   const int nw = n_all * g.NW;
   hipLaunchKernelGGL(k_count, dim3(nw), dim3(64), 0, st, g, p);
   hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, st, g, p, caps);
-  hipLaunchKernelGGL(k_fill_union, dim3(n_all), dim3(256), 0, st, g, p, caps);
-  hipLaunchKernelGGL(k_fill_steps, dim3(nw), dim3(64), 0, st, g, p, caps);
+  hipLaunchKernelGGL(k_fill, dim3(nw + n_all), dim3(64), 0, st, g, p, caps, nw);
   return hip_check(hipGetLastError(), "plan builder launch");
 }
 
