@@ -131,12 +131,7 @@ LV_HD Interval win_interval(const Geom& g, int k, int j, int c) {
   return window_interval(g.s[k], g.s[j], c, j < g.n_sink ? -1 : g.rad[k][j]);
 }
 
-// Where the builder takes its intervals from: the arithmetic above (host sizing, and the
-// kernel that writes the device table) or the device table (every other builder kernel).
-struct ArithWin {
-  const Geom& g;
-  LV_HD Interval operator()(int k, int j, int c) const { return win_interval(g, k, j, c); }
-};
+// The builder's kernels take their intervals from the device table, which k_tables fills.
 struct TableWin {        // win[((k * K + j) * smax + c) * 2 + {0, 1}] of one head group
   const int16_t* win; int K, smax;
   LV_HD Interval operator()(int k, int j, int c) const {
@@ -286,112 +281,50 @@ LV_HD void patch_queries(const Geom& g, int k, const PatchExtent& p, int& q_base
     if (n / kPatch < p.ny && n % kPatch < p.nx) valid |= 1u << n;
 }
 
-LV_HD int popcount32(unsigned v) { return __builtin_popcount(v); }
-
-// ---- the serial walk (host sizing; the device runs a wave-cooperative form of it) -------
-// Visits the key list of one patch in order and packs it into steps.  Sink receives
-//   key(step, idx_in_step, upos, token, qmask16)   for every kept key, and
-//   close(step, n_keys, last_upos)                 when a step is complete.
-// qmask16 bit n is set iff query n of the patch keeps the key.
-// A step is closed when it holds 32 keys or when the next key's 2^logS-key block lies more
-// than A blocks after the block of the step's first key (LDS ring constraint).
-template <class Sink>
-struct StepPacker {
-  const Geom& g; Sink& sink;
-  int step = 0, cnt = 0, first_chunk = 0, last_upos = 0;
-  LV_HD void key(int upos, int tok, unsigned qmask) {
-    const int chunk = upos >> g.logS;
-    if (cnt == kStepKeys || (cnt > 0 && chunk - first_chunk > g.A)) { sink.close(step, cnt, last_upos); ++step; cnt = 0; }
-    if (cnt == 0) first_chunk = chunk;
-    sink.key(step, cnt, upos, tok, qmask);
-    ++cnt; last_upos = upos;
-  }
-  LV_HD int finish() {
-    if (cnt > 0) { sink.close(step, cnt, last_upos); ++step; cnt = 0; }
-    return step;
-  }
-};
-
-// number of keys of a group's union list
-template <class Win, class Rad>
-LV_HD int group_union_keys(const Geom& g, const Win& win, const Rad& rad, const GroupExtent& e) {
+// number of keys of a group's union list (band mode)
+template <class Rad>
+LV_HD int band_union_keys(const Geom& g, const Rad& rad, const GroupExtent& e) {
+  const int nk = g.s[e.k] * g.s[e.k];
   int n = 0;
-  if (g.mode == kModeBand) {
-    const int nk = g.s[e.k] * g.s[e.k];
-    for (int p = 0; p < band_parts(e.k); ++p) {
-      const BandPart b = band_part(g, rad, e.k, p);
-      n += band_interval(b, nk, e.qy1).hi - band_interval(b, nk, e.qy0).lo + 1;
-    }
-    return n;
-  }
-  for (int j = 0; j <= e.k; ++j) {
-    const Box b = window_box(win, e.k, j, e.qy0, e.qy1, e.qx0, e.qx1);
-    n += (b.yhi - b.ylo + 1) * (b.xhi - b.xlo + 1);
+  for (int p = 0; p < band_parts(e.k); ++p) {
+    const BandPart b = band_part(g, rad, e.k, p);
+    n += band_interval(b, nk, e.qy1).hi - band_interval(b, nk, e.qy0).lo + 1;
   }
   return n;
 }
 
-// Returns the number of steps.
-template <class Sink>
-inline int walk_patch(const Geom& g, const GroupExtent& e, const PatchExtent& p, Sink& sink) {
-  if (p.ny == 0) return 0;
-  StepPacker<Sink> pack{g, sink};
-  const ArithWin win{g};
-  const ArithRad rad{g};
-  int ubase = 0;
-  if (g.mode == kModeBand) {
-    const int nk = g.s[e.k] * g.s[e.k];
-    for (int pt = 0; pt < band_parts(e.k); ++pt) {
-      const BandPart b = band_part(g, rad, e.k, pt);
-      const int glo = band_interval(b, nk, e.qy0).lo, ghi = band_interval(b, nk, e.qy1).hi;
-      Interval iv[kPatchQueries];
-      for (int n = 0; n < kPatchQueries; ++n) {
-        iv[n].lo = 1; iv[n].hi = 0;
-        if (n < p.nx) iv[n] = band_interval(b, nk, p.y0 + n);
-      }
-      for (int c = iv[0].lo; c <= iv[p.nx - 1].hi; ++c) {
-        unsigned qmask = 0;
-        for (int n = 0; n < kPatchQueries; ++n) qmask |= (unsigned)(c >= iv[n].lo && c <= iv[n].hi) << n;
-        if (qmask) pack.key(ubase + c - glo, b.tok0 + c, qmask);
-      }
-      ubase += ghi - glo + 1;
+// ---- host sizing: the same steps as the device's walk, counted run by run ---------------
+// A step is closed when it holds 32 keys or when the next key's 2^logS-key block lies more
+// than A blocks after the block of the step's first key (LDS ring constraint).
+struct StepCounter {
+  const Geom& g;
+  int steps = 0, cnt = 0, first_block = 0;
+  void run(int upos, int n) {              // n consecutive keys of the union list, all kept by some query
+    while (n > 0) {
+      const int blk = upos >> g.logS;
+      if (cnt == kStepKeys || (cnt > 0 && blk - first_block > g.A)) { ++steps; cnt = 0; }
+      if (cnt == 0) first_block = blk;
+      const int room = ((first_block + g.A + 1) << g.logS) - upos;
+      int take = kStepKeys - cnt < room ? kStepKeys - cnt : room;
+      if (take > n) take = n;
+      cnt += take; upos += take; n -= take;
     }
-    return pack.finish();
   }
-  for (int j = 0; j <= e.k; ++j) {
-    const Box gb = window_box(win, e.k, j, e.qy0, e.qy1, e.qx0, e.qx1);
-    const int gw = gb.xhi - gb.xlo + 1;
-    const Box pb = window_box(win, e.k, j, p.y0, p.y0 + p.ny - 1, p.x0, p.x0 + p.nx - 1);
-    const int sj = g.s[j], offj = g.off[j];
-    const Interval none = {1, 0};
-    Interval rw[kPatch], cw[kPatch];
-    for (int d = 0; d < kPatch; ++d) {
-      rw[d] = d < p.ny ? win(e.k, j, p.y0 + d) : none;
-      cw[d] = d < p.nx ? win(e.k, j, p.x0 + d) : none;
-    }
-    for (int y = pb.ylo; y <= pb.yhi; ++y) {
-      unsigned rb = 0;
-      for (int d = 0; d < kPatch; ++d) rb |= (unsigned)(y >= rw[d].lo && y <= rw[d].hi) << d;
-      if (!rb) continue;
-      const unsigned rowmask = ((rb & 1) ? 0x000fu : 0u) | ((rb & 2) ? 0x00f0u : 0u) |
-                               ((rb & 4) ? 0x0f00u : 0u) | ((rb & 8) ? 0xf000u : 0u);
-      const int urow = ubase + (y - gb.ylo) * gw - gb.xlo, trow = offj + y * sj;
-      for (int x = pb.xlo; x <= pb.xhi; ++x) {
-        unsigned cb = 0;
-        for (int d = 0; d < kPatch; ++d) cb |= (unsigned)(x >= cw[d].lo && x <= cw[d].hi) << d;
-        if (!cb) continue;
-        pack.key(urow + x, trow + x, (cb * 0x1111u) & rowmask);
-      }
-    }
-    ubase += (gb.yhi - gb.ylo + 1) * gw;
-  }
-  return pack.finish();
-}
+  int finish() { if (cnt > 0) { ++steps; cnt = 0; } return steps; }
+};
 
-struct CountSink {
-  int64_t pairs = 0;
-  LV_HD void key(int, int, int, int, unsigned qmask) { pairs += popcount32(qmask); }
-  LV_HD void close(int, int, int) {}
+// What a patch keeps of one axis of a part: its queries' intervals (both ends grow with the
+// query) merged into runs, and their summed length.
+struct AxisSpan {
+  int n_runs = 0, kept = 0;
+  Interval run[kPatchQueries];
+  void add(const Interval& iv) {
+    kept += iv.hi - iv.lo + 1;
+    if (n_runs > 0 && iv.lo <= run[n_runs - 1].hi + 1) { if (iv.hi > run[n_runs - 1].hi) run[n_runs - 1].hi = iv.hi; }
+    else run[n_runs++] = iv;
+  }
+  int lo() const { return run[0].lo; }
+  int hi() const { return run[n_runs - 1].hi; }
 };
 
 }  // namespace lv
