@@ -78,5 +78,7 @@ litevar_status make_attn_args(const litevar_plan* plan, int32_t B, int32_t H, in
 litevar_status launch_attn_f32(const litevar_plan* pl, const AttnArgs& a, hipStream_t st);
 litevar_status launch_attn_bf16(const litevar_plan* pl, const AttnArgs& a, hipStream_t st);
 litevar_status launch_attn_bf16_pair(const litevar_plan* pl, const AttnArgs& a, hipStream_t st);
+litevar_status launch_attn_bf16_dense(const litevar_plan* pl, const AttnArgs& a, hipStream_t st);
+bool takes_dense_kernel(const litevar_plan* pl);
 
 }  // namespace lv
