@@ -263,9 +263,23 @@ litevar_status make_attn_args(const litevar_plan* plan, int32_t B, int32_t H, in
   a.kv_len = plan->kv_len;
   a.hdr = (Header*)(plan->d_blob);
   a.spin_limit = plan->spin_limit > 0 ? plan->spin_limit : kDefaultSpinLimit;
-  a.n_groups_magic = (uint32_t)(((uint64_t)1 << 32) / (uint64_t)(plan->n_groups > 1 ? plan->n_groups : 1) - (plan->n_groups <= 1));
   a.H_magic = (uint32_t)(((uint64_t)1 << 32) / (uint64_t)(H > 1 ? H : 1) - (H <= 1));
   return LITEVAR_OK;
+}
+
+// One XCD per pair reads the pair's K and V into one L2; it is given up where the busiest XCD then has
+// over 15 % more items than with the pairs spread (fewer pairs than XCDs, or a few pairs too many).
+// Windowed, radius 4, (B H, tokens), one XCD per pair / spread: 1, 34 240: 203 / 47 us; 2: 239 / 73; 9: 208 / 136;
+// 12: 211 / 172; 20 (20 % more): 315 / 277; 12, 2240: 33.0 / 26.5.  36, 2240 (11 % more): 32.8 / 35.3.
+int64_t spread_over_xcds(AttnArgs& a, int64_t items) {
+  const int64_t bh = (int64_t)a.B * a.H;
+  int64_t best = 0;
+  for (int ls = 0; ls <= 3; ++ls) {
+    const int64_t part = (items + (1 << ls) - 1) >> ls, rounds = (bh + (8 >> ls) - 1) / (8 >> ls);
+    if (ls == 0 || 115 * part * rounds < 100 * best) { best = part * rounds; a.spread_log = ls; a.part = (int)part; }
+  }
+  a.part_magic = (uint32_t)(((uint64_t)1 << 32) / (uint64_t)a.part - (a.part <= 1));
+  return 8 * best;
 }
 
 }  // namespace lv

@@ -57,12 +57,9 @@ __global__ __launch_bounds__((NW + 1) * 64) __attribute__((amdgpu_waves_per_eu((
   int32_t* const progress = tokring + 2 * TB;   // [NW] phase each compute wave has reached
   int32_t* const landed = progress + 8;         // number of chunks that are in the ring
 
-  // workgroup i runs on XCD i % 8: keep all groups of one (batch, head) on one XCD so
-  // that its K/V are fetched into a single L2
-  const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
-  const int bh = (seq / a.n_groups) * 8 + xcd, grp = seq % a.n_groups;
-  if (bh >= a.B * a.H) return;
-  const int b = bh / a.H, h = bh % a.H;
+  int me, bh, grp, b, h;
+  if (!xcd_item(a, a.n_groups, me, bh, grp)) return;
+  divmod_by((uint32_t)bh, (uint32_t)a.H, a.H_magic, b, h);
   if (!plan_usable(a.hdr)) return;
   const int grp_g = grp + (a.head_map ? a.head_map[h] * a.n_groups : 0);   // the head group's copy of the work-list
   const GroupDesc gd = a.groups[grp_g];
@@ -331,9 +328,8 @@ __global__ __launch_bounds__((NW + 1) * 64) __attribute__((amdgpu_waves_per_eu((
 }
 
 template <int NW, int C, int A, int D, int S>
-static litevar_status launch(const AttnArgs& a, hipStream_t st) {
-  const int64_t bh8 = ((int64_t)a.B * a.H + 7) / 8 * 8;
-  const int64_t blocks = bh8 * a.n_groups;
+static litevar_status launch(AttnArgs a, hipStream_t st) {
+  const int64_t blocks = spread_over_xcds(a, a.n_groups);
   if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large");
   const float c = a.sm_scale * 1.4426950408889634f;
   hipLaunchKernelGGL((k_attn_bf16<NW, C, A, D, S>), dim3((unsigned)blocks), dim3((NW + 1) * 64), 0, st, a, c);

@@ -140,12 +140,8 @@ void k_attn_bf16_pair(AttnArgs a, float c) {
   unsigned char* const Kring = smem;
   unsigned char* const Vring = smem + VOFF;
 
-  // workgroup i runs on XCD i % 8: all groups of one (batch, head) share one L2
-  const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
-  int me, grp, b, h;                      // me: which of the (batch, head) pairs of this XCD
-  divmod_by((uint32_t)seq, (uint32_t)a.n_groups, a.n_groups_magic, me, grp);
-  const int bh = me * 8 + xcd;
-  if (bh >= a.B * a.H) return;
+  int me, grp, bh, b, h;                  // me: which of the (batch, head) pairs of this XCD
+  if (!xcd_item(a, a.n_groups, me, bh, grp)) return;
   divmod_by((uint32_t)bh, (uint32_t)a.H, a.H_magic, b, h);
   // Scalar round trip 1: the header words that say whether the plan may be used at all (a
   // zeroed, stale or half-built blob makes the launch a no-op) and, for plans with a radius
@@ -588,11 +584,11 @@ void k_attn_bf16_pair(AttnArgs a, float c) {
   if constexpr (PW == 2) store_patch(B, pwB);
 }
 
-litevar_status launch_attn_bf16_pair(const litevar_plan* pl, const AttnArgs& a, hipStream_t st) {
+litevar_status launch_attn_bf16_pair(const litevar_plan* pl, const AttnArgs& args, hipStream_t st) {
   if (pl->waves_per_group != 16 || pl->chunk_keys != kDmaKeys || pl->ring_chunks != kRingChunks)
     return fail(LITEVAR_E_PLAN_CORRUPT, "no 16-patch kernel for chunk=%d ring=%d", pl->chunk_keys, pl->ring_chunks);
-  const int64_t bh8 = ((int64_t)a.B * a.H + 7) / 8 * 8;
-  const int64_t blocks = bh8 * a.n_groups;
+  AttnArgs a = args;
+  const int64_t blocks = spread_over_xcds(a, a.n_groups);
   if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large");
   // One patch per wave when the launch has no more working workgroups than the GPU has CUs
   // (with output sharing about half of them exit at once): sixteen waves then fill the CU that

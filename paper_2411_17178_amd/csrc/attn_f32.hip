@@ -36,12 +36,10 @@ constexpr float kF32Floor = -3.402823466e+38f;   // softmax reference of a query
 __global__ __launch_bounds__(kF32Waves * 64) void k_attn_f32(AttnArgs a, int n_waves) {
   __shared__ __align__(16) f32x4 part_o[kF32Waves][4][64];
   __shared__ float part_m[kF32Waves][16], part_l[kF32Waves][16];
-  // workgroup i runs on XCD i % 8: all patches of one (batch, head) share one L2
-  const int seq = blockIdx.x >> 3;
-  const int bh = (seq / n_waves) * 8 + (int)(blockIdx.x & 7), wv = seq % n_waves;
-  if (bh >= a.B * a.H) return;
+  int me, bh, wv, b, h;
+  if (!xcd_item(a, n_waves, me, bh, wv)) return;
   if (!plan_usable(a.hdr)) return;
-  const int b = bh / a.H, h = bh % a.H;
+  divmod_by((uint32_t)bh, (uint32_t)a.H, a.H_magic, b, h);
   const WaveDesc wd = a.waves[wv + (a.head_map ? a.head_map[h] * n_waves : 0)];   // the head group's patches
   if (wd.ny == 0) return;
   const bool shared = a.cfg_share && a.cfg_share[h * a.n_scales + wd.kq];
@@ -155,9 +153,10 @@ __global__ __launch_bounds__(kF32Waves * 64) void k_attn_f32(AttnArgs a, int n_w
   if (shared) *(f32x4*)(o + (a.B / 2) * a.os[0]) = acc;
 }
 
-litevar_status launch_attn_f32(const litevar_plan* pl, const AttnArgs& a, hipStream_t st) {
+litevar_status launch_attn_f32(const litevar_plan* pl, const AttnArgs& args, hipStream_t st) {
+  AttnArgs a = args;
   const int64_t n_waves = (int64_t)pl->n_groups * pl->waves_per_group;
-  const int64_t blocks = n_waves * (((int64_t)a.B * a.H + 7) / 8 * 8);
+  const int64_t blocks = spread_over_xcds(a, n_waves);
   if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large for the fp32 path");
   hipLaunchKernelGGL(k_attn_f32, dim3((unsigned)blocks), dim3(kF32Waves * 64), 0, st, a, (int)n_waves);
   return hip_check(hipGetLastError(), "fp32 attention launch");

@@ -64,10 +64,17 @@ struct AttnArgs {
   // 8-bit operands (Section 4): q, k, v then hold int8 codes (strides in codes) and these the
   // (scale, zero point) of every token row, packed [B][H][len]; nullptr for bf16 / fp32 operands
   const float2* q_sz; const float2* k_sz; const float2* v_sz;
-  // floor(2^32 / n) for n = n_groups and n = H: a workgroup's index is taken apart with two
+  // floor(2^32 / n) for n = part and n = H: a workgroup's index is taken apart with two
   // multiplications instead of two divisions by run-time values (see divmod_by in the kernels' header)
-  uint32_t n_groups_magic, H_magic;
+  uint32_t part_magic, H_magic;
+  int part, spread_log;          // see spread_over_xcds
 };
+
+// Which workgroup does what: workgroup i runs on XCD i % 8, each with an L2 of its own.  The work
+// items (groups or patches) of one (batch, head) pair are dealt to 2^spread_log neighbouring XCDs, `part`
+// of them to each; see xcd_item in the kernels' header.  Fills a.spread_log, a.part and a.part_magic and
+// returns the number of workgroups.
+int64_t spread_over_xcds(AttnArgs& a, int64_t items);
 
 // Checks what every attention entry point checks (plan, batch and head counts, softmax scale,
 // flags) and fills the fields of `a` that come from the plan and from these arguments; the
