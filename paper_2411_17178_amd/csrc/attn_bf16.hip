@@ -332,8 +332,10 @@ static litevar_status launch(AttnArgs a, hipStream_t st) {
   const int64_t blocks = spread_over_xcds(a, a.n_groups);
   if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large");
   const float c = a.sm_scale * 1.4426950408889634f;
-  hipLaunchKernelGGL((k_attn_bf16<NW, C, A, D, S>), dim3((unsigned)blocks), dim3((NW + 1) * 64), 0, st, a, c);
-  return hip_check(hipGetLastError(), "bf16 attention launch");
+  return launch_in_parts(blocks, (NW + 1) * 64, "bf16 attention launch", [&](int64_t first, unsigned n) {
+    a.first_block = (uint32_t)first;
+    hipLaunchKernelGGL((k_attn_bf16<NW, C, A, D, S>), dim3(n), dim3((NW + 1) * 64), 0, st, a, c);
+  });
 }
 
 litevar_status launch_attn_bf16(const litevar_plan* pl, const AttnArgs& a, hipStream_t st) {

@@ -82,9 +82,10 @@ __device__ inline void divmod_by(uint32_t x, uint32_t n, uint32_t magic, int& q,
 // The work item of this workgroup (the host's spread_over_xcds): item `item` of pair bh, which is the
 // me-th pair of its XCDs.  false: none.
 __device__ inline bool xcd_item(const AttnArgs& a, int items, int& me, int& bh, int& item) {
-  const int xcd = blockIdx.x & 7;
+  const uint32_t block = a.first_block + blockIdx.x;
+  const int xcd = block & 7;
   int in_part;
-  divmod_by(blockIdx.x >> 3, (uint32_t)a.part, a.part_magic, me, in_part);
+  divmod_by(block >> 3, (uint32_t)a.part, a.part_magic, me, in_part);
   bh = me * (8 >> a.spread_log) + (xcd >> a.spread_log);
   item = (in_part << a.spread_log) + (xcd & ((1 << a.spread_log) - 1));
   return bh < a.B * a.H && item < items;

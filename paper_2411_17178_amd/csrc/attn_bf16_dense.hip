@@ -69,7 +69,7 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
   // (Measured against all tiles of a pair on one XCD: 2 pairs of 34 240 tokens 1660 -> 626 us, 288 of
   // 2240 tokens 324 -> 300 us, 480 of 680 tokens 73 -> 67 us, 16 of 34 240 tokens no change.)
   int tile, bh, b, h;
-  divmod_by(blockIdx.x, (uint32_t)(a.B * a.H), d.bh_magic, tile, bh);
+  divmod_by(a.first_block + blockIdx.x, (uint32_t)(a.B * a.H), d.bh_magic, tile, bh);
   divmod_by((uint32_t)bh, (uint32_t)a.H, a.H_magic, b, h);
   if (!plan_usable(a.hdr)) return;
 
@@ -287,10 +287,11 @@ litevar_status launch_attn_bf16_dense(const litevar_plan* pl, const AttnArgs& a,
   if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large");
   d.bh_magic = (uint32_t)(((uint64_t)1 << 32) / (uint64_t)BH - (BH <= 1));
   const float c = a.sm_scale * 1.4426950408889634f;
-  const dim3 grid((unsigned)blocks), wg(nwv * 64);
-  if (nwv == 8) hipLaunchKernelGGL(k_attn_bf16_dense<8>, grid, wg, 0, st, d, c);
-  else hipLaunchKernelGGL(k_attn_bf16_dense<4>, grid, wg, 0, st, d, c);
-  return hip_check(hipGetLastError(), "dense bf16 attention launch");
+  return launch_in_parts(blocks, nwv * 64, "dense bf16 attention launch", [&](int64_t first, unsigned n) {
+    d.a.first_block = (uint32_t)first;
+    if (nwv == 8) hipLaunchKernelGGL(k_attn_bf16_dense<8>, dim3(n), dim3(nwv * 64), 0, st, d, c);
+    else hipLaunchKernelGGL(k_attn_bf16_dense<4>, dim3(n), dim3(nwv * 64), 0, st, d, c);
+  });
 }
 
 }  // namespace lv

@@ -607,12 +607,14 @@ litevar_status launch_attn_bf16_pair(const litevar_plan* pl, const AttnArgs& arg
   }
   const float c = a.sm_scale * 1.4426950408889634f;
   const bool q8 = a.k_sz != nullptr;
-  const dim3 grid((unsigned)blocks), wg1(kGroupPatches * 64), wg2(kGroupPatches / 2 * 64);
-  if (pw == 1 && q8) hipLaunchKernelGGL((k_attn_bf16_pair<1, true>), grid, wg1, 0, st, a, c);
-  else if (pw == 1) hipLaunchKernelGGL((k_attn_bf16_pair<1, false>), grid, wg1, 0, st, a, c);
-  else if (q8) hipLaunchKernelGGL((k_attn_bf16_pair<2, true>), grid, wg2, 0, st, a, c);
-  else hipLaunchKernelGGL((k_attn_bf16_pair<2, false>), grid, wg2, 0, st, a, c);
-  return hip_check(hipGetLastError(), "bf16 attention launch");
+  const dim3 wg(kGroupPatches / pw * 64);
+  return launch_in_parts(blocks, (int)wg.x, "bf16 attention launch", [&](int64_t first, unsigned n) {
+    a.first_block = (uint32_t)first;
+    if (pw == 1 && q8) hipLaunchKernelGGL((k_attn_bf16_pair<1, true>), dim3(n), wg, 0, st, a, c);
+    else if (pw == 1) hipLaunchKernelGGL((k_attn_bf16_pair<1, false>), dim3(n), wg, 0, st, a, c);
+    else if (q8) hipLaunchKernelGGL((k_attn_bf16_pair<2, true>), dim3(n), wg, 0, st, a, c);
+    else hipLaunchKernelGGL((k_attn_bf16_pair<2, false>), dim3(n), wg, 0, st, a, c);
+  });
 }
 
 }  // namespace lv

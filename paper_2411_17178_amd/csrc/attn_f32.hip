@@ -158,8 +158,10 @@ litevar_status launch_attn_f32(const litevar_plan* pl, const AttnArgs& args, hip
   const int64_t n_waves = (int64_t)pl->n_groups * pl->waves_per_group;
   const int64_t blocks = spread_over_xcds(a, n_waves);
   if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large for the fp32 path");
-  hipLaunchKernelGGL(k_attn_f32, dim3((unsigned)blocks), dim3(kF32Waves * 64), 0, st, a, (int)n_waves);
-  return hip_check(hipGetLastError(), "fp32 attention launch");
+  return launch_in_parts(blocks, kF32Waves * 64, "fp32 attention launch", [&](int64_t first, unsigned n) {
+    a.first_block = (uint32_t)first;
+    hipLaunchKernelGGL(k_attn_f32, dim3(n), dim3(kF32Waves * 64), 0, st, a, (int)n_waves);
+  });
 }
 
 }  // namespace lv

@@ -68,7 +68,21 @@ struct AttnArgs {
   // multiplications instead of two divisions by run-time values (see divmod_by in the kernels' header)
   uint32_t part_magic, H_magic;
   int part, spread_log;          // see spread_over_xcds
+  uint32_t first_block;          // of this launch: see launch_in_parts
 };
+
+// A launch holds fewer than 2^32 threads (its size is kept in 32 bits; more of them wrap without an error),
+// so a call that needs more is cut into several.  Parts are multiples of eight workgroups, which leaves
+// every workgroup on its XCD.  launch(first workgroup, number of workgroups) enqueues one part.
+template <class Launch>
+inline litevar_status launch_in_parts(int64_t blocks, int threads, const char* what, Launch launch) {
+  const int64_t most = (((int64_t)1 << 32) / threads - 1) & ~(int64_t)7;
+  for (int64_t first = 0; first < blocks; first += most) {
+    launch(first, (unsigned)(blocks - first < most ? blocks - first : most));
+    if (litevar_status s = hip_check(hipGetLastError(), what)) return s;
+  }
+  return LITEVAR_OK;
+}
 
 // Which workgroup does what: workgroup i runs on XCD i % 8, each with an L2 of its own.  The work
 // items (groups or patches) of one (batch, head) pair are dealt to 2^spread_log neighbouring XCDs, `part`

@@ -1,0 +1,26 @@
+"""Calls whose work exceeds what one launch may hold (fewer than 2^32 threads)."""
+import pytest
+import torch
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+# dtype, waves per group, scales, pairs of heads: each needs 2^32 threads or a little more; the inputs are
+# broadcast over the batch (stride 0)
+@pytest.mark.parametrize("dtype,waves,scales,batch", [
+    ("f32", 0, (1, 1), 131073),                             # 8 patches x 256 threads
+    ("bf16", 4, (1,), 838865), ("bf16", 8, (1,), 466040),   # one group of 320 or 576 threads
+    ("bf16", (16, 0, 0, -1, 1), (1,), 262145), ("bf16", (16, 0, 0, -1, 2), (1,), 524289),
+    ("bf16", 0, (1,) * 17, 174765)])                        # all pairs kept: 3 tiles x 512 threads
+def test_attention_of_more_threads_than_one_launch_holds(dtype, waves, scales, batch):
+    import paper_2411_17178_amd as lv
+    H = 16
+    print(f"  {dtype} waves={waves} scales={scales} pairs={batch * H}", flush=True)
+    plan = lv.litevar_mask_build(scales, -1, waves_per_group=waves)
+    q, k, v = (t.cuda() for t in workloads.make_qkv(scales, 1, H, 64, dtype, 3, 1.0, None))
+    want = lv.litevar_windowed_attn_fwd(plan, q, k, v, 0.125)
+    out = torch.full((batch, H, len(scales), 64), 9.0, dtype=q.dtype, device="cuda")
+    lv.litevar_windowed_attn_fwd(plan, *(t.expand(batch, -1, -1, -1) for t in (q, k, v)), 0.125, out=out)
+    assert bool(out.eq(want).all())
