@@ -68,10 +68,12 @@ inline void stream_plan(StreamGeom& g, int lead, MaxSplits max_splits) {
 
 struct StreamTask { int h, k, ja, jb, split, i0, i1, col0, ncols; };   // key scales [ja, jb), rows [i0, i1)
 
+// (grid (heads, slots): a one-dimensional one would pass 2^32 threads, where launches wrap without an
+// error, at 65 535 heads and 256 slots; workgroups start in the order of x)
 __device__ inline StreamTask stream_task(const StreamGeom& g) {
   StreamTask t;
-  const int slot = (int)(blockIdx.x / (unsigned)g.H);
-  t.h = (int)blockIdx.x - slot * g.H;
+  const int slot = (int)blockIdx.y;
+  t.h = (int)blockIdx.x;
   const int lane = threadIdx.x & 63;
   const bool started = lane < g.K && g.slot_begin[min(lane, g.K)] <= slot;
   const int i = __builtin_amdgcn_readfirstlane(__builtin_popcountll(__ballot(started)) - 1);

@@ -170,7 +170,7 @@ struct WindowWalk {
   }
 };
 
-// grid: slots x heads, the slots with the most work first
+// grid (heads, slots), the slots with the most work first
 template <int NB>
 __global__ __launch_bounds__(kStreamThreads) void k_calib_stream(StreamGeom g, double* partial, int slots_per_part, int smax) {
   extern __shared__ __align__(16) unsigned char calib_smem[];
@@ -393,14 +393,12 @@ litevar_status calibrate_with(CalibArgs& a, const float* d_attn, int32_t N, int3
     g.off[a.K] = a.off[a.K];
     stream_plan(g, 1, [&](int) { return a.splits * a.max_tiles; });
     for (int k = 0; k < a.K; ++k) a.stream_splits[k] = g.splits[k];
-    const int64_t blocks = g.slot_begin[a.K] * (int64_t)H;
-    if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large");
     const size_t lds = (size_t)4 * g.entries * sizeof(double) + (size_t)a.K * a.smax * sizeof(short);
     const auto kernel = stream_pick(N, k_calib_stream<1>, k_calib_stream<2>, k_calib_stream<4>, k_calib_stream<8>);
     if (lds > 64 * 1024)     // (beyond the default limit of dynamically sized LDS; no allocation involved)
       if (litevar_status s = hip_check(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                            (int)lds), "hipFuncSetAttribute")) return s;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kStreamThreads), lds, st, g, a.partial,
+    hipLaunchKernelGGL(kernel, dim3(H, g.slot_begin[a.K]), dim3(kStreamThreads), lds, st, g, a.partial,
                        a.splits * a.max_tiles, a.smax);
   } else {
     hipLaunchKernelGGL(k_calib_mass, dim3(a.n_slots, 1, H), dim3(kCalibThreads), 0, st, a);

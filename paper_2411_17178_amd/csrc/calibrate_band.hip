@@ -68,7 +68,7 @@ struct BandWalk {
   }
 };
 
-// grid: slots x heads, the slots with the most work first.
+// grid (heads, slots), the slots with the most work first.
 // Measured (8 samples x 30 heads x 680^2): 56 us, 4.9 TB/s of the block-causal values; the former
 // kernel, one lane per signed offset (half of them idle in any row) and one load at a time, took 243 us.
 // k_band_pick: 15 us, 46 us before (one thread did the prefix and the 64-bit divisions one by one).
@@ -199,14 +199,12 @@ litevar_status litevar_window_calibrate_band(const int32_t* scales, int32_t n_sc
   if (workspace_bytes < need) return fail(LITEVAR_E_INVALID_ARG, "workspace of %zu bytes, %zu needed", workspace_bytes, need);
   a.g.N = N; a.g.p = d_attn; a.partial = (double*)d_workspace; a.radius = d_radius; a.mass = d_mass; a.r0 = (double)r0;
   hipStream_t st = (hipStream_t)stream;
-  const int64_t blocks = a.g.slot_begin[a.g.K] * (int64_t)H;
-  if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large");
   const size_t lds = (size_t)2 * a.g.entries * sizeof(double);
   const auto kernel = stream_pick(N, k_band_stream<1>, k_band_stream<2>, k_band_stream<4>, k_band_stream<8>);
   if (lds > 64 * 1024)       // (beyond the default limit of dynamically sized LDS; no allocation involved)
     if (litevar_status s = hip_check(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                          (int)lds), "hipFuncSetAttribute")) return s;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kStreamThreads), lds, st, a);
+  hipLaunchKernelGGL(kernel, dim3(H, a.g.slot_begin[a.g.K]), dim3(kStreamThreads), lds, st, a);
   if (litevar_status s = hip_check(hipGetLastError(), "band calibration mass launch")) return s;
   hipLaunchKernelGGL(k_band_pick, dim3(a.n_parts, H), dim3(kBandThreads), 0, st, a);
   return hip_check(hipGetLastError(), "band calibration pick launch");

@@ -24,3 +24,20 @@ def test_attention_of_more_threads_than_one_launch_holds(dtype, waves, scales, b
     out = torch.full((batch, H, len(scales), 64), 9.0, dtype=q.dtype, device="cuda")
     lv.litevar_windowed_attn_fwd(plan, *(t.expand(batch, -1, -1, -1) for t in (q, k, v)), 0.125, out=out)
     assert bool(out.eq(want).all())
+
+
+@pytest.mark.parametrize("band", [False, True])
+def test_calibration_of_more_threads_than_one_launch_holds(band):
+    """65 535 heads x 262 slots x 256 threads, a map of 138 GB: every head has the same (uniform) map."""
+    import paper_2411_17178_amd as lv
+    scales, H = (1, 1, 1, 12, 11, 12, 11, 13) + (1,) * 24, 65535
+    L = sum(s * s for s in scales)
+    if torch.cuda.mem_get_info()[0] < 240e9:
+        pytest.skip("needs 240 GB of free GPU memory")
+    calibrate = lv.litevar_window_calibrate_band if band else lv.litevar_window_calibrate
+    want = calibrate(scales, torch.ones((1, 1, L, L), device="cuda"), 0.8)
+    print(f"  band={band} heads={H} L={L}", flush=True)
+    got = calibrate(scales, torch.ones((1, H, L, L), device="cuda"), 0.8)
+    assert torch.equal(got, want.expand_as(got))
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
