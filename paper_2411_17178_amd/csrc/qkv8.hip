@@ -126,13 +126,17 @@ litevar_status litevar_qkv8_quantize(const void* d_x, litevar_dtype dt, int64_t 
   const int64_t blocks = (rows + 31) / 32;
   if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large");
   hipStream_t st = (hipStream_t)stream;
-  if (dt == LITEVAR_BF16)
-    hipLaunchKernelGGL(k_quantize_rows<__bf16>, dim3((unsigned)blocks), dim3(256), 0, st, (const __bf16*)d_x, rows,
-                       row_stride, d_codes, (float2*)d_scale_zero);
-  else
-    hipLaunchKernelGGL(k_quantize_rows<float>, dim3((unsigned)blocks), dim3(256), 0, st, (const float*)d_x, rows,
-                       row_stride, d_codes, (float2*)d_scale_zero);
-  return hip_check(hipGetLastError(), "quantiser launch");
+  return launch_in_parts(blocks, 256, "quantiser launch", [&](int64_t first, unsigned n) {
+    const int64_t r0 = 32 * first;
+    int8_t* codes = d_codes + r0 * D;
+    float2* sz = (float2*)d_scale_zero + r0;
+    if (dt == LITEVAR_BF16)
+      hipLaunchKernelGGL(k_quantize_rows<__bf16>, dim3(n), dim3(256), 0, st, (const __bf16*)d_x + r0 * row_stride,
+                         rows - r0, row_stride, codes, sz);
+    else
+      hipLaunchKernelGGL(k_quantize_rows<float>, dim3(n), dim3(256), 0, st, (const float*)d_x + r0 * row_stride,
+                         rows - r0, row_stride, codes, sz);
+  });
 }
 
 litevar_status litevar_qkv8_dequantize(const int8_t* d_codes, const float* d_scale_zero, int64_t rows, int32_t D,
@@ -145,9 +149,11 @@ litevar_status litevar_qkv8_dequantize(const int8_t* d_codes, const float* d_sca
   if (rows == 0) return LITEVAR_OK;
   const int64_t blocks = (rows + 31) / 32;
   if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large");
-  hipLaunchKernelGGL(k_dequantize_rows, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, d_codes,
-                     (const float2*)d_scale_zero, rows, (__bf16*)d_out_bf16);
-  return hip_check(hipGetLastError(), "dequantiser launch");
+  return launch_in_parts(blocks, 256, "dequantiser launch", [&](int64_t first, unsigned n) {
+    const int64_t r0 = 32 * first;
+    hipLaunchKernelGGL(k_dequantize_rows, dim3(n), dim3(256), 0, (hipStream_t)stream, d_codes + r0 * D,
+                       (const float2*)d_scale_zero + r0, rows - r0, (__bf16*)d_out_bf16 + r0 * D);
+  });
 }
 
 // Plans whose groups hold 16 patches can be served by the attention kernel's own 8-bit form,

@@ -41,3 +41,24 @@ def test_calibration_of_more_threads_than_one_launch_holds(band):
     assert torch.equal(got, want.expand_as(got))
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
+
+
+def test_quantiser_of_more_rows_than_one_launch_holds():
+    """2^29 + 70 rows, eight threads each: rows at both ends and where a second launch begins."""
+    import paper_2411_17178_amd as lv
+    rows, n = 2 ** 29 + 70, 200
+    if torch.cuda.mem_get_info()[0] < 190e9:
+        pytest.skip("needs 190 GB of free GPU memory")
+    x = torch.zeros((rows, 64), dtype=torch.bfloat16, device="cuda")
+    some = [slice(0, n), slice(2 ** 28, 2 ** 28 + n), slice(2 ** 29 - 2 * n, 2 ** 29 - n), slice(rows - n, rows)]
+    for i, at in enumerate(some):
+        x[at] = torch.randn((n, 64), generator=torch.Generator(device="cuda").manual_seed(i), device="cuda")
+    codes, sz = lv.litevar_qkv8_quantize(x)
+    back = lv.litevar_qkv8_dequantize(codes, sz)
+    for at in some:
+        want = lv.litevar_qkv8_quantize(x[at].contiguous())
+        assert torch.equal(codes[at], want[0]) and torch.equal(sz[at], want[1])
+        assert torch.equal(back[at], lv.litevar_qkv8_dequantize(*want))
+    torch.cuda.synchronize()
+    del x, codes, sz, back
+    torch.cuda.empty_cache()
