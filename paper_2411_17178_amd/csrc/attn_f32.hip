@@ -2,9 +2,9 @@
 // Section 2 of the paper: softmax over the kept keys only.  fp32 operands, products, sums and
 // exponentials throughout.
 //
-// One workgroup = four waves = one query patch of one (batch, head); wave w takes the patch's
-// 32-key steps w, w + 4, ... (the plan's steps and lane masks, as the bf16 kernels walk them) and
-// the four partial results are merged through LDS at the end.  The products run on
+// One workgroup = four waves (one, where every patch has a single step) = one query patch of one
+// (batch, head); wave w takes the patch's 32-key steps w, w + 4, ... (the plan's steps and lane masks, as
+// the bf16 kernels walk them) and the four partial results are merged through LDS at the end.  The products run on
 // v_mfma_f32_16x16x4_f32, straight from global memory: nothing of K or V is shared between the
 // waves of a workgroup, and the operand order can be chosen so that every load is a 16-byte piece
 // of a row and no value has to move between lanes:
@@ -19,7 +19,7 @@
 // Bound: a step is 64 MFMAs of 32 cycles (2048 cycles of a SIMD's matrix pipe) against 16 KB of
 // gathered rows; four waves per patch, because the accuracy workloads have few patches (57 per
 // (batch, head) at 680 tokens) and the longest one would otherwise be a chain of eleven steps.
-// 680 tokens, 32 (batch, head) pairs, radius 2: 30 us a call (one wave per patch with scalar dot
+// 680 tokens, 32 (batch, head) pairs, radius 2: 30.3 us a call (one wave per patch with scalar dot
 // products and a shuffle per key: 233 us); the matrix pipe's share is 8 us, the rest is the chain
 // descriptor -> tokens -> rows -> MFMAs of two rounds of workgroups.
 #include "attn_bf16_common.h"
@@ -28,7 +28,6 @@ namespace lv {
 
 namespace {
 
-constexpr int kF32Waves = 4;            // waves per patch
 constexpr float kF32Floor = -3.402823466e+38f;   // softmax reference of a query without a kept key so far
 
 // (on the bits, behind a barrier for the optimiser: the build lets it assume that no value is NaN)
@@ -40,9 +39,9 @@ __device__ inline bool not_finite(float x) {
 
 }  // namespace
 
-__global__ __launch_bounds__(kF32Waves * 64) void k_attn_f32(AttnArgs a, int n_waves) {
-  __shared__ __align__(16) f32x4 part_o[kF32Waves][4][64];
-  __shared__ float part_m[kF32Waves][16], part_l[kF32Waves][16];
+// W = waves per patch, 4 or 1
+template <int W>
+__global__ __launch_bounds__(W * 64) void k_attn_f32(AttnArgs a, int n_waves) {
   int me, bh, wv, b, h;
   if (!xcd_item(a, n_waves, me, bh, wv)) return;
   if (!plan_usable(a.hdr)) return;
@@ -79,7 +78,7 @@ __global__ __launch_bounds__(kF32Waves * 64) void k_attn_f32(AttnArgs a, int n_w
     return Tokens{{t[n], t[16 + n]}, {*(const int4*)(t + 4 * g4), *(const int4*)(t + 16 + 4 * g4)}};
   };
   Tokens tok = load_tokens(wave);
-  for (int s = wave; s < n_steps; s += kF32Waves) {
+  for (int s = wave; s < n_steps; s += W) {
     // (padding keys carry token -1; they read the row of the step's first key, which every step has)
     const int first = __builtin_amdgcn_readfirstlane(tok.k[0]);
     auto row = [&](int t) -> unsigned {
@@ -102,7 +101,7 @@ __global__ __launch_bounds__(kF32Waves * 64) void k_attn_f32(AttnArgs a, int n_w
     uint64_t keep[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) keep[e] = mk[e];
-    tok = load_tokens(s + kF32Waves);
+    tok = load_tokens(s + W);
 
     f32x4 S[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
@@ -135,34 +134,50 @@ __global__ __launch_bounds__(kF32Waves * 64) void k_attn_f32(AttnArgs a, int n_w
         O[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[e >> 2][e & 3][dt], z[e], O[dt], 0, 0, 0);
   }
 
-  // ---- merge the four waves: wave w forms the head dimensions 16 g4 + 4 w .. + 3 of query n ----
+  // ---- the head dimensions 16 g4 + 4 c .. + 3 of query n, c = 4 / W of 0..3: merged from the four waves, or its own
+  constexpr int kPieces = 4 / W;
+  f32x4 acc[kPieces];
+  float sum = 0.f;
   l += __shfl_xor(l, 16);
   l += __shfl_xor(l, 32);
+  if constexpr (W == 4) {
+    __shared__ __align__(16) f32x4 part_o[W][4][64];
+    __shared__ float part_m[W][16], part_l[W][16];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) part_o[wave][i][lane] = f32x4{O[0][i], O[1][i], O[2][i], O[3][i]};
-  if (g4 == 0) { part_m[wave][n] = m; part_l[wave][n] = l; }
-  __syncthreads();
-  float m_all = part_m[0][n];
+    for (int i = 0; i < 4; ++i) part_o[wave][i][lane] = f32x4{O[0][i], O[1][i], O[2][i], O[3][i]};
+    if (g4 == 0) { part_m[wave][n] = m; part_l[wave][n] = l; }
+    __syncthreads();
+    float m_all = part_m[0][n];
 #pragma unroll
-  for (int w = 1; w < kF32Waves; ++w) m_all = fmaxf(m_all, part_m[w][n]);
-  float sum = 0.f;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int w = 1; w < W; ++w) m_all = fmaxf(m_all, part_m[w][n]);
+    acc[0] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int w = 0; w < kF32Waves; ++w) {
-    const float f = expf(part_m[w][n] - m_all);
-    sum = fmaf(part_l[w][n], f, sum);
-    acc += part_o[w][wave][lane] * f;
+    for (int w = 0; w < W; ++w) {
+      const float f = expf(part_m[w][n] - m_all);
+      sum = fmaf(part_l[w][n], f, sum);
+      acc[0] += part_o[w][wave][lane] * f;
+    }
+  } else {
+    sum = l;
+#pragma unroll
+    for (int c = 0; c < kPieces; ++c) acc[c] = f32x4{O[0][c], O[1][c], O[2][c], O[3][c]};
   }
-  acc *= 1.f / sum;
+  float any = 0.f;
+#pragma unroll
+  for (int c = 0; c < kPieces; ++c) {
+    acc[c] *= 1.f / sum;
+    any += (acc[c][0] + acc[c][1]) + (acc[c][2] + acc[c][3]);
+  }
 
   // The matrix products multiply the V rows of a step with the probability 0 of every query that does not
   // keep them, so a value of V that is not finite makes all queries of its step NaN.  A wave that finds such a
   // result forms its head dimensions once more, key by key, from the kept pairs only.  (680 tokens, 32 pairs:
   // the test costs 0.3 us of 30.)
-  const bool again = qrow >= 0 && not_finite((acc[0] + acc[1]) + (acc[2] + acc[3]));
+  const bool again = qrow >= 0 && not_finite(any);
   if (__builtin_amdgcn_ballot_w64(again) != 0) {
     m = kF32Floor; l = 0.f;
-    acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < kPieces; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int64_t q_at = max(qrow, 0) * a.qs[2] + 4 * g4;   // (Q from memory: its registers are free by now)
     for (int64_t e = S0 * kStepKeys; e < (S0 + n_steps) * kStepKeys; ++e) {
       const int t = a.step_tok[e];
@@ -180,30 +195,44 @@ __global__ __launch_bounds__(kF32Waves * 64) void k_attn_f32(AttnArgs a, int n_w
       const int r = (int)e & 15;
       const uint64_t keep = a.step_mask[(e >> 5) * 8 + 4 * ((e >> 4) & 1) + (r & 3)] >> ((r >> 2) * 16);
       if ((keep >> n) & 1) {
-        const f32x4 vr = *(const f32x4*)(Vp + (o + 48u * (unsigned)g4 + 16u * (unsigned)wave));
         const float z = dot * a.sm_scale, m_new = fmaxf(m, z), alpha = expf(m - m_new), p = expf(z - m_new);
         l = fmaf(l, alpha, p);
         m = m_new;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[i] = fmaf(p, vr[i], acc[i] * alpha);
+        for (int c = 0; c < kPieces; ++c) {
+          const f32x4 vr = *(const f32x4*)(Vp + (o + 48u * (unsigned)g4 + 16u * (unsigned)(wave + c)));
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[c][i] = fmaf(p, vr[i], acc[c][i] * alpha);
+        }
       }
     }
-    acc *= 1.f / l;
+#pragma unroll
+    for (int c = 0; c < kPieces; ++c) acc[c] *= 1.f / l;
   }
   if (qrow < 0) return;
   float* o = (float*)a.o + b * a.os[0] + h * a.os[1] + qrow * a.os[2] + 16 * g4 + 4 * wave;
-  *(f32x4*)o = acc;
-  if (shared) *(f32x4*)(o + (a.B / 2) * a.os[0]) = acc;
+#pragma unroll
+  for (int c = 0; c < kPieces; ++c) {
+    *(f32x4*)(o + 4 * c) = acc[c];
+    if (shared) *(f32x4*)(o + 4 * c + (a.B / 2) * a.os[0]) = acc[c];
+  }
 }
 
 litevar_status launch_attn_f32(const litevar_plan* pl, const AttnArgs& args, hipStream_t st) {
   AttnArgs a = args;
+  // Patches of one step each leave three of four waves without work, and a launch of many such patches is
+  // as long as it takes to start its waves.  Pairs x 14 tokens (scales 1, 2, 3), one wave per patch with scalar
+  // dot products / four waves / one wave: 480: 23.3 / 25.6 / 13.5 us; 3000: 119 / 152 / 63; 100 000: 4346 / 6083 /
+  // 2125.  (One token per pair: 480: 6.3 / 10.0 / 6.3; 3000: 15.4 / 46.3 / 22.4.)  With more steps four waves shorten
+  // the chain of the launch's longest patch: 85 tokens at 8 pairs 5.4 us, 6.4 with one wave.
+  const int W = pl->n_steps <= (int64_t)pl->n_patches * pl->n_head_groups ? 1 : 4;
   const int64_t n_waves = (int64_t)pl->n_groups * pl->waves_per_group;
   const int64_t blocks = spread_over_xcds(a, n_waves);
   if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large for the fp32 path");
-  return launch_in_parts(blocks, kF32Waves * 64, "fp32 attention launch", [&](int64_t first, unsigned n) {
+  return launch_in_parts(blocks, W * 64, "fp32 attention launch", [&](int64_t first, unsigned n) {
     a.first_block = (uint32_t)first;
-    hipLaunchKernelGGL(k_attn_f32, dim3(n), dim3(kF32Waves * 64), 0, st, a, (int)n_waves);
+    if (W == 1) hipLaunchKernelGGL(k_attn_f32<1>, dim3(n), dim3(64), 0, st, a, (int)n_waves);
+    else hipLaunchKernelGGL(k_attn_f32<4>, dim3(n), dim3(256), 0, st, a, (int)n_waves);
   });
 }
 

@@ -10,8 +10,9 @@ import workloads
 pytestmark = pytest.mark.gpu
 
 
-# the key: one that several patches keep in part (windows), the first of a step with padding (it fills it)
-@pytest.mark.parametrize("scales,radius,key", [((1, 2, 3, 5, 8), 1, 45), ((1, 2, 3, 5, 8), 1, 70), ((2, 9), 0, 40),
+# the key: one that several patches keep in part (windows), the first of a step with padding (it fills it), one
+# of a plan with a single step per patch
+@pytest.mark.parametrize("scales,radius,key", [((1, 2, 3, 5, 8), 1, 45), ((1, 2, 3, 5, 8), 1, 70), ((2, 9), 0, 40), ((1, 2, 3), 0, 7),
                                                ((1, 2, 3, 4, 5, 6, 8, 10, 13, 16), 2, 300), ((3, 17), 2, 9)])
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
 def test_value_row_that_is_not_finite(scales, radius, key, value):

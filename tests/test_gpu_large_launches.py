@@ -7,21 +7,22 @@ import workloads
 pytestmark = pytest.mark.gpu
 
 
-# dtype, waves per group, scales, pairs of heads: each needs 2^32 threads or a little more; the inputs are
-# broadcast over the batch (stride 0)
-@pytest.mark.parametrize("dtype,waves,scales,batch", [
-    ("f32", 0, (1, 1), 131073),                             # 8 patches x 256 threads
-    ("bf16", 4, (1,), 838865), ("bf16", 8, (1,), 466040),   # one group of 320 or 576 threads
-    ("bf16", (16, 0, 0, -1, 1), (1,), 262145), ("bf16", (16, 0, 0, -1, 2), (1,), 524289),
-    ("bf16", 0, (1,) * 17, 174765)])                        # all pairs kept: 3 tiles x 512 threads
-def test_attention_of_more_threads_than_one_launch_holds(dtype, waves, scales, batch):
+# dtype, waves per group, scales, query scales, batch: each needs 2^32 threads or a little more; the inputs
+# are broadcast over the batch (stride 0)
+@pytest.mark.parametrize("dtype,waves,scales,q_scales,batch", [
+    ("f32", 0, (1, 1), None, 524289),                       # one step per patch: 8 patches x 64 threads
+    ("f32", 0, (6, 1), (1, 2), 262145),                     # two steps: 4 patches x 256 threads
+    ("bf16", 4, (1,), None, 838865), ("bf16", 8, (1,), None, 466040),   # one group of 320 or 576 threads
+    ("bf16", (16, 0, 0, -1, 1), (1,), None, 262145), ("bf16", (16, 0, 0, -1, 2), (1,), None, 524289),
+    ("bf16", 0, (1,) * 17, None, 174765)])                  # all pairs kept: 3 tiles x 512 threads
+def test_attention_of_more_threads_than_one_launch_holds(dtype, waves, scales, q_scales, batch):
     import paper_2411_17178_amd as lv
     H = 16
     print(f"  {dtype} waves={waves} scales={scales} pairs={batch * H}", flush=True)
-    plan = lv.litevar_mask_build(scales, -1, waves_per_group=waves)
-    q, k, v = (t.cuda() for t in workloads.make_qkv(scales, 1, H, 64, dtype, 3, 1.0, None))
+    plan = lv.litevar_mask_build(scales, -1, None, 0, q_scales, waves_per_group=waves)
+    q, k, v = (t.cuda() for t in workloads.make_qkv(scales, 1, H, 64, dtype, 3, 1.0, q_scales))
     want = lv.litevar_windowed_attn_fwd(plan, q, k, v, 0.125)
-    out = torch.full((batch, H, len(scales), 64), 9.0, dtype=q.dtype, device="cuda")
+    out = torch.full((batch, H, plan.q_len, 64), 9.0, dtype=q.dtype, device="cuda")
     lv.litevar_windowed_attn_fwd(plan, *(t.expand(batch, -1, -1, -1) for t in (q, k, v)), 0.125, out=out)
     assert bool(out.eq(want).all())
 
