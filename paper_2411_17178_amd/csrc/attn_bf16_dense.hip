@@ -45,6 +45,7 @@ struct DenseArgs {
   int q0, qb, qe;                              // token of query row 0; query scales [qb, qe)
   int n_units;                                 // of 32 rows of one scale
   int off[kMaxScales + 1];
+  int unit_begin[kMaxScales + 1];              // units before scale k, k in [qb, qe)
 };
 
 // 16-byte piece p of row r is stored at piece position p ^ swizzle(r): eight consecutive rows put
@@ -80,15 +81,14 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
   // Units of 32 rows of one scale (the last one of a scale may be short), tiles of NWV units laid from
   // the last unit backwards: the longest tiles start first and are full.
   struct Unit { int k, rows_before; };         // query scale, rows of the scale before the unit
+  // (lane k holds scale k's numbers and a ballot finds the scale; a loop over the kernel's arguments is a scalar
+  // round trip per scale: 30 scales of one row, 32 pairs 7.8 -> 4.6 us, 480 pairs 25.6 -> 16.3)
+  const int my_off = d.off[min(lane, kMaxScales)], my_begin = d.unit_begin[min(lane, kMaxScales)];
+  auto off = [&](int k) -> int { return __builtin_amdgcn_readlane(my_off, k); };
   auto unit_at = [&](int u) -> Unit {          // (units below 0: the first)
-    int k = d.qb;
     u = max(u, 0);
-    for (; k + 1 < d.qe; ++k) {
-      const int units = (d.off[k + 1] - d.off[k] + 31) >> 5;
-      if (u < units) break;
-      u -= units;
-    }
-    return Unit{k, 32 * u};
+    const int k = d.qb + __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane >= d.qb && lane < d.qe && my_begin <= u)) - 1;
+    return Unit{k, 32 * (u - __builtin_amdgcn_readlane(my_begin, k))};
   };
   const int tile_end = d.n_units - tile * NWV;           // unit behind the tile's last
   const int k_last = unit_at(tile_end - 1).k;
@@ -101,10 +101,10 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
     for (int k = unit_at(tile_end - NWV).k; k <= k_last; ++k) all = all && is_shared(k);
     if (all) return;
   }
-  const int n_keys = d.off[k_last + 1];                              // keys of the tile
-  const int wave_keys = unit < 0 ? 0 : d.off[un.k + 1];              // keys that the wave's queries see
-  const int scale_rows = d.off[un.k + 1] - d.off[un.k];
-  const int row = d.off[un.k] - d.q0 + un.rows_before + n;
+  const int n_keys = off(k_last + 1);                                // keys of the tile
+  const int wave_keys = unit < 0 ? 0 : off(un.k + 1);                // keys that the wave's queries see
+  const int scale_rows = off(un.k + 1) - off(un.k);
+  const int row = off(un.k) - d.q0 + un.rows_before + n;
   const bool row_ok = unit >= 0 && un.rows_before + n < scale_rows;
 
   // Q^T as the B operand: lane (n, hh) holds Q[query n][16 t + 8 hh .. + 7]
@@ -270,12 +270,15 @@ bool takes_dense_kernel(const litevar_plan* pl) {
 }
 
 litevar_status launch_attn_bf16_dense(const litevar_plan* pl, const AttnArgs& a, hipStream_t st) {
-  DenseArgs d;
+  DenseArgs d{};
   d.a = a;
   d.off[0] = 0;
   for (int k = 0; k < pl->n_scales; ++k) d.off[k + 1] = d.off[k] + pl->scales[k] * pl->scales[k];
   d.n_units = 0;
-  for (int k = pl->q_scale_begin; k < pl->q_scale_end; ++k) d.n_units += (d.off[k + 1] - d.off[k] + 31) / 32;
+  for (int k = 0; k <= pl->n_scales; ++k) {
+    d.unit_begin[k] = d.n_units;
+    if (k >= pl->q_scale_begin && k < pl->q_scale_end) d.n_units += (d.off[k + 1] - d.off[k] + 31) / 32;
+  }
   d.q0 = pl->q_token_begin; d.qb = pl->q_scale_begin; d.qe = pl->q_scale_end;
   // Eight waves (256 rows) per workgroup once the rows would fill 300 such workgroups, with fewer of
   // them CUs stand idle.  (B H, rows), four / eight waves: 2, 34 240 (268 workgroups' worth): 560 / 626 us;
