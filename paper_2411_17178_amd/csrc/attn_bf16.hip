@@ -340,7 +340,7 @@ static litevar_status launch(AttnArgs a, hipStream_t st) {
 
 litevar_status launch_attn_bf16(const litevar_plan* pl, const AttnArgs& a, hipStream_t st) {
   const int nw = pl->waves_per_group, C = pl->chunk_keys, NR = pl->ring_chunks;
-  if (takes_dense_kernel(pl)) return launch_attn_bf16_dense(pl, a, st);
+  if (takes_dense_kernel(pl, (int64_t)a.B * a.H)) return launch_attn_bf16_dense(pl, a, st);
   if (nw == 16) return launch_attn_bf16_pair(pl, a, st);
   const int D = pl->prefetch_chunks, S = NR - 2 - D;
   const int key = nw * 10000 + C * 100 + D * 10 + S;

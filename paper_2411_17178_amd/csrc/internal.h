@@ -100,6 +100,6 @@ litevar_status launch_attn_f32(const litevar_plan* pl, const AttnArgs& a, hipStr
 litevar_status launch_attn_bf16(const litevar_plan* pl, const AttnArgs& a, hipStream_t st);
 litevar_status launch_attn_bf16_pair(const litevar_plan* pl, const AttnArgs& a, hipStream_t st);
 litevar_status launch_attn_bf16_dense(const litevar_plan* pl, const AttnArgs& a, hipStream_t st);
-bool takes_dense_kernel(const litevar_plan* pl);
+bool takes_dense_kernel(const litevar_plan* pl, int64_t bh);
 
 }  // namespace lv
