@@ -80,8 +80,11 @@ def kernel_name(plan, w, working, cus):
     patches = plan.n_patches * plan.n_head_groups
     few = plan.n_steps <= 3 * patches and pairs * plan.n_groups * plan.n_steps <= 512 * patches
     if w.dtype == "bf16" and dense and plan.q_len > 16 and plan.patches_per_wave == 0 and not few:
-        # the library's rule: eight waves per workgroup when the rows fill 300 such workgroups
-        return f"k_attn_bf16_dense<{8 if pairs * plan.q_len >= 300 * 256 else 4}>"
+        # the library's rule: eight waves per workgroup when the rows fill 300 such workgroups, or when eight
+        # take all units of 32 rows in one pass over many keys
+        units = sum((w.scales[k] ** 2 + 31) // 32 for k in range(first, last))
+        eight = pairs * plan.q_len >= 300 * 256 or (4 < units <= 8 and pairs >= 300 and ends[last - 1] >= 1024)
+        return f"k_attn_bf16_dense<{8 if eight else 4}>"
     if w.dtype == "bf16" and plan.waves_per_group == 16:
         # the library's rule: one patch per wave when the working workgroups fit the CUs
         pw = plan.patches_per_wave or (1 if working <= cus else 2)

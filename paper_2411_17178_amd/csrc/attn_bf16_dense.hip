@@ -289,9 +289,11 @@ litevar_status launch_attn_bf16_dense(const litevar_plan* pl, const AttnArgs& a,
   // Eight waves (256 rows) per workgroup once the rows would fill 300 such workgroups, with fewer of
   // them CUs stand idle.  (B H, rows), four / eight waves: 2, 34 240 (268 workgroups' worth): 560 / 626 us;
   // 480, 100 (188): 11.8 / 12.3; 32, 680 (85): 16.4 / 20.3; 480, 169 (317): 25.1 / 23.6; 480, 256 (480):
-  // 38.7 / 35.6; 60, 2240 (525): 70.5 / 67.2.
+  // 38.7 / 35.6; 60, 2240 (525): 70.5 / 67.2.  With fewer rows where eight waves take all units of a pair and four
+  // would pass twice over many keys.  480 pairs, 144 rows: 4240 keys 160 / 136; 1168: 42.0 / 39.3; 169: 11.8 / 12.4.
   const int64_t BH = (int64_t)a.B * a.H;
-  const int nwv = BH * a.q_len >= 300 * 256 ? 8 : 4;
+  const bool one_pass = d.n_units > 4 && d.n_units <= 8 && BH >= 300 && d.off[d.qe] >= 1024;
+  const int nwv = BH * a.q_len >= 300 * 256 || one_pass ? 8 : 4;
   const int64_t blocks = BH * ((d.n_units + nwv - 1) / nwv);
   if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large");
   d.bh_magic = (uint32_t)(((uint64_t)1 << 32) / (uint64_t)BH - (BH <= 1));

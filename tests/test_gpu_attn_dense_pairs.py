@@ -88,3 +88,16 @@ def test_dense_later_scales_and_unusable_plans():
     out = torch.full_like(q, 3.0)
     lv.litevar_windowed_attn_fwd(plan, q, k, v, 0.125, out=out)
     assert bool((out == 3.0).all())
+
+
+@pytest.mark.parametrize("side,H", [(12, 299), (12, 300), (16, 300), (17, 300)])   # 5, 8 and 10 units of a 1168-key call
+def test_dense_one_pass_of_eight_waves(side, H):
+    import paper_2411_17178_amd as lv
+    scales = (32, side)
+    plan = lv.litevar_mask_build(scales, -1, None, 0, (1, 2))
+    q, k, v = _inputs(scales, H, 7, (1, 2), B=1)
+    got = lv.litevar_windowed_attn_fwd(plan, q.cuda(), k.cuda(), v.cuda(), 0.125).float().cpu()
+    ref = oracle.attn(scales, oracle.expand_radii(scales, -1), *[workloads.to_oracle_array(t[:, :3].contiguous()) for t in (q, k, v)],
+                      0.125, 0, (1, 2))
+    assert np.abs(got[:, :3].numpy() - ref).max() <= 2e-2
+    assert torch.equal(got[:, 3:], got[:, :3].repeat(1, -(-H // 3), 1, 1)[:, 3:H])
