@@ -261,22 +261,32 @@ litevar_status make_attn_args(const litevar_plan* plan, int32_t B, int32_t H, in
   a.head_map = plan->n_heads > 0 ? (const int32_t*)(blob + plan->off[kSecHeadMap]) : nullptr;
   a.q_len = plan->q_len;
   a.kv_len = plan->kv_len;
+  for (int k = 0; k < plan->q_scale_end; ++k) a.keys += (int64_t)plan->scales[k] * plan->scales[k];
   a.hdr = (Header*)(plan->d_blob);
   a.spin_limit = plan->spin_limit > 0 ? plan->spin_limit : kDefaultSpinLimit;
   a.H_magic = (uint32_t)(((uint64_t)1 << 32) / (uint64_t)(H > 1 ? H : 1) - (H <= 1));
   return LITEVAR_OK;
 }
 
-// One XCD per pair reads the pair's K and V into one L2; it is given up where the busiest XCD then has
-// over 15 % more items than with the pairs spread (fewer pairs than XCDs, or a few pairs too many).
-// Windowed, radius 4, (B H, tokens), one XCD per pair / spread: 1, 34 240: 203 / 47 us; 2: 239 / 73; 9: 208 / 136;
-// 12: 211 / 172; 20 (20 % more): 315 / 277; 12, 2240: 33.0 / 26.5.  36, 2240 (11 % more): 32.8 / 35.3.
-int64_t spread_over_xcds(AttnArgs& a, int64_t items) {
-  const int64_t bh = (int64_t)a.B * a.H;
-  int64_t best = 0;
+// One XCD per pair reads the pair's K and V into one L2; spreading a pair evens out the XCDs' items (fewer
+// pairs than XCDs, or a few pairs too many) and makes several L2s hold it.  It is done where the busiest XCD
+// then has an eighth fewer items (each further doubling: 2 %), and the pairs that an XCD works on at a time
+// fit its L2 of 4 MB, did not fit it before either, or the busiest XCD loses 35 %.  Windowed bf16, (B H, tokens),
+// one XCD per pair / spread: 1, 34 240: 203 / 47 us; 9: 206 / 135; 13: 213 / 181; 20: 316 / 277; 9, 2240: 32.2 / 25.4; 17:
+// 31.3 / 30.3; 25, 6144: 81.6 / 63.5; declined: 13, 2240 (15 % fewer items): 22.4 / 27.9; 33 (15 %): 32.6 / 53.4; 41 (15 %):
+// 38.5 / 53.5; 5, 6144 (34 %): 47.4 / 50.6.  fp32: 1, 680: 11.6 / 9.1; 9, 2240: 63.5 / 50.8.
+int64_t spread_over_xcds(AttnArgs& a, int64_t items, int row_bytes) {
+  constexpr int64_t kL2 = 3500000, kResident = 96;        // bytes for K and V; workgroups on an XCD at a time
+  const int64_t bh = (int64_t)a.B * a.H, kv = 2 * a.keys * row_bytes;
+  int64_t first = 0, best = 0;
+  bool fitted = false;
   for (int ls = 0; ls <= 3; ++ls) {
-    const int64_t part = (items + (1 << ls) - 1) >> ls, rounds = (bh + (8 >> ls) - 1) / (8 >> ls);
-    if (ls == 0 || 115 * part * rounds < 100 * best) { best = part * rounds; a.spread_log = ls; a.part = (int)part; }
+    const int64_t part = (items + (1 << ls) - 1) >> ls, rounds = (bh + (8 >> ls) - 1) / (8 >> ls), n = part * rounds;
+    const int64_t at_a_time = (kResident + part - 1) / part;
+    const bool fits = (rounds < at_a_time ? rounds : at_a_time) * kv <= kL2;
+    if (ls == 0) { first = n; fitted = fits; }
+    else if (!(113 * n < 100 * first && 102 * n < 100 * best && (fits || !fitted || 100 * n <= 65 * first))) continue;
+    best = n; a.spread_log = ls; a.part = (int)part;
   }
   a.part_magic = (uint32_t)(((uint64_t)1 << 32) / (uint64_t)a.part - (a.part <= 1));
   return 8 * best;

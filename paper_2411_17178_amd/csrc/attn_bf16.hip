@@ -329,7 +329,7 @@ __global__ __launch_bounds__((NW + 1) * 64) __attribute__((amdgpu_waves_per_eu((
 
 template <int NW, int C, int A, int D, int S>
 static litevar_status launch(AttnArgs a, hipStream_t st) {
-  const int64_t blocks = spread_over_xcds(a, a.n_groups);
+  const int64_t blocks = spread_over_xcds(a, a.n_groups, 128);
   if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large");
   const float c = a.sm_scale * 1.4426950408889634f;
   return launch_in_parts(blocks, (NW + 1) * 64, "bf16 attention launch", [&](int64_t first, unsigned n) {

@@ -588,7 +588,7 @@ litevar_status launch_attn_bf16_pair(const litevar_plan* pl, const AttnArgs& arg
   if (pl->waves_per_group != 16 || pl->chunk_keys != kDmaKeys || pl->ring_chunks != kRingChunks)
     return fail(LITEVAR_E_PLAN_CORRUPT, "no 16-patch kernel for chunk=%d ring=%d", pl->chunk_keys, pl->ring_chunks);
   AttnArgs a = args;
-  const int64_t blocks = spread_over_xcds(a, a.n_groups);
+  const int64_t blocks = spread_over_xcds(a, a.n_groups, a.k_sz ? 72 : 128);
   if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large");
   // One patch per wave when the launch has no more working workgroups than the GPU has CUs
   // (with output sharing about half of them exit at once): sixteen waves then fill the CU that

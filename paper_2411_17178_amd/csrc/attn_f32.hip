@@ -227,7 +227,7 @@ litevar_status launch_attn_f32(const litevar_plan* pl, const AttnArgs& args, hip
   // the chain of the launch's longest patch: 85 tokens at 8 pairs 5.4 us, 6.4 with one wave.
   const int W = pl->n_steps <= (int64_t)pl->n_patches * pl->n_head_groups ? 1 : 4;
   const int64_t n_waves = (int64_t)pl->n_groups * pl->waves_per_group;
-  const int64_t blocks = spread_over_xcds(a, n_waves);
+  const int64_t blocks = spread_over_xcds(a, n_waves, 256);
   if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large for the fp32 path");
   return launch_in_parts(blocks, W * 64, "fp32 attention launch", [&](int64_t first, unsigned n) {
     a.first_block = (uint32_t)first;

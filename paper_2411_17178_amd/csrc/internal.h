@@ -69,6 +69,7 @@ struct AttnArgs {
   uint32_t part_magic, H_magic;
   int part, spread_log;          // see spread_over_xcds
   uint32_t first_block;          // of this launch: see launch_in_parts
+  int64_t keys;                  // tokens that the queries see (host only)
 };
 
 // A launch holds fewer than 2^32 threads (its size is kept in 32 bits; more of them wrap without an error),
@@ -86,9 +87,9 @@ inline litevar_status launch_in_parts(int64_t blocks, int threads, const char* w
 
 // Which workgroup does what: workgroup i runs on XCD i % 8, each with an L2 of its own.  The work
 // items (groups or patches) of one (batch, head) pair are dealt to 2^spread_log neighbouring XCDs, `part`
-// of them to each; see xcd_item in the kernels' header.  Fills a.spread_log, a.part and a.part_magic and
-// returns the number of workgroups.
-int64_t spread_over_xcds(AttnArgs& a, int64_t items);
+// of them to each; see xcd_item in the kernels' header.  row_bytes: of a K or V row.  Fills a.spread_log, a.part
+// and a.part_magic and returns the number of workgroups.
+int64_t spread_over_xcds(AttnArgs& a, int64_t items, int row_bytes);
 
 // Checks what every attention entry point checks (plan, batch and head counts, softmax scale,
 // flags) and fills the fields of `a` that come from the plan and from these arguments; the
