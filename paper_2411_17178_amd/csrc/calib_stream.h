@@ -88,9 +88,9 @@ __device__ inline StreamTask stream_task(const StreamGeom& g) {
   return t;
 }
 
-// rows that a workgroup walks side by side
+// rows that a workgroup walks side by side (no more than it has: they are folded one after the other)
 __device__ inline int stream_rows_at_once(const StreamTask& t) {
-  return t.ncols > kStreamThreads / 2 ? 1 : min(kStreamThreads / t.ncols, kStreamRowsAtOnce);
+  return t.ncols > kStreamThreads / 2 ? 1 : max(1, min(min(kStreamThreads / t.ncols, kStreamRowsAtOnce), t.i1 - t.i0));
 }
 
 // Fills acc[class][row at once x column] (pitch g.entries) with the sums of the task's values.
