@@ -16,7 +16,11 @@ namespace lv {
 namespace {
 
 constexpr int kBandThreads = 256;
-constexpr int kBandRowBlocks = 16;    // row shares of a part at most
+// Row shares of a part: sixteen at most, up to 31 where a share keeps 64 rows (more shares of fewer rows cost
+// more than they spread: eight scales of side 24, 36 / 19 rows: 84 / 115 us).  One scale of side 64, four samples,
+// sixteen / 31 shares: 945 / 596 us; scales 1 to 64, 3 samples x 2 heads: 1172 / 705.  The workspace stays
+// below twice sixteen offsets per column.
+inline int band_row_shares(int rows) { return rows / 64 <= 16 ? 16 : rows / 64 < 31 ? rows / 64 : 31; }
 constexpr int kMaxPartCols = 4096;    // per-distance sums of a part live in LDS in the pick kernel
 
 struct BandArgs {
@@ -158,7 +162,7 @@ litevar_status band_geom(const int32_t* scales, int32_t n_scales, int32_t H, Ban
       if (n > a.mcols) a.mcols = n;
     }
   }
-  stream_plan(g, kMergedScales, [](int) { return kBandRowBlocks; });
+  stream_plan(g, kMergedScales, [&](int k) { return band_row_shares(g.s[k] * g.s[k]); });
   int64_t stride = 0;
   for (int k = 0; k < n_scales; ++k) {
     a.base[k] = stride;
