@@ -79,7 +79,7 @@ def kernel_name(plan, w, working, cus):
     pairs = w.batch * w.heads
     patches = plan.n_patches * plan.n_head_groups
     few = plan.n_steps <= 3 * patches and pairs * plan.n_groups * plan.n_steps <= 512 * patches
-    if w.dtype == "bf16" and dense and plan.q_len > 16 and plan.patches_per_wave == 0 and not few:
+    if w.dtype == "bf16" and dense and plan.q_len > 16 and not plan.tiling_chosen and plan.patches_per_wave == 0 and not few:
         # the library's rule: eight waves per workgroup when the rows fill 300 such workgroups, or when eight
         # take all units of 32 rows in one pass over many keys
         units = sum((w.scales[k] ** 2 + 31) // 32 for k in range(first, last))

@@ -128,6 +128,7 @@ typedef struct litevar_plan {
   int32_t prefetch_chunks;  /* chunks the loader keeps in flight */
   int32_t n_groups;         /* workgroup tiles per (batch, head) */
   int32_t n_patches;        /* 4x4 query patches per (batch, head) */
+  int32_t tiling_chosen;    /* 1: the options asked for waves_per_group, chunk_keys or prefetch_chunks */
   int64_t n_steps;          /* 32-key MFMA steps per (batch, head) */
   int64_t n_union_keys;     /* keys staged through LDS per (batch, head), padded */
   int64_t retained_pairs;   /* allowed (query, key) pairs per (batch, head) */
@@ -147,7 +148,13 @@ typedef struct litevar_plan {
   int64_t retained_pairs_of_group[LITEVAR_MAX_HEADS]; /* kept pairs per (batch, head) of a head group */
 } litevar_plan;
 
-/* Tuning knobs of the plan; zero-initialise for the defaults. */
+/*
+ * Tuning knobs of the plan; zero-initialise for the defaults.  They describe the kernels that walk the
+ * plan's work-list (n_steps, computed_pairs and the sizes above are theirs).  A bf16 call whose plan keeps
+ * every pair of the block-causal map runs a kernel without a work-list instead, unless the options ask for a
+ * shape of the others (waves_per_group, chunk_keys, prefetch_chunks, patches_per_wave, or a spin_limit other than the
+ * default), or the call has few rows and (batch, head) pairs.  Results agree to the bf16 path's rounding.
+ */
 typedef struct litevar_plan_opts {
   int32_t waves_per_group;  /* 4x4 query patches per workgroup: 0 = choose; else 4, 8 or 16 */
   int32_t chunk_keys;       /* keys per phase of the key stream: 0 = choose; else 32, 64 or 128 */

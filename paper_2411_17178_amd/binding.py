@@ -52,6 +52,7 @@ class _Plan(C.Structure):
                 ("side_max", C.c_int32), ("waves_per_group", C.c_int32),
                 ("chunk_keys", C.c_int32), ("ring_chunks", C.c_int32),
                 ("prefetch_chunks", C.c_int32), ("n_groups", C.c_int32), ("n_patches", C.c_int32),
+                ("tiling_chosen", C.c_int32),
                 ("n_steps", C.c_int64), ("n_union_keys", C.c_int64),
                 ("retained_pairs", C.c_int64), ("computed_pairs", C.c_int64),
                 ("off", C.c_uint64 * 12), ("scales", C.c_int32 * MAX_SCALES),

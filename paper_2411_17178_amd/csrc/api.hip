@@ -103,6 +103,7 @@ static void fill_handle(const PlanSpec& sp, const PlanSizes& z, const litevar_pl
   plan->waves_per_group = g.NW; plan->chunk_keys = g.C; plan->ring_chunks = g.NR;
   plan->prefetch_chunks = g.D;
   plan->n_groups = g.n_groups; plan->n_patches = g.n_patches;
+  plan->tiling_chosen = opts && (opts->waves_per_group != 0 || opts->chunk_keys != 0 || opts->prefetch_chunks != 0);
   plan->n_steps = z.n_steps; plan->n_union_keys = z.n_union;
   plan->retained_pairs = z.retained_pairs;
   plan->computed_pairs = z.n_steps * 16 * kStepKeys;

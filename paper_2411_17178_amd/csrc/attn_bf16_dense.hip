@@ -253,7 +253,7 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
 }
 
 // Plans that keep every pair of the block-causal map, however their radii say so, go to the kernel
-// above, unless the plan asks for a shape of the windowed kernels (patches_per_wave, spin_limit).  Up to
+// above, unless the plan asks for a shape of the windowed kernels (waves_per_group and the like).  Up to
 // 16 rows -- one patch -- the four- and eight-patch kernel is as fast: (B H, rows), windowed / dense:
 // 480, 9: 4.6 / 5.0 us; 480, 25: 5.7 / 5.1; 480, 30: 9.8 / 5.8; 8, 64: 6.8 / 6.7; 4, 256: 16.5 / 13.9.
 // So it is, or faster, while the windowed workgroups are about two per CU or fewer and their patches take
@@ -261,7 +261,8 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
 // 5.2; scales 1 to 6, 192 x 2: 5.1 / 5.7, 720 x 2: 7.4 / 5.8; ten of side 4, 80 x 3: 5.9 / 6.5, 1200 x 3: 10.4 / 6.8; three
 // of side 6, 96 x 3: 5.7 / 5.8, 360 x 3: 6.6 / 5.9; one of 12 x 12, 24 x 6: 6.8 / 6.9; one of 13 x 13, 32 x 14: 11.5 / 10.2.
 bool takes_dense_kernel(const litevar_plan* pl, int64_t bh) {
-  if (pl->q_len <= kPatchQueries || pl->patches_per_wave != 0 || pl->spin_limit != kDefaultSpinLimit) return false;
+  if (pl->q_len <= kPatchQueries || pl->tiling_chosen || pl->patches_per_wave != 0 || pl->spin_limit != kDefaultSpinLimit)
+    return false;
   const int64_t patches = (int64_t)pl->n_patches * pl->n_head_groups;
   if (pl->n_steps <= 3 * patches && bh * pl->n_groups * pl->n_steps <= 512 * patches) return false;
   int64_t off = 0, all = 0;
