@@ -60,8 +60,8 @@ __device__ inline bool plan_usable(const Header* hdr) {
 
 // The bounds-checking build (-DLITEVAR_DEBUG_BOUNDS, a second library for tests and for chasing
 // a suspected plan/kernel mismatch): every token that addresses a K/V row, every query row
-// that addresses Q or O and every LDS offset taken from a step descriptor is compared with
-// its limit before use; a value out of range is replaced by 0 and the plan's header is
+// that addresses Q or O (from the plan, or from the dense kernel's own units and tiles) and every LDS
+// offset taken from a step descriptor is compared with its limit before use; a value out of range is replaced by 0 and the plan's header is
 // marked (litevar_plan_check then says so).  The normal build compiles the checks away.
 __device__ inline int checked_index([[maybe_unused]] Header* hdr, int value, [[maybe_unused]] int limit) {
 #ifdef LITEVAR_DEBUG_BOUNDS

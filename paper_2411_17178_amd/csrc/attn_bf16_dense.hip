@@ -110,7 +110,8 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
   // Q^T as the B operand: lane (n, hh) holds Q[query n][16 t + 8 hh .. + 7]
   bf16x8 qf[4];
   {
-    const int r = min(row, a.q_len - 1);       // (a lane without a query holds some other one; it is not stored)
+    // (a lane without a query holds some other one; it is not stored)
+    const int r = row_ok ? checked_index(a.hdr, row, a.q_len) : min(row, a.q_len - 1);
     const __bf16* qp = (const __bf16*)a.q + b * a.qs[0] + h * a.qs[1] + r * a.qs[2] + 8 * hh;
 #pragma unroll
     for (int t = 0; t < 4; ++t) qf[t] = as_bf16x8(*(const uint4*)(qp + 16 * t));
@@ -126,7 +127,8 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
   auto load_rows = [&](const unsigned char* p, int key0, u32x4 (&r)[kRowsPerThread]) {
 #pragma unroll
     for (int i = 0; i < kRowsPerThread; ++i)
-      r[i] = *(const u32x4*)(p + __umul24((unsigned)min(key0 + lrow + kRowsAtOnce * i, n_keys - 1), row_bytes));
+      r[i] = *(const u32x4*)(p + __umul24((unsigned)checked_index(a.hdr, min(key0 + lrow + kRowsAtOnce * i, n_keys - 1), a.kv_len),
+                                          row_bytes));
   };
   auto store_rows = [&](unsigned char* buf, const u32x4 (&r)[kRowsPerThread]) {
 #pragma unroll
@@ -239,7 +241,7 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
   if (!row_ok) return;
   const bool shared = is_shared(un.k);
   if (shared && partner) return;               // the conditional workgroup writes this row
-  __bf16* op = (__bf16*)a.o + b * a.os[0] + h * a.os[1] + row * a.os[2] + 4 * hh;
+  __bf16* op = (__bf16*)a.o + b * a.os[0] + h * a.os[1] + checked_index(a.hdr, row, a.q_len) * a.os[2] + 4 * hh;
 #pragma unroll
   for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
