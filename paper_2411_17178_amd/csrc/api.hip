@@ -275,19 +275,22 @@ litevar_status make_attn_args(const litevar_plan* plan, int32_t B, int32_t H, in
 // fit its L2 of 4 MB, did not fit it before either, or the busiest XCD loses 35 %.  Windowed bf16, (B H, tokens),
 // one XCD per pair / spread: 1, 34 240: 203 / 47 us; 9: 206 / 135; 13: 213 / 181; 20: 316 / 277; 9, 2240: 32.2 / 25.4; 17:
 // 31.3 / 30.3; 25, 6144: 81.6 / 63.5; declined: 13, 2240 (15 % fewer items): 22.4 / 27.9; 33 (15 %): 32.6 / 53.4; 41 (15 %):
-// 38.5 / 53.5; 5, 6144 (34 %): 47.4 / 50.6.  fp32: 1, 680: 11.6 / 9.1; 9, 2240: 63.5 / 50.8.
+// 38.5 / 53.5; 5, 6144 (34 %): 47.4 / 50.6; 26, 2240 with sharing everywhere (13 pairs work): 23.8 / 27.0.  fp32: 1, 680: 11.6 / 9.1; 9, 2240: 63.5 / 50.8.
 int64_t spread_over_xcds(AttnArgs& a, int64_t items, int row_bytes) {
   constexpr int64_t kL2 = 3500000, kResident = 96;        // bytes for K and V; workgroups on an XCD at a time
   const int64_t bh = (int64_t)a.B * a.H, kv = 2 * a.keys * row_bytes;
-  int64_t first = 0, best = 0;
+  const int64_t busy = a.cfg_share ? bh / 2 : bh;         // with output sharing the second half of the pairs may have nothing to do
+  int64_t first = 0, best = 0, first_busy = 0, best_busy = 0;
   bool fitted = false;
   for (int ls = 0; ls <= 3; ++ls) {
-    const int64_t part = (items + (1 << ls) - 1) >> ls, rounds = (bh + (8 >> ls) - 1) / (8 >> ls), n = part * rounds;
+    const int64_t part = (items + (1 << ls) - 1) >> ls, xcds = 8 >> ls;
+    const int64_t rounds = (bh + xcds - 1) / xcds, n = part * rounds, n_busy = part * ((busy + xcds - 1) / xcds);
     const int64_t at_a_time = (kResident + part - 1) / part;
     const bool fits = (rounds < at_a_time ? rounds : at_a_time) * kv <= kL2;
-    if (ls == 0) { first = n; fitted = fits; }
+    if (ls == 0) { first = n; first_busy = n_busy; fitted = fits; }
     else if (!(113 * n < 100 * first && 102 * n < 100 * best && (fits || !fitted || 100 * n <= 65 * first))) continue;
-    best = n; a.spread_log = ls; a.part = (int)part;
+    else if (!(113 * n_busy < 100 * first_busy && 102 * n_busy < 100 * best_busy)) continue;
+    best = n; best_busy = n_busy; a.spread_log = ls; a.part = (int)part;
   }
   a.part_magic = (uint32_t)(((uint64_t)1 << 32) / (uint64_t)a.part - (a.part <= 1));
   return 8 * best;
