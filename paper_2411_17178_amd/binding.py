@@ -118,8 +118,8 @@ def _stream_handle(stream):
 
 
 def _int32s(values, n):
-    """ctypes array of `n` integers.  Values that already are integers pass through array.array (30
-    tables of 10 x 10: 50 us instead of 350 us one by one); anything else goes through int()."""
+    """ctypes array of `n` integers.  Values that already are integers pass through array.array (a descriptor
+    with 30 tables of 10 x 10, checks included: 48 us, 190 us one by one); anything else goes through int()."""
     values = list(values)
     try:
         buf = array("i", values)

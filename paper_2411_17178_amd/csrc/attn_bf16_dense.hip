@@ -14,12 +14,13 @@
 //       tile's registers hold them), row sums of the rounded probabilities by v_dot2_f32_bf16.
 // A wave's queries share their key limit; only the last block before it is masked.
 //
-// Why not the windowed kernels: a wave there reads 8 KiB of LDS per 32 keys x 16 queries, and LDS
-// bandwidth bounds it when every key is kept; here the same reads serve 32 queries, and there are
-// no step descriptors and lane masks to fetch.  What bounds it now is the issue of vector and
-// matrix instructions of one SIMD, which overlap little: at 2240 tokens and 288 (batch, head) pairs
-// the matrix pipe is busy a third of the time, the vector ALU half of it.  124-132 registers let three to
-// four waves share a SIMD.  Not faster, at that size: 64 queries per wave (342 us), the next chunk's
+// Why not the windowed kernels: a wave there issues 51 vector, 9 matrix and 12 LDS instructions (on such a
+// plan) per 32 keys x 16 queries and fetches a step descriptor and lane masks; here 67, 8 and 13 serve 32
+// queries (keys' rows on their way into LDS included), with nothing to fetch.  What bounds it now is the issue
+// of vector and matrix instructions of one SIMD, which overlap little: at 2240 tokens and 288
+// (batch, head) pairs the vector issue is busy 63 % of the cycles, the matrix pipe 44 %, the LDS pipe 39 %
+// (windowed kernel on the same plan: 53, 28, 25).  119 and 127 registers (eight and four waves) let four waves
+// share a SIMD.  Not faster, at that size: 64 queries per wave (342 us), the next chunk's
 // score products issued between the exponentials, which takes 203 registers (365), chunks of 128
 // keys (360), raised wave priority around the products (310, against 310 without).
 // Measured against the windowed kernels (B H, tokens): 288, 2240: 427 -> 297 us (810 TFLOP/s of kept

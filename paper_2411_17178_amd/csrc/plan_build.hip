@@ -158,7 +158,7 @@ litevar_status make_spec(const litevar_mask_desc* d, const litevar_plan_opts* op
 static uint64_t align256(uint64_t x) { return (x + 255) & ~(uint64_t)255; }
 
 // The sizing walk visits every run of consecutive kept keys of every patch on the host (30 tables of
-// 13 x 13 queries: 0.1 ms; 0.96 ms key by key).
+// 13 x 13 queries: 0.06 ms; 0.54 ms key by key).
 // Callers size and then build with the same descriptor, often repeatedly,
 // so the last result is remembered per thread, keyed by the whole specification.
 static thread_local struct { bool valid; PlanSpec sp; PlanSizes z; } g_last_sizing = {false, {}, {}};
@@ -380,8 +380,8 @@ struct WavePacker {
   }
 };
 
-// Wave-cooperative form of walk_patch(): the 64 lanes of a wave take 64 consecutive candidate
-// keys at a time (window mode: several rows of a narrow box, or 64 columns of one row of the
+// The walk over a patch's kept keys in the order of its group's list: the 64 lanes of a wave take 64
+// consecutive candidate keys at a time (window mode: several rows of a narrow box, or 64 columns of one row of the
 // patch's box in a key scale; band mode: 64 columns of the patch's range in a part).
 template <class Sink>
 __device__ int wave_walk_patch(const Geom& g, const TableWin& win, const TableRad& rad, const GroupExtent& e,

@@ -35,14 +35,15 @@ template <int kCtrl> __device__ inline float dpp(float x) {
 }
 constexpr int kXor1 = 0xb1, kXor2 = 0x4e, kHalfMirror = 0x141;   // quad_perm [1 0 3 2], [2 3 0 1]; lane i <- 7 - i
 
-// Eight lanes per row; a 256-thread block handles 32 rows.  What bounds it is the division of every
-// value by its row's scale: an IEEE division is ten instructions and a reciprocal.  With the correctly
+// Eight lanes per row; a 256-thread block handles 32 rows.  Dividing every value by its row's scale would
+// be ten instructions and a reciprocal each.  With the correctly
 // rounded reciprocal r of the scale, formed once per row, q = d r and two corrections q += (d - q s) r give
 // the correctly rounded quotient (Markstein's theorem: the remainder is exact in an fma, the first
 // correction brings q within one unit in the last place, the second rounds correctly) while nothing
 // overflows or loses bits, for which the scale is kept between 2^-100 and 2^100: |d / s| <= 128, and a
 // remainder that underflows belongs to a quotient that rounds to code 0 either way.  Other rows divide.
-// 122 880 rows of bf16: 8.9 -> 7.6 us (3.2 TB/s); three such calls and the attention on their codes: 61 -> 58 us.
+// 122 880 rows of bf16: 8.9 us with divisions, 7.6 so (3.2 TB/s); three such calls and the attention on their codes:
+// 61 / 58 us.  What is left is one 16-byte load in flight per lane and short blocks.
 template <typename T>
 __global__ __launch_bounds__(256) void k_quantize_rows(const T* __restrict__ x, int64_t rows, int64_t row_stride,
                                                        int8_t* __restrict__ xq, float2* __restrict__ sz) {
@@ -162,6 +163,9 @@ litevar_status litevar_qkv8_dequantize(const int8_t* d_codes, const float* d_sca
 // sequence); once they stream a quarter more rows than the three tensors hold (q_len + 2 kv_len
 // per (batch, head)), a single dequantising pass over the tensors is cheaper (measured: both
 // cost 35-40 ps per row; 2240 tokens: 9088 rows streamed against 6720, 276 against 262 us).
+// Plans that keep every pair are weighed like the others, although the copy's attention then runs on the
+// dense kernel.  480 pairs, in-kernel / copy: 256 x 680 43 / 60 us, 2240 tokens (288 pairs) 539 / 349, both as the
+// rule has it, but 680 x 680 149 / 99.
 static bool fused(const litevar_plan* plan) {
   if (plan->waves_per_group != 16) return false;
   const int64_t streamed = plan->n_union_keys / (plan->n_head_groups > 0 ? plan->n_head_groups : 1);
