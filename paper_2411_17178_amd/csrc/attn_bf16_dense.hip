@@ -24,7 +24,7 @@
 // score products issued between the exponentials, which takes 203 registers (365), chunks of 128
 // keys (360), raised wave priority around the products (310, against 310 without).
 // Measured against the windowed kernels (B H, tokens): 288, 2240: 427 -> 297 us (810 TFLOP/s of kept
-// pairs); 480, 680: 117 -> 68 us; 2, 34 240: 6930 -> 560 us (the windowed kernel keeps to two XCDs there).
+// pairs); 480, 680: 117 -> 64 us; 2, 34 240: 6950 -> 503 us (the windowed kernel on one XCD per pair).
 #include <type_traits>
 
 #include "attn_bf16_common.h"
