@@ -24,7 +24,7 @@
 // score products issued between the exponentials, which takes 203 registers (365), chunks of 128
 // keys (360), raised wave priority around the products (310, against 310 without).
 // Measured against the windowed kernels (B H, tokens): 288, 2240: 427 -> 297 us (810 TFLOP/s of kept
-// pairs); 480, 680: 117 -> 64 us; 2, 34 240: 6950 -> 503 us (the windowed kernel on one XCD per pair).
+// pairs); 480, 680: 117 -> 62 us; 2, 34 240: 6950 -> 500 us (the windowed kernel on one XCD per pair; 1820 spread).
 #include <type_traits>
 
 #include "attn_bf16_common.h"
@@ -291,9 +291,9 @@ litevar_status launch_attn_bf16_dense(const litevar_plan* pl, const AttnArgs& a,
   }
   d.q0 = pl->q_token_begin; d.qb = pl->q_scale_begin; d.qe = pl->q_scale_end;
   // Eight waves (256 rows) per workgroup once the rows would fill 300 such workgroups, with fewer of
-  // them CUs stand idle.  (B H, rows), four / eight waves: 2, 34 240 (268 workgroups' worth): 560 / 626 us;
-  // 480, 100 (188): 11.8 / 12.3; 32, 680 (85): 16.4 / 20.3; 480, 169 (317): 25.1 / 23.6; 480, 256 (480):
-  // 38.7 / 35.6; 60, 2240 (525): 70.5 / 67.2.  With fewer rows where eight waves take all units of a pair and four
+  // them CUs stand idle.  (B H, rows), four / eight waves: 2, 34 240 (268 workgroups' worth): 496 / 611 us;
+  // 480, 100 (188): 11.0 / 11.7; 32, 680 (85): 14.3 / 18.6; 480, 169 (317): 22.8 / 21.6; 480, 256 (480):
+  // 35.2 / 33.1; 60, 2240 (525): 64.6 / 60.8.  With fewer rows where eight waves take all units of a pair and four
   // would pass twice over many keys.  480 pairs, 144 rows: 4240 keys 160 / 136; 1168: 42.0 / 39.3; 169: 11.8 / 12.4.
   const int64_t BH = (int64_t)a.B * a.H;
   const bool one_pass = d.n_units > 4 && d.n_units <= 8 && BH >= 300 && d.off[d.qe] >= 1024;
