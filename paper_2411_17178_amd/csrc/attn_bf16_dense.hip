@@ -267,7 +267,7 @@ bool takes_dense_kernel(const litevar_plan* pl, int64_t bh) {
   if (pl->q_len <= kPatchQueries || pl->tiling_chosen || pl->patches_per_wave != 0 || pl->spin_limit != kDefaultSpinLimit)
     return false;
   const int64_t patches = (int64_t)pl->n_patches * pl->n_head_groups;
-  if (pl->n_steps <= 3 * patches && bh * pl->n_groups * pl->n_steps <= 512 * patches) return false;
+  if (pl->n_steps <= 3 * patches && (pl->n_steps < 1 || bh * pl->n_groups <= 512 * patches / pl->n_steps)) return false;
   int64_t off = 0, all = 0;
   for (int k = 0; k < pl->q_scale_end; ++k) {
     const int64_t n = (int64_t)pl->scales[k] * pl->scales[k];
