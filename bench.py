@@ -72,7 +72,7 @@ def measured_traffic(workload, kernel, kernel_us):
     return int(kv["traffic_bytes_per_launch"])
 
 
-def kernel_name(plan, w, working, cus):
+def kernel_name(plan, w):
     first, last = w.q_scales or (0, len(w.scales))
     ends = [sum(s * s for s in w.scales[:k + 1]) for k in range(len(w.scales))]
     dense = plan.retained_pairs == sum(w.scales[k] ** 2 * ends[k] for k in range(first, last))
@@ -86,8 +86,7 @@ def kernel_name(plan, w, working, cus):
         eight = pairs * plan.q_len >= 300 * 256 or (4 < units <= 8 and pairs >= 300 and ends[last - 1] >= 1024)
         return f"k_attn_bf16_dense<{8 if eight else 4}>"
     if w.dtype == "bf16" and plan.waves_per_group == 16:
-        # the library's rule: one patch per wave when the working workgroups fit the CUs
-        pw = plan.patches_per_wave or (1 if working <= cus else 2)
+        pw = plan.patches_per_wave or 2
         return f"k_attn_bf16_pair<{pw}, false>"
     if w.dtype == "bf16":
         return (f"k_attn_bf16<{plan.waves_per_group}, {plan.chunk_keys}, 1, {plan.prefetch_chunks}, "
@@ -183,11 +182,7 @@ def run_workload(name, dense, steps, warmup, layers, tiling, keep_layer0=False):
     t_mfma_us = flops_layer / (MFMA_BF16_PEAK_TFLOPS * 1e12) * 1e6
     t_hbm_us = bytes_layer / (HBM_PEAK_GBS * 1e9) * 1e6
 
-    working = BH * plan.n_groups
-    if share is not None:
-        working = (working + 1) // 2
-    cus = torch.cuda.get_device_properties(0).multi_processor_count
-    kname = kernel_name(plan, w, working, cus)
+    kname = kernel_name(plan, w)
     res = {
         "workload": w.name + ("_dense" if dense else ""), "kernel": kname,
         "us_per_layer": round(kernel_us, 3), "ms_per_step": round(ms_per_step, 4),

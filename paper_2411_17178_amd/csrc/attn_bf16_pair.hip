@@ -2,9 +2,19 @@
 // with 16 patches per group: O = softmax(sm_scale * Q K^T over the kept keys) V, with the
 // Section 3 cond -> uncond output reuse folded into the store.
 //
-// One workgroup = eight waves = one group of up to 16 query patches (16 x 16 queries of
-// one scale) of one (batch, head).  Every wave owns two patches (a top and a bottom one,
-// so that it has keys in most parts of the stream) and one eighth of the loading.
+// One workgroup = eight waves = one group of up to 16 x 16 queries of one scale of one (batch, head), which its
+// wide patches tile: every wave owns 32 queries (4 x 8, or whatever covers the group best) and one eighth of the
+// loading.  (A second form, sixteen waves with a patch of 16 queries each, serves plans that ask for it.)
+//
+// Why 32 queries per wave: what bounds a step is the vector issue of its SIMD, four waves of which run steps at the same
+// time, and its own chain of latencies.  A step of 32 keys costs 69 vector and 9 matrix instructions for 32 queries
+// (v_mfma_f32_32x32x16_bf16), where 16 queries (v_mfma_f32_16x16x32_bf16) took 45 and 9, for 1.13 to 1.18 times the pairs.
+// The descriptor carries the step's mask, so that nothing on the step's way waits for a scalar load.
+// Measured against two 16-query patches per wave: 2240 tokens, radius 4, 288 pairs 176.5 -> 159.7 us; 34 240 tokens, 32 pairs
+// with sharing 393 -> 321 us; 256 queries on 680 keys, 480 pairs 29.3 -> 28.6 us, 240 working pairs of ten steps 90.9 -> 87.7
+// us (there against one 16-query patch per wave).  Of a wave's time at 2240 tokens (31 000 cycles): start-up 22 % (the loads
+// before the first barrier pass the CU's address unit at 64 bytes a cycle, then a trip to memory), steps 40 %, barriers
+// 20 %, waits for loads 10 %.
 //
 // The group's key list is streamed once through an LDS ring of five chunks of 64 keys
 // (one 128-byte K row and one 128-byte V row per key, 16-byte pieces XOR-swizzled by
@@ -16,18 +26,16 @@
 // chunks 2p-2 .. 2p, which are three of the five slots; the other two slots held chunks
 // 2p-4 and 2p-3, which nobody reads after the barrier that ended phase p-1, and receive
 // chunks 2p+1 and 2p+2 (phase p+1) while phase p computes.
-//   Prologue: all scalar plan words, then Q, the first step descriptors and the other small
-//     loads, then chunks 0, 1 and 2.  (Where the list does not start with whole key scales,
-//     the tokens of the chunks that need them travel with the small loads; the chunks that
-//     need none go out meanwhile, one wait, then the rest.)  With at most the three chunks
-//     outstanding (a wave issues PW transfers per chunk: vmcnt 3 PW) Q is in; with at most
-//     chunks 1 and 2 outstanding (vmcnt 2 PW) comes the first barrier: chunk 0 is in.
+//   Prologue: all scalar plan words, then the tokens of the first chunks, the first step descriptors, Q and the other
+//     small loads, then chunks 0, 1 and 2 (which wait for the tokens only where the list does not start with whole key
+//     scales).  With at most chunks 1 and 2 outstanding (a wave issues PW transfers per chunk: vmcnt 2 PW) comes the
+//     first barrier: Q, the descriptors and chunk 0 are in.
 //   Phase p: a wave
-//     issues the descriptor loads of its steps of this phase beyond the first of each patch,
-//     runs the first step of each patch,
+//     issues the descriptor loads of its steps of this phase beyond the first,
+//     runs the first step,
 //     waits for all its vector memory operations (p >= 1: the descriptors just requested;
 //       chunks 2p-1 and 2p were waited for at the end of phase p-1),
-//     requests the first descriptors and the tokens of phase p+1 and then issues its share
+//     requests the first descriptor and the tokens of phase p+1 and then issues its share
 //       of chunks 2p+1 and 2p+2 (p >= 1; in phase 0 chunks 1 and 2 are already in flight) --
 //       not right behind the barrier, where the loads of all eight waves would queue up in
 //       front of the first K reads, and behind the small loads, because a load issued behind
@@ -39,9 +47,11 @@
 //
 // A wave that issues LDS-DMA loads must read LDS through inline assembly: the compiler
 // cannot tell which of them a plain LDS read depends on and would wait for all
-// (vmcnt(0)) before every read.
+// (vmcnt(0)) before every read.  And no loaded register may be copied or loaded again under a condition while transfers
+// are in flight: the compiler then waits for everything at the copy (tokens that were loaded only where the list needs
+// them cost 5 % of a launch that way).
 //
-// Step arithmetic is that of the 8-patch kernel: S^T = K_tile . Q^T by
+// Step arithmetic (16 queries) is that of the 8-patch kernel: S^T = K_tile . Q^T by
 // v_mfma_f32_16x16x32_bf16 (a lane owns one query column and four keys per tile) on
 // accumulators that start at minus the softmax reference where the scalar lane mask keeps the
 // pair and at -inf elsewhere (one v_cndmask per score), so the tiles leave the matrix pipe as
@@ -63,10 +73,14 @@ constexpr int kDmaKeys = 64;          // keys per chunk (the unit of loading and
 constexpr int kRingChunks = 5;        // ring depth: look-back, two current, two landing
 constexpr int kBufferFlags = 0x00020000;   // word 3 of a raw buffer resource on gfx9: 32-bit data format
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+typedef __attribute__((ext_vector_type(2))) short s16x2;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 constexpr int kBoostPhases = 3;       // phases that a later-arrived workgroup runs at raised priority
-constexpr int kLater = 2;             // descriptors per patch, beyond the first step of a phase, that are
-                                      // fetched at the start of the phase
+constexpr int kLater = 2;             // descriptors, beyond the first step of a phase, that are fetched at
+                                      // the start of the phase
+constexpr float kMostSum = 0x1p40f, kLeastSum = 0x1p-40f;   // row sums outside move the wide patches' softmax reference
 
 __device__ inline unsigned lds_addr(const void* p) {
   return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
@@ -107,6 +121,44 @@ __device__ inline void lds_wait(uint2 (&va)[4][2]) {
                  "+v"(va[2][0]), "+v"(va[2][1]), "+v"(va[3][0]), "+v"(va[3][1]) : : "memory");
 }
 
+// the same for a wide patch: four 16-byte pieces of one key's K row ...
+__device__ inline void lds_read_k_row_issue(unsigned k, u32x4 (&r)[4]) {
+  asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\t"
+               "ds_read_b128 %2, %6\n\tds_read_b128 %3, %7"
+               : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
+               : "v"(k), "v"(k ^ 32u), "v"(k ^ 64u), "v"(k ^ 96u) : "memory");
+}
+// ... and V^T: two slices of 16 keys (t), two halves of one (j), two head-dim tiles (dt); va[4 t + 2 j + dt]
+template <int VOFF>
+__device__ inline void lds_read_v_wide(const unsigned (&v)[4], const unsigned (&x)[4], uint2 (&va)[8]) {
+  asm volatile("ds_read_b64_tr_b16 %0, %8 offset:%16\n\tds_read_b64_tr_b16 %1, %9 offset:%16\n\t"
+               "ds_read_b64_tr_b16 %2, %10 offset:%16\n\tds_read_b64_tr_b16 %3, %11 offset:%16\n\t"
+               "ds_read_b64_tr_b16 %4, %12 offset:%16\n\tds_read_b64_tr_b16 %5, %13 offset:%16\n\t"
+               "ds_read_b64_tr_b16 %6, %14 offset:%16\n\tds_read_b64_tr_b16 %7, %15 offset:%16"
+               : "=&v"(va[0]), "=&v"(va[1]), "=&v"(va[2]), "=&v"(va[3]),
+                 "=&v"(va[4]), "=&v"(va[5]), "=&v"(va[6]), "=&v"(va[7])
+               : "v"(v[0]), "v"(x[0]), "v"(v[1]), "v"(x[1]), "v"(v[2]), "v"(x[2]), "v"(v[3]), "v"(x[3]),
+                 "i"(VOFF) : "memory");
+}
+__device__ inline void lds_wait_v_wide(uint2 (&va)[8]) {
+  asm volatile("s_waitcnt lgkmcnt(0)"
+               : "+v"(va[0]), "+v"(va[1]), "+v"(va[2]), "+v"(va[3]), "+v"(va[4]), "+v"(va[5]), "+v"(va[6]),
+                 "+v"(va[7]) : : "memory");
+}
+
+struct WideArgs {         // the wide patches' entries in the blob, where the plan has them
+  const WaveDesc* waves; const int32_t* phase_end; const unsigned char* step_addr; const int32_t* union_tok;
+  int boost;              // all workgroups of the launch are resident at once
+};
+
+struct WidePatchState {   // a wave's 32 queries
+  bf16x8 q[4];            // Q^T as the B operand: lane (n, h) holds Q[query n][16 t + 8 h .. + 7]
+  f32x16 O[2];            // O^T accumulators: dims 32 dt + 8 (e / 4) + 4 h + e % 4 of query n
+  float L, negm;          // this lane's part of the row sum, minus the softmax reference m (base 2, whole numbers)
+  uint64_t unset;         // lanes whose query's sum is still below kLeastSum
+  bf16x8 b;               // B operand of the mask product, see run_step32
+};
+
 struct PatchState {       // one query patch of a wave
   bf16x8 qb0, qb1;        // Q^T as the B operand: lane (n, g4) holds Q[query n][16 g4 .. +15]
   f32x4 O[4], Lacc;       // O^T accumulators and row sums
@@ -114,12 +166,94 @@ struct PatchState {       // one query patch of a wave
                           // before m moves: kFloor while m is unset
 };
 
+constexpr bf16x2 kOnes = {(__bf16)1.0f, (__bf16)1.0f};
+
+// the value in the other lane of a query (l ^ 32)
+__device__ inline float other_half(float x) {
+  const unsigned u = __float_as_uint(x);
+  auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  const unsigned s0 = sw[0], s1 = sw[1];       // (lower half's value, upper half's value) in every lane
+  return __uint_as_float((threadIdx.x & 32) ? s0 : s1);
+}
+
+// (on the bits, behind a barrier for the optimiser: the build lets it assume that no value is NaN)
+__device__ inline bool not_finite(float x) {
+  unsigned u = __float_as_uint(x);
+  asm volatile("" : "+v"(u));
+  return (u & 0x7f800000u) == 0x7f800000u;
+}
+
+// eight values of a row, bf16 or 8-bit codes with the row's (scale, zero point)
+template <bool Q8> __device__ inline void load_row8(const void* base, int64_t at, const float2* sz, float (&x)[8]) {
+  if constexpr (Q8) {
+    const u32x2 r = *(const u32x2*)((const int8_t*)base + at);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = (float)(__bf16)fmaf(sz->x, (float)(int8_t)((r[e >> 2] >> (8 * (e & 3))) & 0xffu), sz->y);
+  } else {
+    const bf16x8 r = as_bf16x8(*(const uint4*)((const __bf16*)base + at));
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = (float)r[e];
+  }
+}
+
+// Query row `qrow` (none: -1) of pair (b, h), key by key over the steps of the patch of 16 that holds it, one of the
+// group's sixteen from `patch0` on: head dimensions 32 dt + 8 j + 4 h .. + 3 of lane h of the query's two.  Only for results that
+// are not finite; every lane walks its own list.
+template <bool Q8>
+__device__ inline void attend_key_by_key(const AttnArgs& a, float c, int b, int h, int patch0, int qrow,
+                                                            int hi, unsigned (&out)[2][8]) {
+  int found = -1, n16 = 0;
+  for (int w = 0; w < kGroupPatches; ++w) {
+    const WaveDesc wd = a.waves[patch0 + w];
+    const int d = qrow - wd.q_base;
+    if (qrow < 0 || d < 0 || wd.sk < 1) continue;
+    const int dy = d / wd.sk, dx = d - dy * wd.sk;
+    if (dy < kPatch && dx < kPatch && ((wd.valid >> (kPatch * dy + dx)) & 1u)) { found = w; n16 = kPatch * dy + dx; }
+  }
+  if (found < 0) return;
+  const WaveDesc wd = a.waves[patch0 + found];
+  const int64_t q_at = b * a.qs[0] + h * a.qs[1] + checked_index(a.hdr, qrow, a.q_len) * a.qs[2];
+  const int64_t kv_at = b * a.ks[0] + h * a.ks[1], rows = Q8 ? a.ks[1] / a.ks[2] : 0, pair = (int64_t)b * a.H + h;
+  float m = kFloor, l = 0.f, O[2][16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) O[0][e] = O[1][e] = 0.f;
+  for (int64_t s = wd.step_begin; s < (int64_t)wd.step_begin + wd.n_steps; ++s)
+    for (int i = 0; i < kStepKeys; ++i) {
+      const int r = i & 15;
+      const uint64_t keep = a.step_mask[s * 8 + 4 * (i >> 4) + (r & 3)];
+      if (!((keep >> ((r >> 2) * 16 + n16)) & 1)) continue;
+      const int tok = checked_index(a.hdr, a.step_tok[s * kStepKeys + i], a.kv_len);
+      const int64_t at = kv_at + tok * a.ks[2];
+      float dot = 0.f, x[8], y[8];
+      for (int d = 0; d < 64; d += 8) {
+        load_row8<Q8>(a.q, q_at + d, Q8 ? a.q_sz + pair * a.q_len + qrow : nullptr, x);
+        load_row8<Q8>(a.k, at + d, Q8 ? a.k_sz + pair * rows + tok : nullptr, y);
+        for (int e = 0; e < 8; ++e) dot = fmaf(x[e], y[e], dot);
+      }
+      const float z = dot * c, m_new = fmaxf(m, z), alpha = __builtin_amdgcn_exp2f(m - m_new), p = __builtin_amdgcn_exp2f(z - m_new);
+      l = fmaf(l, alpha, p);
+      m = m_new;
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          load_row8<Q8>(a.v, at + 32 * dt + 8 * j, Q8 ? a.v_sz + pair * rows + tok : nullptr, x);
+#pragma unroll
+          for (int i4 = 0; i4 < 4; ++i4) O[dt][4 * j + i4] = fmaf(p, hi ? x[4 + i4] : x[i4], O[dt][4 * j + i4] * alpha);
+        }
+    }
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; e += 2)
+      out[dt][e / 2] = __builtin_bit_cast(unsigned, bf16x2{(__bf16)(O[dt][e] * (1.f / l)), (__bf16)(O[dt][e + 1] * (1.f / l))});
+}
+
 }  // namespace
 
-// PW = query patches per wave: 2 (8 waves per workgroup, two workgroups per CU: the form for
-// launches that fill the GPU) or 1 (16 waves per workgroup, one workgroup per CU: a launch with
-// no more workgroups than CUs then still has four waves on every SIMD).  Same plan, same
-// phases; with 16 waves the loading duty of a chunk is one K or one V transfer per wave.
+// PW = 2: a wide patch, 32 queries, per wave (8 waves per workgroup, two workgroups per CU); PW = 1: a patch of 16
+// queries per wave (16 waves per workgroup, one workgroup per CU).  Same plan, same phases, each its own steps and, where
+// boxes are dealt, its own order of the key list; with 16 waves the loading duty of a chunk is one K or one V transfer per wave.
 //
 // Q8 (Section 4, 8-bit Q, K, V): the operands are int8 codes with one (scale, zero point) per
 // token row.  A wave's share of a chunk then comes through registers instead of LDS-DMA: one
@@ -131,8 +265,8 @@ struct PatchState {       // one query patch of a wave
 // there, so the results equal those of the bf16 kernel on such a copy bit for bit.
 template <int PW, bool Q8>
 __global__ __launch_bounds__((kGroupPatches / PW) * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void k_attn_bf16_pair(AttnArgs a, float c) {
-  [[maybe_unused]] constexpr int NWV = kGroupPatches / PW;   // waves per workgroup
+void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
+  constexpr bool WIDE = PW == 2;                   // the group's wide patches (32 queries), else its patches (16)
   constexpr int C = kDmaKeys;
   constexpr int R = kRingChunks * C;               // ring slots
   constexpr int VOFF = R * kRingRowBytes;          // V ring follows the K ring
@@ -163,13 +297,14 @@ void k_attn_bf16_pair(AttnArgs a, float c) {
   // alone, the workgroup that arrived first runs as if it had the CU to itself and the other
   // one finishes a quarter later, alone on a CU that it cannot fill.  The later arrival (it
   // gets the higher wave slots of each SIMD) therefore runs at raised priority through its
-  // first phases, which evens out the two finishing times.
-  const bool later_arrival = PW == 2 && (__builtin_amdgcn_s_getreg(4 | (3 << 11)) & 0xf) >= 2;   // HW_ID.WAVE_ID
+  // first phases, which evens out the two finishing times (480 workgroups: 29.7 -> 28.5 us).  Only where the launch
+  // is resident at once: with workgroups waiting for a place it is better to finish the older one (4608: 162.5, 159.7 without).
+  const bool later_arrival = PW == 2 && wide.boost && (__builtin_amdgcn_s_getreg(4 | (3 << 11)) & 0xf) >= 2;   // HW_ID.WAVE_ID
   if (later_arrival) __builtin_amdgcn_s_setprio(1);
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
-  const int n = lane & 15, g4 = lane >> 4;
+  const int n = WIDE ? lane & 31 : lane & 15, hi = WIDE ? lane >> 5 : lane >> 4;   // query column, part of the other index
   // The plan counts 64-key chunks.  Phase 0 is chunk 0 alone, so that the first steps start
   // on the smallest possible amount of data; phase p >= 1 is chunks 2 p - 1 and 2 p.
   const int NC = __builtin_amdgcn_readfirstlane(gd.n_phases);   // chunks of the (padded) key list
@@ -181,8 +316,7 @@ void k_attn_bf16_pair(AttnArgs a, float c) {
   const unsigned char* Kp = (const unsigned char*)a.k + (b * a.ks[0] + h * a.ks[1]) * kElem;
   const unsigned char* Vp = (const unsigned char*)a.v + (b * a.ks[0] + h * a.ks[1]) * kElem;
   const unsigned row_bytes = (unsigned)a.ks[2] * kElem;   // a (batch, head) slab spans < 2 GiB (checked by the API)
-  const int32_t* utok = a.union_tok + gd.union_base;
-  const int ident = __builtin_amdgcn_readfirstlane(gd.ident);   // union entries [0, ident) are token i at position i
+  const int32_t* utok = (WIDE ? wide.union_tok : a.union_tok) + gd.union_base;
   // bf16: eight lanes per 128-byte row; Q8: four lanes per 64-byte row of codes
   const int row = Q8 ? 8 * (wave & 7) + ((lane >> 2) & 7) : 8 * (wave & 7) + (lane >> 3);
   // A lane's row of chunk t goes to slot (t % 5) * 64 + row.  Chunks start at multiples of 64
@@ -190,10 +324,11 @@ void k_attn_bf16_pair(AttnArgs a, float c) {
   // this lane fetches -- does not depend on t.
   const unsigned piece_off = (((unsigned)lane & 7u) ^ ring_swizzle((unsigned)row)) << 4;
   static_assert((kDmaKeys & 63) == 0, "the swizzle folds slot bits 0..5 only");
-  auto issue_chunk = [&](int t, int tok) {             // chunk t -> ring slots (t % 5) * 64 ...
-    tok = checked_index(a.hdr, tok, a.kv_len);
+  auto row_at = [&](int tok) -> unsigned {             // this lane's piece of token tok's row
+    return __umul24((unsigned)checked_index(a.hdr, tok, a.kv_len), row_bytes) + piece_off;   // (both below 2^24, checked by the API)
+  };
+  auto issue_chunk = [&](int t, unsigned src) {        // chunk t -> ring slots (t % 5) * 64 ...
     const int slot0 = (t % kRingChunks) * C + 8 * (wave & 7);
-    const unsigned src = __umul24((unsigned)tok, row_bytes) + piece_off;   // (both below 2^24, checked by the API)
     if (PW == 2 || wave < 8)
       __builtin_amdgcn_global_load_lds((global_void*)(Kp + src), (lds_void*)(Kring + slot0 * kRingRowBytes), 16, 0, 0);
     if (PW == 2 || wave >= 8)
@@ -234,47 +369,38 @@ void k_attn_bf16_pair(AttnArgs a, float c) {
   };  // (tokens and descriptors through buffer loads: a scalar resource and a scalar offset plus a
   // lane offset register, where a flat address costs 64-bit vector arithmetic per load)
   const __amdgpu_buffer_rsrc_t tok_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)utok, 0, NC * C * 4, kBufferFlags);
-  // this lane's row of chunk t (clamped to the last chunk): load_tok() fetches the list entry
-  // unless the whole chunk lies in the identity prefix, tok_of() applied to its result at the
-  // time of use (when the load has been waited for) gives the token
+  // the list entry of this lane's row of chunk t (clamped to the last chunk)
   auto load_tok = [&](int t) -> int {
     const int tc = min(t, NC - 1);
-    if ((tc + 1) * C <= ident) return 0;               // (uniform)
     return (int)__builtin_amdgcn_raw_buffer_load_b32(tok_rsrc, row * 4, tc * C * 4, 0);
   };
-  auto tok_of = [&](int t, int loaded) -> int {
-    const int i = min(t, NC - 1) * C + row;
-    return i < ident ? i : loaded;
-  };
-
   // ---- prologue, scalar part.  Everything that comes through scalar loads (patch
   // descriptors, phase tables, the extent of the group's steps) is fetched before the first
   // vector memory operation: behind the burst of first chunks of all workgroups a scalar
   // miss would take microseconds, and the vector loads below depend on these values.
   // Patch descriptor words: {step_begin, n_steps, q_base, sk | ny << 16, nx | kq << 16, pairs, valid, first_ends}
   // (two patches per wave: p and its partner two patch rows below, columns swapped)
-  const int pa = wave, pb_ = PW == 2 ? ((wave >> 2) + 2) * 4 + ((wave & 3) ^ 1) : wave;
-  const const_i32_ptr wA = (const_i32_ptr)(a.waves + grp_g * 16 + pa), wB = (const_i32_ptr)(a.waves + grp_g * 16 + pb_);
-  const const_i32_ptr wF = (const_i32_ptr)(a.waves + grp_g * 16), wL = (const_i32_ptr)(a.waves + grp_g * 16 + 15);
-  const const_i32_ptr peA = (const_i32_ptr)(a.phase_end + gd.phase_base + pa * NC);
-  const const_i32_ptr peB = (const_i32_ptr)(a.phase_end + gd.phase_base + pb_ * NC);
+  // (wide patches: {.., nx | kq << 16, ceil(65536 / nx), ..})
+  constexpr int kPerGroup = kGroupPatches / PW;          // patches of the list that this form walks
+  const WaveDesc* const patches = (WIDE ? wide.waves : a.waves) + grp_g * kPerGroup;
+  const const_i32_ptr wA = (const_i32_ptr)(patches + wave);
+  const const_i32_ptr wF = (const_i32_ptr)patches, wL = (const_i32_ptr)(patches + kPerGroup - 1);
+  const const_i32_ptr pe = (const_i32_ptr)((WIDE ? wide.phase_end + gd.phase_base / 2 : a.phase_end + gd.phase_base) + wave * NC);
   auto last_chunk = [&](int ph) -> int { return min(2 * ph, NC - 1); };   // of phase ph (clamped)
-  struct PatchWords { int step_begin, q_base, sk_ny, valid; };
-  const PatchWords pwA = {wA[0], wA[2], wA[3], wA[6]}, pwB = {wB[0], wB[2], wB[3], wB[6]};
+  struct PatchWords { int step_begin, q_base, sk_ny, nx_kq, magic, valid; };   // (the wide patches' band has sk = 0)
+  const PatchWords pw = {wA[0], wA[2], wA[3], WIDE ? wA[4] : 0, WIDE ? wA[5] : 0, wA[6]};
   const int first_step = wF[0], n_group_steps = wL[0] + wL[1] - first_step;
-  const int lastA = max(wA[1] - 1, 0), lastB = max(wB[1] - 1, 0);     // last step of each patch
+  const int last = max(wA[1] - 1, 0);                    // last step of the patch
   // cumulative step counts of phases 0 and 1 (an idle patch has zeros); the entry of
   // phase p + 2 is fetched during phase p
-  // (one patch per wave: the second patch's counts are the constant 0 and its code goes away)
   // (those of phases 0 and 1 sit in the patch descriptor, so that nothing the first vector
   // loads depend on waits for a second round of scalar loads behind the group descriptor)
-  const unsigned feA = (unsigned)wA[7], feB = PW == 2 ? (unsigned)wB[7] : 0u;
-  int endA = (int)(feA & 0xffffu), endB = (int)(feB & 0xffffu);
-  int end1A = (int)(feA >> 16), end1B = (int)(feB >> 16);
-  asm volatile("" : : "s"(pwA.step_begin), "s"(pwA.q_base), "s"(pwA.sk_ny), "s"(pwA.valid),
-               "s"(pwB.step_begin), "s"(pwB.q_base), "s"(pwB.sk_ny), "s"(pwB.valid),
-               "s"(n_group_steps), "s"(endA), "s"(endB), "s"(end1A), "s"(end1B), "s"(lastA), "s"(lastB),
+  const unsigned fe = (unsigned)wA[7];
+  int end = (int)(fe & 0xffffu), end1 = (int)(fe >> 16);
+  asm volatile("" : : "s"(pw.step_begin), "s"(pw.q_base), "s"(pw.sk_ny), "s"(pw.nx_kq), "s"(pw.magic), "s"(pw.valid),
+               "s"(n_group_steps), "s"(end), "s"(end1), "s"(last),
                "s"(gd.union_base), "s"(gd.n_phases), "s"(gd.k), "s"(gd.phase_base), "s"(gd.ident));   // all in
+  asm volatile("" : "+s"(c));                            // (so that no step waits for it)
   // Scalar round trip 3, only with an output sharing table: the flag of (head, query scale),
   // as the aligned word that holds the byte (a naturally aligned word lies in its byte's page).
   bool shared = false;
@@ -286,144 +412,153 @@ void k_attn_bf16_pair(AttnArgs a, float c) {
   if (shared && b >= a.B / 2) return;      // the conditional workgroup writes this row
 
   // ---- prologue, vector part.  The key list usually starts with whole key scales (token =
-  // position), which needs no token load; the tokens of the other chunks among the first
-  // three are requested here and waited for together with the small loads below.
-  // leading chunks (of the first three) that lie in the identity prefix: their transfers need no token
-  auto in_prefix = [&](int t) -> bool { return (min(t, NC - 1) + 1) * C <= ident; };
-  const int n_id = (int)in_prefix(0) + (int)in_prefix(1) + (int)in_prefix(2);   // (uniform; non-increasing in t)
+  // position): the transfers of the first three chunks then wait for no token.
+  const bool in_prefix = (min(2, NC - 1) + 1) * C <= gd.ident;
 
-  const int64_t sbA = pwA.step_begin, sbB = pwB.step_begin;
-  const __amdgpu_buffer_rsrc_t descA = __builtin_amdgcn_make_buffer_rsrc((void*)(a.step_addr + sbA * 64), 0, (lastA + 1) * 512, kBufferFlags);
-  const __amdgpu_buffer_rsrc_t descB = __builtin_amdgcn_make_buffer_rsrc((void*)(a.step_addr + sbB * 64), 0, (lastB + 1) * 512, kBufferFlags);
-  const int lane8 = lane * 8;
-  auto load_desc = [&](const __amdgpu_buffer_rsrc_t& rsrc, int s) -> uint2 {
-    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, lane8, s * 512, 0);
-    return make_uint2(v.x, v.y);
+  // Step descriptors: 8 bytes per lane; wide patches 16, the mask included.
+  using Desc = std::conditional_t<WIDE, u32x4, uint2>;
+  constexpr int kDescLane = WIDE ? kWideDesc : 8, kDescBytes = 64 * kDescLane;
+  const unsigned char* const step_desc = WIDE ? wide.step_addr : (const unsigned char*)a.step_addr;
+  const __amdgpu_buffer_rsrc_t desc_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(step_desc + (int64_t)pw.step_begin * kDescBytes), 0, (last + 1) * kDescBytes, kBufferFlags);
+  const int lane_desc = lane * kDescLane;
+  auto load_desc = [&](int s) -> Desc {
+    if constexpr (WIDE) {
+      return __builtin_amdgcn_raw_buffer_load_b128(desc_rsrc, lane_desc, s * kDescBytes, 0);
+    } else {
+      const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(desc_rsrc, lane_desc, s * kDescBytes, 0);
+      return make_uint2(v.x, v.y);
+    }
   };
-  const uint64_t* maskA = a.step_mask + sbA * 8;
-  const uint64_t* maskB = a.step_mask + sbB * 8;
+  [[maybe_unused]] const uint64_t* masks = a.step_mask + (int64_t)pw.step_begin * 8;
 
   // local query row of this lane's query column (-1 = none)
-  auto query_row = [&](const PatchWords& w, int n, bool clamped) -> int {
-    const int sk = w.sk_ny & 0xffff;
-    const int dy = n >> 2, dx = n & 3;
-    const int r = w.q_base + dy * sk + dx;
+  auto query_row = [&](int n, bool clamped) -> int {
+    const int sk = pw.sk_ny & 0xffff;
+    int dy = n >> 2, dx = n & 3;
+    if constexpr (WIDE) { dy = (n * pw.magic) >> 16; dx = n - dy * (pw.nx_kq & 0xffff); }
+    const int r = pw.q_base + dy * sk + dx;
     if (clamped) return max(min(r, a.q_len - 1), 0);
-    return ((w.valid >> n) & 1) ? r : -1;
+    return ((pw.valid >> n) & 1) ? r : -1;
   };
-  // Q rows are loaded unconditionally, from a clamped row where the lane has no query: such
-  // a column of S^T holds scores of some other query, all of its mask bits are clear and it
-  // is never stored, and MFMA columns do not mix
-  auto init_patch = [&](PatchState& ps, const PatchWords& w) {
-    const int ld_row = query_row(w, n, true);
-    if constexpr (Q8) {
-      const int8_t* qp = (const int8_t*)a.q + b * a.qs[0] + h * a.qs[1] + ld_row * a.qs[2] + 16 * g4;
-      const u32x4 qc = *(const u32x4*)qp;
-      const float2 qz = a.q_sz[(int64_t)(b * a.H + h) * a.q_len + ld_row];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        ps.qb0[e] = (__bf16)fmaf(qz.x, (float)(int8_t)((qc[e >> 2] >> (8 * (e & 3))) & 0xffu), qz.y);
-        ps.qb1[e] = (__bf16)fmaf(qz.x, (float)(int8_t)((qc[2 + (e >> 2)] >> (8 * (e & 3))) & 0xffu), qz.y);
-      }
-    } else {
-      const __bf16* qp = (const __bf16*)a.q + b * a.qs[0] + h * a.qs[1] + ld_row * a.qs[2] + 16 * g4;
-      // (inline assembly: the compiler then does not know of a load into these registers and
-      // places no wait of its own, which would cover the chunk transfers too, before their use)
-      u32x4 r0, r1;
-      asm volatile("global_load_dwordx4 %0, %2, off\n\tglobal_load_dwordx4 %1, %2, off offset:16"
-                   : "=&v"(r0), "=&v"(r1) : "v"(qp) : "memory");
-      ps.qb0 = __builtin_bit_cast(bf16x8, r0); ps.qb1 = __builtin_bit_cast(bf16x8, r1);
-    }
-    ps.thr = kFloor; ps.negm = 0.f;
-    ps.Lacc = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) ps.O[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  };
-  PatchState A, B;
-  init_patch(A, pwA);
-  if constexpr (PW == 2) init_patch(B, pwB);
-
-  bf16x8 ones;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
-  asm volatile("" : "+v"(ones));     // kept in four registers (the compiler would rebuild it in every step)
-  const float slack = kSlack / c;
-  // Step descriptors of a patch for one phase: the first step's is fetched during the phase
+  // The loads go out in the order in which their results are needed: tokens (the transfers of the first three chunks
+  // wait for them), step descriptors, Q.  The transfers follow (a load issued behind a chunk is held up until the
+  // chunk's data is in), and what needs no memory is formed behind them.
+  int tok0 = load_tok(0), tok1 = load_tok(1), tok2 = load_tok(2);
+  // Step descriptors for one phase: the first step's is fetched during the phase
   // before (d0), those of the next kLater steps at the start of the phase (dl).
-  uint2 dA0 = make_uint2(0u, 0u), dB0 = dA0, dAl[kLater], dBl[kLater];
-#pragma unroll
-  for (int i = 0; i < kLater; ++i) { dAl[i] = dA0; dBl[i] = dA0; }
   // (Every register that a vector load fills is used only behind an explicit wait for all
   // of the wave's loads: with chunks in flight the compiler would otherwise place such a wait,
   // the chunks included, before the use.  That also allows loads under uniform conditions,
   // whose number the compiler cannot know: only the descriptors that the phase needs.)
-  auto load_later = [&](uint2 (&d)[kLater], const __amdgpu_buffer_rsrc_t& rsrc, int first, int end) {
+  Desc d0 = load_desc(0), dl[kLater];
+#pragma unroll
+  for (int i = 0; i < kLater; ++i) dl[i] = Desc{};
+  auto load_later = [&](int first, int end) {
 #pragma unroll
     for (int i = 0; i < kLater; ++i)
-      if (first + 1 + i < end) d[i] = load_desc(rsrc, first + 1 + i);
+      if (first + 1 + i < end) dl[i] = load_desc(first + 1 + i);
   };
-  dA0 = load_desc(descA, 0);
-  if constexpr (PW == 2) dB0 = load_desc(descB, 0);
-  int tokn0 = load_tok(3), tokn1 = load_tok(4);         // tokens of the chunks issued in phase 1
-  // the later descriptors of phase 0, which has no wait of its own before their use
-  load_later(dAl, descA, 0, endA);
-  load_later(dBl, descB, 0, endB);
+  load_later(0, end);                                   // (phase 0 has no wait of its own before their use)
+  // Q rows are loaded unconditionally, from a clamped row where the lane has no query: such
+  // a column of S^T holds scores of some other query and is never stored, and MFMA columns do not mix
+  constexpr int kQPieces = WIDE ? 4 : 2;
+  u32x4 q_raw[kQPieces];                                // 16-byte pieces of the lane's query; Q8: 16 codes each
+  [[maybe_unused]] float2 q_sz = make_float2(0.f, 0.f);
+  {
+    const int ld_row = query_row(n, true);
+    const unsigned char* qp = (const unsigned char*)a.q + (b * a.qs[0] + h * a.qs[1] + ld_row * a.qs[2]) * kElem;
+    if constexpr (Q8) {
+      q_sz = a.q_sz[(int64_t)(b * a.H + h) * a.q_len + ld_row];
+      if constexpr (WIDE) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {                   // dims 16 t + 8 hi .. + 7
+          const u32x2 r = *(const u32x2*)(qp + 16 * t + 8 * hi);
+          q_raw[t >> 1][2 * (t & 1)] = r.x; q_raw[t >> 1][2 * (t & 1) + 1] = r.y;
+        }
+      } else {
+        q_raw[0] = *(const u32x4*)(qp + 16 * hi);
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < kQPieces; ++t) q_raw[t] = *(const u32x4*)(qp + (WIDE ? 32 * t + 16 * hi : 32 * hi + 16 * t));
+    }
+  }
   // All workgroups walk the same plan in lock-step, so each phase's first access to its part
   // of the plan would be an HBM miss on every workgroup's critical path.  The workgroups of
   // one XCD (they share an L2) therefore touch the group's step descriptors and lane masks
   // once, each its own slice of the 128-byte lines, while the first chunks are on their way.
+  int tokn0 = load_tok(3), tokn1 = load_tok(4);         // tokens of the chunks issued in phase 1
   int warm = 0;
   {
-    const char* da = (const char*)(a.step_addr + (int64_t)first_step * 64);
+    const char* da = (const char*)step_desc + (int64_t)first_step * kDescBytes;
     const char* ma = (const char*)(a.step_mask + (int64_t)first_step * 8);
     // one load per thread: workgroup `me` of this group on this XCD touches the lines
     // [me T, me T + T), T = threads per workgroup (the workgroups beyond the plan's end all
     // touch its last line; with more lines than workgroups x T the rest is touched in part
     // only, which costs nothing but speed)
-    const int lines_d = n_group_steps * 4, lines = lines_d + (n_group_steps + 1) / 2;
-    const int l = min(me * (int)blockDim.x + tid, lines - 1);
-    const char* src = l < lines_d ? da + (int64_t)l * 128 : ma + (int64_t)(l - lines_d) * 128;
+    const int lines_d = n_group_steps * (kDescBytes / 128), lines = lines_d + (WIDE ? 0 : (n_group_steps + 1) / 2);
+    const int l = min(me * (kGroupPatches / PW * 64) + tid, lines - 1);
+    const char* src = WIDE || l < lines_d ? da + (int64_t)l * 128 : ma + (int64_t)(l - lines_d) * 128;
     warm = *(const int*)src;
   }
-  // The chunks go out behind the small loads (a load issued behind a chunk is held up until
-  // the chunk's data is in), chunks 1 and 2 (phase 1) last: phase 0 waits for everything but them.
+  int t0 = row, t1 = min(1, NC - 1) * C + row, t2 = min(2, NC - 1) * C + row;
+  if (!in_prefix) { t0 = tok0; t1 = tok1; t2 = tok2; }   // (waits for the tokens only)
+  asm volatile("" : "+v"(t0), "+v"(t1), "+v"(t2));      // (all three formed before the first transfer)
   if constexpr (Q8) {
     // through registers: the three chunks are requested together, converted and written, and
     // the first barrier finds all of them in the ring
-    int tok0 = 0, tok1 = 0, tok2 = 0;
-    if (n_id < 3) { tok0 = load_tok(0); tok1 = load_tok(1); tok2 = load_tok(2); }
-    const ChunkRegs c0 = load_chunk(tok_of(0, tok0)), c1 = load_chunk(tok_of(1, tok1)), c2 = load_chunk(tok_of(2, tok2));
+    const ChunkRegs c0 = load_chunk(t0), c1 = load_chunk(t1), c2 = load_chunk(t2);
     commit_chunk(0, c0); commit_chunk(1, c1); commit_chunk(2, c2);
-  } else if (n_id == 3) {
-    issue_chunk(0, tok_of(0, 0)); issue_chunk(1, tok_of(1, 0)); issue_chunk(2, tok_of(2, 0));
   } else {
-    // Some of the three chunks need their tokens: these are requested behind the small loads
-    // and travel with them; the chunks of the prefix go out meanwhile; then one wait for
-    // everything issued so far.  (All in this branch, so that on the other one the compiler
-    // knows of no token load in flight.)
-    int tok0 = load_tok(0), tok1 = load_tok(1), tok2 = load_tok(2);
-    if (n_id >= 1) issue_chunk(0, tok_of(0, 0));
-    if (n_id >= 2) issue_chunk(1, tok_of(1, 0));
-    wait_vmcnt<0>();
-    asm volatile("" : "+v"(tok0), "+v"(tok1), "+v"(tok2));
-    if (n_id < 1) issue_chunk(0, tok_of(0, tok0));
-    if (n_id < 2) issue_chunk(1, tok_of(1, tok1));
-    issue_chunk(2, tok_of(2, tok2));
+    issue_chunk(0, row_at(t0)); issue_chunk(1, row_at(t1)); issue_chunk(2, row_at(t2));
   }
-  // (Q was loaded through inline assembly: everything older than the three chunks is in once
-  // at most their transfers are outstanding, and the registers are tied to that point)
-  if constexpr (Q8) {
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (the ring writes above are visible)
-  } else {
-    wait_vmcnt<3 * kDmaPerChunk>();
-    asm volatile("" : "+v"(A.qb0), "+v"(A.qb1));
-    if constexpr (PW == 2) asm volatile("" : "+v"(B.qb0), "+v"(B.qb1));
-    wait_vmcnt<2 * kDmaPerChunk>();
-    asm volatile("s_barrier" ::: "memory");
-  }
+  __builtin_amdgcn_sched_barrier(0);
 
-  // One step: 32 keys against the 16 queries of patch ps.
-  auto run_step = [&](PatchState& ps, const uint2 cur, const uint64_t* masks, int s) {
+  std::conditional_t<WIDE, WidePatchState, PatchState> ps;
+  [[maybe_unused]] const uint64_t queries = (uint64_t)(unsigned)pw.valid * 0x100000001ull;   // wide: the lanes that hold a query
+  [[maybe_unused]] const bool band = (pw.sk_ny & 0xffff) == 0;
+  [[maybe_unused]] const float slack = kSlack / c;
+  [[maybe_unused]] bf16x8 ones;
+  ps.negm = 0.f;
+  if constexpr (WIDE) {
+    ps.L = 0.f; ps.unset = queries;
+    const int nx = pw.nx_kq & 0xffff, ny = pw.sk_ny >> 16, dy = (n * pw.magic) >> 16, dx = n - dy * nx;
+    const int i0 = (band ? n : dy) - 8 * hi, i1 = (band ? n : ny + dx) - 8 * hi;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ps.b[e] = (__bf16)(((int)(i0 == e) | (int)(i1 == e)) ? 1.0f : 0.0f);
+    ps.O[0] = f32x16{}; ps.O[1] = f32x16{};
+  } else {
+    ps.thr = kFloor;
+    ps.Lacc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) ps.O[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+    asm volatile("" : "+v"(ones));   // kept in four registers (the compiler would rebuild it in every step)
+  }
+  // everything older than chunks 1 and 2 is in: Q, the descriptors and tokens, chunk 0 (Q8: all three chunks)
+  if constexpr (Q8) wait_vmcnt<0>(); else wait_vmcnt<2 * kDmaPerChunk>();
+#pragma unroll
+  for (int t = 0; t < kQPieces; ++t) {
+    bf16x8 piece;
+    if constexpr (Q8) {
+      const unsigned w0 = q_raw[t >> 1][2 * (t & 1)], w1 = q_raw[t >> 1][2 * (t & 1) + 1];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) piece[e] = (__bf16)fmaf(q_sz.x, (float)(int8_t)(((e < 4 ? w0 : w1) >> (8 * (e & 3))) & 0xffu), q_sz.y);
+    } else {
+      piece = __builtin_bit_cast(bf16x8, q_raw[t]);
+    }
+    if constexpr (WIDE) ps.q[t] = piece;
+    else if (t == 0) ps.qb0 = piece;
+    else ps.qb1 = piece;
+  }
+  if constexpr (Q8) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (the ring writes above are visible)
+  else asm volatile("s_barrier" ::: "memory");
+  asm volatile("" : : "v"(tok0), "v"(tok1), "v"(tok2));   // (their registers stay theirs until here: no wait before another use)
+
+  // One step: 32 keys against the patch's 16 queries.
+  [[maybe_unused]] auto run_step16 = [&](auto& ps, const uint2 cur, int s) {
     // lane masks of the step (a scalar load): requested ahead of the K pieces so that the
     // two latencies overlap
     const const_u64_ptr mkp = (const_u64_ptr)((const char*)masks + (unsigned)s * 64u);
@@ -496,81 +631,207 @@ void k_attn_bf16_pair(AttnArgs a, float c) {
     ps.Lacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb, ps.Lacc, 0, 0, 0);
   };
 
-  // ---- phases ----
-  int doneA = 0, doneB = 0;                             // steps finished so far
-  auto run_phase = [&](int ph, auto is_first, auto has_next) {
-    constexpr bool FIRST = decltype(is_first)::value, NEXT = decltype(has_next)::value;
-    if (!FIRST && ph == kBoostPhases) __builtin_amdgcn_s_setprio(0);
-    [[maybe_unused]] ChunkRegs cr0, cr1;                 // Q8: the chunks of phase ph + 1 on their way
-    // (scalar loads, two phases ahead of their use)
-    const int end2A = peA[last_chunk(ph + 2)], end2B = PW == 2 ? peB[last_chunk(ph + 2)] : 0;
-    if constexpr (!FIRST) {            // (phase 0: fetched in the prologue)
-      load_later(dAl, descA, doneA, endA);
-      load_later(dBl, descB, doneB, endB);
+  // One step of a wide patch: 32 keys against 32 queries.  The arithmetic is that of a 16-query step; what differs:
+  //  * The mask is a matrix product too.  A window is a product of rows and columns: dimension i < ny of it stands for
+  //    query row i, dimension ny + j for query column j; the B operand has a one where the query lies in that
+  //    row or column, the A operand -2^127 or more where the key is not kept by it (else zero or nearly), from the
+  //    descriptor's sixteen bits per lane.  So the score tile starts at zero or at minus a number that no score
+  //    makes up for, with seven vector instructions, where sixteen selects took a scalar load of 128 bytes per
+  //    step on the wave's critical path.  Bands take two products with one dimension per query.
+  //  * The row sums are the lane's own (v_dot2 on the rounded probabilities; a product with ones would need
+  //    sixteen more registers).
+  //  * No maximum is formed.  The softmax reference starts at zero and moves only when a query's sum leaves
+  //    [2^-40, 2^40] (the lower end is looked at until every query has passed it), which costs one comparison
+  //    where the maximum of sixteen scores costs eight.  Probabilities and sums keep their relative precision
+  //    under any common factor, and the factors are powers of two.
+  [[maybe_unused]] auto run_step32 = [&](auto& ps, const u32x4 cur) {
+    constexpr int kRingBytes = R * kRingRowBytes;
+    u32x4 kr[4];
+    lds_read_k_row_issue(lds_addr(Kring + checked_index(a.hdr, cur.x, kRingBytes)), kr);
+    unsigned v[4] = {cur.y & 0xffffu, cur.y >> 16, cur.z & 0xffffu, cur.z >> 16}, x[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[i] = lds_addr(Kring + checked_index(a.hdr, v[i], kRingBytes));
+      x[i] = v[i] ^ 64u;
     }
-    if (doneA < endA) run_step(A, dA0, maskA, doneA);
-    if (doneB < endB) run_step(B, dB0, maskB, doneB);
-    if constexpr (NEXT) {
-      if constexpr (!FIRST) {
-        // The later descriptors have had two steps to arrive; with nothing else outstanding
-        // when the chunks go out, no later use of a loaded register has to wait for them
-        // (the compiler would otherwise wait for everything, the chunks included).
-        wait_vmcnt<0>();
+    const unsigned mask_bits = cur.w;          // (a bit cast of a vector's element would read element 0)
+    // 16-bit halves of the descriptor's mask word: bits 15, 13, .. are elements 0, 2, .. (low half) or 1, 3, .. (high half);
+    // moved to the sign and spread over eight bits, a set one reads as bf16 -2^127 or up to twice that
+    auto mask_operand = [&](int first) -> bf16x8 {
+      u32x4 m;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const s16x2 bits = __builtin_bit_cast(s16x2, mask_bits) << (short)(2 * (first + r));
+        m[r] = __builtin_bit_cast(unsigned, bits >> (short)7);
       }
-      // first descriptors and tokens of the next phase: in place, their users are done
+      return __builtin_bit_cast(bf16x8, m);
+    };
+    f32x16 S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mask_operand(0), ps.b, f32x16{}, 0, 0, 0);
+    if (band) {
+      int i = n - 16 - 8 * hi;                           // (formed here: not worth four registers of every plan)
+      asm volatile("" : "+v"(i));
+      bf16x8 upper;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) upper[e] = (__bf16)(i == e ? 1.0f : 0.0f);
+      S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mask_operand(4), upper, S, 0, 0, 0);
+    }
+    asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+    lds_wait_k(kr[0], kr[1], kr[2], kr[3]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kr[t]), ps.q[t], S, 0, 0, 0);
+    uint2 va[8];
+    lds_read_v_wide<VOFF>(v, x, va);
+    __builtin_amdgcn_sched_barrier(0);         // (the reads go out here, not behind the exponentials)
+    bf16x8 pb[2];
+    float sum;
+    auto exponentials = [&]() {
+      sum = ps.L;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pb[t][e] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(S[8 * t + e], c, ps.negm));
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+          const bf16x2 two = {pb[t][e], pb[t][e + 1]};
+          sum = __builtin_amdgcn_fdot2_f32_bf16(two, kOnes, sum, false);
+        }
+      }
+    };
+    exponentials();
+    uint64_t move = __builtin_amdgcn_ballot_w64(sum > kMostSum);
+    if (__builtin_expect(ps.unset != 0, 0)) {
+      ps.unset = __builtin_amdgcn_ballot_w64(sum + other_half(sum) < kLeastSum) & queries;
+      move |= ps.unset;
+    }
+    if (__builtin_expect(move != 0, 0)) {
+      float mx = S[0];
+#pragma unroll
+      for (int e = 1; e < 16; ++e) mx = fmaxf(mx, S[e]);
+      mx = fmaxf(mx, other_half(mx));                    // over both lanes of the query
+      const float now = sum + other_half(sum), before = ps.L + other_half(ps.L);
+      float to = mx > -1.0e30f ? __builtin_fmaf(mx, c, ps.negm) : kFloor;      // (masked scores lie far below)
+      if (before > 0.f) to = fmaxf(to, __builtin_amdgcn_logf(before));         // (base 2)
+      const float shift = (now > kMostSum || now < kLeastSum) && to > kFloor ? rintf(to) : 0.f;
+      const float alpha = before > 0.f ? __builtin_amdgcn_exp2f(-shift) : 1.f;
+      ps.negm -= shift; ps.L *= alpha;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) { ps.O[0][e] *= alpha; ps.O[1][e] *= alpha; }
+      exponentials();
+      if (ps.unset) ps.unset = __builtin_amdgcn_ballot_w64(sum + other_half(sum) < kLeastSum) & queries;
+    }
+    ps.L = sum;
+    lds_wait_v_wide(va);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt) {
+        const uint4 v8 = {va[4 * t + dt].x, va[4 * t + dt].y, va[4 * t + 2 + dt].x, va[4 * t + 2 + dt].y};
+        ps.O[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(v8), pb[t], ps.O[dt], 0, 0, 0);
+      }
+  };
+  auto run_step = [&](const Desc cur, int s) {
+    if constexpr (WIDE) run_step32(ps, cur); else run_step16(ps, cur, s);
+  };
+
+  // ---- phases ----
+  int done = 0;                                         // steps finished so far
+  // (phase 0 is a copy of its own: of a condition that stands twice the compiler also considers the mixed paths, on
+  // which it would have to wait for loads that are long in)
+  auto run_phase = [&](int ph, auto is_first) -> bool {
+    constexpr bool FIRST = decltype(is_first)::value;
+    const bool next = ph + 1 < P;                        // (P >= 1; a list of one chunk has no steps after phase 0)
+    if (!FIRST && ph == kBoostPhases) __builtin_amdgcn_s_setprio(0);
+    [[maybe_unused]] ChunkRegs cr0{}, cr1{};             // Q8: the chunks of phase ph + 1 on their way
+    const int end2 = pe[last_chunk(ph + 2)];            // (a scalar load, two phases ahead of its use)
+    if constexpr (!FIRST) load_later(done, end);        // (phase 0: fetched in the prologue)
+    if (done < end) run_step(d0, done);
+    // The later descriptors have had a step to arrive; with nothing else outstanding
+    // when the chunks go out, no later use of a loaded register has to wait for them
+    // (the compiler would otherwise wait for everything, the chunks included).
+    if constexpr (!FIRST) wait_vmcnt<0>();
+    if (next) {
+      // first descriptor and tokens of the next phase: in place, their users are done
       // (ahead of the chunks: a load issued behind a chunk is held up until its data is in)
-      dA0 = load_desc(descA, min(endA, lastA));
-      if constexpr (PW == 2) dB0 = load_desc(descB, min(endB, lastB));
+      d0 = load_desc(min(end, last));
       if constexpr (!FIRST) {
-        const int t0 = tok_of(2 * ph + 1, tokn0), t1 = tok_of(2 * ph + 2, tokn1);
+        [[maybe_unused]] unsigned r0 = 0, r1 = 0;
+        if constexpr (Q8) { cr0 = load_chunk(tokn0); cr1 = load_chunk(tokn1); }
+        else { r0 = row_at(tokn0); r1 = row_at(tokn1); asm volatile("" : "+v"(r0), "+v"(r1)); }   // (formed before the registers are loaded again)
         tokn0 = load_tok(2 * ph + 3); tokn1 = load_tok(2 * ph + 4);
         // the chunks of phase ph + 1, into the slots of chunks 2 ph - 4 and 2 ph - 3
-        if constexpr (Q8) { cr0 = load_chunk(t0); cr1 = load_chunk(t1); }
-        else { issue_chunk(2 * ph + 1, t0); issue_chunk(2 * ph + 2, t1); }
+        if constexpr (!Q8) { issue_chunk(2 * ph + 1, r0); issue_chunk(2 * ph + 2, r1); }
       }
     }
 #pragma unroll
     for (int i = 0; i < kLater; ++i)
-      if (doneA + 1 + i < endA) run_step(A, dAl[i], maskA, doneA + 1 + i);
+      if (done + 1 + i < end) run_step(dl[i], done + 1 + i);
     // (a patch rarely has more steps in a phase; their descriptors are loaded on the spot)
-    for (int s = doneA + 1 + kLater; s < endA; ++s) run_step(A, load_desc(descA, s), maskA, s);
-#pragma unroll
-    for (int i = 0; i < kLater; ++i)
-      if (doneB + 1 + i < endB) run_step(B, dBl[i], maskB, doneB + 1 + i);
-    for (int s = doneB + 1 + kLater; s < endB; ++s) run_step(B, load_desc(descB, s), maskB, s);
-    doneA = endA; doneB = endB;
-    endA = end1A; endB = end1B; end1A = end2A; end1B = end2B;
+    for (int s = done + 1 + kLater; s < end; ++s) run_step(load_desc(s), s);
+    done = end;
+    end = end1; end1 = end2;
     // The chunks of phase ph + 1, the next descriptors and tokens are in once nothing of
     // this wave is outstanding.  All LDS reads of the phase have returned (each step waits
     // for its own), so after the barrier the slots of chunks 2 ph - 3 and 2 ph - 2 are free.
     wait_vmcnt<0>();
-    if constexpr (Q8 && NEXT && !FIRST) {
+    if (!next) return false;
+    if constexpr (Q8 && !FIRST) {
       // (their slots held chunks 2 ph - 4 and 2 ph - 3, which nobody has read since the
       // barrier that ended phase ph - 1; the writes are complete before this phase's barrier)
       commit_chunk(2 * ph + 1, cr0); commit_chunk(2 * ph + 2, cr1);
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
-    if constexpr (NEXT) asm volatile("s_barrier" ::: "memory");
+    asm volatile("s_barrier" ::: "memory");
+    return true;
   };
-  {
-    run_phase(0, std::true_type{}, std::true_type{});
+  if (run_phase(0, std::true_type{})) {
     int ph = 1;
-    for (; ph + 1 < P; ++ph) run_phase(ph, std::false_type{}, std::true_type{});
-    run_phase(ph, std::false_type{}, std::false_type{});    // (no steps left when the list is one chunk)
+    while (run_phase(ph, std::false_type{})) ++ph;
   }
-
 
   asm volatile("" : : "v"(warm));      // the only use of the plan-touching load: keeps it
 
   // ---- epilogue ----
-  auto store_patch = [&](const PatchState& ps, const PatchWords& w) {
-    int n_again = n;                           // recomputed from scratch: the row is not worth a
-    asm volatile("" : "+v"(n_again));          // register (or a spill slot) through the loop
-    int qrow = query_row(w, n_again, false);
+  int n_again = n;                             // recomputed from scratch: the row is not worth a
+  asm volatile("" : "+v"(n_again));            // register (or a spill slot) through the loop
+  int qrow = query_row(n_again, false);
+  if constexpr (WIDE) {
+    const float inv = 1.f / (ps.L + other_half(ps.L));
+    float any = 0.f;
+    unsigned r[2][8];
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+      for (int e = 0; e < 16; e += 2) {
+        const bf16x2 two = {(__bf16)(ps.O[dt][e] * inv), (__bf16)(ps.O[dt][e + 1] * inv)};
+        any = __builtin_amdgcn_fdot2_f32_bf16(two, kOnes, any, false);
+        r[dt][e / 2] = __builtin_bit_cast(unsigned, two);
+      }
+    // A matrix product multiplies the rows of a step with the probability 0 of the queries that do not keep
+    // them, so a value of K or V that is not finite makes all queries of its step NaN.  A wave that finds such a
+    // result forms it once more, key by key, from the kept pairs alone.
+    const bool again = qrow >= 0 && (not_finite(any) || not_finite(other_half(any)));
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(again) != 0, 0))
+      attend_key_by_key<Q8>(a, c, b, h, grp_g * kGroupPatches, again ? qrow : -1, hi, r);
+    if (qrow < 0) return;
+    qrow = checked_index(a.hdr, qrow, a.q_len);
+    __bf16* op = (__bf16*)a.o + b * a.os[0] + h * a.os[1] + qrow * a.os[2] + 8 * hi;
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        // dims 32 dt + 16 j .. + 15 of the query: its lanes hold 4 of each 8; exchanged, 8 in a row
+        const auto x0 = __builtin_amdgcn_permlane32_swap(r[dt][4 * j], r[dt][4 * j + 2], false, false);
+        const auto x1 = __builtin_amdgcn_permlane32_swap(r[dt][4 * j + 1], r[dt][4 * j + 3], false, false);
+        const u32x4 piece = {x0[0], x1[0], x0[1], x1[1]};
+        *(u32x4*)(op + 32 * dt + 16 * j) = piece;
+        if (shared) *(u32x4*)(op + (a.B / 2) * a.os[0] + 32 * dt + 16 * j) = piece;
+      }
+  } else {
     if (qrow < 0) return;
     qrow = checked_index(a.hdr, qrow, a.q_len);
     const float inv = 1.f / ps.Lacc[0];
-    __bf16* op = (__bf16*)a.o + b * a.os[0] + h * a.os[1] + qrow * a.os[2] + 4 * g4;
+    __bf16* op = (__bf16*)a.o + b * a.os[0] + h * a.os[1] + qrow * a.os[2] + 4 * hi;
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt) {
       bf16x4 r;
@@ -579,9 +840,7 @@ void k_attn_bf16_pair(AttnArgs a, float c) {
       *(bf16x4*)(op + 16 * dt) = r;
       if (shared) *(bf16x4*)(op + (a.B / 2) * a.os[0] + 16 * dt) = r;
     }
-  };
-  store_patch(A, pwA);
-  if constexpr (PW == 2) store_patch(B, pwB);
+  }
 }
 
 litevar_status launch_attn_bf16_pair(const litevar_plan* pl, const AttnArgs& args, hipStream_t st) {
@@ -590,30 +849,40 @@ litevar_status launch_attn_bf16_pair(const litevar_plan* pl, const AttnArgs& arg
   AttnArgs a = args;
   const int64_t blocks = spread_over_xcds(a, a.n_groups, a.k_sz ? 72 : 128);
   if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large");
-  // One patch per wave when the launch has no more working workgroups than the GPU has CUs
-  // (with output sharing about half of them exit at once): sixteen waves then fill the CU that
-  // eight would leave half empty.
-  int pw = pl->patches_per_wave;
-  if (pw == 0) {
-    static thread_local int n_cu[64] = {0};
-    int dev = 0;
-    if (litevar_status s = hip_check(hipGetDevice(&dev), "hipGetDevice")) return s;
-    if (dev >= 0 && dev < 64 && n_cu[dev] == 0)
-      if (litevar_status s = hip_check(hipDeviceGetAttribute(&n_cu[dev], hipDeviceAttributeMultiprocessorCount, dev),
-                                       "hipDeviceGetAttribute")) return s;
-    const int cus = dev >= 0 && dev < 64 ? n_cu[dev] : 256;
-    const int64_t working = a.cfg_share ? ((int64_t)a.B * a.H * a.n_groups + 1) / 2 : (int64_t)a.B * a.H * a.n_groups;
-    pw = working <= cus ? 1 : 2;
+  // Sixteen waves with a 16-query patch each where the plan asks for them, or has no wide patches.  They are nowhere
+  // quicker, on a CU of their own either: 256 queries on 680 keys, 60 / 240 pairs 14.0 / 17.0 us, wide 13.4 / 16.4; 169
+  // queries 10.5 / 11.6, wide 10.4 / 11.6; 1024 on 2240 keys, 60 pairs 22.8, wide 21.2; 680 tokens, 8 pairs 12.7, wide 12.1.
+  // (A blob laid out before there were wide patches has none of their descriptors.  Its section of patches says so
+  // without doubt: a group's 16 descriptors are 512 bytes and its eight wide ones 256, so it has no padding.)
+  const int64_t groups = (int64_t)pl->n_groups * pl->n_head_groups;
+  const bool has_wide = pl->off[kSecPhaseEnd] - pl->off[kSecWaves] == (uint64_t)groups * (16 + kWidePatches) * sizeof(WaveDesc);
+  const int pw = has_wide && pl->patches_per_wave != 1 ? 2 : 1;
+  WideArgs w{};
+  if (has_wide) {
+    w.waves = a.waves + groups * 16;
+    w.phase_end = a.phase_end + pl->n_union_keys / pl->chunk_keys * 16;
+    w.union_tok = a.union_tok + pl->n_union_keys;
+    // (the wide steps come first in their section, which has no padding either)
+    w.step_addr = (const unsigned char*)a.step_addr;
+    a.step_addr = (const uint2*)((const char*)pl->d_blob + pl->off[kSecStepMask]) - pl->n_steps * 64;
   }
+  // all workgroups are resident at once (two per CU): see later_arrival
+  static thread_local int n_cu[64] = {0};
+  int dev = 0;
+  if (litevar_status s = hip_check(hipGetDevice(&dev), "hipGetDevice")) return s;
+  if (dev >= 0 && dev < 64 && n_cu[dev] == 0)
+    if (litevar_status s = hip_check(hipDeviceGetAttribute(&n_cu[dev], hipDeviceAttributeMultiprocessorCount, dev),
+                                     "hipDeviceGetAttribute")) return s;
+  w.boost = blocks <= 2 * (dev >= 0 && dev < 64 ? n_cu[dev] : 256);
   const float c = a.sm_scale * 1.4426950408889634f;
   const bool q8 = a.k_sz != nullptr;
   const dim3 wg(kGroupPatches / pw * 64);
   return launch_in_parts(blocks, (int)wg.x, "bf16 attention launch", [&](int64_t first, unsigned n) {
     a.first_block = (uint32_t)first;
-    if (pw == 1 && q8) hipLaunchKernelGGL((k_attn_bf16_pair<1, true>), dim3(n), wg, 0, st, a, c);
-    else if (pw == 1) hipLaunchKernelGGL((k_attn_bf16_pair<1, false>), dim3(n), wg, 0, st, a, c);
-    else if (q8) hipLaunchKernelGGL((k_attn_bf16_pair<2, true>), dim3(n), wg, 0, st, a, c);
-    else hipLaunchKernelGGL((k_attn_bf16_pair<2, false>), dim3(n), wg, 0, st, a, c);
+    if (pw == 1 && q8) hipLaunchKernelGGL((k_attn_bf16_pair<1, true>), dim3(n), wg, 0, st, a, w, c);
+    else if (pw == 1) hipLaunchKernelGGL((k_attn_bf16_pair<1, false>), dim3(n), wg, 0, st, a, w, c);
+    else if (q8) hipLaunchKernelGGL((k_attn_bf16_pair<2, true>), dim3(n), wg, 0, st, a, w, c);
+    else hipLaunchKernelGGL((k_attn_bf16_pair<2, false>), dim3(n), wg, 0, st, a, w, c);
   });
 }
 

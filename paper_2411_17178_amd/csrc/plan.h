@@ -15,7 +15,12 @@
 //           (query, key);
 //   phase   the group processes the union list in chunks of C keys; a step is
 //           run in the phase of its last key and may reach back A chunks;
-//   head group   heads that share one radius table share one set of groups, lists and steps.
+//   head group   heads that share one radius table share one set of groups, lists and steps;
+//   wide patch   32 queries of one scale = the 32 columns of one 32x32 MFMA tile.  The groups of 16 patches
+//           carry a second work-list over the same key list: up to eight wide patches (4 x 8
+//           queries, or what covers the group's queries with the fewest key rows; band mode: 32
+//           consecutive queries) with steps of 32 keys of their own.  The 16-patch kernel's eight-wave form
+//           walks it; the exports and the other kernels walk the patches of 16.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -31,6 +36,9 @@ constexpr int kMaxHeads = 256;       // heads with their own radius table
 constexpr int kStepKeys = 32;
 constexpr int kPatch = 4;
 constexpr int kPatchQueries = 16;
+constexpr int kWidePatches = 8;      // wide patches of a group (plans with 16 patches per group)
+constexpr int kWideQueries = 32;
+constexpr int kWideDesc = 16;        // bytes of a wide step's descriptor per lane
 constexpr int kMergedScales = 3;     // band mode: the first part spans the first three scales
 constexpr uint64_t kMagic = 0x4c56415257494e32ull;  // "LVARWIN2"
 
@@ -41,6 +49,7 @@ struct Geom {
   int L, Lq, q0, smax;
   int NW;               // patches per group
   short grh[kMaxScales], grw[kMaxScales];   // window mode: group shape in patches (grh x grw <= NW) of every query scale
+  short wph[kMaxScales], wpw[kMaxScales];   // window mode, NW = 16: queries of a wide patch of every query scale
   int C, NR, A, D;      // chunk keys (a power of two), ring depth in chunks, look-back and
                         // prefetch depth in chunks; NR = A + 1 + D
   int logC;
@@ -82,6 +91,8 @@ struct WaveDesc {    // 32 bytes
   uint32_t first_ends; // phase_end[0] | phase_end[min(2, n_phases - 1)] << 16: the step counts that the
                        // 16-patch kernel needs before it can start, next to the patch's other words
 };
+// (Wide patches use the same words: their query n is row q_base + (n / nx) * sk + n % nx, nx being the
+// patch's own extent, and `pairs` holds ceil(65536 / nx), with which n / nx is one multiplication.)
 static_assert(sizeof(WaveDesc) == 32 && sizeof(GroupDesc) == 32, "descriptor size");
 
 struct Header {      // first 256 bytes of the blob
@@ -96,7 +107,8 @@ struct Header {      // first 256 bytes of the blob
                        // kErrBounds: a kernel of the bounds-checking build found a token, a query
                        // row or an LDS offset out of range (it used index 0 instead)
   int32_t pad0;
-  uint64_t pad[24];
+  int64_t n_wide_steps;  // steps of the wide patches (16 patches per group), else 0
+  uint64_t pad[23];
 };
 static_assert(sizeof(Header) == 256, "header size");
 
@@ -190,6 +202,37 @@ inline void choose_group_shape(int pps, int nw, int& rh, int& rw) {
   }
 }
 
+// Shape of a wide patch for scale side s whose groups hold rh x rw patches: at most 32 queries, at most
+// eight patches per group, at most twelve rows and columns together (their windows travel in twelve lanes of
+// the builder's walk).  The least sum of (rows + 6) (columns + 6) over the scale's patches, which is what
+// they keep at a radius of three at equal scale sides; then the wider one, whose keys lie in longer runs.
+inline bool choose_wide_shape(int s, int rh, int rw, short& wph, short& wpw) {
+  const int H = rh * kPatch < s ? rh * kPatch : s, W = rw * kPatch < s ? rw * kPatch : s;
+  long best = -1;
+  for (int ph = 1; ph <= H && ph <= 11; ++ph)
+    for (int pw = 1; pw <= W && ph * pw <= kWideQueries && ph + pw <= 12; ++pw) {
+      if (((H + ph - 1) / ph) * ((W + pw - 1) / pw) > kWidePatches) continue;
+      long ny = 0, nx = 0;
+      for (int y = 0; y < s; y += rh * kPatch) ny += ((s - y < H ? s - y : H) + ph - 1) / ph;
+      for (int x = 0; x < s; x += rw * kPatch) nx += ((s - x < W ? s - x : W) + pw - 1) / pw;
+      const long key = ny * nx * (ph + 6) * (pw + 6) * 16 - pw;
+      if (best < 0 || key < best) { best = key; wph = (short)ph; wpw = (short)pw; }
+    }
+  return best >= 0;
+}
+
+// Order of the rows of a box in the wide patches' key list.  Row by row a box serves its group's patches one
+// after the other, and every phase ends when the patch whose rows are passing is done; with the rows dealt from four
+// strips in turn, each phase holds keys of all of them.  (Longest wave over the mean, summed over the phases:
+// 1.31 -> 1.19 for 256 queries on 680 keys, 1.48 -> 1.31 for side 64 of a 14-scale list.)  The first three chunks
+// keep the order of the scales, so that lists that begin with whole scales need no tokens for them.
+constexpr int kPlainKeys = 192;
+LV_HD bool dealt_box(int mode, int ubase) { return mode == kModeWindow && ubase >= kPlainKeys; }
+LV_HD int dealt_row(int i, int rows) {     // row of the box at place i
+  const int a = rows >> 2, b = rows & 3, strip = i < 4 * a ? i & 3 : i - 4 * a, round = i < 4 * a ? i >> 2 : a;
+  return strip * a + (strip < b ? strip : b) + round;
+}
+
 LV_HD int patches_per_side(const Geom& g, int k) { return (g.s[k] + kPatch - 1) / kPatch; }
 LV_HD int scale_patches(const Geom& g, int k) {
   if (g.mode == kModeBand) return (g.s[k] * g.s[k] + kPatchQueries - 1) / kPatchQueries;
@@ -267,6 +310,28 @@ LV_HD PatchExtent patch_extent(const Geom& g, int k, int gy, int gx, int wave) {
   return p;
 }
 
+// the same of wide patch `wave` of a group
+LV_HD PatchExtent wide_extent(const Geom& g, int k, int gy, int gx, int wave) {
+  PatchExtent p;
+  const int sk = g.s[k];
+  if (g.mode == kModeBand) {
+    p.y0 = gy * g.NW * kPatchQueries + wave * kWideQueries; p.x0 = 0;
+    const int left = sk * sk - p.y0;
+    if (left <= 0) { p.ny = p.nx = 0; return p; }
+    p.ny = 1; p.nx = left < kWideQueries ? left : kWideQueries;
+    return p;
+  }
+  const int ph = g.wph[k], pw = g.wpw[k], gh = g.grh[k] * kPatch, gw = g.grw[k] * kPatch;
+  const int per_row = ((gw < sk ? gw : sk) + pw - 1) / pw;
+  const int y = wave / per_row * ph, x = wave % per_row * pw;      // inside the group
+  p.y0 = gy * gh + y; p.x0 = gx * gw + x;
+  const int h = sk - gy * gh < gh ? sk - gy * gh : gh, w = sk - gx * gw < gw ? sk - gx * gw : gw;
+  if (y >= h || x >= w) { p.ny = p.nx = 0; return p; }
+  p.ny = h - y < ph ? h - y : ph;
+  p.nx = w - x < pw ? w - x : pw;
+  return p;
+}
+
 // descriptor fields of a patch: first local query row, row stride of the 4x4 arrangement,
 // and the columns that hold a query
 LV_HD void patch_queries(const Geom& g, int k, const PatchExtent& p, int& q_base, int& sk, uint32_t& valid) {
@@ -317,7 +382,7 @@ struct StepCounter {
 // query) merged into runs, and their summed length.
 struct AxisSpan {
   int n_runs = 0, kept = 0;
-  Interval run[kPatchQueries];
+  Interval run[kWideQueries];
   void add(const Interval& iv) {
     kept += iv.hi - iv.lo + 1;
     if (n_runs > 0 && iv.lo <= run[n_runs - 1].hi + 1) { if (iv.hi > run[n_runs - 1].hi) run[n_runs - 1].hi = iv.hi; }

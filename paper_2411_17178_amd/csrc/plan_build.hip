@@ -21,6 +21,7 @@ static void choose_tiling(Geom& g, int waves, int chunk, int depth, int spare) {
     int rh, rw;
     choose_group_shape((g.s[k] + kPatch - 1) / kPatch, waves, rh, rw);
     g.grh[k] = (short)rh; g.grw[k] = (short)rw;
+    if (waves == 16) choose_wide_shape(g.s[k], rh, rw, g.wph[k], g.wpw[k]);   // (there is one for every side up to kMaxSide)
   }
   g.NR = g.A + 1 + g.D + spare;
   g.logC = 0;
@@ -180,10 +181,38 @@ litevar_status size_plan(PlanSpec& sp, PlanSizes& z) {
   return rc;
 }
 
+// a patch's keys of one key scale: rows x columns of the group's box, which starts at entry `ubase` of the
+// list, at (gylo, gxlo) of the scale, and is gw wide
+static void add_box(StepCounter& steps, const AxisSpan& rows, const AxisSpan& cols, int ubase, int gylo, int gxlo, int gw) {
+  for (int r = 0; r < rows.n_runs; ++r) {
+    const int y0 = rows.run[r].lo, y1 = rows.run[r].hi;
+    if (cols.n_runs == 1 && cols.hi() - cols.lo() + 1 == gw) {      // whole rows of the group's box
+      steps.run(ubase + (y0 - gylo) * gw, (y1 - y0 + 1) * gw);
+      continue;
+    }
+    for (int y = y0; y <= y1; ++y)
+      for (int i = 0; i < cols.n_runs; ++i)
+        steps.run(ubase + (y - gylo) * gw + cols.run[i].lo - gxlo, cols.run[i].hi - cols.run[i].lo + 1);
+  }
+}
+
+// the same with the box's rows dealt (see dealt_row)
+static void add_dealt_box(StepCounter& steps, const AxisSpan& rows, const AxisSpan& cols, int ubase, int gylo, int n_rows,
+                          int gxlo, int gw) {
+  for (int i = 0; i < n_rows; ++i) {
+    const int y = gylo + dealt_row(i, n_rows);
+    bool kept = false;
+    for (int r = 0; r < rows.n_runs; ++r) kept |= y >= rows.run[r].lo && y <= rows.run[r].hi;
+    for (int c = 0; kept && c < cols.n_runs; ++c)
+      steps.run(ubase + i * gw + cols.run[c].lo - gxlo, cols.run[c].hi - cols.run[c].lo + 1);
+  }
+}
+
 static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
   Geom& g = sp.g;
   memset(&z, 0, sizeof z);
   std::vector<AxisSpan> ax;            // window mode: [key scale][patch row or column of the query scale]
+  std::vector<AxisSpan> wide_rows, wide_cols;   // the same of the wide patches: [key scale][group row, patch row in it]
   for (int hg = 0; hg < g.n_hg; ++hg) {
     sp.load_head_group(hg);
     const ArithRad rad{g};
@@ -196,6 +225,21 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
           for (int c = 0; c < g.s[k]; ++c) ax[(size_t)j * pps + c / kPatch].add(win_interval(g, k, j, c));
       }
       const int ngy = groups_y(g, k), ngx = groups_x(g, k);
+      const bool wide = g.NW == 16;
+      // wide patch rows of a group, and columns (window mode)
+      int wny = 0, wnx = 0;
+      if (wide && g.mode == kModeWindow) {
+        const int gh = g.grh[k] * kPatch, gw = g.grw[k] * kPatch, ph = g.wph[k], pw = g.wpw[k];
+        wny = ((gh < g.s[k] ? gh : g.s[k]) + ph - 1) / ph; wnx = ((gw < g.s[k] ? gw : g.s[k]) + pw - 1) / pw;
+        wide_rows.assign((size_t)(k + 1) * ngy * wny, AxisSpan());
+        wide_cols.assign((size_t)(k + 1) * ngx * wnx, AxisSpan());
+        for (int j = 0; j <= k; ++j)
+          for (int c = 0; c < g.s[k]; ++c) {
+            const Interval iv = win_interval(g, k, j, c);
+            wide_rows[((size_t)j * ngy + c / gh) * wny + c % gh / ph].add(iv);
+            wide_cols[((size_t)j * ngx + c / gw) * wnx + c % gw / pw].add(iv);
+          }
+      }
       for (int gi = 0; gi < ngy * ngx; ++gi) {
         const int gy = gi / ngx, gx = gi % ngx;
         const GroupExtent e = group_extent(g, k, gy, gx);
@@ -232,16 +276,7 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
               const AxisSpan &rows = a[p.y0 / kPatch], &cols = a[p.x0 / kPatch];
               const int gylo = a[e.qy0 / kPatch].lo(), gyhi = a[e.qy1 / kPatch].hi();
               const int gxlo = a[e.qx0 / kPatch].lo(), gw = a[e.qx1 / kPatch].hi() - gxlo + 1;
-              for (int r = 0; r < rows.n_runs; ++r) {
-                const int y0 = rows.run[r].lo, y1 = rows.run[r].hi;
-                if (cols.n_runs == 1 && cols.hi() - cols.lo() + 1 == gw) {      // whole rows of the group's box
-                  steps.run(ubase + (y0 - gylo) * gw, (y1 - y0 + 1) * gw);
-                  continue;
-                }
-                for (int y = y0; y <= y1; ++y)
-                  for (int i = 0; i < cols.n_runs; ++i)
-                    steps.run(ubase + (y - gylo) * gw + cols.run[i].lo - gxlo, cols.run[i].hi - cols.run[i].lo + 1);
-              }
+              add_box(steps, rows, cols, ubase, gylo, gxlo, gw);
               pairs_hg += (int64_t)rows.kept * cols.kept;
               ubase += (gyhi - gylo + 1) * gw;
             }
@@ -250,14 +285,45 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
           if (ns > 65535) return fail(LITEVAR_E_UNSUPPORTED, "a query patch needs more than 65535 steps");
           z.n_steps += ns;
         }
+        for (int w = 0; wide && w < kWidePatches; ++w) {
+          const PatchExtent p = wide_extent(g, k, gy, gx, w);
+          if (p.ny == 0) continue;
+          StepCounter steps{g};
+          int ubase = 0;
+          if (g.mode == kModeBand) {
+            for (int pt = 0; pt < band_parts(k); ++pt) {
+              const BandPart b = band_part(g, rad, k, pt);
+              const int glo = band_interval(b, nk, e.qy0).lo, ghi = band_interval(b, nk, e.qy1).hi;
+              AxisSpan a;
+              for (int n = 0; n < p.nx; ++n) a.add(band_interval(b, nk, p.y0 + n));
+              for (int i = 0; i < a.n_runs; ++i) steps.run(ubase + a.run[i].lo - glo, a.run[i].hi - a.run[i].lo + 1);
+              ubase += ghi - glo + 1;
+            }
+          } else {
+            for (int j = 0; j <= k; ++j) {
+              const AxisSpan* a = &ax[(size_t)j * pps];
+              const int gylo = a[e.qy0 / kPatch].lo(), gyhi = a[e.qy1 / kPatch].hi();
+              const int gxlo = a[e.qx0 / kPatch].lo(), gw = a[e.qx1 / kPatch].hi() - gxlo + 1;
+              const AxisSpan &rows = wide_rows[((size_t)j * ngy + gy) * wny + w / wnx],
+                             &cols = wide_cols[((size_t)j * ngx + gx) * wnx + w % wnx];
+              if (dealt_box(g.mode, ubase)) add_dealt_box(steps, rows, cols, ubase, gylo, gyhi - gylo + 1, gxlo, gw);
+              else add_box(steps, rows, cols, ubase, gylo, gxlo, gw);
+              ubase += (gyhi - gylo + 1) * gw;
+            }
+          }
+          const int ns = steps.finish();
+          if (ns > 65535) return fail(LITEVAR_E_UNSUPPORTED, "a query patch needs more than 65535 steps");
+          z.n_wide_steps += ns;
+        }
       }
     }
     z.retained_pairs += pairs_hg;
     if (hg < kMaxHeads) z.pairs_of_group[hg] = pairs_hg;
   }
-  if (z.n_steps > (int64_t)1 << 26 || z.n_union > (int64_t)1 << 30)
+  if (z.n_steps > (int64_t)1 << 26 || z.n_wide_steps > (int64_t)1 << 26 || z.n_union > (int64_t)1 << 30)
     return fail(LITEVAR_E_UNSUPPORTED, "work-list too large (%lld steps)", (long long)z.n_steps);
   const uint64_t ngt = (uint64_t)g.n_groups * g.n_hg;
+  const bool wide = g.NW == 16;        // (the wide patches' entries follow the others in their sections; their steps' descriptors come first)
   uint64_t o = 0;
   z.off[kSecHeader] = o; o += sizeof(Header);
   z.off[kSecWin] = o;
@@ -265,10 +331,10 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
   z.off[kSecRad] = o; o = align256(o + (uint64_t)g.n_hg * g.K * g.K * sizeof(int16_t));
   z.off[kSecHeadMap] = o; o = align256(o + (uint64_t)kMaxHeads * sizeof(int32_t));
   z.off[kSecGroups] = o; o = align256(o + ngt * sizeof(GroupDesc));
-  z.off[kSecWaves] = o; o = align256(o + ngt * g.NW * sizeof(WaveDesc));
-  z.off[kSecPhaseEnd] = o; o = align256(o + (uint64_t)z.n_phase_entries * sizeof(int32_t));
-  z.off[kSecUnion] = o; o = align256(o + (uint64_t)z.n_union * sizeof(int32_t));
-  z.off[kSecStepAddr] = o; o = align256(o + (uint64_t)z.n_steps * 64 * sizeof(uint2));
+  z.off[kSecWaves] = o; o = align256(o + ngt * (g.NW + (wide ? kWidePatches : 0)) * sizeof(WaveDesc));
+  z.off[kSecPhaseEnd] = o; o = align256(o + (uint64_t)(z.n_phase_entries + (wide ? z.n_phase_entries / 2 : 0)) * sizeof(int32_t));
+  z.off[kSecUnion] = o; o = align256(o + (uint64_t)z.n_union * (wide ? 2 : 1) * sizeof(int32_t));
+  z.off[kSecStepAddr] = o; o = align256(o + (uint64_t)z.n_steps * 64 * sizeof(uint2) + (uint64_t)z.n_wide_steps * 64 * kWideDesc);
   z.off[kSecStepMask] = o; o = align256(o + (uint64_t)z.n_steps * 8 * sizeof(uint64_t));
   z.off[kSecStepTok] = o; o = align256(o + (uint64_t)z.n_steps * kStepKeys * sizeof(int32_t));
   z.off[kSecEnd] = o;
@@ -295,7 +361,7 @@ static BlobPtrs blob_ptrs(void* blob, const uint64_t* off) {
   return p;
 }
 
-struct Caps { int64_t n_steps, n_union, n_phase_entries, retained_pairs; uint64_t bytes; };
+struct Caps { int64_t n_steps, n_union, n_phase_entries, retained_pairs, n_wide_steps; uint64_t bytes; int n_groups; };
 
 // K1: the radius tables rad[hg][k][j] (-1: dense part), in window mode the window tables
 // win[hg][k][j][c] = inclusive [lo, hi] ((-1,-1) where undefined), and the head map.  Every other
@@ -380,12 +446,44 @@ struct WavePacker {
   }
 };
 
+// One key scale of the walk over a wide patch (window mode): ny + nx <= 12 lanes from l0 on hold the windows of its
+// query rows and columns, the last four of the sixteen those of the group's first and last row and column.
+template <class Sink>
+__device__ int wave_walk_wide_box(const PatchExtent& p, const Interval& mine, int l0, int sj, int offj, int ubase,
+                                  WavePacker<Sink>& pack, int lane) {
+  const int gylo = lane_value(mine.lo, l0 + 12), gyhi = lane_value(mine.hi, l0 + 13);
+  const int gxlo = lane_value(mine.lo, l0 + 14), gw = lane_value(mine.hi, l0 + 15) - gxlo + 1;
+  const int ylo = lane_value(mine.lo, l0), yhi = lane_value(mine.hi, l0 + p.ny - 1);
+  const int xlo = lane_value(mine.lo, l0 + p.ny), xhi = lane_value(mine.hi, l0 + p.ny + p.nx - 1);
+  const int W = xhi - xlo + 1, WL = W < 64 ? W : 64, RP = 64 / WL;
+  const int ry = lane / WL, xx = lane - ry * WL;
+  // places of the box's rows in the list: the patch's own rows, or all of them where they are dealt
+  const bool dealt = dealt_box(kModeWindow, ubase);
+  const int n_rows = gyhi - gylo + 1, i_lo = dealt ? 0 : ylo - gylo, i_hi = dealt ? n_rows - 1 : yhi - gylo;
+  for (int i0 = i_lo; i0 <= i_hi; i0 += RP) {
+    const int i = i0 + ry, y = gylo + (dealt ? dealt_row(i, n_rows) : i);
+    const bool in_box = ry < RP && i <= i_hi && y >= ylo && y <= yhi;
+    const int urow = ubase + i * gw - gxlo, trow = offj + y * sj;
+    for (int x0 = xlo; x0 <= xhi; x0 += WL) {
+      const int x = x0 + xx;
+      unsigned rb = 0, cb = 0;                          // the query rows and columns that keep the key
+      for (int d = 0; d < p.ny; ++d) rb |= (unsigned)(y >= lane_value(mine.lo, l0 + d) && y <= lane_value(mine.hi, l0 + d)) << d;
+      for (int d = 0; d < p.nx; ++d)
+        cb |= (unsigned)(x >= lane_value(mine.lo, l0 + p.ny + d) && x <= lane_value(mine.hi, l0 + p.ny + d)) << d;
+      pack.pass(in_box && x <= xhi && rb && cb, urow + x, trow + x, rb | (cb << p.ny));
+    }
+  }
+  return n_rows * gw;
+}
+
 // The walk over a patch's kept keys in the order of its group's list: the 64 lanes of a wave take 64
 // consecutive candidate keys at a time (window mode: several rows of a narrow box, or 64 columns of one row of the
 // patch's box in a key scale; band mode: 64 columns of the patch's range in a part).
-template <class Sink>
+// WIDE: a wide patch.
+template <bool WIDE, class Sink>
 __device__ int wave_walk_patch(const Geom& g, const TableWin& win, const TableRad& rad, const GroupExtent& e,
                                const PatchExtent& p, Sink& sink, int lane) {
+  constexpr int kQ = WIDE ? kWideQueries : kPatchQueries;
   if (p.ny == 0) return 0;
   WavePacker<Sink> pack{g, sink, lane};
   int ubase = 0;
@@ -394,19 +492,19 @@ __device__ int wave_walk_patch(const Geom& g, const TableWin& win, const TableRa
     for (int pt = 0; pt < band_parts(e.k); ++pt) {
       const BandPart b = band_part(g, rad, e.k, pt);
       const int glo = band_interval(b, nk, e.qy0).lo, ghi = band_interval(b, nk, e.qy1).hi;
-      // the sixteen queries' intervals: one lane each (a 64-bit division), handed round
+      // the queries' intervals: one lane each (a 64-bit division), handed round
       Interval mine = {1, 0};
       if (lane < p.nx) mine = band_interval(b, nk, p.y0 + lane);
-      Interval iv[kPatchQueries];
+      Interval iv[kQ];
 #pragma unroll
-      for (int n = 0; n < kPatchQueries; ++n) { iv[n].lo = lane_value(mine.lo, n); iv[n].hi = lane_value(mine.hi, n); }
+      for (int n = 0; n < kQ; ++n) { iv[n].lo = lane_value(mine.lo, n); iv[n].hi = lane_value(mine.hi, n); }
       const int clo = iv[0].lo, chi = lane_value(mine.hi, p.nx - 1);
       for (int c0 = clo; c0 <= chi; c0 += 64) {
         const int c = c0 + lane;
         unsigned qmask = 0;
         if (c <= chi) {
 #pragma unroll
-          for (int n = 0; n < kPatchQueries; ++n) qmask |= (unsigned)(c >= iv[n].lo && c <= iv[n].hi) << n;
+          for (int n = 0; n < kQ; ++n) qmask |= (unsigned)(c >= iv[n].lo && c <= iv[n].hi) << n;
         }
         pack.pass(qmask != 0, ubase + c - glo, b.tok0 + c, qmask);
       }
@@ -426,13 +524,15 @@ __device__ int wave_walk_patch(const Geom& g, const TableWin& win, const TableRa
   {
     const int sk = g.s[e.k];
     const int role = lane & 15;
-    int cq = role < 4 ? p.y0 + role : role < 8 ? p.x0 + role - 4 : role == 8 ? e.qy0 : role == 9 ? e.qy1 : role == 10 ? e.qx0 : e.qx1;
+    int cq = WIDE ? (role < p.ny ? p.y0 + role : role < p.ny + p.nx ? p.x0 + role - p.ny
+                     : role < 12 ? p.y0 : role == 12 ? e.qy0 : role == 13 ? e.qy1 : role == 14 ? e.qx0 : e.qx1)
+             : role < 4 ? p.y0 + role : role < 8 ? p.x0 + role - 4 : role == 8 ? e.qy0 : role == 9 ? e.qy1 : role == 10 ? e.qx0 : e.qx1;
     cq = cq < sk ? cq : sk - 1;
 #pragma unroll
     for (int t = 0; t < kRounds; ++t) {
       pre[t].lo = 1; pre[t].hi = 0;
       const int j = 4 * t + (lane >> 4);
-      if (4 * t <= e.k && j <= e.k && role < 12) pre[t] = win(e.k, j, cq);
+      if (4 * t <= e.k && j <= e.k && role < (WIDE ? 16 : 12)) pre[t] = win(e.k, j, cq);
     }
   }
   for (int j = 0; j <= e.k; ++j) {
@@ -441,6 +541,10 @@ __device__ int wave_walk_patch(const Geom& g, const TableWin& win, const TableRa
     for (int t = 1; t < kRounds; ++t)
       if ((j >> 2) == t) mine_iv = pre[t];             // (uniform)
     const int l0 = (j & 3) * 16;                         // first lane of this key scale's sixteen
+    if constexpr (WIDE) {
+      ubase += wave_walk_wide_box(p, mine_iv, l0, lane_value(my_side, j), lane_value(my_off, j), ubase, pack, lane);
+      continue;
+    }
     const Interval none = {1, 0};
     Interval rw[kPatch], cw[kPatch];
 #pragma unroll
@@ -505,9 +609,29 @@ __device__ inline GroupTables group_tables(const Geom& g, const BlobPtrs& p, int
 }
 
 // K2a: one wave per (group, patch): number of steps and kept pairs; patch 0 also
-// sizes the group's union list
-__global__ __launch_bounds__(64) void k_count(Geom g, BlobPtrs p) {
+// sizes the group's union list.  Waves from n_waves on: the wide patches.
+__global__ __launch_bounds__(64) void k_count(Geom g, BlobPtrs p, int n_waves) {
   const int idx = blockIdx.x, lane = threadIdx.x;
+  if (idx >= n_waves) {
+    const int G = (idx - n_waves) / kWidePatches, w = (idx - n_waves) % kWidePatches;
+    const GroupTables t = group_tables(g, p, G);
+    int k, gy, gx;
+    group_coords(g, t.grp, k, gy, gx);
+    const PatchExtent pe = wide_extent(g, k, gy, gx, w);
+    WaveCountSink sink;
+    const int ns = wave_walk_patch<true>(g, t.win, t.rad, group_extent(g, k, gy, gx), pe, sink, lane);
+    if (lane == 0) {
+      WaveDesc wd;
+      const int n = pe.ny * pe.nx;
+      wd.step_begin = 0; wd.n_steps = ns;
+      wd.q_base = g.off[k] - g.q0 + (g.mode == kModeBand ? pe.y0 : pe.y0 * g.s[k] + pe.x0);
+      wd.sk = (int16_t)(g.mode == kModeBand ? 0 : g.s[k]); wd.ny = (int16_t)pe.ny; wd.nx = (int16_t)pe.nx; wd.kq = (int16_t)k;
+      wd.pairs = pe.nx ? (65536 + pe.nx - 1) / pe.nx : 0;
+      wd.valid = n >= 32 ? 0xffffffffu : (1u << n) - 1u; wd.first_ends = 0;
+      p.waves[idx] = wd;
+    }
+    return;
+  }
   const int G = idx / g.NW, w = idx % g.NW;
   const GroupTables t = group_tables(g, p, G);
   int k, gy, gx;
@@ -515,7 +639,7 @@ __global__ __launch_bounds__(64) void k_count(Geom g, BlobPtrs p) {
   const GroupExtent e = group_extent(g, k, gy, gx);
   const PatchExtent pe = patch_extent(g, k, gy, gx, w);
   WaveCountSink sink;
-  const int ns = wave_walk_patch(g, t.win, t.rad, e, pe, sink, lane);
+  const int ns = wave_walk_patch<false>(g, t.win, t.rad, e, pe, sink, lane);
   int pairs = sink.pairs;
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) pairs += __shfl_xor(pairs, d);
@@ -574,22 +698,27 @@ __global__ __launch_bounds__(64) void k_count(Geom g, BlobPtrs p) {
 // 1024-thread block: per-thread partial sums over a contiguous slice of groups, a scan of the
 // partials inside each wave, then over the waves' totals, then the slice is revisited.
 // (60 groups of 8 patches: 5.5 us; 8.1 us with ten rounds through LDS)
-__global__ __launch_bounds__(1024) void k_scan(Geom g, BlobPtrs p, Caps caps) {
-  __shared__ int64_t wave_total[4][16];
+__global__ __launch_bounds__(1024) void k_scan(Geom g, BlobPtrs p, Caps caps, int n_waves) {
+  constexpr int kSums = 5;
+  __shared__ int64_t wave_total[kSums][16];
+  const int n_wide = g.NW == 16 ? kWidePatches : 0;     // per group
+  WaveDesc* const wide = p.waves + n_waves;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int n_all = g.n_groups * g.n_hg;
   const int per = (n_all + 1023) / 1024;
   const int g0 = t * per < n_all ? t * per : n_all;
   const int g1 = g0 + per < n_all ? g0 + per : n_all;
-  int64_t v[4] = {0, 0, 0, 0};                          // steps, union keys, phase entries, pairs
+  int64_t v[kSums] = {0, 0, 0, 0, 0};                   // steps, union keys, phase entries, pairs, wide patches' steps
   for (int grp = g0; grp < g1; ++grp) {
     v[1] += (int64_t)p.groups[grp].n_phases * g.C; v[2] += (int64_t)p.groups[grp].n_phases * g.NW;
 #pragma unroll 4
     for (int w = 0; w < g.NW; ++w) { v[0] += p.waves[grp * g.NW + w].n_steps; v[3] += p.waves[grp * g.NW + w].pairs; }
+#pragma unroll 4
+    for (int w = 0; w < n_wide; ++w) v[4] += wide[grp * n_wide + w].n_steps;
   }
-  int64_t sum[4];                                       // inclusive
+  int64_t sum[kSums];                                   // inclusive
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < kSums; ++i) {
     sum[i] = v[i];
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
@@ -600,9 +729,9 @@ __global__ __launch_bounds__(1024) void k_scan(Geom g, BlobPtrs p, Caps caps) {
   }
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < kSums; ++i)
     for (int w = 0; w < wave; ++w) sum[i] += wave_total[i][w];
-  int64_t steps = sum[0] - v[0], uni = sum[1] - v[1], phe = sum[2] - v[2];
+  int64_t steps = sum[0] - v[0], uni = sum[1] - v[1], phe = sum[2] - v[2], wide_steps = sum[4] - v[4];
   for (int grp = g0; grp < g1; ++grp) {
     GroupDesc& gd = p.groups[grp];
     gd.union_base = (int32_t)uni; gd.phase_base = (int32_t)phe;
@@ -611,6 +740,10 @@ __global__ __launch_bounds__(1024) void k_scan(Geom g, BlobPtrs p, Caps caps) {
       WaveDesc& wd = p.waves[grp * g.NW + w];
       wd.step_begin = (int32_t)steps; steps += wd.n_steps;
     }
+    for (int w = 0; w < n_wide; ++w) {
+      WaveDesc& wd = wide[grp * n_wide + w];
+      wd.step_begin = (int32_t)wide_steps; wide_steps += wd.n_steps;
+    }
   }
   if (t == 1023) {
     Header h;
@@ -618,9 +751,10 @@ __global__ __launch_bounds__(1024) void k_scan(Geom g, BlobPtrs p, Caps caps) {
     h.magic = kMagic; h.blob_bytes = caps.bytes;
     h.n_groups = n_all; h.n_waves = n_all * g.NW;
     h.n_steps = sum[0]; h.n_union = sum[1]; h.n_phase_entries = sum[2];
-    h.retained_pairs = sum[3];
+    h.retained_pairs = sum[3]; h.n_wide_steps = sum[4];
     h.error = (h.n_steps != caps.n_steps || h.n_union != caps.n_union ||
-               h.n_phase_entries != caps.n_phase_entries || h.retained_pairs != caps.retained_pairs) ? kErrBuilder : kErrNone;
+               h.n_phase_entries != caps.n_phase_entries || h.retained_pairs != caps.retained_pairs ||
+               h.n_wide_steps != caps.n_wide_steps) ? kErrBuilder : kErrNone;
     *p.hdr = h;
   }
 }
@@ -631,6 +765,7 @@ __device__ void fill_union(const Geom& g, const BlobPtrs& p, const Caps& caps, i
   const GroupDesc gd = p.groups[G];
   const GroupExtent e = group_extent(g, gd.k, gd.gy, gd.gx);
   int32_t* out = p.union_tok + gd.union_base;
+  int32_t* wide = g.NW == 16 ? out + caps.n_union : nullptr;   // the wide patches' list, some of whose boxes are dealt
   if ((int64_t)gd.union_base + (int64_t)gd.n_phases * g.C > caps.n_union) return;
   int ubase = 0, last_tok = 0;
   if (g.mode == kModeBand) {
@@ -639,7 +774,10 @@ __device__ void fill_union(const Geom& g, const BlobPtrs& p, const Caps& caps, i
       const BandPart b = band_part(g, t.rad, e.k, pt);
       const int glo = band_interval(b, nk, e.qy0).lo, ghi = band_interval(b, nk, e.qy1).hi;
       const int n = ghi - glo + 1;
-      for (int i = threadIdx.x; i < n; i += blockDim.x) out[ubase + i] = b.tok0 + glo + i;
+      for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        out[ubase + i] = b.tok0 + glo + i;
+        if (wide) wide[ubase + i] = b.tok0 + glo + i;
+      }
       ubase += n;
       last_tok = b.tok0 + ghi;
     }
@@ -650,13 +788,20 @@ __device__ void fill_union(const Geom& g, const BlobPtrs& p, const Caps& caps, i
     for (int j = 0; j <= e.k; ++j) {
       const Box b = boxes[j];
       const int gw = b.xhi - b.xlo + 1, n = (b.yhi - b.ylo + 1) * gw;
-      for (int i = threadIdx.x; i < n; i += blockDim.x)
-        out[ubase + i] = g.off[j] + (b.ylo + i / gw) * g.s[j] + b.xlo + i % gw;
+      const bool dealt = dealt_box(g.mode, ubase);
+      for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const int row = i / gw, first = g.off[j] + b.xlo + i - row * gw;
+        out[ubase + i] = first + (b.ylo + row) * g.s[j];
+        if (wide) wide[ubase + i] = first + (b.ylo + (dealt ? dealt_row(row, b.yhi - b.ylo + 1) : row)) * g.s[j];
+      }
       ubase += n;
       last_tok = g.off[j] + b.yhi * g.s[j] + b.xhi;
     }
   }
-  for (int i = gd.n_union + threadIdx.x; i < gd.n_phases * g.C; i += blockDim.x) out[i] = last_tok;
+  for (int i = gd.n_union + threadIdx.x; i < gd.n_phases * g.C; i += blockDim.x) {
+    out[i] = last_tok;
+    if (wide) wide[i] = last_tok;
+  }
 }
 
 // Step under construction: the wave's lanes deposit the keys they place (ring slot, token,
@@ -668,6 +813,11 @@ __device__ void fill_union(const Geom& g, const BlobPtrs& p, const Caps& caps, i
 //   mask bits  element e = 4*t + i  <->  key 16*t + 4*g4 + i against query n
 struct StepBuf { uint32_t slot[kStepKeys]; int32_t tok[kStepKeys]; uint32_t qmask[kStepKeys]; };
 
+//   Wide patches, lane (n, h) = (lane % 32, lane / 32):
+//   K operand  row of key n                                                   -> byte offset of its 16-byte piece h
+//   V operand  rows of keys 16*t + 8*j + 4*h + (lane % 16) / 4, t, j = 0, 1   -> byte offset of its read of dims 0..31
+//   mask       key n against the patch's dimensions (see close)
+template <bool WIDE>
 struct FillSink {
   uint2* addr; uint64_t* mask; int32_t* toks; int32_t* phase_end;
   StepBuf* buf;
@@ -682,6 +832,10 @@ struct FillSink {
   __device__ static uint32_t k_off(uint32_t slot, int g4) {
     return slot * kRingRowBytes + (((2u * g4) ^ ring_swizzle(slot)) << 4);
   }
+  // wide patches: piece `piece` (0..3, of dims 0..31) of the row in `slot`
+  __device__ static uint32_t piece_off(uint32_t slot, int piece) {
+    return slot * kRingRowBytes + (((uint32_t)piece ^ ring_swizzle(slot)) << 4);
+  }
   __device__ static uint32_t v_off(uint32_t slot, int n) {
     const uint32_t sw = ring_swizzle(slot), b = (n >> 1) & 1, half = n & 1;
     return slot * kRingRowBytes + 8u * half + 16u * ((b ^ sw) & 1u) + ((sw >> 1) << 5);
@@ -694,6 +848,24 @@ struct FillSink {
     const int n = lane & 15, g4 = lane >> 4;
     const uint32_t pad = (uint32_t)(last_upos % R);    // padding keys read the step's last row
     auto slot_of = [&](int idx) { return idx < n_keys ? buf->slot[idx] : pad; };
+    if constexpr (WIDE) {
+      const int n5 = lane & 31, h = lane >> 5, l16 = lane & 15, piece = 2 * ((lane >> 4) & 1) + ((l16 & 3) >> 1);
+      uint32_t v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = piece_off(slot_of(8 * i + 4 * h + (l16 >> 2)), piece) + 8u * (l16 & 1);
+      // not kept by dimension i, i = 8 h + e (window mode: the query rows, then the query columns; bands: the queries)
+      // -> bit 15 - 2 r of half e % 2, r = e / 2; bands: queries 16 + 8 h + e -> r + 4
+      const uint32_t out = n5 < n_keys ? ~buf->qmask[n5] : ~0u;
+      uint32_t m = 0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        m |= ((out >> (8 * h + e)) & 1u) << (15 - 2 * (e >> 1) + 16 * (e & 1));
+        m |= ((out >> (16 + 8 * h + e)) & 1u) << (7 - 2 * (e >> 1) + 16 * (e & 1));
+      }
+      ((uint4*)addr)[(int64_t)step * 64 + lane] = make_uint4(piece_off(slot_of(n5), h), v[0] | (v[1] << 16), v[2] | (v[3] << 16), m);
+      end_step(step, last_upos);
+      return;
+    }
     const uint32_t k0 = k_off(slot_of(n), g4), k1 = k_off(slot_of(16 + n), g4);
     const uint32_t v0 = v_off(slot_of(4 * g4 + (n >> 2)), n), v1 = v_off(slot_of(16 + 4 * g4 + (n >> 2)), n);
     addr[(int64_t)step * 64 + lane] = make_uint2(k0 | (k1 << 16), v0 | (v1 << 16));
@@ -707,6 +879,9 @@ struct FillSink {
     }
     if (lane < 8) mask[(int64_t)step * 8 + lane] = mine;
     if (lane < kStepKeys) toks[(int64_t)step * kStepKeys + lane] = lane < n_keys ? buf->tok[lane] : -1;
+    end_step(step, last_upos);
+  }
+  __device__ void end_step(int step, int last_upos) {
     const int c = last_upos >> logC;
     if (c > chunk) { fill_ends(chunk, c, step); chunk = c; }
     if (c == 0) end0 = step + 1;
@@ -715,7 +890,7 @@ struct FillSink {
   }
 };
 
-// K2c: one wave per (group, patch): steps (ring addresses, lane masks, tokens) and the
+// K2c: one wave per (group, patch) and (group, wide patch): steps (ring addresses, lane masks, tokens) and the
 // cumulative number of steps that are runnable after each phase; then one wave per group: its
 // key list (in the same launch: neither needs the other).  Bound: the serial walk of one wave.
 // 480 patches of 30 head groups: 27 us, 35 us as two launches with counters that were read back.
@@ -723,7 +898,26 @@ __global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int 
   __shared__ StepBuf buf;
   const int idx = blockIdx.x, lane = threadIdx.x;
   if (p.hdr->error) return;
-  if (idx >= n_waves) { fill_union(g, p, caps, idx - n_waves); return; }
+  const int n_wide = g.NW == 16 ? caps.n_groups * kWidePatches : 0;
+  if (idx >= n_waves + n_wide) { fill_union(g, p, caps, idx - n_waves - n_wide); return; }
+  if (idx >= n_waves) {
+    const int G = (idx - n_waves) / kWidePatches, w = (idx - n_waves) % kWidePatches;
+    const GroupTables t = group_tables(g, p, G);
+    const GroupDesc gd = p.groups[G];
+    const WaveDesc wd = p.waves[idx];
+    if ((int64_t)wd.step_begin + wd.n_steps > caps.n_wide_steps ||
+        (int64_t)gd.phase_base + (int64_t)gd.n_phases * g.NW > caps.n_phase_entries) return;
+    FillSink<true> sink;
+    sink.addr = (uint2*)((char*)p.step_addr + (int64_t)wd.step_begin * 64 * kWideDesc);
+    sink.mask = nullptr; sink.toks = nullptr;
+    sink.phase_end = p.phase_end + caps.n_phase_entries + gd.phase_base / 2 + (int64_t)w * gd.n_phases;
+    sink.buf = &buf; sink.R = g.R; sink.logC = g.logC; sink.lane = lane;
+    const int ns = wave_walk_patch<true>(g, t.win, t.rad, group_extent(g, gd.k, gd.gy, gd.gx),
+                                         wide_extent(g, gd.k, gd.gy, gd.gx, w), sink, lane);
+    sink.fill_ends(sink.chunk, gd.n_phases, ns);
+    if (lane == 0) p.waves[idx].first_ends = (uint32_t)sink.end0 | ((uint32_t)sink.end2 << 16);
+    return;
+  }
   const int G = idx / g.NW, w = idx % g.NW;
   const GroupTables t = group_tables(g, p, G);
   const GroupDesc gd = p.groups[G];
@@ -731,13 +925,13 @@ __global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int 
   if ((int64_t)wd.step_begin + wd.n_steps > caps.n_steps ||
       (int64_t)gd.phase_base + (int64_t)gd.n_phases * g.NW > caps.n_phase_entries) return;
   const GroupExtent e = group_extent(g, gd.k, gd.gy, gd.gx);
-  FillSink sink;
-  sink.addr = p.step_addr + (int64_t)wd.step_begin * 64;
+  FillSink<false> sink;
+  sink.addr = p.step_addr + (caps.n_wide_steps * (64 * kWideDesc) / (int64_t)sizeof(uint2)) + (int64_t)wd.step_begin * 64;
   sink.mask = p.step_mask + (int64_t)wd.step_begin * 8;
   sink.toks = p.step_tok + (int64_t)wd.step_begin * kStepKeys;
   sink.phase_end = p.phase_end + gd.phase_base + (int64_t)w * gd.n_phases;
   sink.buf = &buf; sink.R = g.R; sink.logC = g.logC; sink.lane = lane;
-  const int ns = wave_walk_patch(g, t.win, t.rad, e, patch_extent(g, gd.k, gd.gy, gd.gx, w), sink, lane);
+  const int ns = wave_walk_patch<false>(g, t.win, t.rad, e, patch_extent(g, gd.k, gd.gy, gd.gx, w), sink, lane);
   sink.fill_ends(sink.chunk, gd.n_phases, ns);
   if (lane == 0) p.waves[idx].first_ends = (uint32_t)sink.end0 | ((uint32_t)sink.end2 << 16);   // (a patch has at most 65535 steps)
 }
@@ -745,7 +939,7 @@ __global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int 
 litevar_status build_plan(PlanSpec& sp, const PlanSizes& z, void* d_blob, hipStream_t st) {
   Geom& g = sp.g;
   const BlobPtrs p = blob_ptrs(d_blob, z.off);
-  Caps caps{z.n_steps, z.n_union, z.n_phase_entries, z.retained_pairs, z.bytes};
+  Caps caps{z.n_steps, z.n_union, z.n_phase_entries, z.retained_pairs, z.n_wide_steps, z.bytes, g.n_groups * g.n_hg};
   const int ntab = g.mode == kModeWindow ? g.K * g.K * g.smax : g.K * g.K;
   const int tri = g.K * (g.K + 1) / 2, per_launch = kTableRadii / tri;
   TablesArg ta;
@@ -762,9 +956,10 @@ litevar_status build_plan(PlanSpec& sp, const PlanSizes& z, void* d_blob, hipStr
   }
   const int n_all = g.n_groups * g.n_hg;
   const int nw = n_all * g.NW;
-  hipLaunchKernelGGL(k_count, dim3(nw), dim3(64), 0, st, g, p);
-  hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, st, g, p, caps);
-  hipLaunchKernelGGL(k_fill, dim3(nw + n_all), dim3(64), 0, st, g, p, caps, nw);
+  const int n_wide = g.NW == 16 ? n_all * kWidePatches : 0;
+  hipLaunchKernelGGL(k_count, dim3(nw + n_wide), dim3(64), 0, st, g, p, nw);
+  hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, st, g, p, caps, nw);
+  hipLaunchKernelGGL(k_fill, dim3(nw + n_wide + n_all), dim3(64), 0, st, g, p, caps, nw);
   return hip_check(hipGetLastError(), "plan builder launch");
 }
 
