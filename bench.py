@@ -80,11 +80,14 @@ def kernel_name(plan, w):
     patches = plan.n_patches * plan.n_head_groups
     few = plan.n_steps <= 3 * patches and pairs * plan.n_groups * plan.n_steps <= 512 * patches
     if w.dtype == "bf16" and dense and plan.q_len > 16 and not plan.tiling_chosen and plan.patches_per_wave == 0 and not few:
-        # the library's rule: eight waves per workgroup when the rows fill 300 such workgroups, or when eight
-        # take all units of 32 rows in one pass over many keys
+        # the library's rule for waves per workgroup and LDS buffers
         units = sum((w.scales[k] ** 2 + 31) // 32 for k in range(first, last))
-        eight = pairs * plan.q_len >= 300 * 256 or (4 < units <= 8 and pairs >= 300 and ends[last - 1] >= 1024)
-        return f"k_attn_bf16_dense<{8 if eight else 4}>"
+        keys, fours, eights = ends[last - 1], pairs * -(-units // 4), pairs * -(-units // 8)
+        if units > 8:
+            eight = pairs * plan.q_len >= 300 * 256 and 10 * pairs * units >= 64 * eights and (eights >= 1024 or keys >= 1024)
+        else:
+            eight = units > 4 and (256 < fours <= 512 or (fours > 768 and keys >= 512))
+        return "k_attn_bf16_dense<8, 3>" if eight else f"k_attn_bf16_dense<4, {2 if fours > 512 else 3}>"
     if w.dtype == "bf16" and plan.waves_per_group == 16:
         pw = plan.patches_per_wave or 2
         return f"k_attn_bf16_pair<{pw}, false>"

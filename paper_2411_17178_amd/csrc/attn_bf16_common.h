@@ -11,6 +11,10 @@ typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 typedef __attribute__((address_space(3))) void lds_void;
 typedef const __attribute__((address_space(1))) void global_void;
 // constant address space: a load from a wave-uniform address becomes a scalar load
@@ -19,6 +23,7 @@ typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
 
 constexpr float kFloor = -1.0e30f;   // initial softmax reference: keeps exp2 arguments finite
 constexpr float kSlack = 6.0f;       // base-2 exponent by which a score may exceed the reference
+constexpr float kMostSum = 0x1p40f, kLeastSum = 0x1p-40f;   // row sums outside move the reference of the 32-query kernels
 
 __device__ inline bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -45,6 +50,38 @@ __device__ inline float max_across_rows(float x) {
   auto b = __builtin_amdgcn_permlane16_swap(v, v, false, false);
   const unsigned b0 = b[0], b1 = b[1];
   return fmaxf(__uint_as_float(b0), __uint_as_float(b1));
+}
+
+constexpr bf16x2 kOnes = {(__bf16)1.0f, (__bf16)1.0f};
+
+// the value in the other lane of a query (l ^ 32)
+__device__ inline float other_half(float x) {
+  const unsigned u = __float_as_uint(x);
+  auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  const unsigned s0 = sw[0], s1 = sw[1];       // (lower half's value, upper half's value) in every lane
+  return __uint_as_float((threadIdx.x & 32) ? s0 : s1);
+}
+
+// (on the bits, behind a barrier for the optimiser: the build lets it assume that no value is NaN)
+__device__ inline bool not_finite(float x) {
+  unsigned u = __float_as_uint(x);
+  asm volatile("" : "+v"(u));
+  return (u & 0x7f800000u) == 0x7f800000u;
+}
+
+__device__ inline unsigned lds_addr(const void* p) {
+  return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
+}
+
+// waits for LDS reads that inline assembly has issued; the operands are tied so that no use is scheduled above
+__device__ inline void lds_wait_k(u32x4& k00, u32x4& k01, u32x4& k10, u32x4& k11) {
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(k00), "+v"(k01), "+v"(k10), "+v"(k11) : : "memory");
+}
+
+__device__ inline void lds_wait_v_wide(u32x2 (&va)[8]) {
+  asm volatile("s_waitcnt lgkmcnt(0)"
+               : "+v"(va[0]), "+v"(va[1]), "+v"(va[2]), "+v"(va[3]), "+v"(va[4]), "+v"(va[5]), "+v"(va[6]),
+                 "+v"(va[7]) : : "memory");
 }
 
 // What every attention kernel checks before it reads anything else of the plan: the blob's

@@ -3,28 +3,26 @@
 // [0, off[k + 1]), so no work-list is needed and the queries are taken in token order.
 //
 // One workgroup = NWV waves of one (batch, head); a wave owns 32 consecutive query rows of one scale.
-// The keys pass through LDS in chunks of 64 (K and V rows of 128 bytes, two buffers); the next
-// chunk is requested into registers before the present one is computed and written to the other
-// buffer after it, one barrier per chunk.  Per 32 keys:
+// The keys pass through LDS in chunks of 64 (K and V rows of 128 bytes, two or three buffers), which LDS-DMA transfers
+// fill while the chunk before is computed.  Per 32 keys:
 //   S^T (32 keys x 32 queries) = K (A operand) . Q^T (B operand): v_mfma_f32_32x32x16_bf16; a
 //       lane ends up with one query column and 16 of the 32 keys,
-//   online softmax in base 2 with a lazily moved reference, as in the windowed kernels,
+//   softmax in base 2 with a reference that moves only when a row sum leaves [2^-40, 2^40], as for the windowed
+//       kernel's wide patches,
 //   O^T (64 x queries) += V^T (A operand, ds_read_b64_tr_b16) . P^T (B operand: the lane's own
 //       probabilities rounded to bf16; the key order of the slices is the order in which the score
-//       tile's registers hold them), row sums of the rounded probabilities by v_dot2_f32_bf16.
-// A wave's queries share their key limit; only the last block before it is masked.
+//       tile's registers hold them), row sums of the rounded probabilities by v_dot2_f32_bf16, one chain per slice.
+// The score products of a block are issued before the exponentials of the block before it, so that the matrix pipe works
+// under them.  A wave's queries share their key limit; only the last block before it is masked.
 //
-// Why not the windowed kernels: a wave there issues 51 vector, 9 matrix and 12 LDS instructions (on such a
-// plan) per 32 keys x 16 queries and fetches a step descriptor and lane masks; here 67, 8 and 13 serve 32
-// queries (keys' rows on their way into LDS included), with nothing to fetch.  What bounds it now is the issue
-// of vector and matrix instructions of one SIMD, which overlap little: at 2240 tokens and 288
-// (batch, head) pairs the vector issue is busy 63 % of the cycles, the matrix pipe 44 %, the LDS pipe 39 %
-// (windowed kernel on the same plan: 53, 28, 25).  119 and 127 registers (eight and four waves) let four waves
-// share a SIMD.  Not faster, at that size: 64 queries per wave (342 us), the next chunk's
-// score products issued between the exponentials, which takes 203 registers (365), chunks of 128
-// keys (360), raised wave priority around the products (310, against 310 without).
-// Measured against the windowed kernels (B H, tokens): 288, 2240: 427 -> 297 us (810 TFLOP/s of kept
-// pairs); 480, 680: 117 -> 62 us; 2, 34 240: 6950 -> 500 us (the windowed kernel on one XCD per pair; 1820 spread).
+// Why not the windowed kernels: their steps fetch descriptors and masks; here 61 vector, 8 matrix and 12 LDS instructions
+// serve 32 keys x 32 queries, with nothing to fetch.  At 2240 tokens and 288 (batch, head) pairs the vector issue is
+// busy 67 % of the cycles and the matrix pipe 50 % (with the maximum of the scores, transfers through registers and no
+// products ahead: 63 and 44 %, 297 us; now 275 us, 875 TFLOP/s of kept pairs), but the clock falls to 1.7 GHz under it
+// (1.8 before): what bounds it is the power that the instructions take, more than their number per cycle.  127 registers let
+// four waves share a SIMD.  One chain of row sums: 280 us.  Not faster in the kernel before: 64 queries per wave
+// (342 us), chunks of 128 keys (360), raised wave priority around the products (310, against 310 without).
+// Before / now (B H, tokens): 480, 680: 62.5 / 57.7 us; 32, 680: 14.3 / 13.1; 2, 34 240: 513 / 476; 8, 256 queries on 680: 14.0 / 12.8.
 #include <type_traits>
 
 #include "attn_bf16_common.h"
@@ -33,12 +31,9 @@ namespace lv {
 
 namespace {
 
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
-
 constexpr int kChunk = 64;                     // keys per LDS buffer
 constexpr int kRow = 128;                      // bytes of a K or V row
+constexpr int kBufBytes = 2 * kChunk * kRow;   // K rows, V rows
 
 struct DenseArgs {
   AttnArgs a;
@@ -54,17 +49,38 @@ struct DenseArgs {
 // units of the row (the transposing V reads: 4 keys x 32 bytes per 16 lanes).
 __device__ inline unsigned dense_swizzle(unsigned r) { return ((r & 3u) << 1) | ((r >> 2) & 1u); }
 
+// K rows of a block as the A operand and its V rows, transposed: va[4 t + 2 j + dt], slice t of 16 keys, its half j, head
+// dimension tile dt.  Issued only; a wait must precede the first use.  AT: byte offset of the block's rows.
+template <int AT>
+__device__ inline void read_k(const unsigned (&k)[4], u32x4 (&r)[4]) {
+  asm volatile("ds_read_b128 %0, %4 offset:%8\n\tds_read_b128 %1, %5 offset:%8\n\t"
+               "ds_read_b128 %2, %6 offset:%8\n\tds_read_b128 %3, %7 offset:%8"
+               : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
+               : "v"(k[0]), "v"(k[1]), "v"(k[2]), "v"(k[3]), "i"(AT) : "memory");
+}
+template <int AT>
+__device__ inline void read_v(const unsigned (&v)[2], u32x2 (&va)[8]) {
+  asm volatile("ds_read_b64_tr_b16 %0, %8 offset:%10\n\tds_read_b64_tr_b16 %1, %9 offset:%10\n\t"
+               "ds_read_b64_tr_b16 %2, %8 offset:%11\n\tds_read_b64_tr_b16 %3, %9 offset:%11\n\t"
+               "ds_read_b64_tr_b16 %4, %8 offset:%12\n\tds_read_b64_tr_b16 %5, %9 offset:%12\n\t"
+               "ds_read_b64_tr_b16 %6, %8 offset:%13\n\tds_read_b64_tr_b16 %7, %9 offset:%13"
+               : "=&v"(va[0]), "=&v"(va[1]), "=&v"(va[2]), "=&v"(va[3]),
+                 "=&v"(va[4]), "=&v"(va[5]), "=&v"(va[6]), "=&v"(va[7])
+               : "v"(v[0]), "v"(v[1]), "i"(AT), "i"(AT + 8 * kRow), "i"(AT + 16 * kRow), "i"(AT + 24 * kRow) : "memory");
+}
+
 }  // namespace
 
-// NWV = 8: two workgroups per CU, half the passes over K and V; NWV = 4: for launches that would not
-// give every CU two of those.
-template <int NWV>
-__global__ __launch_bounds__(NWV * 64, 3)
+// NWV = 8: half the passes over K and V; NWV = 4: for launches that would not fill the chip with those.
+// BUFS = 3: one chunk being read, one landing, one whose last readers may be behind, one barrier per chunk; BUFS = 2: a
+// second barrier, behind which the chunk that has just been read is replaced; four workgroups of four waves then share a
+// CU instead of three.
+template <int NWV, int BUFS>
+__global__ __launch_bounds__(NWV * 64) __attribute__((amdgpu_waves_per_eu(NWV == 4 && BUFS == 3 ? 3 : 4, NWV == 4 && BUFS == 3 ? 3 : 4)))
 void k_attn_bf16_dense(DenseArgs d, float c) {
-  constexpr int kRowsAtOnce = NWV * 8;         // rows that the workgroup loads at once, eight lanes each
-  constexpr int kRowsPerThread = kChunk / kRowsAtOnce;
+  constexpr int kRowsPerWave = kChunk / NWV, kTransfers = kRowsPerWave / 8;   // per chunk; a transfer is 8 rows, eight lanes each
   const AttnArgs& a = d.a;
-  __shared__ __align__(1024) unsigned char Kbuf[2][kChunk * kRow], Vbuf[2][kChunk * kRow];
+  __shared__ __align__(1024) unsigned char smem[BUFS * kBufBytes];
 
   // Tile by tile, the longest first, all (batch, head) pairs of one tile next to each other: the grid
   // ends on short tiles, and workgroup i runs on XCD i % 8, so that few pairs still use all XCDs.
@@ -74,6 +90,7 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
   divmod_by(a.first_block + blockIdx.x, (uint32_t)(a.B * a.H), d.bh_magic, tile, bh);
   divmod_by((uint32_t)bh, (uint32_t)a.H, a.H_magic, b, h);
   if (!plan_usable(a.hdr)) return;
+  asm volatile("" : "+s"(c));                // (so that no block waits for it)
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -118,140 +135,198 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
     for (int t = 0; t < 4; ++t) qf[t] = as_bf16x8(*(const uint4*)(qp + 16 * t));
   }
 
-  // loading duty: piece tid % 8 of rows tid / 8 + kRowsAtOnce i of every chunk (keys past the last are
-  // read from the last row: always in bounds, masked)
-  const unsigned char* Kp = (const unsigned char*)((const __bf16*)a.k + b * a.ks[0] + h * a.ks[1]) + 16 * (tid & 7);
-  const unsigned char* Vp = (const unsigned char*)((const __bf16*)a.v + b * a.ks[0] + h * a.ks[1]) + 16 * (tid & 7);
+  // loading duty: rows kRowsPerWave wave .. of every chunk, lane l piece l % 8 of row l / 8 of a transfer, put where the
+  // swizzle wants it by choosing the piece that is fetched (keys past the last are read from the last row: always in
+  // bounds, masked)
+  const unsigned char* Kp = (const unsigned char*)((const __bf16*)a.k + b * a.ks[0] + h * a.ks[1]);
+  const unsigned char* Vp = (const unsigned char*)((const __bf16*)a.v + b * a.ks[0] + h * a.ks[1]);
   const unsigned row_bytes = (unsigned)a.ks[2] * 2u;     // (a slab spans < 2 GiB, checked by the API)
-  const int lrow = tid >> 3;
-  const unsigned lds_dst = (unsigned)lrow * kRow + ((((unsigned)tid & 7u) ^ dense_swizzle((unsigned)lrow)) << 4);
-  auto load_rows = [&](const unsigned char* p, int key0, u32x4 (&r)[kRowsPerThread]) {
+  const int lrow = lane >> 3;
+  const unsigned piece_off = (((unsigned)lane & 7u) ^ dense_swizzle((unsigned)lrow)) << 4;
+  auto issue_chunk = [&](int chunk, int buf) {
 #pragma unroll
-    for (int i = 0; i < kRowsPerThread; ++i)
-      r[i] = *(const u32x4*)(p + __umul24((unsigned)checked_index(a.hdr, min(key0 + lrow + kRowsAtOnce * i, n_keys - 1), a.kv_len),
-                                          row_bytes));
-  };
-  auto store_rows = [&](unsigned char* buf, const u32x4 (&r)[kRowsPerThread]) {
-#pragma unroll
-    for (int i = 0; i < kRowsPerThread; ++i)   // (32 or 64 rows on, the swizzle is the same)
-      *(u32x4*)(buf + lds_dst + kRowsAtOnce * kRow * i) = r[i];
+    for (int i = 0; i < kTransfers; ++i) {
+      const int row0 = kRowsPerWave * wave + 8 * i, key = min(kChunk * chunk + row0 + lrow, n_keys - 1);
+      const unsigned src = __umul24((unsigned)checked_index(a.hdr, key, a.kv_len), row_bytes) + piece_off;
+      unsigned char* dst = smem + buf * kBufBytes + row0 * kRow;
+      __builtin_amdgcn_global_load_lds((global_void*)(Kp + src), (lds_void*)dst, 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((global_void*)(Vp + src), (lds_void*)(dst + kChunk * kRow), 16, 0, 0);
+    }
   };
 
   // LDS read offsets: K piece 2 t + hh of row n; V: 4 keys x 16 dims per 16 lanes
   unsigned k_off[4], v_off[2];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) k_off[t] = (unsigned)n * kRow + ((((unsigned)(2 * t + hh)) ^ dense_swizzle((unsigned)n)) << 4);
+  for (int t = 0; t < 4; ++t)
+    k_off[t] = lds_addr(smem) + (unsigned)n * kRow + ((((unsigned)(2 * t + hh)) ^ dense_swizzle((unsigned)n)) << 4);
 #pragma unroll
   for (int dt = 0; dt < 2; ++dt) {
     const unsigned l16 = (unsigned)lane & 15u, r = 4u * (unsigned)hh + (l16 >> 2);
     const unsigned piece = 4u * dt + 2u * (((unsigned)lane >> 4) & 1u) + ((l16 & 3u) >> 1);
-    v_off[dt] = r * kRow + ((piece ^ dense_swizzle(r)) << 4) + 8u * (l16 & 1u);
+    v_off[dt] = lds_addr(smem) + r * kRow + ((piece ^ dense_swizzle(r)) << 4) + 8u * (l16 & 1u);
   }
 
   f32x16 O[2] = {f32x16{}, f32x16{}};
-  float L = 0.f, negmc = 0.f, thr = kFloor;    // row sum of this lane's keys, -m c, and the score above which m moves
-  const float slack = kSlack / c;
-  const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+  float L[2] = {0.f, 0.f}, negm = 0.f;         // this lane's part of the row sum, one chain per slice; minus the softmax reference (base 2)
+  const uint64_t queries = __builtin_amdgcn_ballot_w64(row_ok);
+  uint64_t unset = queries;                    // lanes whose query's sum is still below kLeastSum
 
-  // 32 keys against the wave's 32 queries (K, V: their rows in LDS)
-  auto run_block = [&](const unsigned char* K, const unsigned char* V, int key0) {
+  // S^T of a block whose K rows have been requested
+  auto scores = [&](u32x4 (&kr)[4]) -> f32x16 {
+    lds_wait_k(kr[0], kr[1], kr[2], kr[3]);
     f32x16 S = f32x16{};
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
-      S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(*(const uint4*)(K + k_off[t])), qf[t], S, 0, 0, 0);
-    s16x4 va[2][2][2];                         // [slice of 16 keys][dim tile][half]
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) va[t][dt][j] = lds_read_tr16(V + v_off[dt] + (16 * t + 8 * j) * kRow);
+    for (int t = 3; t >= 0; --t)               // (not the windowed kernel's order of sums: a test tells the two by their bits)
+      S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kr[t]), qf[t], S, 0, 0, 0);
+    return S;
+  };
+  // The rest of a block, its V rows requested: the softmax reference starts at zero and moves only when a query's sum
+  // leaves [2^-40, 2^40] (the lower end until every query has passed it).
+  auto absorb = [&](f32x16& S, u32x2 (&va)[8], int key0) {
     if (key0 + 32 > wave_keys) {               // (uniform)
       // keys of later scales: no score, and V rows of zeros (whatever they hold must not reach the sums)
       const int left = wave_keys - key0 - 4 * hh;
+      lds_wait_v_wide(va);
 #pragma unroll
-      for (int e = 0; e < 16; ++e)
-#pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
-          va[e >> 3][dt][(e >> 2) & 1][e & 3] = 8 * (e >> 2) + (e & 3) < left ? va[e >> 3][dt][(e >> 2) & 1][e & 3] : (short)0;
+      for (int i = 0; i < 8; ++i) {
+        const int first = left - 8 * (i >> 1);           // of the four keys of va[i]: that many are the wave's
+        va[i].x &= first > 1 ? ~0u : first > 0 ? 0xffffu : 0u;
+        va[i].y &= first > 3 ? ~0u : first > 2 ? 0xffffu : 0u;
+      }
 #pragma unroll
       for (int e = 0; e < 16; ++e) S[e] = 8 * (e >> 2) + (e & 3) < left ? S[e] : -INFINITY;
     }
-    float mx = S[0], my = S[1];
+    bf16x8 pb[2];
+    float sum[2];
+    auto exponentials = [&]() {
 #pragma unroll
-    for (int e = 2; e < 14; e += 4) { mx = fmaxf(fmaxf(mx, S[e]), S[e + 1]); my = fmaxf(fmaxf(my, S[e + 2]), S[e + 3]); }
-    mx = fmaxf(fmaxf(mx, S[14]), S[15]);
-    mx = fmaxf(mx, my);
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(mx > thr) != 0, 0)) {   // rare after the first blocks
-      const unsigned u = __float_as_uint(mx);
-      auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-      const unsigned s0 = sw[0], s1 = sw[1];
-      const float mxr = fmaxf(__uint_as_float(s0), __uint_as_float(s1));   // over both lanes of the query
-      if (mxr > thr) {
-        const float nmc = -mxr * c;
-        const float alpha = thr == kFloor ? 1.f : __builtin_amdgcn_exp2f(nmc - negmc);   // (while m is unset the sums are zero)
-        negmc = nmc; thr = mxr + slack;
-        L *= alpha; O[0] *= alpha; O[1] *= alpha;
+      for (int t = 0; t < 2; ++t) {
+        sum[t] = L[t];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pb[t][e] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(S[8 * t + e], c, negm));
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+          const bf16x2 two = {pb[t][e], pb[t][e + 1]};
+          sum[t] = __builtin_amdgcn_fdot2_f32_bf16(two, kOnes, sum[t], false);
+        }
       }
+    };
+    exponentials();
+    auto both = [&](const float (&x)[2]) { const float y = x[0] + x[1]; return y + other_half(y); };   // slices, lanes
+    uint64_t move = __builtin_amdgcn_ballot_w64(fmaxf(sum[0], sum[1]) > kMostSum);
+    if (__builtin_expect(unset != 0, 0)) {
+      unset = __builtin_amdgcn_ballot_w64(both(sum) < kLeastSum) & queries;
+      move |= unset;
     }
+    if (__builtin_expect(move != 0, 0)) {
+      float mx = S[0];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      bf16x8 pb;
+      for (int e = 1; e < 16; ++e) mx = fmaxf(mx, S[e]);
+      mx = fmaxf(mx, other_half(mx));                    // over both lanes of the query
+      const float now = both(sum), before = both(L);
+      float to = mx > kFloor ? __builtin_fmaf(mx, c, negm) : kFloor;
+      if (before > 0.f) to = fmaxf(to, __builtin_amdgcn_logf(before));         // (base 2)
+      const float shift = (now > kMostSum || now < kLeastSum) && to > kFloor ? rintf(to) : 0.f;
+      const float alpha = before > 0.f ? __builtin_amdgcn_exp2f(-shift) : 1.f;
+      negm -= shift; L[0] *= alpha; L[1] *= alpha;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) pb[e] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(S[8 * t + e], c, negmc));
+      for (int e = 0; e < 16; ++e) { O[0][e] *= alpha; O[1][e] *= alpha; }
+      exponentials();
+      if (unset) unset = __builtin_amdgcn_ballot_w64(both(sum) < kLeastSum) & queries;
+    }
+    L[0] = sum[0]; L[1] = sum[1];
+    lds_wait_v_wide(va);
 #pragma unroll
-      for (int e = 0; e < 8; e += 2) {
-        const bf16x2 two = {pb[e], pb[e + 1]};
-        L = __builtin_amdgcn_fdot2_f32_bf16(two, ones, L, false);
-      }
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int dt = 0; dt < 2; ++dt) {
-        const s16x8 v8 = {va[t][dt][0][0], va[t][dt][0][1], va[t][dt][0][2], va[t][dt][0][3],
-                          va[t][dt][1][0], va[t][dt][1][1], va[t][dt][1][2], va[t][dt][1][3]};
-        O[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v8), pb, O[dt], 0, 0, 0);
+        const uint4 v8 = {va[4 * t + dt].x, va[4 * t + dt].y, va[4 * t + 2 + dt].x, va[4 * t + 2 + dt].y};
+        O[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(v8), pb[t], O[dt], 0, 0, 0);
       }
-    }
   };
-  u32x4 kr[kRowsPerThread], vr[kRowsPerThread];
-  load_rows(Kp, 0, kr); load_rows(Vp, 0, vr);
-  store_rows(Kbuf[0], kr); store_rows(Vbuf[0], vr);
-  // (the queries' registers are tied to this point: a wait for them inside the loop would also wait
-  // for the chunk that has just been requested)
-  asm volatile("" : "+v"(qf[0]), "+v"(qf[1]), "+v"(qf[2]), "+v"(qf[3]));
-  __syncthreads();
-  auto one = [&](int key0, auto odd) {
-    constexpr int p = decltype(odd)::value;
-    const bool more = key0 + kChunk < n_keys;
-    if (more) { load_rows(Kp, key0 + kChunk, kr); load_rows(Vp, key0 + kChunk, vr); }
-#pragma unroll
-    for (int blk = 0; blk < kChunk / 32; ++blk) {
-      if (key0 + 32 * blk < wave_keys) run_block(Kbuf[p] + blk * 32 * kRow, Vbuf[p] + blk * 32 * kRow, key0 + blk * 32);
+
+  const int n_chunks = (n_keys + kChunk - 1) / kChunk;
+  issue_chunk(0, 0);
+  if (n_chunks > 1) { issue_chunk(1, 1); wait_vmcnt<2 * kTransfers>(); } else wait_vmcnt<0>();
+  asm volatile("" : "+v"(qf[0]), "+v"(qf[1]), "+v"(qf[2]), "+v"(qf[3]));   // (older than the chunks: in)
+  asm volatile("s_barrier" ::: "memory");
+  f32x16 S0 = f32x16{};                        // scores of the chunk's first block
+  if (wave_keys > 0) {
+    u32x4 kr[4];
+    read_k<0>(k_off, kr);
+    S0 = scores(kr);
+  }
+  // A chunk: its two blocks, each with the next block's score products in front of its own exponentials, which then
+  // run under them.  Between the blocks the next chunk is waited for -- the only transfers in flight -- and the
+  // one after it is requested, into the buffer that every wave has read to its end by then.
+  auto one = [&](int chunk, auto which) -> bool {
+    constexpr int p = decltype(which)::value, AT = p * kBufBytes, NEXT = (p + 1) % BUFS * kBufBytes;
+    const int key0 = chunk * kChunk;
+    const bool more = chunk + 1 < n_chunks;
+    f32x16 S1;
+    asm volatile("" : "=v"(S1));            // (not set where the wave has no second block, and not used then)
+    if (key0 < wave_keys) {
+      u32x2 va[8];
+      if (key0 + 32 < wave_keys) {
+        u32x4 kr[4];
+        read_k<AT + 32 * kRow>(k_off, kr);
+        S1 = scores(kr);
+      }
+      read_v<AT + kChunk * kRow>(v_off, va);
+      __builtin_amdgcn_sched_barrier(0);
+      absorb(S0, va, key0);
     }
-    if (more) { store_rows(Kbuf[p ^ 1], kr); store_rows(Vbuf[p ^ 1], vr); }   // (read last in the chunk before)
-    __syncthreads();
+    if (more) {
+      wait_vmcnt<0>();
+      asm volatile("s_barrier" ::: "memory");
+      if (BUFS == 3 && chunk + 2 < n_chunks) issue_chunk(chunk + 2, (p + 2) % BUFS);
+    }
+    if (key0 + 32 < wave_keys) {
+      u32x2 va[8];
+      if (key0 + kChunk < wave_keys) {
+        u32x4 kr[4];
+        read_k<NEXT>(k_off, kr);
+        S0 = scores(kr);
+      }
+      read_v<AT + (kChunk + 32) * kRow>(v_off, va);
+      __builtin_amdgcn_sched_barrier(0);
+      absorb(S1, va, key0 + 32);
+    }
+    if (BUFS == 2 && chunk + 2 < n_chunks) {
+      asm volatile("s_barrier" ::: "memory");
+      issue_chunk(chunk + 2, p);
+    }
+    return more;
   };
-  for (int key0 = 0; key0 < n_keys; key0 += 2 * kChunk) {
-    one(key0, std::integral_constant<int, 0>{});
-    if (key0 + kChunk < n_keys) one(key0 + kChunk, std::integral_constant<int, 1>{});
+  for (int chunk = 0;; chunk += BUFS) {
+    if (!one(chunk, std::integral_constant<int, 0>{})) break;
+    if (!one(chunk + 1, std::integral_constant<int, 1>{})) break;
+    if constexpr (BUFS == 3) {
+      if (!one(chunk + 2, std::integral_constant<int, 2>{})) break;
+    }
   }
 
-  const unsigned u = __float_as_uint(L);
-  auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  const unsigned s0 = sw[0], s1 = sw[1];
-  const float inv = 1.f / (__uint_as_float(s0) + __uint_as_float(s1));
-  if (!row_ok) return;
-  const bool shared = is_shared(un.k);
-  if (shared && partner) return;               // the conditional workgroup writes this row
-  __bf16* op = (__bf16*)a.o + b * a.os[0] + h * a.os[1] + checked_index(a.hdr, row, a.q_len) * a.os[2] + 4 * hh;
+  const float l = L[0] + L[1], inv = 1.f / (l + other_half(l));
+  unsigned r[2][8];
 #pragma unroll
   for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      bf16x4 r;
+    for (int e = 0; e < 16; e += 2)
+      r[dt][e / 2] = __builtin_bit_cast(unsigned, bf16x2{(__bf16)(O[dt][e] * inv), (__bf16)(O[dt][e + 1] * inv)});
+  if (!row_ok) return;
+  const bool shared = is_shared(un.k);
+  if (shared && partner) return;               // the conditional workgroup writes this row
+  __bf16* op = (__bf16*)a.o + b * a.os[0] + h * a.os[1] + checked_index(a.hdr, row, a.q_len) * a.os[2] + 8 * hh;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) r[i] = (__bf16)(O[dt][4 * j + i] * inv);
-      *(bf16x4*)(op + 32 * dt + 8 * j) = r;
-      if (shared) *(bf16x4*)(op + (a.B / 2) * a.os[0] + 32 * dt + 8 * j) = r;
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      // dims 32 dt + 16 j .. + 15 of the query: its lanes hold 4 of each 8; exchanged, 8 in a row
+      const auto x0 = __builtin_amdgcn_permlane32_swap(r[dt][4 * j], r[dt][4 * j + 2], false, false);
+      const auto x1 = __builtin_amdgcn_permlane32_swap(r[dt][4 * j + 1], r[dt][4 * j + 3], false, false);
+      const u32x4 piece = {x0[0], x1[0], x0[1], x1[1]};
+      *(u32x4*)(op + 32 * dt + 16 * j) = piece;
+      if (shared) *(u32x4*)(op + (a.B / 2) * a.os[0] + 32 * dt + 16 * j) = piece;
     }
 }
 
@@ -290,22 +365,32 @@ litevar_status launch_attn_bf16_dense(const litevar_plan* pl, const AttnArgs& a,
     if (k >= pl->q_scale_begin && k < pl->q_scale_end) d.n_units += (d.off[k + 1] - d.off[k] + 31) / 32;
   }
   d.q0 = pl->q_token_begin; d.qb = pl->q_scale_begin; d.qe = pl->q_scale_end;
-  // Eight waves (256 rows) per workgroup once the rows would fill 300 such workgroups, with fewer of
-  // them CUs stand idle.  (B H, rows), four / eight waves: 2, 34 240 (268 workgroups' worth): 496 / 611 us;
-  // 480, 100 (188): 11.0 / 11.7; 32, 680 (85): 14.3 / 18.6; 480, 169 (317): 22.8 / 21.6; 480, 256 (480):
-  // 35.2 / 33.1; 60, 2240 (525): 64.6 / 60.8.  With fewer rows where eight waves take all units of a pair and four
-  // would pass twice over many keys.  480 pairs, 144 rows: 4240 keys 160 / 136; 1168: 42.0 / 39.3; 169: 11.8 / 12.4.
-  const int64_t BH = (int64_t)a.B * a.H;
-  const bool one_pass = d.n_units > 4 && d.n_units <= 8 && BH >= 300 && d.off[d.qe] >= 1024;
-  const int nwv = BH * a.q_len >= 300 * 256 || one_pass ? 8 : 4;
+  // Eight waves per workgroup halve the passes over K and V, four leave less of a workgroup idle and more of the chip
+  // at work.  Up to four units: four waves.  Up to eight units, (B H, rows, keys), four / eight waves: where eight take
+  // the place of a second workgroup of four on the CU (256, 169, 680: 13.0 / 12.2 us; 256, 256, 680: 21.3 / 19.7) and, over
+  // many keys, where four would not be resident at once (480, 256, 680: 33.6 / 31.6; 480, 144, 1744: 58.5 / 50.1; but 600, 144,
+  // 174: 15.5 / 16.4; 300, 256, 680: 26.7 / 28.0).  More units: where the last workgroup of a pair is nearly full and there are many
+  // (288, 2240 tokens: 293 / 271; 60, 1024, 2240: 46.3 / 43.6; 480, 680, 680: 60.2 / 58.0; but 120, 680, 680: 17.6 / 19.2; 480, 243, 243:
+  // 17.0 / 18.9; 2, 34 240: 476 / 590).
+  // Two buffers instead of three let a fourth workgroup of four waves onto the CU, for a second barrier: from 512
+  // workgroups on (900 workgroups, 216 rows: 13.6 / 12.0; 600, 100 rows: 14.6 / 14.3; but 120, 256 rows: 13.2 / 14.0).
+  const int64_t BH = (int64_t)a.B * a.H, fours = BH * ((d.n_units + 3) / 4), eights = BH * ((d.n_units + 7) / 8);
+  const int keys = d.off[d.qe];
+  bool eight = false;
+  if (d.n_units > 8)
+    eight = BH * a.q_len >= 300 * 256 && 10 * (int64_t)BH * d.n_units >= 8 * 8 * eights && (eights >= 1024 || keys >= 1024);
+  else if (d.n_units > 4)
+    eight = (fours > 256 && fours <= 512) || (fours > 768 && keys >= 512);
+  const int nwv = eight ? 8 : 4;
   const int64_t blocks = BH * ((d.n_units + nwv - 1) / nwv);
   if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large");
   d.bh_magic = (uint32_t)(((uint64_t)1 << 32) / (uint64_t)BH - (BH <= 1));
   const float c = a.sm_scale * 1.4426950408889634f;
   return launch_in_parts(blocks, nwv * 64, "dense bf16 attention launch", [&](int64_t first, unsigned n) {
     d.a.first_block = (uint32_t)first;
-    if (nwv == 8) hipLaunchKernelGGL(k_attn_bf16_dense<8>, dim3(n), dim3(nwv * 64), 0, st, d, c);
-    else hipLaunchKernelGGL(k_attn_bf16_dense<4>, dim3(n), dim3(nwv * 64), 0, st, d, c);
+    if (nwv == 8) hipLaunchKernelGGL((k_attn_bf16_dense<8, 3>), dim3(n), dim3(nwv * 64), 0, st, d, c);
+    else if (blocks > 512) hipLaunchKernelGGL((k_attn_bf16_dense<4, 2>), dim3(n), dim3(nwv * 64), 0, st, d, c);
+    else hipLaunchKernelGGL((k_attn_bf16_dense<4, 3>), dim3(n), dim3(nwv * 64), 0, st, d, c);
   });
 }
 

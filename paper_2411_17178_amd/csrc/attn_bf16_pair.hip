@@ -72,19 +72,10 @@ constexpr int kGroupPatches = 16;     // query patches per workgroup
 constexpr int kDmaKeys = 64;          // keys per chunk (the unit of loading and of ring slot reuse)
 constexpr int kRingChunks = 5;        // ring depth: look-back, two current, two landing
 constexpr int kBufferFlags = 0x00020000;   // word 3 of a raw buffer resource on gfx9: 32-bit data format
-typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 typedef __attribute__((ext_vector_type(2))) short s16x2;
-typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 constexpr int kBoostPhases = 3;       // phases that a later-arrived workgroup runs at raised priority
 constexpr int kLater = 2;             // descriptors, beyond the first step of a phase, that are fetched at
                                       // the start of the phase
-constexpr float kMostSum = 0x1p40f, kLeastSum = 0x1p-40f;   // row sums outside move the wide patches' softmax reference
-
-__device__ inline unsigned lds_addr(const void* p) {
-  return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
-}
 
 // four 16-byte K pieces (two keys x two halves of the head dimension): issued only,
 // lds_wait_k() must precede the first use
@@ -93,10 +84,6 @@ __device__ inline void lds_read_k_issue(unsigned a0, unsigned a1, u32x4& k00, u3
                "ds_read_b128 %2, %6\n\tds_read_b128 %3, %7"
                : "=&v"(k00), "=&v"(k01), "=&v"(k10), "=&v"(k11)
                : "v"(a0), "v"(a0 ^ 16u), "v"(a1), "v"(a1 ^ 16u) : "memory");
-}
-
-__device__ inline void lds_wait_k(u32x4& k00, u32x4& k01, u32x4& k10, u32x4& k11) {
-  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(k00), "+v"(k01), "+v"(k10), "+v"(k11) : : "memory");
 }
 
 // transposing reads of the V^T operands of one step (4 head-dim tiles x 2 key halves);
@@ -130,7 +117,7 @@ __device__ inline void lds_read_k_row_issue(unsigned k, u32x4 (&r)[4]) {
 }
 // ... and V^T: two slices of 16 keys (t), two halves of one (j), two head-dim tiles (dt); va[4 t + 2 j + dt]
 template <int VOFF>
-__device__ inline void lds_read_v_wide(const unsigned (&v)[4], const unsigned (&x)[4], uint2 (&va)[8]) {
+__device__ inline void lds_read_v_wide(const unsigned (&v)[4], const unsigned (&x)[4], u32x2 (&va)[8]) {
   asm volatile("ds_read_b64_tr_b16 %0, %8 offset:%16\n\tds_read_b64_tr_b16 %1, %9 offset:%16\n\t"
                "ds_read_b64_tr_b16 %2, %10 offset:%16\n\tds_read_b64_tr_b16 %3, %11 offset:%16\n\t"
                "ds_read_b64_tr_b16 %4, %12 offset:%16\n\tds_read_b64_tr_b16 %5, %13 offset:%16\n\t"
@@ -140,12 +127,6 @@ __device__ inline void lds_read_v_wide(const unsigned (&v)[4], const unsigned (&
                : "v"(v[0]), "v"(x[0]), "v"(v[1]), "v"(x[1]), "v"(v[2]), "v"(x[2]), "v"(v[3]), "v"(x[3]),
                  "i"(VOFF) : "memory");
 }
-__device__ inline void lds_wait_v_wide(uint2 (&va)[8]) {
-  asm volatile("s_waitcnt lgkmcnt(0)"
-               : "+v"(va[0]), "+v"(va[1]), "+v"(va[2]), "+v"(va[3]), "+v"(va[4]), "+v"(va[5]), "+v"(va[6]),
-                 "+v"(va[7]) : : "memory");
-}
-
 struct WideArgs {         // the wide patches' entries in the blob, where the plan has them
   const WaveDesc* waves; const int32_t* phase_end; const unsigned char* step_addr; const int32_t* union_tok;
   int boost;              // all workgroups of the launch are resident at once
@@ -165,23 +146,6 @@ struct PatchState {       // one query patch of a wave
   float thr, negm;        // minus the softmax reference m; thr = how far a score may rise above m
                           // before m moves: kFloor while m is unset
 };
-
-constexpr bf16x2 kOnes = {(__bf16)1.0f, (__bf16)1.0f};
-
-// the value in the other lane of a query (l ^ 32)
-__device__ inline float other_half(float x) {
-  const unsigned u = __float_as_uint(x);
-  auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  const unsigned s0 = sw[0], s1 = sw[1];       // (lower half's value, upper half's value) in every lane
-  return __uint_as_float((threadIdx.x & 32) ? s0 : s1);
-}
-
-// (on the bits, behind a barrier for the optimiser: the build lets it assume that no value is NaN)
-__device__ inline bool not_finite(float x) {
-  unsigned u = __float_as_uint(x);
-  asm volatile("" : "+v"(u));
-  return (u & 0x7f800000u) == 0x7f800000u;
-}
 
 // eight values of a row, bf16 or 8-bit codes with the row's (scale, zero point)
 template <bool Q8> __device__ inline void load_row8(const void* base, int64_t at, const float2* sz, float (&x)[8]) {
@@ -680,7 +644,7 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
 #pragma unroll
     for (int t = 0; t < 4; ++t)
       S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kr[t]), ps.q[t], S, 0, 0, 0);
-    uint2 va[8];
+    u32x2 va[8];
     lds_read_v_wide<VOFF>(v, x, va);
     __builtin_amdgcn_sched_barrier(0);         // (the reads go out here, not behind the exponentials)
     bf16x8 pb[2];

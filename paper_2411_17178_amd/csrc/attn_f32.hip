@@ -30,13 +30,6 @@ namespace {
 
 constexpr float kF32Floor = -3.402823466e+38f;   // softmax reference of a query without a kept key so far
 
-// (on the bits, behind a barrier for the optimiser: the build lets it assume that no value is NaN)
-__device__ inline bool not_finite(float x) {
-  unsigned u = __float_as_uint(x);
-  asm volatile("" : "+v"(u));
-  return (u & 0x7f800000u) == 0x7f800000u;
-}
-
 }  // namespace
 
 // W = waves per patch, 4 or 1
