@@ -153,25 +153,64 @@ __device__ inline void stream_sums(const StreamGeom& g, const StreamTask& t, Wal
 template <class F1, class F2, class F4, class F8>
 inline auto stream_pick(int N, F1 f1, F2 f2, F4 f4, F8 f8) { return N >= 5 ? f8 : N >= 3 ? f4 : N == 2 ? f2 : f1; }
 
-// val[0 .. n) (LDS, sums by distance) becomes its prefix sums, added in order by one thread; returns
-// the smallest d with val[d] >= r0 of the total, n - 1 if there is none.  All threads of the
-// workgroup call it.  (The ratio is tested by all threads at once: it is a 64-bit division.)
-__device__ inline int prefix_and_pick(double* val, int n, double r0, int* found) {
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double in = 0.0;
-    int d = 0;
-    for (; d + 16 <= n; d += 16) {       // (sixteen reads in flight: one at a time is an LDS round trip per value)
-      double v[16];
+// Sum of `count` partial sums `stride` values apart, in order, sixteen loads in flight (a row share
+// past the last is read again and not added).  Each round is a trip to memory: the partial sums come
+// from other XCDs.
+__device__ inline double sum_partials(const double* p, int count, int64_t stride) {
+  constexpr int kInFlight = 16;
+  double sum = 0.0;
+  for (int i = 0; i < count; i += kInFlight) {
+    double v[kInFlight];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] = val[d + u];
+    for (int u = 0; u < kInFlight; ++u) v[u] = p[min(i + u, count - 1) * stride];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) { in += v[u]; val[d + u] = in; }
-    }
-    for (; d < n; ++d) { in += val[d]; val[d] = in; }
-    *found = n - 1;
+    for (int u = 0; u < kInFlight; ++u) sum += i + u < count ? v[u] : 0.0;
   }
+  return sum;
+}
+
+// val[0 .. n) (LDS, sums by distance) becomes its prefix sums; returns the smallest d with val[d] >= r0
+// of the total, n - 1 if there is none.  All threads of the workgroup call it, carry: n / kPrefixRun + 1
+// words.  Runs of kPrefixRun values are added in order side by side, then their totals in order, so
+// that the sums never fall and a run of zeros adds nothing.  (One thread's chain over all values is an
+// LDS round trip for every sixteen of them: band calibrations of one scale of side 64 took 342 us, 285
+// like this; side 48 163 and 130; 30 heads of sides up to 16, 8 samples 66.1 and 63.3.  The ratio is a
+// 64-bit division, by all threads at once.)
+constexpr int kPrefixRun = 16;
+__device__ inline int prefix_and_pick(double* val, int n, double r0, double* carry, int* found) {
   __syncthreads();
+  const int runs = (n + kPrefixRun - 1) / kPrefixRun;
+  for (int b = threadIdx.x; b < runs; b += blockDim.x) {
+    double v[kPrefixRun];
+#pragma unroll
+    for (int u = 0; u < kPrefixRun; ++u) v[u] = val[min(b * kPrefixRun + u, n - 1)];
+    double in = 0.0;
+#pragma unroll
+    for (int u = 0; u < kPrefixRun; ++u) {
+      in += v[u];
+      if (b * kPrefixRun + u < n) val[b * kPrefixRun + u] = in;
+    }
+  }
+  if (threadIdx.x == 0) *found = n - 1;
+  __syncthreads();
+  if (runs > 1) {
+    if (threadIdx.x == 0) {
+      double in = 0.0;
+      for (int b0 = 0; b0 < runs - 1; b0 += kPrefixRun) {
+        double v[kPrefixRun];
+#pragma unroll
+        for (int u = 0; u < kPrefixRun; ++u) v[u] = val[min((b0 + u + 1) * kPrefixRun, n) - 1];
+#pragma unroll
+        for (int u = 0; u < kPrefixRun; ++u) {
+          in += v[u];
+          if (b0 + u < runs - 1) carry[b0 + u] = in;
+        }
+      }
+    }
+    __syncthreads();
+    for (int d = kPrefixRun + threadIdx.x; d < n; d += blockDim.x) val[d] += carry[d / kPrefixRun - 1];
+    __syncthreads();
+  }
   const double total = val[n - 1];
   int mine = n - 1;
   for (int d = threadIdx.x; d < n; d += blockDim.x)

@@ -231,13 +231,13 @@ __global__ __launch_bounds__(64) void k_calib_pick(CalibArgs a, bool stream) {
   }
   const int sj = a.s[j], nt = tiles_of(sj);
   __shared__ double inside[kMaxSide];        // values at distance exactly d, then within d
+  __shared__ double carry[kMaxSide / kPrefixRun + 1];
   __shared__ int found;
   const double* in = a.partial + part * a.splits * a.max_tiles * a.smax;
   for (int d = threadIdx.x; d < sj; d += 64) {
     double s = 0.0;
     if (stream) {
-#pragma unroll 8
-      for (int sp = 0; sp < a.stream_splits[k]; ++sp) s += in[(int64_t)sp * a.smax + d];   // (loads in flight together)
+      s = sum_partials(in + d, a.stream_splits[k], a.smax);
     } else {
       for (int sp = 0; sp < a.splits; ++sp)
         for (int t = 0; t < nt; ++t) s += in[((int64_t)sp * a.max_tiles + t) * a.smax + d];
@@ -245,7 +245,7 @@ __global__ __launch_bounds__(64) void k_calib_pick(CalibArgs a, bool stream) {
     inside[d] = s;
   }
   // the window grows from zero until the ratio reaches the threshold
-  const int r = prefix_and_pick(inside, sj, a.r0, &found);
+  const int r = prefix_and_pick(inside, sj, a.r0, carry, &found);
   if (mass) for (int d = threadIdx.x; d < a.smax; d += 64) mass[d] = inside[min(d, sj - 1)];
   if (threadIdx.x == 0) a.radius[part] = r;
 }

@@ -75,7 +75,8 @@ struct BandWalk {
 // grid (heads, slots), the slots with the most work first.
 // Measured (8 samples x 30 heads x 680^2): 56 us, 4.9 TB/s of the block-causal values; the former
 // kernel, one lane per signed offset (half of them idle in any row) and one load at a time, took 243 us.
-// k_band_pick: 15 us, 46 us before (one thread did the prefix and the 64-bit divisions one by one).
+// k_band_pick: 12 us; 14.5 with LDS for the widest part that there can be (four workgroups per CU, two rounds of
+// them), 46 with one thread for the prefix and the 64-bit divisions.
 template <int NB>
 __global__ __launch_bounds__(kStreamThreads) void k_band_stream(BandArgs a) {
   extern __shared__ __align__(16) unsigned char band_smem[];
@@ -103,7 +104,9 @@ __global__ __launch_bounds__(kStreamThreads) void k_band_stream(BandArgs a) {
 
 // grid (parts, heads): per-distance sums of the part, prefix, radius
 __global__ __launch_bounds__(kBandThreads) void k_band_pick(BandArgs a) {
-  __shared__ double by_dist[kMaxPartCols];
+  extern __shared__ __align__(16) unsigned char band_smem[];
+  double* const by_dist = (double*)band_smem;                    // [a.mcols]
+  double* const carry = by_dist + a.mcols;
   __shared__ int found_at;
   const StreamGeom& g = a.g;
   const int h = blockIdx.y, K = g.K;
@@ -112,13 +115,8 @@ __global__ __launch_bounds__(kBandThreads) void k_band_pick(BandArgs a) {
   const int first = pt == 0 ? 0 : pt + kMergedScales - 1, last = part_last(k, first);
   const int tok0 = g.off[first], n = g.off[last + 1] - tok0;
   const double* part = a.partial + (int64_t)h * a.head_stride + a.base[k] + tok0;
-  for (int d = threadIdx.x; d < n; d += kBandThreads) {
-    double m = 0.0;
-#pragma unroll 8
-    for (int sp = 0; sp < g.splits[k]; ++sp) m += part[(int64_t)sp * g.off[k + 1] + d];   // (fixed order)
-    by_dist[d] = m;
-  }
-  const int found = prefix_and_pick(by_dist, n, a.r0, &found_at);   // the band grows from zero
+  for (int d = threadIdx.x; d < n; d += kBandThreads) by_dist[d] = sum_partials(part + d, g.splits[k], g.off[k + 1]);
+  const int found = prefix_and_pick(by_dist, n, a.r0, carry, &found_at);   // the band grows from zero
   if (threadIdx.x == 0) {
     int32_t* rad = a.radius + ((int64_t)h * K + k) * K;
     for (int j = first; j <= last; ++j) rad[j] = found;
@@ -210,7 +208,8 @@ litevar_status litevar_window_calibrate_band(const int32_t* scales, int32_t n_sc
                                                          (int)lds), "hipFuncSetAttribute")) return s;
   hipLaunchKernelGGL(kernel, dim3(H, a.g.slot_begin[a.g.K]), dim3(kStreamThreads), lds, st, a);
   if (litevar_status s = hip_check(hipGetLastError(), "band calibration mass launch")) return s;
-  hipLaunchKernelGGL(k_band_pick, dim3(a.n_parts, H), dim3(kBandThreads), 0, st, a);
+  const size_t pick_lds = (size_t)(a.mcols + a.mcols / kPrefixRun + 1) * sizeof(double);   // (at most 34.8 KB)
+  hipLaunchKernelGGL(k_band_pick, dim3(a.n_parts, H), dim3(kBandThreads), pick_lds, st, a);
   return hip_check(hipGetLastError(), "band calibration pick launch");
 }
 
