@@ -87,6 +87,7 @@ def load_library():
                  "litevar_qkv8_dequantize", "litevar_windowed_attn_qkv8_workspace_bytes",
                  "litevar_windowed_attn_qkv8_fwd"):
         getattr(lib, name).restype = C.c_int32
+    lib.attn_fwd = _ATTN_FWD(("litevar_windowed_attn_fwd", lib))
     _lib = lib
     return lib
 
@@ -112,14 +113,30 @@ def _check(rc):
 
 
 def _stream_handle(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    return C.c_void_p(_stream_address(stream))
+
+
+def _stream_address(stream):
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
+
+
+_tables_module = None
+
+
+def _radius_tables(rows, K):
+    """The tables as a bytearray of int32, or None (see csrc/py_tables.cpp; built with the library)."""
+    global _tables_module
+    if _tables_module is None:
+        try:
+            from . import _tables as _tables_module
+        except ImportError:        # (a library built without this interpreter's headers: the general path takes every list)
+            _tables_module = False
+    return _tables_module.radius_tables(rows, K) if _tables_module else None
 
 
 def _int32s(values, n):
     """ctypes array of `n` integers.  Values that already are integers pass through array.array (a descriptor
-    with 30 tables of 10 x 10, checks included: 48 us, 190 us one by one); anything else goes through int()."""
+    with 30 tables of 10 x 10, checks included: 48 us, 190 us one by one, 7 us by the walk over lists of integers); anything else goes through int()."""
     values = list(values)
     try:
         buf = array("i", values)
@@ -140,8 +157,12 @@ def _make_desc(scales, radius, radius_per_key_scale, n_sink_scales, q_scales, ma
         rows = list(radius_per_key_scale)
         if len(rows) and hasattr(rows[0], "__len__") and len(rows[0]) and hasattr(rows[0][0], "__len__"):
             n_heads = len(rows)
-            assert all(len(t) == K and all(len(r) == K for r in t) for t in rows), "radius tables must be [H][K][K]"
-            heads = _int32s(chain.from_iterable(chain.from_iterable(rows)), n_heads * K * K)
+            flat = _radius_tables(rows, K)
+            if flat is not None:
+                heads = (C.c_int32 * (n_heads * K * K)).from_buffer(flat)
+            else:
+                assert all(len(t) == K and all(len(r) == K for r in t) for t in rows), "radius tables must be [H][K][K]"
+                heads = _int32s(chain.from_iterable(chain.from_iterable(rows)), n_heads * K * K)
         elif len(rows) and hasattr(rows[0], "__len__"):
             assert len(rows) == K and all(len(r) == K for r in rows), "radius table must be [K][K]"
             pair = _int32s(chain.from_iterable(rows), K * K)
@@ -270,9 +291,22 @@ def litevar_mask_export_csr(plan, stream=None, head=0):
     return rowptr, cols[:kept]
 
 
+_Strides = C.c_int64 * 3
+
+
 def _strides(t):
-    assert t.dim() == 4 and t.stride(3) == 1, "expected [B, H, tokens, D] with contiguous D"
-    return (C.c_int64 * 3)(t.stride(0), t.stride(1), t.stride(2))
+    st = t.stride()
+    assert len(st) == 4 and st[3] == 1, "expected [B, H, tokens, D] with contiguous D"
+    return _Strides(st[0], st[1], st[2])
+
+
+# The attention entry with its argument types declared: numbers go in as they are.  (Wrapped one by one in
+# ctypes objects, with the plan's fields read through Plan.__getattr__, a generation step of 16 queries took
+# 12.0 us, all of it the host's; 9.7 like this.)
+_ATTN_FWD = C.CFUNCTYPE(C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32,
+                        C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_float, C.c_void_p, C.c_uint32,
+                        C.c_void_p)
+_DTYPES = {torch.bfloat16: DT_BF16, torch.float32: DT_F32}
 
 
 def litevar_windowed_attn_fwd(plan, q, k, v, sm_scale, out=None, cfg_share=None, stream=None):
@@ -281,31 +315,30 @@ def litevar_windowed_attn_fwd(plan, q, k, v, sm_scale, out=None, cfg_share=None,
     cfg_share: optional uint8 CUDA tensor [H, K]; when given, the CFG shared-output
     flag is set and rows b + B/2 reuse rows b where the table is non-zero.
     """
-    lib = load_library()
+    fn = load_library().attn_fwd
     assert q.is_cuda and k.is_cuda and v.is_cuda
-    assert q.dtype == k.dtype == v.dtype
-    if q.dtype == torch.bfloat16:
-        dt = DT_BF16
-    elif q.dtype == torch.float32:
-        dt = DT_F32
-    else:
-        raise TypeError(f"unsupported dtype {q.dtype}")
-    B, H, Lq, D = q.shape
-    assert Lq == plan.q_len and k.shape == (B, H, plan.kv_len, D) and v.shape == k.shape
+    dtype = q.dtype
+    assert dtype == k.dtype == v.dtype
+    dt = _DTYPES.get(dtype)
+    if dt is None:
+        raise TypeError(f"unsupported dtype {dtype}")
+    handle = plan.handle
+    shape, kv_shape = q.shape, k.shape
+    B, H, Lq, D = shape
+    assert Lq == handle.q_len and kv_shape == (B, H, handle.kv_len, D) and v.shape == kv_shape
     if out is None:
         out = torch.empty_like(q)
-    assert out.shape == q.shape and out.dtype == q.dtype and out.is_cuda
+    assert out.shape == shape and out.dtype == dtype and out.is_cuda
     flags, share_ptr = 0, None
     if cfg_share is not None:
         assert cfg_share.is_cuda and cfg_share.dtype == torch.uint8 and cfg_share.is_contiguous()
-        assert cfg_share.shape == (H, plan.n_scales)
-        flags, share_ptr = FLAG_CFG_SHARE, C.c_void_p(cfg_share.data_ptr())
+        assert cfg_share.shape == (H, handle.n_scales)
+        flags, share_ptr = FLAG_CFG_SHARE, cfg_share.data_ptr()
     assert k.stride() == v.stride(), "k and v must share strides"
-    _check(lib.litevar_windowed_attn_fwd(
-        C.byref(plan.handle), C.c_void_p(q.data_ptr()), C.c_void_p(k.data_ptr()),
-        C.c_void_p(v.data_ptr()), C.c_void_p(out.data_ptr()), C.c_int32(B), C.c_int32(H),
-        C.c_int32(D), C.c_int32(dt), _strides(q), _strides(k), _strides(out),
-        C.c_float(sm_scale), share_ptr, C.c_uint32(flags), _stream_handle(stream)))
+    rc = fn(C.addressof(handle), q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), B, H, D, dt,
+            _strides(q), _strides(k), _strides(out), sm_scale, share_ptr, flags, _stream_address(stream))
+    if rc != 0:
+        _check(rc)
     return out
 
 

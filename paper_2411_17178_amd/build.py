@@ -2,11 +2,13 @@
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblitevar.so")
+TABLES = os.path.join(HERE, "_tables" + sysconfig.get_config_var("EXT_SUFFIX"))   # the Python binding's own module
 OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["api.hip", "plan_build.hip", "attn_f32.hip", "attn_bf16.hip", "attn_bf16_pair.hip", "attn_bf16_dense.hip",
            "calibrate.hip", "calibrate_band.hip", "peaks.hip", "qkv8.hip"]
@@ -47,6 +49,10 @@ def build(verbose: bool = False, debug_bounds: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         jobs = [ex.submit(_run, [hipcc] + flags + ["-c", "-o", o, os.path.join(CSRC, s)], verbose)
                 for s, o in zip(SOURCES, objs)]
+        if not debug_bounds:
+            jobs.append(ex.submit(_run, [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall",
+                                         "-I" + sysconfig.get_paths()["include"], "-o", TABLES,
+                                         os.path.join(CSRC, "py_tables.cpp")], verbose))
         for j in jobs:
             j.result()
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib] + objs, verbose)

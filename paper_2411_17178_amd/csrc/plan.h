@@ -212,9 +212,8 @@ inline bool choose_wide_shape(int s, int rh, int rw, short& wph, short& wpw) {
   for (int ph = 1; ph <= H && ph <= 11; ++ph)
     for (int pw = 1; pw <= W && ph * pw <= kWideQueries && ph + pw <= 12; ++pw) {
       if (((H + ph - 1) / ph) * ((W + pw - 1) / pw) > kWidePatches) continue;
-      long ny = 0, nx = 0;
-      for (int y = 0; y < s; y += rh * kPatch) ny += ((s - y < H ? s - y : H) + ph - 1) / ph;
-      for (int x = 0; x < s; x += rw * kPatch) nx += ((s - x < W ? s - x : W) + pw - 1) / pw;
+      const long ny = s / H * ((H + ph - 1) / ph) + (s % H + ph - 1) / ph;    // whole groups, then the last one
+      const long nx = s / W * ((W + pw - 1) / pw) + (s % W + pw - 1) / pw;
       const long key = ny * nx * (ph + 6) * (pw + 6) * 16 - pw;
       if (best < 0 || key < best) { best = key; wph = (short)ph; wpw = (short)pw; }
     }
@@ -362,17 +361,39 @@ LV_HD int band_union_keys(const Geom& g, const Rad& rad, const GroupExtent& e) {
 // A step is closed when it holds 32 keys or when the next key's 2^logS-key block lies more
 // than A blocks after the block of the step's first key (LDS ring constraint).
 struct StepCounter {
-  const Geom& g;
+  const int logS, A;
+  explicit StepCounter(const Geom& g) : logS(g.logS), A(g.A) {}
   int steps = 0, cnt = 0, first_block = 0;
   void run(int upos, int n) {              // n consecutive keys of the union list, all kept by some query
     while (n > 0) {
-      const int blk = upos >> g.logS;
-      if (cnt == kStepKeys || (cnt > 0 && blk - first_block > g.A)) { ++steps; cnt = 0; }
+      const int blk = upos >> logS;
+      if (cnt == kStepKeys || (cnt > 0 && blk - first_block > A)) { ++steps; cnt = 0; }
       if (cnt == 0) first_block = blk;
-      const int room = ((first_block + g.A + 1) << g.logS) - upos;
+      const int room = ((first_block + A + 1) << logS) - upos;
       int take = kStepKeys - cnt < room ? kStepKeys - cnt : room;
       if (take > n) take = n;
       cnt += take; upos += take; n -= take;
+    }
+  }
+  // n_rows runs of w keys each, `pitch` entries apart: the same as run() for each of them, but the rows that end
+  // ahead of the open step's last block are counted together (no step that starts in them is cut by its span)
+  void rows(int upos, int w, int pitch, int n_rows) {
+    while (n_rows > 0) {
+      const int blk = upos >> logS;
+      if (cnt == kStepKeys || (cnt > 0 && blk - first_block > A)) { ++steps; cnt = 0; }
+      if (cnt == 0) first_block = blk;
+      const int room = ((first_block + A + 1) << logS) - upos;
+      if (room < w) { run(upos, w); upos += pitch; --n_rows; continue; }
+      int m = n_rows;
+      if ((int64_t)(n_rows - 1) * pitch > room - w) m = 1 + (unsigned)(room - w) / (unsigned)pitch;
+      const int n = m * w, full = (cnt + n - 1) / kStepKeys;
+      if (full > 0) {
+        const unsigned first = (unsigned)(full * kStepKeys - cnt);      // of these keys, the open step's first one
+        first_block = (upos + (int)(first / (unsigned)w) * (pitch - w) + (int)first) >> logS;
+        steps += full;
+      }
+      cnt += n - full * kStepKeys;
+      upos += m * pitch; n_rows -= m;
     }
   }
   int finish() { if (cnt > 0) { ++steps; cnt = 0; } return steps; }
@@ -383,6 +404,7 @@ struct StepCounter {
 struct AxisSpan {
   int n_runs = 0, kept = 0;
   Interval run[kWideQueries];
+  void clear() { n_runs = kept = 0; }
   void add(const Interval& iv) {
     kept += iv.hi - iv.lo + 1;
     if (n_runs > 0 && iv.lo <= run[n_runs - 1].hi + 1) { if (iv.hi > run[n_runs - 1].hi) run[n_runs - 1].hi = iv.hi; }

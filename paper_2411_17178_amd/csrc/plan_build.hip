@@ -21,7 +21,7 @@ static void choose_tiling(Geom& g, int waves, int chunk, int depth, int spare) {
     int rh, rw;
     choose_group_shape((g.s[k] + kPatch - 1) / kPatch, waves, rh, rw);
     g.grh[k] = (short)rh; g.grw[k] = (short)rw;
-    if (waves == 16) choose_wide_shape(g.s[k], rh, rw, g.wph[k], g.wpw[k]);   // (there is one for every side up to kMaxSide)
+    if (waves == 16 && k >= g.qb && k < g.qe) choose_wide_shape(g.s[k], rh, rw, g.wph[k], g.wpw[k]);   // (there is one for every side up to kMaxSide)
   }
   g.NR = g.A + 1 + g.D + spare;
   g.logC = 0;
@@ -158,8 +158,8 @@ litevar_status make_spec(const litevar_mask_desc* d, const litevar_plan_opts* op
 
 static uint64_t align256(uint64_t x) { return (x + 255) & ~(uint64_t)255; }
 
-// The sizing walk visits every run of consecutive kept keys of every patch on the host (30 tables of
-// 13 x 13 queries: 0.06 ms; 0.54 ms key by key).
+// The sizing walk visits every patch's box in every key scale on the host, rows at a time (30 tables of 13 x 13
+// queries: 36 us, 48 row by row with the windows' centres divided anew for every table; 540 key by key).
 // Callers size and then build with the same descriptor, often repeatedly,
 // so the last result is remembered per thread, keyed by the whole specification.
 static thread_local struct { bool valid; PlanSpec sp; PlanSizes z; } g_last_sizing = {false, {}, {}};
@@ -181,30 +181,44 @@ litevar_status size_plan(PlanSpec& sp, PlanSizes& z) {
   return rc;
 }
 
-// a patch's keys of one key scale: rows x columns of the group's box, which starts at entry `ubase` of the
-// list, at (gylo, gxlo) of the scale, and is gw wide
-static void add_box(StepCounter& steps, const AxisSpan& rows, const AxisSpan& cols, int ubase, int gylo, int gxlo, int gw) {
+// a group's box in a key scale: its rows and columns and its first entry in the group's list
+struct ListBox { int base, ylo, n_rows, xlo, w; const int16_t* order; };   // order: the rows of a dealt box, from place 0 on
+
+// a patch's keys of one key scale: rows x columns of the group's box
+static void add_box(StepCounter& steps, const AxisSpan& rows, const AxisSpan& cols, const ListBox& b) {
   for (int r = 0; r < rows.n_runs; ++r) {
-    const int y0 = rows.run[r].lo, y1 = rows.run[r].hi;
-    if (cols.n_runs == 1 && cols.hi() - cols.lo() + 1 == gw) {      // whole rows of the group's box
-      steps.run(ubase + (y0 - gylo) * gw, (y1 - y0 + 1) * gw);
+    const int at = b.base + (rows.run[r].lo - b.ylo) * b.w - b.xlo, n = rows.run[r].hi - rows.run[r].lo + 1;
+    if (cols.n_runs == 1) {
+      const int w = cols.run[0].hi - cols.run[0].lo + 1;
+      steps.rows(at + cols.run[0].lo, w, b.w, n);
       continue;
     }
-    for (int y = y0; y <= y1; ++y)
+    for (int y = 0; y < n; ++y)
       for (int i = 0; i < cols.n_runs; ++i)
-        steps.run(ubase + (y - gylo) * gw + cols.run[i].lo - gxlo, cols.run[i].hi - cols.run[i].lo + 1);
+        steps.run(at + y * b.w + cols.run[i].lo, cols.run[i].hi - cols.run[i].lo + 1);
   }
 }
 
 // the same with the box's rows dealt (see dealt_row)
-static void add_dealt_box(StepCounter& steps, const AxisSpan& rows, const AxisSpan& cols, int ubase, int gylo, int n_rows,
-                          int gxlo, int gw) {
-  for (int i = 0; i < n_rows; ++i) {
-    const int y = gylo + dealt_row(i, n_rows);
-    bool kept = false;
-    for (int r = 0; r < rows.n_runs; ++r) kept |= y >= rows.run[r].lo && y <= rows.run[r].hi;
-    for (int c = 0; kept && c < cols.n_runs; ++c)
-      steps.run(ubase + i * gw + cols.run[c].lo - gxlo, cols.run[c].hi - cols.run[c].lo + 1);
+static void add_dealt_box(StepCounter& steps, const AxisSpan& rows, const AxisSpan& cols, const ListBox& b) {
+  auto kept = [&](int i) {
+    for (int r = 0; r < rows.n_runs; ++r)
+      if (b.order[i] >= rows.run[r].lo && b.order[i] <= rows.run[r].hi) return true;
+    return false;
+  };
+  for (int i = 0; i < b.n_rows;) {
+    int n = 0;
+    while (i + n < b.n_rows && kept(i + n)) ++n;
+    if (n == 0) { ++i; continue; }
+    const int at = b.base + i * b.w - b.xlo;
+    if (cols.n_runs == 1) {
+      steps.rows(at + cols.run[0].lo, cols.run[0].hi - cols.run[0].lo + 1, b.w, n);
+    } else {
+      for (int y = 0; y < n; ++y)
+        for (int c = 0; c < cols.n_runs; ++c)
+          steps.run(at + y * b.w + cols.run[c].lo, cols.run[c].hi - cols.run[c].lo + 1);
+    }
+    i += n + 1;                                                       // (the row after the run is not kept)
   }
 }
 
@@ -213,32 +227,58 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
   memset(&z, 0, sizeof z);
   std::vector<AxisSpan> ax;            // window mode: [key scale][patch row or column of the query scale]
   std::vector<AxisSpan> wide_rows, wide_cols;   // the same of the wide patches: [key scale][group row, patch row in it]
+  // (entries are cleared and not assigned: one holds the runs of 32 queries)
+  auto cleared = [](std::vector<AxisSpan>& v, size_t n) {
+    if (v.size() < n) v.resize(n);
+    for (size_t i = 0; i < n; ++i) v[i].clear();
+  };
+  // window mode: the windows' centres, which are the same for every head group: [query scale][key scale][coordinate]
+  std::vector<int16_t> centres;
+  size_t centre_of[kMaxScales] = {};
+  for (int k = g.qb; k < g.qe && g.mode == kModeWindow; ++k) {
+    centre_of[k] = centres.size();
+    for (int j = 0; j <= k; ++j)
+      for (int c = 0; c < g.s[k]; ++c) centres.push_back((int16_t)window_interval(g.s[k], g.s[j], c, 0).lo);
+  }
+  ListBox boxes[kMaxScales];
+  std::vector<int16_t> orders((size_t)(g.NW == 16 ? g.K : 0) * g.smax);
   for (int hg = 0; hg < g.n_hg; ++hg) {
     sp.load_head_group(hg);
     const ArithRad rad{g};
     int64_t pairs_hg = 0;
     for (int k = g.qe - 1; k >= g.qb; --k) {
       const int pps = patches_per_side(g, k), nk = g.s[k] * g.s[k];
-      if (g.mode == kModeWindow) {
-        ax.assign((size_t)(k + 1) * pps, AxisSpan());
-        for (int j = 0; j <= k; ++j)
-          for (int c = 0; c < g.s[k]; ++c) ax[(size_t)j * pps + c / kPatch].add(win_interval(g, k, j, c));
-      }
       const int ngy = groups_y(g, k), ngx = groups_x(g, k);
       const bool wide = g.NW == 16;
       // wide patch rows of a group, and columns (window mode)
       int wny = 0, wnx = 0;
-      if (wide && g.mode == kModeWindow) {
-        const int gh = g.grh[k] * kPatch, gw = g.grw[k] * kPatch, ph = g.wph[k], pw = g.wpw[k];
-        wny = ((gh < g.s[k] ? gh : g.s[k]) + ph - 1) / ph; wnx = ((gw < g.s[k] ? gw : g.s[k]) + pw - 1) / pw;
-        wide_rows.assign((size_t)(k + 1) * ngy * wny, AxisSpan());
-        wide_cols.assign((size_t)(k + 1) * ngx * wnx, AxisSpan());
-        for (int j = 0; j <= k; ++j)
-          for (int c = 0; c < g.s[k]; ++c) {
-            const Interval iv = win_interval(g, k, j, c);
-            wide_rows[((size_t)j * ngy + c / gh) * wny + c % gh / ph].add(iv);
-            wide_cols[((size_t)j * ngx + c / gw) * wnx + c % gw / pw].add(iv);
-          }
+      if (g.mode == kModeWindow) {
+        const int gh = g.grh[k] * kPatch, gw = g.grw[k] * kPatch, ph = g.wph[k], pw = g.wpw[k], sk = g.s[k];
+        cleared(ax, (size_t)(k + 1) * pps);
+        if (wide) {
+          wny = ((gh < sk ? gh : sk) + ph - 1) / ph; wnx = ((gw < sk ? gw : sk) + pw - 1) / pw;
+          cleared(wide_rows, (size_t)(k + 1) * ngy * wny);
+          cleared(wide_cols, (size_t)(k + 1) * ngx * wnx);
+        }
+        const int16_t* ctr = &centres[centre_of[k]];
+        for (int j = 0; j <= k; ++j, ctr += sk) {
+          const int last = g.s[j] - 1, r = j < g.n_sink ? -1 : g.rad[k][j];
+          auto window = [&](int c) {
+            if (r < 0) return Interval{0, last};
+            return Interval{ctr[c] - r < 0 ? 0 : ctr[c] - r, ctr[c] + r > last ? last : ctr[c] + r};
+          };
+          AxisSpan* a = &ax[(size_t)j * pps];
+          for (int c = 0; c < sk; ++c) a[c / kPatch].add(window(c));
+          if (!wide) continue;
+          a = &wide_rows[(size_t)j * ngy * wny];
+          for (int y = 0; y < sk; y += gh, a += wny)
+            for (int p = 0, c = y, end = std::min(sk, y + gh); c < end; ++p)
+              for (int to = std::min(end, c + ph); c < to; ++c) a[p].add(window(c));
+          a = &wide_cols[(size_t)j * ngx * wnx];
+          for (int x = 0; x < sk; x += gw, a += wnx)
+            for (int p = 0, c = x, end = std::min(sk, x + gw); c < end; ++p)
+              for (int to = std::min(end, c + pw); c < to; ++c) a[p].add(window(c));
+        }
       }
       for (int gi = 0; gi < ngy * ngx; ++gi) {
         const int gy = gi / ngx, gx = gi % ngx;
@@ -249,7 +289,16 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
         } else {
           for (int j = 0; j <= k; ++j) {
             const AxisSpan* a = &ax[(size_t)j * pps];
-            nu += (a[e.qy1 / kPatch].hi() - a[e.qy0 / kPatch].lo() + 1) * (a[e.qx1 / kPatch].hi() - a[e.qx0 / kPatch].lo() + 1);
+            ListBox& b = boxes[j];
+            b.base = nu;
+            b.ylo = a[e.qy0 / kPatch].lo(); b.n_rows = a[e.qy1 / kPatch].hi() - b.ylo + 1;
+            b.xlo = a[e.qx0 / kPatch].lo(); b.w = a[e.qx1 / kPatch].hi() - b.xlo + 1;
+            if (wide && dealt_box(g.mode, nu)) {
+              int16_t* order = &orders[(size_t)j * g.smax];
+              for (int i = 0; i < b.n_rows; ++i) order[i] = (int16_t)(b.ylo + dealt_row(i, b.n_rows));
+              b.order = order;
+            }
+            nu += b.n_rows * b.w;
           }
         }
         const int nph = (nu + g.C - 1) / g.C;
@@ -259,8 +308,8 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
           const PatchExtent p = patch_extent(g, k, gy, gx, w);
           if (p.ny == 0) continue;
           StepCounter steps{g};
-          int ubase = 0;
           if (g.mode == kModeBand) {
+            int ubase = 0;
             for (int pt = 0; pt < band_parts(k); ++pt) {
               const BandPart b = band_part(g, rad, k, pt);
               const int glo = band_interval(b, nk, e.qy0).lo, ghi = band_interval(b, nk, e.qy1).hi;
@@ -271,14 +320,10 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
               ubase += ghi - glo + 1;
             }
           } else {
-            for (int j = 0; j <= k; ++j) {
-              const AxisSpan* a = &ax[(size_t)j * pps];
-              const AxisSpan &rows = a[p.y0 / kPatch], &cols = a[p.x0 / kPatch];
-              const int gylo = a[e.qy0 / kPatch].lo(), gyhi = a[e.qy1 / kPatch].hi();
-              const int gxlo = a[e.qx0 / kPatch].lo(), gw = a[e.qx1 / kPatch].hi() - gxlo + 1;
-              add_box(steps, rows, cols, ubase, gylo, gxlo, gw);
-              pairs_hg += (int64_t)rows.kept * cols.kept;
-              ubase += (gyhi - gylo + 1) * gw;
+            const AxisSpan *rows = &ax[p.y0 / kPatch], *cols = &ax[p.x0 / kPatch];
+            for (int j = 0; j <= k; ++j, rows += pps, cols += pps) {
+              add_box(steps, *rows, *cols, boxes[j]);
+              pairs_hg += (int64_t)rows->kept * cols->kept;
             }
           }
           const int ns = steps.finish();
@@ -289,8 +334,8 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
           const PatchExtent p = wide_extent(g, k, gy, gx, w);
           if (p.ny == 0) continue;
           StepCounter steps{g};
-          int ubase = 0;
           if (g.mode == kModeBand) {
+            int ubase = 0;
             for (int pt = 0; pt < band_parts(k); ++pt) {
               const BandPart b = band_part(g, rad, k, pt);
               const int glo = band_interval(b, nk, e.qy0).lo, ghi = band_interval(b, nk, e.qy1).hi;
@@ -300,15 +345,10 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
               ubase += ghi - glo + 1;
             }
           } else {
-            for (int j = 0; j <= k; ++j) {
-              const AxisSpan* a = &ax[(size_t)j * pps];
-              const int gylo = a[e.qy0 / kPatch].lo(), gyhi = a[e.qy1 / kPatch].hi();
-              const int gxlo = a[e.qx0 / kPatch].lo(), gw = a[e.qx1 / kPatch].hi() - gxlo + 1;
-              const AxisSpan &rows = wide_rows[((size_t)j * ngy + gy) * wny + w / wnx],
-                             &cols = wide_cols[((size_t)j * ngx + gx) * wnx + w % wnx];
-              if (dealt_box(g.mode, ubase)) add_dealt_box(steps, rows, cols, ubase, gylo, gyhi - gylo + 1, gxlo, gw);
-              else add_box(steps, rows, cols, ubase, gylo, gxlo, gw);
-              ubase += (gyhi - gylo + 1) * gw;
+            const AxisSpan *rows = &wide_rows[gy * wny + w / wnx], *cols = &wide_cols[gx * wnx + w % wnx];
+            for (int j = 0; j <= k; ++j, rows += ngy * wny, cols += ngx * wnx) {
+              if (dealt_box(g.mode, boxes[j].base)) add_dealt_box(steps, *rows, *cols, boxes[j]);
+              else add_box(steps, *rows, *cols, boxes[j]);
             }
           }
           const int ns = steps.finish();
