@@ -7,8 +7,7 @@
 // fill while the chunk before is computed.  Per 32 keys:
 //   S^T (32 keys x 32 queries) = K (A operand) . Q^T (B operand): v_mfma_f32_32x32x16_bf16; a
 //       lane ends up with one query column and 16 of the 32 keys,
-//   softmax in base 2 with a reference that moves only when a row sum leaves [2^-40, 2^40], as for the windowed
-//       kernel's wide patches,
+//   softmax in base 2 with the first block's largest score as the reference, which moves only when a row sum passes 2^40,
 //   O^T (64 x queries) += V^T (A operand, ds_read_b64_tr_b16) . P^T (B operand: the lane's own
 //       probabilities rounded to bf16; the key order of the slices is the order in which the score
 //       tile's registers hold them), row sums of the rounded probabilities by v_dot2_f32_bf16, one chain per slice.
@@ -169,19 +168,19 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
   f32x16 O[2] = {f32x16{}, f32x16{}};
   float L[2] = {0.f, 0.f}, negm = 0.f;         // this lane's part of the row sum, one chain per slice; minus the softmax reference (base 2)
   const uint64_t queries = __builtin_amdgcn_ballot_w64(row_ok);
-  uint64_t unset = queries;                    // lanes whose query's sum is still below kLeastSum
+  uint64_t unset = queries;                    // lanes whose query has no reference yet
 
   // S^T of a block whose K rows have been requested
   auto scores = [&](u32x4 (&kr)[4]) -> f32x16 {
     lds_wait_k(kr[0], kr[1], kr[2], kr[3]);
     f32x16 S = f32x16{};
 #pragma unroll
-    for (int t = 3; t >= 0; --t)               // (not the windowed kernel's order of sums: a test tells the two by their bits)
+    for (int t = 0; t < 4; ++t)
       S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kr[t]), qf[t], S, 0, 0, 0);
     return S;
   };
-  // The rest of a block, its V rows requested: the softmax reference starts at zero and moves only when a query's sum
-  // leaves [2^-40, 2^40] (the lower end until every query has passed it).
+  // The rest of a block, its V rows requested.  The softmax reference is the largest score of the first block (so that few
+  // keys give the bits that the windowed kernels give) and moves only when a query's sum passes 2^40.
   auto absorb = [&](f32x16& S, u32x2 (&va)[8], int key0) {
     if (key0 + 32 > wave_keys) {               // (uniform)
       // keys of later scales: no score, and V rows of zeros (whatever they hold must not reach the sums)
@@ -195,6 +194,18 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
       }
 #pragma unroll
       for (int e = 0; e < 16; ++e) S[e] = 8 * (e >> 2) + (e & 3) < left ? S[e] : -INFINITY;
+    }
+    auto largest = [&]() {                     // score of the query, over both of its lanes
+      float mx = S[0];
+#pragma unroll
+      for (int e = 1; e < 16; ++e) mx = fmaxf(mx, S[e]);
+      return fmaxf(mx, other_half(mx));
+    };
+    if (__builtin_expect(unset != 0, 0)) {
+      const float mx = largest();
+      const bool set = __builtin_amdgcn_inverse_ballot_w64(unset) && mx > kFloor;
+      negm = set ? -mx * c : negm;
+      unset &= ~__builtin_amdgcn_ballot_w64(set);
     }
     bf16x8 pb[2];
     float sum[2];
@@ -212,27 +223,17 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
       }
     };
     exponentials();
-    auto both = [&](const float (&x)[2]) { const float y = x[0] + x[1]; return y + other_half(y); };   // slices, lanes
-    uint64_t move = __builtin_amdgcn_ballot_w64(fmaxf(sum[0], sum[1]) > kMostSum);
-    if (__builtin_expect(unset != 0, 0)) {
-      unset = __builtin_amdgcn_ballot_w64(both(sum) < kLeastSum) & queries;
-      move |= unset;
-    }
-    if (__builtin_expect(move != 0, 0)) {
-      float mx = S[0];
-#pragma unroll
-      for (int e = 1; e < 16; ++e) mx = fmaxf(mx, S[e]);
-      mx = fmaxf(mx, other_half(mx));                    // over both lanes of the query
-      const float now = both(sum), before = both(L);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(fmaxf(sum[0], sum[1]) > kMostSum) != 0, 0)) {
+      auto both = [&](const float (&x)[2]) { const float y = x[0] + x[1]; return y + other_half(y); };   // slices, lanes
+      const float mx = largest(), now = both(sum), before = both(L);
       float to = mx > kFloor ? __builtin_fmaf(mx, c, negm) : kFloor;
       if (before > 0.f) to = fmaxf(to, __builtin_amdgcn_logf(before));         // (base 2)
-      const float shift = (now > kMostSum || now < kLeastSum) && to > kFloor ? rintf(to) : 0.f;
+      const float shift = now > kMostSum && to > kFloor ? rintf(to) : 0.f;
       const float alpha = before > 0.f ? __builtin_amdgcn_exp2f(-shift) : 1.f;
       negm -= shift; L[0] *= alpha; L[1] *= alpha;
 #pragma unroll
       for (int e = 0; e < 16; ++e) { O[0][e] *= alpha; O[1][e] *= alpha; }
       exponentials();
-      if (unset) unset = __builtin_amdgcn_ballot_w64(both(sum) < kLeastSum) & queries;
     }
     L[0] = sum[0]; L[1] = sum[1];
     lds_wait_v_wide(va);
