@@ -21,14 +21,21 @@ struct PlanSizes {
   uint64_t bytes;
 };
 
+constexpr int kPlaceWords = 768;                        // (of k_fill's arguments)
+constexpr int kMostPlacedGroups = kPlaceWords / 3;
+
 // What a mask descriptor asks for: the geometry, and one radius table per head group
 // (heads with equal tables share a group).  g.rad holds the table of the group that was
 // loaded last; make_spec and size_plan leave group 0 loaded.
 struct PlanSpec {
-  Geom g;
+  HostGeom g;
   int n_heads = 0;                      // 0: one table for all heads
   std::vector<int16_t> rad_all;         // [n_hg][K][K]
   uint8_t head_group[kMaxHeads] = {};   // head -> head group
+  // set by size_plan, for plans of at most kMostPlacedGroups groups: the phases of every group, and the steps of
+  // every patch of every group (the wide ones after the others)
+  std::vector<int32_t> group_phases;
+  std::vector<uint16_t> patch_steps;
   void load_head_group(int hg) {
     for (int k = 0; k < g.K; ++k)
       for (int j = 0; j < g.K; ++j) g.rad[k][j] = rad_all[((size_t)hg * g.K + k) * g.K + j];

@@ -60,13 +60,15 @@ struct Geom {
   int n_hg;             // head groups (1 unless the plan has one radius table per head)
   int s[kMaxScales];
   int off[kMaxScales + 1];
-  short rad[kMaxScales][kMaxScales];   // radii of ONE head group, [query scale][key scale]
-                                       // (Section 2, step (3): one window size per scale and
-                                       // part); < 0: dense part.  The host sizes one head
-                                       // group at a time; the device kernels read tables in
-                                       // the blob and never this field.
   int grp_off[kMaxScales + 1];  // groups are ordered by DESCENDING query scale:
                                 // slot i holds scale qe-1-i; grp_off is its prefix sum
+};
+
+// The host's geometry, with the radii of ONE head group, [query scale][key scale] (Section 2, step (3): one window
+// size per scale and part); < 0: dense part.  The host sizes one head group at a time; the device kernels get
+// the Geom alone (2 KB less of kernel arguments in every launch) and read the tables in the blob.
+struct HostGeom : Geom {
+  short rad[kMaxScales][kMaxScales];
 };
 
 struct GroupDesc {   // 32 bytes
@@ -101,8 +103,9 @@ struct Header {      // first 256 bytes of the blob
   int32_t n_groups, n_waves;
   int64_t n_steps, n_union, n_phase_entries;
   int64_t retained_pairs;
-  int32_t error;       // kErrBuilder: set by the builder when a capacity would be exceeded (the
-                       // work-list sections are then not written and no kernel uses the plan);
+  int32_t error;       // kErrBuilder: set by the builder when the device's walk and the host's counts differ
+                       // (the work-list sections are then not written beyond the counts and no kernel
+                       // uses the plan);
                        // kErrWaitGaveUp: an attention kernel's bounded wait on an LDS flag ran out;
                        // kErrBounds: a kernel of the bounds-checking build found a token, a query
                        // row or an LDS offset out of range (it used index 0 instead)
@@ -139,7 +142,7 @@ LV_HD Interval window_interval(int sk, int sj, int c, int rad) {
   iv.hi = ctr + rad > sj - 1 ? sj - 1 : ctr + rad;
   return iv;
 }
-LV_HD Interval win_interval(const Geom& g, int k, int j, int c) {
+inline Interval win_interval(const HostGeom& g, int k, int j, int c) {
   return window_interval(g.s[k], g.s[j], c, j < g.n_sink ? -1 : g.rad[k][j]);
 }
 
@@ -184,7 +187,7 @@ LV_HD Interval band_interval(const BandPart& b, int nk, int i) {
   return iv;
 }
 
-struct ArithRad { const Geom& g; LV_HD int operator()(int k, int j) const { return g.rad[k][j]; } };
+struct ArithRad { const HostGeom& g; int operator()(int k, int j) const { return g.rad[k][j]; } };
 struct TableRad { const int16_t* rad; int K; LV_HD int operator()(int k, int j) const { return rad[k * K + j]; } };
 
 // ---- groups and patches ------------------------------------------------------------

@@ -36,7 +36,7 @@ static void choose_tiling(Geom& g, int waves, int chunk, int depth, int spare) {
 }
 
 litevar_status make_spec(const litevar_mask_desc* d, const litevar_plan_opts* opts, PlanSpec& sp) {
-  Geom& g = sp.g;
+  HostGeom& g = sp.g;
   if (!d) return fail(LITEVAR_E_INVALID_ARG, "desc is NULL");
   if (d->n_scales < 1 || d->n_scales > kMaxScales)
     return fail(LITEVAR_E_INVALID_ARG, "n_scales must be in 1..%d (got %d)", kMaxScales, d->n_scales);
@@ -174,7 +174,11 @@ static bool same_spec(const PlanSpec& a, const PlanSpec& b) {
 }
 
 litevar_status size_plan(PlanSpec& sp, PlanSizes& z) {
-  if (g_last_sizing.valid && same_spec(g_last_sizing.sp, sp)) { z = g_last_sizing.z; return LITEVAR_OK; }
+  if (g_last_sizing.valid && same_spec(g_last_sizing.sp, sp)) {
+    z = g_last_sizing.z;
+    sp.group_phases = g_last_sizing.sp.group_phases; sp.patch_steps = g_last_sizing.sp.patch_steps;
+    return LITEVAR_OK;
+  }
   const litevar_status rc = size_plan_uncached(sp, z);
   sp.load_head_group(0);
   if (rc == LITEVAR_OK) { g_last_sizing.sp = sp; g_last_sizing.z = z; g_last_sizing.valid = true; }
@@ -223,7 +227,9 @@ static void add_dealt_box(StepCounter& steps, const AxisSpan& rows, const AxisSp
 }
 
 static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
-  Geom& g = sp.g;
+  HostGeom& g = sp.g;
+  const bool keep_places = (int64_t)g.n_groups * g.n_hg <= kMostPlacedGroups;
+  sp.group_phases.clear(); sp.patch_steps.clear();
   memset(&z, 0, sizeof z);
   std::vector<AxisSpan> ax;            // window mode: [key scale][patch row or column of the query scale]
   std::vector<AxisSpan> wide_rows, wide_cols;   // the same of the wide patches: [key scale][group row, patch row in it]
@@ -304,9 +310,10 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
         const int nph = (nu + g.C - 1) / g.C;
         z.n_union += (int64_t)nph * g.C;
         z.n_phase_entries += (int64_t)nph * g.NW;
+        if (keep_places) sp.group_phases.push_back(nph);
         for (int w = 0; w < g.NW; ++w) {
           const PatchExtent p = patch_extent(g, k, gy, gx, w);
-          if (p.ny == 0) continue;
+          if (p.ny == 0) { if (keep_places) sp.patch_steps.push_back(0); continue; }
           StepCounter steps{g};
           if (g.mode == kModeBand) {
             int ubase = 0;
@@ -329,10 +336,11 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
           const int ns = steps.finish();
           if (ns > 65535) return fail(LITEVAR_E_UNSUPPORTED, "a query patch needs more than 65535 steps");
           z.n_steps += ns;
+          if (keep_places) sp.patch_steps.push_back((uint16_t)ns);
         }
         for (int w = 0; wide && w < kWidePatches; ++w) {
           const PatchExtent p = wide_extent(g, k, gy, gx, w);
-          if (p.ny == 0) continue;
+          if (p.ny == 0) { if (keep_places) sp.patch_steps.push_back(0); continue; }
           StepCounter steps{g};
           if (g.mode == kModeBand) {
             int ubase = 0;
@@ -354,6 +362,7 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
           const int ns = steps.finish();
           if (ns > 65535) return fail(LITEVAR_E_UNSUPPORTED, "a query patch needs more than 65535 steps");
           z.n_wide_steps += ns;
+          if (keep_places) sp.patch_steps.push_back((uint16_t)ns);
         }
       }
     }
@@ -403,6 +412,38 @@ static BlobPtrs blob_ptrs(void* blob, const uint64_t* off) {
 
 struct Caps { int64_t n_steps, n_union, n_phase_entries, retained_pairs, n_wide_steps; uint64_t bytes; int n_groups; };
 
+// Where the patches and groups of a smaller plan go: the host counts the steps of every patch anyway, so as many as
+// fit the 4 KiB argument block travel with k_fill, which then needs no count and no scan ahead of it.  (30 tables
+// of 13 x 13 queries, 60 groups: k_count and k_scan took 16 + 6 of the 52 us that the builder's launches took.)
+// Words: first step, first wide step and first phase of every group; then the phases of all; then, two to a word,
+// for every patch the steps of its group up to it, itself included (the wide patches after the others).
+struct Places { uint32_t w[kPlaceWords]; };
+struct NoPlaces { uint32_t w[1]; };
+static_assert(sizeof(Places) + sizeof(Geom) + sizeof(BlobPtrs) + sizeof(Caps) + 16 <= 4096, "kernel argument block");
+
+// false: they don't fit
+static bool place(const PlanSpec& sp, Places& s) {
+  const int n = (int)sp.group_phases.size(), per = sp.g.NW + (sp.g.NW == 16 ? kWidePatches : 0);
+  if (n == 0 || n != sp.g.n_groups * sp.g.n_hg || 3 * n + 1 + (n * per + 1) / 2 > kPlaceWords) return false;
+  uint32_t at[2] = {0, 0}, phases = 0;
+  uint16_t* ends = (uint16_t*)(s.w + 3 * n + 1);
+  const uint16_t* steps = sp.patch_steps.data();
+  for (int G = 0; G < n; ++G) {
+    s.w[3 * G] = at[0]; s.w[3 * G + 1] = at[1]; s.w[3 * G + 2] = phases;
+    phases += (uint32_t)sp.group_phases[G];
+    uint32_t in[2] = {0, 0};
+    for (int w = 0; w < per; ++w) {
+      uint32_t& sum = in[w >= sp.g.NW];
+      sum += *steps++;
+      if (sum > 65535) return false;
+      *ends++ = (uint16_t)sum;
+    }
+    at[0] += in[0]; at[1] += in[1];
+  }
+  s.w[3 * n] = phases;
+  return true;
+}
+
 // K1: the radius tables rad[hg][k][j] (-1: dense part), in window mode the window tables
 // win[hg][k][j][c] = inclusive [lo, hi] ((-1,-1) where undefined), and the head map.  Every other
 // builder kernel reads these tables and never the radii of the descriptor.
@@ -417,13 +458,15 @@ struct TablesArg {
   uint8_t head_group[kMaxHeads];
   int16_t rad[kTableRadii];                        // [hg - hg0][k (k + 1) / 2 + j]
 };
-static_assert(sizeof(TablesArg) + 3 * sizeof(void*) <= 4096, "kernel argument block");
+static_assert(sizeof(TablesArg) + 4 * sizeof(void*) <= 4096, "kernel argument block");
 
 // grid (entries of a head group's window table / 256, head groups of the launch)
-__global__ __launch_bounds__(256) void k_tables(TablesArg a, int16_t* win, int16_t* rad, int32_t* head_map) {
+__global__ __launch_bounds__(256) void k_tables(TablesArg a, int16_t* win, int16_t* rad, int32_t* head_map, Header* hdr) {
   const int idx = blockIdx.x * 256 + threadIdx.x, hg = a.hg0 + blockIdx.y;
-  if (blockIdx.x == 0 && blockIdx.y == 0 && a.n_heads >= 0)
+  if (blockIdx.x == 0 && blockIdx.y == 0 && a.n_heads >= 0) {
     head_map[threadIdx.x] = (int)threadIdx.x < a.n_heads ? a.head_group[threadIdx.x] : 0;
+    if (threadIdx.x == 0) hdr->error = kErrNone;       // (k_fill without a count ahead of it marks what it finds wrong)
+  }
   const int16_t* r = a.rad + blockIdx.y * (a.K * (a.K + 1) / 2);
   if (idx < a.K * a.K) {
     const int k = idx / a.K, j = idx - k * a.K;
@@ -648,88 +691,97 @@ __device__ inline GroupTables group_tables(const Geom& g, const BlobPtrs& p, int
   return t;
 }
 
+__device__ inline int sum_of_lanes(int v) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d);
+  return v;
+}
+
+// a patch's descriptor without what its walk and its place in the plan say
+__device__ inline WaveDesc patch_desc(const Geom& g, int k, const PatchExtent& pe) {
+  WaveDesc wd;
+  int q_base, sk; uint32_t valid;
+  patch_queries(g, k, pe, q_base, sk, valid);
+  wd.step_begin = 0; wd.n_steps = 0;
+  wd.q_base = q_base;
+  wd.sk = (int16_t)sk; wd.ny = (int16_t)pe.ny; wd.nx = (int16_t)pe.nx; wd.kq = (int16_t)k;
+  wd.pairs = 0; wd.valid = valid; wd.first_ends = 0;
+  return wd;
+}
+__device__ inline WaveDesc wide_desc(const Geom& g, int k, const PatchExtent& pe) {
+  WaveDesc wd;
+  const int n = pe.ny * pe.nx;
+  wd.step_begin = 0; wd.n_steps = 0;
+  wd.q_base = g.off[k] - g.q0 + (g.mode == kModeBand ? pe.y0 : pe.y0 * g.s[k] + pe.x0);
+  wd.sk = (int16_t)(g.mode == kModeBand ? 0 : g.s[k]); wd.ny = (int16_t)pe.ny; wd.nx = (int16_t)pe.nx; wd.kq = (int16_t)k;
+  wd.pairs = pe.nx ? (65536 + pe.nx - 1) / pe.nx : 0;
+  wd.valid = n >= 32 ? 0xffffffffu : (1u << n) - 1u; wd.first_ends = 0;
+  return wd;
+}
+
+// a group's descriptor without its place in the plan, by one wave
+__device__ GroupDesc group_desc(const Geom& g, const GroupTables& t, int k, int gy, int gx, int lane) {
+  const GroupExtent e = group_extent(g, k, gy, gx);
+  GroupDesc gd;
+  int ident = 0;                                        // leading union entries whose token equals their position
+  if (g.mode == kModeBand) {
+    gd.n_union = band_union_keys(g, t.rad, e);
+    const int nk = g.s[k] * g.s[k];
+    for (int pt = 0; pt < band_parts(k); ++pt) {
+      const BandPart b = band_part(g, t.rad, k, pt);
+      const int glo = band_interval(b, nk, e.qy0).lo, ghi = band_interval(b, nk, e.qy1).hi;
+      if (b.tok0 + glo != ident) break;
+      ident += ghi - glo + 1;
+      if (ghi != b.cols - 1) break;
+    }
+  } else {
+    Box mine = {0, -1, 0, -1};
+    if (lane <= k) mine = window_box(t.win, k, lane, e.qy0, e.qy1, e.qx0, e.qx1);
+    int n = (mine.yhi - mine.ylo + 1) * (mine.xhi - mine.xlo + 1);
+    gd.n_union = sum_of_lanes(n);
+    // whole key scales from scale 0 on, then the first rows of the next box if it starts
+    // at the scale's origin
+    for (int j = 0; j <= k; ++j) {
+      const Box b = {lane_value(mine.ylo, j), lane_value(mine.yhi, j), lane_value(mine.xlo, j), lane_value(mine.xhi, j)};
+      const int gw = b.xhi - b.xlo + 1, rows = b.yhi - b.ylo + 1;
+      if (b.ylo != 0 || b.xlo != 0 || g.off[j] != ident) break;
+      if (gw != g.s[j]) { ident += gw; break; }
+      ident += rows * gw;
+      if (rows != g.s[j]) break;
+    }
+  }
+  gd.union_base = 0;
+  gd.n_phases = (gd.n_union + g.C - 1) / g.C;
+  gd.k = k; gd.gy = gy; gd.gx = gx; gd.phase_base = 0;
+  gd.ident = ident;
+  return gd;
+}
+
 // K2a: one wave per (group, patch): number of steps and kept pairs; patch 0 also
 // sizes the group's union list.  Waves from n_waves on: the wide patches.
 __global__ __launch_bounds__(64) void k_count(Geom g, BlobPtrs p, int n_waves) {
   const int idx = blockIdx.x, lane = threadIdx.x;
-  if (idx >= n_waves) {
-    const int G = (idx - n_waves) / kWidePatches, w = (idx - n_waves) % kWidePatches;
-    const GroupTables t = group_tables(g, p, G);
-    int k, gy, gx;
-    group_coords(g, t.grp, k, gy, gx);
-    const PatchExtent pe = wide_extent(g, k, gy, gx, w);
-    WaveCountSink sink;
-    const int ns = wave_walk_patch<true>(g, t.win, t.rad, group_extent(g, k, gy, gx), pe, sink, lane);
-    if (lane == 0) {
-      WaveDesc wd;
-      const int n = pe.ny * pe.nx;
-      wd.step_begin = 0; wd.n_steps = ns;
-      wd.q_base = g.off[k] - g.q0 + (g.mode == kModeBand ? pe.y0 : pe.y0 * g.s[k] + pe.x0);
-      wd.sk = (int16_t)(g.mode == kModeBand ? 0 : g.s[k]); wd.ny = (int16_t)pe.ny; wd.nx = (int16_t)pe.nx; wd.kq = (int16_t)k;
-      wd.pairs = pe.nx ? (65536 + pe.nx - 1) / pe.nx : 0;
-      wd.valid = n >= 32 ? 0xffffffffu : (1u << n) - 1u; wd.first_ends = 0;
-      p.waves[idx] = wd;
-    }
-    return;
-  }
-  const int G = idx / g.NW, w = idx % g.NW;
+  const bool wide = idx >= n_waves;
+  const int G = wide ? (idx - n_waves) / kWidePatches : idx / g.NW, w = wide ? (idx - n_waves) % kWidePatches : idx % g.NW;
   const GroupTables t = group_tables(g, p, G);
   int k, gy, gx;
   group_coords(g, t.grp, k, gy, gx);
   const GroupExtent e = group_extent(g, k, gy, gx);
-  const PatchExtent pe = patch_extent(g, k, gy, gx, w);
   WaveCountSink sink;
-  const int ns = wave_walk_patch<false>(g, t.win, t.rad, e, pe, sink, lane);
-  int pairs = sink.pairs;
-#pragma unroll
-  for (int d = 32; d > 0; d >>= 1) pairs += __shfl_xor(pairs, d);
-  if (lane == 0) {
-    WaveDesc wd;
-    int q_base, sk; uint32_t valid;
-    patch_queries(g, k, pe, q_base, sk, valid);
-    wd.step_begin = 0; wd.n_steps = ns;
-    wd.q_base = q_base;
-    wd.sk = (int16_t)sk; wd.ny = (int16_t)pe.ny; wd.nx = (int16_t)pe.nx; wd.kq = (int16_t)k;
-    wd.pairs = pairs; wd.valid = valid; wd.first_ends = 0;
-    p.waves[idx] = wd;
+  if (wide) {
+    const PatchExtent pe = wide_extent(g, k, gy, gx, w);
+    WaveDesc wd = wide_desc(g, k, pe);
+    wd.n_steps = wave_walk_patch<true>(g, t.win, t.rad, e, pe, sink, lane);
+    if (lane == 0) p.waves[idx] = wd;
+    return;
   }
+  const PatchExtent pe = patch_extent(g, k, gy, gx, w);
+  WaveDesc wd = patch_desc(g, k, pe);
+  wd.n_steps = wave_walk_patch<false>(g, t.win, t.rad, e, pe, sink, lane);
+  wd.pairs = sum_of_lanes(sink.pairs);
+  if (lane == 0) p.waves[idx] = wd;
   if (w == 0) {
-    // the group's descriptor; in window mode lane j holds the group's box in key scale j, so
-    // that the table is read once, by all lanes at the same time
-    GroupDesc gd;
-    int ident = 0;                                      // leading union entries whose token equals their position
-    if (g.mode == kModeBand) {
-      gd.n_union = band_union_keys(g, t.rad, e);
-      const int nk = g.s[k] * g.s[k];
-      for (int pt = 0; pt < band_parts(k); ++pt) {
-        const BandPart b = band_part(g, t.rad, k, pt);
-        const int glo = band_interval(b, nk, e.qy0).lo, ghi = band_interval(b, nk, e.qy1).hi;
-        if (b.tok0 + glo != ident) break;
-        ident += ghi - glo + 1;
-        if (ghi != b.cols - 1) break;
-      }
-    } else {
-      Box mine = {0, -1, 0, -1};
-      if (lane <= k) mine = window_box(t.win, k, lane, e.qy0, e.qy1, e.qx0, e.qx1);
-      int n = (mine.yhi - mine.ylo + 1) * (mine.xhi - mine.xlo + 1);
-#pragma unroll
-      for (int d = 32; d > 0; d >>= 1) n += __shfl_xor(n, d);
-      gd.n_union = n;
-      // whole key scales from scale 0 on, then the first rows of the next box if it starts
-      // at the scale's origin
-      for (int j = 0; j <= k; ++j) {
-        const Box b = {lane_value(mine.ylo, j), lane_value(mine.yhi, j), lane_value(mine.xlo, j), lane_value(mine.xhi, j)};
-        const int gw = b.xhi - b.xlo + 1, rows = b.yhi - b.ylo + 1;
-        if (b.ylo != 0 || b.xlo != 0 || g.off[j] != ident) break;
-        if (gw != g.s[j]) { ident += gw; break; }
-        ident += rows * gw;
-        if (rows != g.s[j]) break;
-      }
-    }
-    gd.union_base = 0;
-    gd.n_phases = (gd.n_union + g.C - 1) / g.C;
-    gd.k = k; gd.gy = gy; gd.gx = gx; gd.phase_base = 0;
-    gd.ident = ident;
+    const GroupDesc gd = group_desc(g, t, k, gy, gx, lane);
     if (lane == 0) p.groups[G] = gd;
   }
 }
@@ -800,9 +852,7 @@ __global__ __launch_bounds__(1024) void k_scan(Geom g, BlobPtrs p, Caps caps, in
 }
 
 // the group's key list (token indices), padded to whole chunks with its last key; one wave
-__device__ void fill_union(const Geom& g, const BlobPtrs& p, const Caps& caps, int G) {
-  const GroupTables t = group_tables(g, p, G);
-  const GroupDesc gd = p.groups[G];
+__device__ void fill_union(const Geom& g, const BlobPtrs& p, const Caps& caps, const GroupTables& t, const GroupDesc& gd) {
   const GroupExtent e = group_extent(g, gd.k, gd.gy, gd.gx);
   int32_t* out = p.union_tok + gd.union_base;
   int32_t* wide = g.NW == 16 ? out + caps.n_union : nullptr;   // the wide patches' list, some of whose boxes are dealt
@@ -862,12 +912,14 @@ struct FillSink {
   uint2* addr; uint64_t* mask; int32_t* toks; int32_t* phase_end;
   StepBuf* buf;
   int R, logC, lane;
+  int n_steps, n_phases;               // what the plan has room for (the counts agree with the walk, or nothing beyond is written)
   int chunk = 0;                       // chunk of the last closed step: phase_end is written up to it
+  int pairs = 0;                       // this lane's share of the kept pairs
   int end0 = 0, end2 = 0;              // steps that end in chunk 0, in chunks 0 to 2
   // steps close in the order of their chunks, so the cumulative counts of the chunks that a step
   // skips are final when it closes: no counter is read back
   __device__ void fill_ends(int from, int to, int steps) {
-    for (int i = from + lane; i < to; i += 64) phase_end[i] = steps;
+    for (int i = from + lane; i < min(to, n_phases); i += 64) phase_end[i] = steps;
   }
   __device__ static uint32_t k_off(uint32_t slot, int g4) {
     return slot * kRingRowBytes + (((2u * g4) ^ ring_swizzle(slot)) << 4);
@@ -881,9 +933,11 @@ struct FillSink {
     return slot * kRingRowBytes + 8u * half + 16u * ((b ^ sw) & 1u) + ((sw >> 1) << 5);
   }
   __device__ void keys(int, int idx, int upos, int t, unsigned qmask, bool take) {
+    if (take) pairs += __builtin_popcount(qmask);
     if (take) { buf->slot[idx] = (uint32_t)(upos % R); buf->tok[idx] = t; buf->qmask[idx] = qmask; }
   }
   __device__ void close(int step, int n_keys, int last_upos) {
+    if (step >= n_steps) return;
     __syncthreads();                                   // (one wave per block) deposits are visible
     const int n = lane & 15, g4 = lane >> 4;
     const uint32_t pad = (uint32_t)(last_upos % R);    // padding keys read the step's last row
@@ -933,51 +987,111 @@ struct FillSink {
 // K2c: one wave per (group, patch) and (group, wide patch): steps (ring addresses, lane masks, tokens) and the
 // cumulative number of steps that are runnable after each phase; then one wave per group: its
 // key list (in the same launch: neither needs the other).  Bound: the serial walk of one wave.
-// 480 patches of 30 head groups: 27 us, 35 us as two launches with counters that were read back.
-__global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int n_waves) {
+// 480 patches of 30 head groups: 27 us, 35 us as two launches with counters that were read back; 30 us with the
+// places in its arguments, where k_count, k_scan and it took 50 and the launches' gaps.
+// With Places the places come with the arguments, and the descriptors and the header are written here; a patch whose
+// walk ends at another count than the host's marks the header, as k_scan does.
+template <class PlacesArg>
+__global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int n_waves, PlacesArg s) {
+  constexpr bool PLACED = sizeof(PlacesArg) > sizeof(NoPlaces);
   __shared__ StepBuf buf;
-  const int idx = blockIdx.x, lane = threadIdx.x;
-  if (p.hdr->error) return;
+  const int lane = threadIdx.x;
+  if (!PLACED && p.hdr->error) return;
   const int n_wide = g.NW == 16 ? caps.n_groups * kWidePatches : 0;
-  if (idx >= n_waves + n_wide) { fill_union(g, p, caps, idx - n_waves - n_wide); return; }
-  if (idx >= n_waves) {
-    const int G = (idx - n_waves) / kWidePatches, w = (idx - n_waves) % kWidePatches;
-    const GroupTables t = group_tables(g, p, G);
-    const GroupDesc gd = p.groups[G];
-    const WaveDesc wd = p.waves[idx];
-    if ((int64_t)wd.step_begin + wd.n_steps > caps.n_wide_steps ||
-        (int64_t)gd.phase_base + (int64_t)gd.n_phases * g.NW > caps.n_phase_entries) return;
-    FillSink<true> sink;
-    sink.addr = (uint2*)((char*)p.step_addr + (int64_t)wd.step_begin * 64 * kWideDesc);
-    sink.mask = nullptr; sink.toks = nullptr;
-    sink.phase_end = p.phase_end + caps.n_phase_entries + gd.phase_base / 2 + (int64_t)w * gd.n_phases;
-    sink.buf = &buf; sink.R = g.R; sink.logC = g.logC; sink.lane = lane;
-    const int ns = wave_walk_patch<true>(g, t.win, t.rad, group_extent(g, gd.k, gd.gy, gd.gx),
-                                         wide_extent(g, gd.k, gd.gy, gd.gx, w), sink, lane);
-    sink.fill_ends(sink.chunk, gd.n_phases, ns);
-    if (lane == 0) p.waves[idx].first_ends = (uint32_t)sink.end0 | ((uint32_t)sink.end2 << 16);
+  const bool wide = (int)blockIdx.x >= n_waves, lists = (int)blockIdx.x >= n_waves + n_wide;
+  const int idx = lists ? blockIdx.x - n_waves - n_wide : wide ? blockIdx.x - n_waves : blockIdx.x;
+  const int per = lists ? 1 : wide ? kWidePatches : g.NW;
+  const int G = idx / per, w = idx - G * per;
+  const GroupTables t = group_tables(g, p, G);
+  GroupDesc gd;
+  if (PLACED) {
+    group_coords(g, t.grp, gd.k, gd.gy, gd.gx);
+    const int phase0 = (int)s.w[3 * G + 2];
+    gd.n_phases = (int)s.w[G + 1 < caps.n_groups ? 3 * G + 5 : 3 * caps.n_groups] - phase0;
+    gd.union_base = phase0 * g.C; gd.phase_base = phase0 * g.NW;
+  } else {
+    gd = p.groups[G];
+  }
+  if (lists) {
+    if (PLACED) {
+      GroupDesc own = group_desc(g, t, gd.k, gd.gy, gd.gx, lane);
+      if (own.n_phases != gd.n_phases) { p.hdr->error = kErrBuilder; return; }
+      own.union_base = gd.union_base; own.phase_base = gd.phase_base;
+      gd = own;
+      if (lane == 0) p.groups[G] = gd;
+      if (G == 0) {                                     // the header, but for the error that others may be marking
+        Header h;
+        memset(&h, 0, sizeof h);
+        h.magic = kMagic; h.blob_bytes = caps.bytes;
+        h.n_groups = caps.n_groups; h.n_waves = n_waves;
+        h.n_steps = caps.n_steps; h.n_union = caps.n_union; h.n_phase_entries = caps.n_phase_entries;
+        h.retained_pairs = caps.retained_pairs; h.n_wide_steps = caps.n_wide_steps;
+        constexpr int kUsed = offsetof(Header, pad) / 4, kError = offsetof(Header, error) / 4;
+#pragma unroll
+        for (int i = 0; i < kUsed; ++i)
+          if (i != kError && lane == 0) ((uint32_t*)p.hdr)[i] = ((const uint32_t*)&h)[i];
+        if (lane >= kUsed) ((uint32_t*)p.hdr)[lane] = 0;
+      }
+    }
+    fill_union(g, p, caps, t, gd);
     return;
   }
-  const int G = idx / g.NW, w = idx % g.NW;
-  const GroupTables t = group_tables(g, p, G);
-  const GroupDesc gd = p.groups[G];
-  const WaveDesc wd = p.waves[idx];
-  if ((int64_t)wd.step_begin + wd.n_steps > caps.n_steps ||
-      (int64_t)gd.phase_base + (int64_t)gd.n_phases * g.NW > caps.n_phase_entries) return;
   const GroupExtent e = group_extent(g, gd.k, gd.gy, gd.gx);
-  FillSink<false> sink;
-  sink.addr = p.step_addr + (caps.n_wide_steps * (64 * kWideDesc) / (int64_t)sizeof(uint2)) + (int64_t)wd.step_begin * 64;
-  sink.mask = p.step_mask + (int64_t)wd.step_begin * 8;
-  sink.toks = p.step_tok + (int64_t)wd.step_begin * kStepKeys;
-  sink.phase_end = p.phase_end + gd.phase_base + (int64_t)w * gd.n_phases;
-  sink.buf = &buf; sink.R = g.R; sink.logC = g.logC; sink.lane = lane;
-  const int ns = wave_walk_patch<false>(g, t.win, t.rad, e, patch_extent(g, gd.k, gd.gy, gd.gx, w), sink, lane);
-  sink.fill_ends(sink.chunk, gd.n_phases, ns);
-  if (lane == 0) p.waves[idx].first_ends = (uint32_t)sink.end0 | ((uint32_t)sink.end2 << 16);   // (a patch has at most 65535 steps)
+  const PatchExtent pe = wide ? wide_extent(g, gd.k, gd.gy, gd.gx, w) : patch_extent(g, gd.k, gd.gy, gd.gx, w);
+  WaveDesc* const out = p.waves + blockIdx.x;
+  WaveDesc wd;
+  if (PLACED) {
+    wd = wide ? wide_desc(g, gd.k, pe) : patch_desc(g, gd.k, pe);
+    const uint16_t* ends = (const uint16_t*)(s.w + 3 * caps.n_groups + 1) + G * (g.NW + (g.NW == 16 ? kWidePatches : 0)) + (wide ? g.NW : 0);
+    const int begin = w > 0 ? ends[w - 1] : 0;
+    wd.step_begin = (int)s.w[3 * G + (wide ? 1 : 0)] + begin;
+    wd.n_steps = ends[w] - begin;
+  } else {
+    wd = *out;
+  }
+  if ((int64_t)wd.step_begin + wd.n_steps > (wide ? caps.n_wide_steps : caps.n_steps) ||
+      (int64_t)gd.phase_base + (int64_t)gd.n_phases * g.NW > caps.n_phase_entries) {
+    if (PLACED) p.hdr->error = kErrBuilder;
+    return;
+  }
+  int ns, pairs = 0;
+  uint32_t first_ends;
+  auto fill = [&](auto& sink, bool is_wide) {
+    sink.buf = &buf; sink.R = g.R; sink.logC = g.logC; sink.lane = lane;
+    sink.n_steps = wd.n_steps; sink.n_phases = gd.n_phases;
+    sink.phase_end = p.phase_end + (is_wide ? caps.n_phase_entries + gd.phase_base / 2 : (int64_t)gd.phase_base) + (int64_t)w * gd.n_phases;
+  };
+  if (wide) {
+    FillSink<true> sink;
+    fill(sink, true);
+    sink.addr = (uint2*)((char*)p.step_addr + (int64_t)wd.step_begin * 64 * kWideDesc);
+    sink.mask = nullptr; sink.toks = nullptr;
+    ns = wave_walk_patch<true>(g, t.win, t.rad, e, pe, sink, lane);
+    sink.fill_ends(sink.chunk, gd.n_phases, ns);
+    first_ends = (uint32_t)sink.end0 | ((uint32_t)sink.end2 << 16);   // (a patch has at most 65535 steps)
+  } else {
+    FillSink<false> sink;
+    fill(sink, false);
+    sink.addr = p.step_addr + (caps.n_wide_steps * (64 * kWideDesc) / (int64_t)sizeof(uint2)) + (int64_t)wd.step_begin * 64;
+    sink.mask = p.step_mask + (int64_t)wd.step_begin * 8;
+    sink.toks = p.step_tok + (int64_t)wd.step_begin * kStepKeys;
+    ns = wave_walk_patch<false>(g, t.win, t.rad, e, pe, sink, lane);
+    sink.fill_ends(sink.chunk, gd.n_phases, ns);
+    first_ends = (uint32_t)sink.end0 | ((uint32_t)sink.end2 << 16);
+    if (PLACED) pairs = sum_of_lanes(sink.pairs);
+  }
+  if (PLACED) {
+    if (ns != wd.n_steps) { p.hdr->error = kErrBuilder; return; }
+    if (!wide) wd.pairs = pairs;
+    wd.first_ends = first_ends;
+    if (lane == 0) *out = wd;
+  } else if (lane == 0) {
+    out->first_ends = first_ends;
+  }
 }
 
 litevar_status build_plan(PlanSpec& sp, const PlanSizes& z, void* d_blob, hipStream_t st) {
-  Geom& g = sp.g;
+  const Geom& g = sp.g;                  // (the host's part stays here)
   const BlobPtrs p = blob_ptrs(d_blob, z.off);
   Caps caps{z.n_steps, z.n_union, z.n_phase_entries, z.retained_pairs, z.n_wide_steps, z.bytes, g.n_groups * g.n_hg};
   const int ntab = g.mode == kModeWindow ? g.K * g.K * g.smax : g.K * g.K;
@@ -992,14 +1106,19 @@ litevar_status build_plan(PlanSpec& sp, const PlanSizes& z, void* d_blob, hipStr
     for (int hg = hg0; hg < hg0 + ta.n_hg; ++hg)
       for (int k = 0; k < g.K; ++k)
         for (int j = 0; j <= k; ++j) ta.rad[at++] = sp.rad_all[((size_t)hg * g.K + k) * g.K + j];
-    hipLaunchKernelGGL(k_tables, dim3((ntab + 255) / 256, ta.n_hg), dim3(256), 0, st, ta, p.win, p.rad, p.head_map);
+    hipLaunchKernelGGL(k_tables, dim3((ntab + 255) / 256, ta.n_hg), dim3(256), 0, st, ta, p.win, p.rad, p.head_map, p.hdr);
   }
   const int n_all = g.n_groups * g.n_hg;
   const int nw = n_all * g.NW;
   const int n_wide = g.NW == 16 ? n_all * kWidePatches : 0;
-  hipLaunchKernelGGL(k_count, dim3(nw + n_wide), dim3(64), 0, st, g, p, nw);
-  hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, st, g, p, caps, nw);
-  hipLaunchKernelGGL(k_fill, dim3(nw + n_wide + n_all), dim3(64), 0, st, g, p, caps, nw);
+  Places s;
+  if (place(sp, s)) {
+    hipLaunchKernelGGL(k_fill<Places>, dim3(nw + n_wide + n_all), dim3(64), 0, st, g, p, caps, nw, s);
+  } else {
+    hipLaunchKernelGGL(k_count, dim3(nw + n_wide), dim3(64), 0, st, g, p, nw);
+    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, st, g, p, caps, nw);
+    hipLaunchKernelGGL(k_fill<NoPlaces>, dim3(nw + n_wide + n_all), dim3(64), 0, st, g, p, caps, nw, NoPlaces{});
+  }
   return hip_check(hipGetLastError(), "plan builder launch");
 }
 

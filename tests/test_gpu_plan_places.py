@@ -1,0 +1,34 @@
+"""Plans around the size up to which the places of patches and groups travel with the builder's launch: every head's
+work-list against the oracle's mask, for the largest plan that fits and the smallest that is counted on the device."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("waves,side,tables", [(4, 13, 38), (4, 13, 39), (8, 13, 54), (8, 13, 55), (16, 16, 51), (16, 16, 52),
+                                               (16, 1, 1), (4, 1, 153), (4, 1, 154)])
+def test_places(waves, side, tables):
+    import oracle
+    import paper_2411_17178_amd as lv
+    scales = (1, 3, 7, side)
+    K = len(scales)
+    # distinct tables (equal ones would share a work-list): the number of the table in the query scale's row
+    rad = [[[-1] * K for _ in range(K)] for _ in range(tables)]
+    for h in range(tables):
+        rad[h][3] = [-1 + h % 2, h // 2 % 3, h // 6 % 6, h // 36]
+    print(f"  waves={waves} side={side} tables={tables}", flush=True)
+    plan = lv.litevar_mask_build(scales, 1, rad, 0, (3, 4), waves_per_group=waves)
+    assert plan.n_head_groups == tables
+    lv.litevar_plan_check(plan)
+    total = 0
+    for h in range(tables):
+        mask, _ = lv.litevar_mask_export_dense(plan, head=h)
+        mask = mask.cpu().numpy()
+        if h in (0, 1, tables // 2, tables - 1):
+            assert (mask == oracle.mask_dense(scales, rad[h], 0)[-side * side:]).all()
+        assert int(mask.sum()) == int(plan.retained_pairs_of_group[plan.head_group[h]])
+        total += int(mask.sum())
+    header = plan.blob[:256].cpu().numpy().view(np.int64)
+    assert total == int(plan.retained_pairs) == int(header[6]) and int(header[3]) == plan.n_steps
