@@ -19,9 +19,11 @@
 // Bound: a step is 64 MFMAs of 32 cycles (2048 cycles of a SIMD's matrix pipe) against 16 KB of
 // gathered rows; four waves per patch, because the accuracy workloads have few patches (57 per
 // (batch, head) at 680 tokens) and the longest one would otherwise be a chain of eleven steps.
-// 680 tokens, 32 (batch, head) pairs, radius 2: 30.3 us a call (one wave per patch with scalar dot
+// 680 tokens, 32 (batch, head) pairs, radius 2: 29.5 us a call (one wave per patch with scalar dot
 // products and a shuffle per key: 233 us); the matrix pipe's share is 8 us, the rest is the chain
-// descriptor -> tokens -> rows -> MFMAs of two rounds of workgroups.
+// descriptor -> tokens -> rows -> MFMAs of two rounds of workgroups.  (30.1 with the patch's words in three round
+// trips and the queries ahead of the first tokens; 2 pairs at radius 4 11.2 -> 11.05.  K rows requested a step
+// ahead take 136 registers instead of 99: 31.6.  Steps dealt from another wave in every patch: no change.)
 #include "attn_bf16_common.h"
 
 namespace lv {
@@ -37,9 +39,15 @@ template <int W>
 __global__ __launch_bounds__(W * 64) void k_attn_f32(AttnArgs a, int n_waves) {
   int me, bh, wv, b, h;
   if (!xcd_item(a, n_waves, me, bh, wv)) return;
-  if (!plan_usable(a.hdr)) return;
   divmod_by((uint32_t)bh, (uint32_t)a.H, a.H_magic, b, h);
-  const WaveDesc wd = a.waves[wv + (a.head_map ? a.head_map[h] * n_waves : 0)];   // the head group's patches
+  const int head_group = a.head_map ? ((const_i32_ptr)a.head_map)[h] : 0;   // (in the header's round trip)
+  if (!plan_usable(a.hdr)) return;
+  // the patch's words in one scalar load (left alone they come in three round trips, the first for ny)
+  const const_u64_ptr wp = (const_u64_ptr)(a.waves + (wv + head_group * n_waves));
+  uint64_t w0 = wp[0], w1 = wp[1], w2 = wp[2], w3 = wp[3];
+  asm volatile("" : "+s"(w0), "+s"(w1), "+s"(w2), "+s"(w3));
+  const uint64_t words[4] = {w0, w1, w2, w3};
+  const WaveDesc wd = __builtin_bit_cast(WaveDesc, words);
   if (wd.ny == 0) return;
   const bool shared = a.cfg_share && a.cfg_share[h * a.n_scales + wd.kq];
   if (shared && b >= a.B / 2) return;
@@ -56,10 +64,7 @@ __global__ __launch_bounds__(W * 64) void k_attn_f32(AttnArgs a, int n_waves) {
   f32x4 qv[4], O[4];
   const float* Q = (const float*)a.q + b * a.qs[0] + h * a.qs[1];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    qv[j] = f32x4{0.f, 0.f, 0.f, 0.f}; O[j] = qv[j];
-    if (qrow >= 0) qv[j] = *(const f32x4*)(Q + qrow * a.qs[2] + 16 * j + 4 * g4);
-  }
+  for (int j = 0; j < 4; ++j) { qv[j] = f32x4{0.f, 0.f, 0.f, 0.f}; O[j] = qv[j]; }
   float m = kF32Floor, l = 0.f;          // softmax reference of query n (the same in its four lanes), this lane's row sum
 
   const int64_t S0 = wd.step_begin;
@@ -71,6 +76,10 @@ __global__ __launch_bounds__(W * 64) void k_attn_f32(AttnArgs a, int n_waves) {
     return Tokens{{t[n], t[16 + n]}, {*(const int4*)(t + 4 * g4), *(const int4*)(t + 16 + 4 * g4)}};
   };
   Tokens tok = load_tokens(wave);
+  __builtin_amdgcn_sched_barrier(0);         // (the queries behind the tokens, for which the rows wait)
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (qrow >= 0) qv[j] = *(const f32x4*)(Q + qrow * a.qs[2] + 16 * j + 4 * g4);
   for (int s = wave; s < n_steps; s += W) {
     // (padding keys carry token -1; they read the row of the step's first key, which every step has)
     const int first = __builtin_amdgcn_readfirstlane(tok.k[0]);
