@@ -16,7 +16,7 @@
 //
 // Why not the windowed kernels: their steps fetch descriptors and masks; here 61 vector, 8 matrix and 12 LDS instructions
 // serve 32 keys x 32 queries, with nothing to fetch.  At 2240 tokens and 288 (batch, head) pairs the vector issue is
-// busy 67 % of the cycles and the matrix pipe 50 % (with the maximum of the scores, transfers through registers and no
+// busy 67 % of the cycles and the matrix pipe 48 % (with the maximum of the scores, transfers through registers and no
 // products ahead: 63 and 44 %, 297 us; now 275 us, 875 TFLOP/s of kept pairs), but the clock falls to 1.7 GHz under it
 // (1.8 before): what bounds it is the power that the instructions take, more than their number per cycle.  127 registers let
 // four waves share a SIMD.  One chain of row sums: 280 us.  Not faster in the kernel before: 64 queries per wave
