@@ -162,10 +162,10 @@ litevar_status litevar_qkv8_dequantize(const int8_t* d_codes, const float* d_sca
 // a (batch, head) stream few rows more than once (KV-cache steps: one group; the 680-token
 // sequence); once they stream a quarter more rows than the three tensors hold (q_len + 2 kv_len
 // per (batch, head)), a single dequantising pass over the tensors is cheaper (measured: both
-// cost 35-40 ps per row; 2240 tokens: 9088 rows streamed against 6720, 276 against 262 us).
+// cost 35-40 ps per row; 2240 tokens: 9088 rows streamed against 6720, 239 against 237 us).
 // Plans that keep every pair are weighed like the others, although the copy's attention then runs on the
-// dense kernel.  480 pairs, in-kernel / copy: 256 x 680 43 / 60 us, 2240 tokens (288 pairs) 539 / 349, both as the
-// rule has it, but 680 x 680 149 / 99.
+// dense kernel.  480 pairs, in-kernel / copy: 256 x 680 43 / 62 us, 2240 tokens (288 pairs) 483 / 333, both as the
+// rule has it, but 680 x 680 138 / 94.
 static bool fused(const litevar_plan* plan) {
   if (plan->waves_per_group != 16) return false;
   const int64_t streamed = plan->n_union_keys / (plan->n_head_groups > 0 ? plan->n_head_groups : 1);
