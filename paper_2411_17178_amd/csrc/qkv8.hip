@@ -43,7 +43,8 @@ constexpr int kXor1 = 0xb1, kXor2 = 0x4e, kHalfMirror = 0x141;   // quad_perm [1
 // overflows or loses bits, for which the scale is kept between 2^-100 and 2^100: |d / s| <= 128, and a
 // remainder that underflows belongs to a quotient that rounds to code 0 either way.  Other rows divide.
 // 122 880 rows of bf16: 8.9 us with divisions, 7.6 so (3.2 TB/s); three such calls and the attention on their codes:
-// 61 / 58 us.  What is left is one 16-byte load in flight per lane and short blocks.
+// 61 / 58 us.  Two or four rows per thread, requested together, are slower: three calls and the attention 56.7 / 58.3 /
+// 59.8 us with one, two and four.
 template <typename T>
 __global__ __launch_bounds__(256) void k_quantize_rows(const T* __restrict__ x, int64_t rows, int64_t row_stride,
                                                        int8_t* __restrict__ xq, float2* __restrict__ sz) {
