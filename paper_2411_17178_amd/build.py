@@ -49,9 +49,10 @@ def build(verbose: bool = False, debug_bounds: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         jobs = [ex.submit(_run, [hipcc] + flags + ["-c", "-o", o, os.path.join(CSRC, s)], verbose)
                 for s, o in zip(SOURCES, objs)]
-        if not debug_bounds:
+        include = sysconfig.get_paths()["include"]
+        if not debug_bounds and os.path.exists(os.path.join(include, "Python.h")):    # (without it the binding takes its general path)
             jobs.append(ex.submit(_run, [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall",
-                                         "-I" + sysconfig.get_paths()["include"], "-o", TABLES,
+                                         "-I" + include, "-o", TABLES,
                                          os.path.join(CSRC, "py_tables.cpp")], verbose))
         for j in jobs:
             j.result()

@@ -45,5 +45,7 @@ def test_ragged_tables_are_refused(rows):
 
 def test_values_beyond_the_type():
     for big in (2 ** 31, -2 ** 31 - 1, 2 ** 80):
-        assert binding._radius_tables([[[big]]], 1) in (None,)
+        assert binding._radius_tables([[[big]]], 1) is None
+    if binding._tables_module is False:
+        pytest.skip("built without the interpreter's headers")
     assert bytes(binding._radius_tables([[[2 ** 31 - 1]], [[-2 ** 31]]], 1)) == np.array([2 ** 31 - 1, -2 ** 31], np.int32).tobytes()
