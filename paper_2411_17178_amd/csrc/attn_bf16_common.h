@@ -107,6 +107,101 @@ __device__ inline int checked_index([[maybe_unused]] Header* hdr, int value, [[m
   return value;
 }
 
+// (counted anew, where threadIdx.x would hold a register from the kernel's start)
+__device__ inline int lane_of_wave() { return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
+
+// One query row of pair (b, h), by all 64 lanes of a wave, for results that the matrix products cannot give: 32 keys at a
+// time, lane i and lane i + 32 the two halves of key i's score, then lane d head dimension d of the output.  Nothing
+// is formed from a key that the query does not keep, and the softmax reference is the largest score itself, so that
+// any scores that fp32 holds give their probabilities.  mine: the lane's dimension is stored; once none of these is finite
+// any more, the rest of the keys is left.
+// keys.key(block, i, tok): the query keeps key i of block `block`, which is token `tok`; keys.n_blocks blocks.
+// Bound: about 400 instructions and two trips to memory for 32 keys.  2240 tokens, 288 pairs, a bad V element in a token
+// that all queries keep, K all NaN, a bad V element in a late token: 1.3 / 0.9 / 3.2 ms a call (with a row per lane, key
+// by key and to the end: 10.8 / 12.9 / 2.9).
+template <bool Q8, class Keys>
+__device__ inline void attend_row(const AttnArgs& a, float c, int b, int h, int qrow, bool shared, bool mine,
+                                  const Keys keys) {
+  constexpr int kElem = Q8 ? 1 : 2;
+  const int lane = lane_of_wave(), i = lane & 31, first_dim = lane & 32;
+  const int64_t kv_at = (b * a.ks[0] + h * a.ks[1]) * kElem, pair = (int64_t)b * a.H + h;
+  const unsigned char *K = (const unsigned char*)a.k + kv_at, *V = (const unsigned char*)a.v + kv_at;
+  const unsigned row_bytes = (unsigned)a.ks[2] * kElem;    // (a (batch, head) slab spans < 2 GiB)
+  [[maybe_unused]] const int64_t first_row = Q8 ? pair * (a.ks[1] / a.ks[2]) : 0;
+  qrow = checked_index(a.hdr, qrow, a.q_len);
+  // 32 dimensions of a row: bf16, or 8-bit codes with the row's (scale, zero point) as the kernels convert them
+  auto load_half = [&](const unsigned char* row, [[maybe_unused]] const float2* sz, float (&x)[32]) {
+    const u32x4* p = (const u32x4*)(row + first_dim * kElem);
+    u32x4 raw[2 * kElem];
+#pragma unroll
+    for (int t = 0; t < 2 * kElem; ++t) raw[t] = p[t];
+    float2 f = make_float2(0.f, 0.f);
+    if constexpr (Q8) f = *sz;
+#pragma unroll
+    for (int e = 0; e < 32; ++e) {
+      if constexpr (Q8) x[e] = (float)(__bf16)fmaf(f.x, (float)(int8_t)((raw[e >> 4][(e >> 2) & 3] >> (8 * (e & 3))) & 0xffu), f.y);
+      else x[e] = __uint_as_float(e & 1 ? raw[e >> 3][(e >> 1) & 3] & 0xffff0000u : raw[e >> 3][(e >> 1) & 3] << 16);
+    }
+  };
+  float q[32];
+  load_half((const unsigned char*)a.q + (b * a.qs[0] + h * a.qs[1] + qrow * a.qs[2]) * kElem,
+            Q8 ? a.q_sz + pair * a.q_len + qrow : nullptr, q);
+  float m = -INFINITY, l = 0.f, o = 0.f;
+  bool nan = false;                            // a kept key's score is
+  for (int block = 0; block < keys.n_blocks; ++block) {
+    int tok = 0;
+    const bool keep = keys.key(block, i, tok);
+    const unsigned kept = (unsigned)__builtin_amdgcn_ballot_w64(keep);
+    if (kept == 0) continue;
+    tok = checked_index(a.hdr, keep ? tok : __builtin_amdgcn_readlane(tok, __builtin_ctz(kept)), a.kv_len);
+    float dot = 0.f, x[32];
+    load_half(K + (unsigned)tok * row_bytes, Q8 ? a.k_sz + first_row + tok : nullptr, x);
+#pragma unroll
+    for (int e = 0; e < 32; ++e) dot = fmaf(q[e], x[e], dot);
+    dot += __shfl_xor(dot, 32);
+    unsigned bits = __float_as_uint(dot);
+    asm volatile("" : "+v"(bits));             // (see not_finite)
+    if ((nan = __builtin_amdgcn_ballot_w64(keep && (bits & 0x7fffffffu) > 0x7f800000u) != 0)) break;
+    float mx = keep ? dot : -INFINITY;
+#pragma unroll
+    for (int d = 16; d > 0; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d));
+    const float m_new = fmaxf(m, mx);
+    const float p = keep ? __builtin_amdgcn_exp2f((dot - m_new) * c) : 0.f;
+    const float alpha = m > -INFINITY ? __builtin_amdgcn_exp2f((m - m_new) * c) : 0.f;
+    float sum = p;
+#pragma unroll
+    for (int d = 16; d > 0; d >>= 1) sum += __shfl_xor(sum, d);
+    if (m_new == -INFINITY) continue;          // (only scores of -inf so far)
+    l = fmaf(l, alpha, sum); m = m_new; o *= alpha;
+#pragma unroll
+    for (int j0 = 0; j0 < 32; j0 += 16) {      // (sixteen rows of V in flight)
+      float v[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int t = __builtin_amdgcn_readlane(tok, j0 + j);
+        const unsigned char* row = V + (unsigned)t * row_bytes;      // (in scalar registers)
+        if constexpr (Q8) {
+          const float2 f = a.v_sz[first_row + t];
+          v[j] = (float)(__bf16)fmaf(f.x, (float)((const int8_t*)row)[lane], f.y);
+        } else {
+          v[j] = (float)((const __bf16*)row)[lane];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const float pj = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(p), j0 + j));
+        o = (kept >> (j0 + j)) & 1u ? fmaf(pj, v[j], o) : o;
+      }
+    }
+    if (not_finite(l) || __builtin_amdgcn_ballot_w64(mine && !not_finite(o)) == 0) break;
+  }
+  if (!mine) return;
+  __bf16* op = (__bf16*)a.o + b * a.os[0] + h * a.os[1] + qrow * a.os[2] + lane;
+  const __bf16 r = nan ? __builtin_bit_cast(__bf16, (unsigned short)0x7fc0) : (__bf16)(o * (1.f / l));
+  *op = r;
+  if (shared) op[(a.B / 2) * a.os[0]] = r;
+}
+
 // x = q n + r for a divisor n whose magic = floor(2^32 / n) came with the kernel arguments
 // (n = 1: magic = 2^32 - 1): the estimate floor(x magic / 2^32) is the quotient or one below it
 // for every x < 2^32, so one correction step makes it exact.

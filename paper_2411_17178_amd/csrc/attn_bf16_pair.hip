@@ -147,71 +147,29 @@ struct PatchState {       // one query patch of a wave
                           // before m moves: kFloor while m is unset
 };
 
-// eight values of a row, bf16 or 8-bit codes with the row's (scale, zero point)
-template <bool Q8> __device__ inline void load_row8(const void* base, int64_t at, const float2* sz, float (&x)[8]) {
-  if constexpr (Q8) {
-    const u32x2 r = *(const u32x2*)((const int8_t*)base + at);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = (float)(__bf16)fmaf(sz->x, (float)(int8_t)((r[e >> 2] >> (8 * (e & 3))) & 0xffu), sz->y);
-  } else {
-    const bf16x8 r = as_bf16x8(*(const uint4*)((const __bf16*)base + at));
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = (float)r[e];
+// The keys of one query for attend_row, in the steps of the patch of 16 that holds the query's row, one of the group's
+// sixteen from `patches` on
+struct StepKeys {
+  const AttnArgs& a;
+  int64_t step0; int n_blocks, column;
+  __device__ StepKeys(const AttnArgs& args, const WaveDesc* patches, int qrow) : a(args), step0(0), n_blocks(0), column(0) {
+    const WaveDesc wd = patches[lane_of_wave() & (kGroupPatches - 1)];
+    const int d = qrow - wd.q_base, dy = d / max((int)wd.sk, 1), dx = d - dy * wd.sk;
+    const bool holds = d >= 0 && dy < kPatch && dx < kPatch && ((wd.valid >> (kPatch * dy + dx)) & 1u);
+    const uint64_t who = __builtin_amdgcn_ballot_w64(holds);
+    if (who == 0) return;
+    const int at = __builtin_ctzll(who);
+    step0 = __builtin_amdgcn_readlane(wd.step_begin, at);
+    n_blocks = __builtin_amdgcn_readlane(wd.n_steps, at);
+    column = __builtin_amdgcn_readlane(kPatch * dy + dx, at);
   }
-}
-
-// Query row `qrow` (none: -1) of pair (b, h), key by key over the steps of the patch of 16 that holds it, one of the
-// group's sixteen from `patch0` on: head dimensions 32 dt + 8 j + 4 h .. + 3 of lane h of the query's two.  Only for results that
-// are not finite; every lane walks its own list.
-template <bool Q8>
-__device__ inline void attend_key_by_key(const AttnArgs& a, float c, int b, int h, int patch0, int qrow,
-                                                            int hi, unsigned (&out)[2][8]) {
-  int found = -1, n16 = 0;
-  for (int w = 0; w < kGroupPatches; ++w) {
-    const WaveDesc wd = a.waves[patch0 + w];
-    const int d = qrow - wd.q_base;
-    if (qrow < 0 || d < 0 || wd.sk < 1) continue;
-    const int dy = d / wd.sk, dx = d - dy * wd.sk;
-    if (dy < kPatch && dx < kPatch && ((wd.valid >> (kPatch * dy + dx)) & 1u)) { found = w; n16 = kPatch * dy + dx; }
+  __device__ bool key(int block, int i, int& tok) const {
+    const int64_t s = step0 + block;
+    const int r = i & 15;
+    tok = a.step_tok[s * kStepKeys + i];
+    return (a.step_mask[s * 8 + 4 * (i >> 4) + (r & 3)] >> ((r >> 2) * 16 + column)) & 1;
   }
-  if (found < 0) return;
-  const WaveDesc wd = a.waves[patch0 + found];
-  const int64_t q_at = b * a.qs[0] + h * a.qs[1] + checked_index(a.hdr, qrow, a.q_len) * a.qs[2];
-  const int64_t kv_at = b * a.ks[0] + h * a.ks[1], rows = Q8 ? a.ks[1] / a.ks[2] : 0, pair = (int64_t)b * a.H + h;
-  float m = kFloor, l = 0.f, O[2][16];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) O[0][e] = O[1][e] = 0.f;
-  for (int64_t s = wd.step_begin; s < (int64_t)wd.step_begin + wd.n_steps; ++s)
-    for (int i = 0; i < kStepKeys; ++i) {
-      const int r = i & 15;
-      const uint64_t keep = a.step_mask[s * 8 + 4 * (i >> 4) + (r & 3)];
-      if (!((keep >> ((r >> 2) * 16 + n16)) & 1)) continue;
-      const int tok = checked_index(a.hdr, a.step_tok[s * kStepKeys + i], a.kv_len);
-      const int64_t at = kv_at + tok * a.ks[2];
-      float dot = 0.f, x[8], y[8];
-      for (int d = 0; d < 64; d += 8) {
-        load_row8<Q8>(a.q, q_at + d, Q8 ? a.q_sz + pair * a.q_len + qrow : nullptr, x);
-        load_row8<Q8>(a.k, at + d, Q8 ? a.k_sz + pair * rows + tok : nullptr, y);
-        for (int e = 0; e < 8; ++e) dot = fmaf(x[e], y[e], dot);
-      }
-      const float z = dot * c, m_new = fmaxf(m, z), alpha = __builtin_amdgcn_exp2f(m - m_new), p = __builtin_amdgcn_exp2f(z - m_new);
-      l = fmaf(l, alpha, p);
-      m = m_new;
-#pragma unroll
-      for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          load_row8<Q8>(a.v, at + 32 * dt + 8 * j, Q8 ? a.v_sz + pair * rows + tok : nullptr, x);
-#pragma unroll
-          for (int i4 = 0; i4 < 4; ++i4) O[dt][4 * j + i4] = fmaf(p, hi ? x[4 + i4] : x[i4], O[dt][4 * j + i4] * alpha);
-        }
-    }
-#pragma unroll
-  for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-    for (int e = 0; e < 16; e += 2)
-      out[dt][e / 2] = __builtin_bit_cast(unsigned, bf16x2{(__bf16)(O[dt][e] * (1.f / l)), (__bf16)(O[dt][e + 1] * (1.f / l))});
-}
+};
 
 }  // namespace
 
@@ -760,7 +718,7 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
   asm volatile("" : "+v"(n_again));            // register (or a spill slot) through the loop
   int qrow = query_row(n_again, false);
   if constexpr (WIDE) {
-    const float inv = 1.f / (ps.L + other_half(ps.L));
+    const float sum = ps.L + other_half(ps.L), inv = 1.f / sum;
     float any = 0.f;
     unsigned r[2][8];
 #pragma unroll
@@ -771,26 +729,45 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
         any = __builtin_amdgcn_fdot2_f32_bf16(two, kOnes, any, false);
         r[dt][e / 2] = __builtin_bit_cast(unsigned, two);
       }
-    // A matrix product multiplies the rows of a step with the probability 0 of the queries that do not keep
-    // them, so a value of K or V that is not finite makes all queries of its step NaN.  A wave that finds such a
-    // result forms it once more, key by key, from the kept pairs alone.
-    const bool again = qrow >= 0 && (not_finite(any) || not_finite(other_half(any)));
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(again) != 0, 0))
-      attend_key_by_key<Q8>(a, c, b, h, grp_g * kGroupPatches, again ? qrow : -1, hi, r);
-    if (qrow < 0) return;
-    qrow = checked_index(a.hdr, qrow, a.q_len);
-    __bf16* op = (__bf16*)a.o + b * a.os[0] + h * a.os[1] + qrow * a.os[2] + 8 * hi;
+    // A matrix product multiplies the rows of a step with the probability 0 of the queries that do not keep them, so a
+    // value that is not finite makes all queries of its step NaN: in every dimension where it is K's, in its own where
+    // it is V's.  Those dimensions (bit e of r's 32 values of the lane) are formed once more behind the store, query by
+    // query, from the kept pairs alone.
+    const float rest_of_row = other_half(any);
+    const bool bad = qrow >= 0 && (not_finite(any) || not_finite(rest_of_row));
+    unsigned rows_again = (unsigned)__builtin_amdgcn_ballot_w64(bad), bad_dims = 0;
+    if (__builtin_expect(rows_again != 0, 0)) {
 #pragma unroll
-    for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        // dims 32 dt + 16 j .. + 15 of the query: its lanes hold 4 of each 8; exchanged, 8 in a row
-        const auto x0 = __builtin_amdgcn_permlane32_swap(r[dt][4 * j], r[dt][4 * j + 2], false, false);
-        const auto x1 = __builtin_amdgcn_permlane32_swap(r[dt][4 * j + 1], r[dt][4 * j + 3], false, false);
-        const u32x4 piece = {x0[0], x1[0], x0[1], x1[1]};
-        *(u32x4*)(op + 32 * dt + 16 * j) = piece;
-        if (shared) *(u32x4*)(op + (a.B / 2) * a.os[0] + 32 * dt + 16 * j) = piece;
+      for (int e = 0; e < 32; ++e) {
+        const unsigned half = (r[e >> 4][(e & 15) >> 1] >> (16 * (e & 1))) & 0x7f80u;
+        bad_dims |= (unsigned)(half == 0x7f80u) << e;
       }
+      if (not_finite(sum)) bad_dims = ~0u;
+    }
+    if (qrow >= 0) {
+      const int to = checked_index(a.hdr, qrow, a.q_len);
+      __bf16* op = (__bf16*)a.o + b * a.os[0] + h * a.os[1] + to * a.os[2] + 8 * hi;
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          // dims 32 dt + 16 j .. + 15 of the query: its lanes hold 4 of each 8; exchanged, 8 in a row
+          const auto x0 = __builtin_amdgcn_permlane32_swap(r[dt][4 * j], r[dt][4 * j + 2], false, false);
+          const auto x1 = __builtin_amdgcn_permlane32_swap(r[dt][4 * j + 1], r[dt][4 * j + 3], false, false);
+          const u32x4 piece = {x0[0], x1[0], x0[1], x1[1]};
+          *(u32x4*)(op + 32 * dt + 16 * j) = piece;
+          if (shared) *(u32x4*)(op + (a.B / 2) * a.os[0] + 32 * dt + 16 * j) = piece;
+        }
+    }
+    for (; __builtin_expect(rows_again != 0, 0); rows_again &= rows_again - 1) {
+      wait_vmcnt<0>();                         // (what is stored next goes to places that were just stored to)
+      const int at = __builtin_ctz(rows_again), row = __builtin_amdgcn_readlane(qrow, at);
+      // lane d for dimension d: value 16 (d / 32) + 4 (d / 8 % 4) + d % 4 of the query's lane half d / 4 % 2
+      const unsigned lo = __builtin_amdgcn_readlane(bad_dims, at), up = __builtin_amdgcn_readlane(bad_dims, at + 32);
+      const int l = lane_of_wave();
+      const bool mine = ((l & 4 ? up : lo) >> (16 * (l >> 5) + 4 * ((l >> 3) & 3) + (l & 3))) & 1u;
+      attend_row<Q8>(a, c, b, h, row, shared, mine, StepKeys(a, a.waves + (size_t)grp_g * kGroupPatches, row));
+    }
   } else {
     if (qrow < 0) return;
     qrow = checked_index(a.hdr, qrow, a.q_len);
