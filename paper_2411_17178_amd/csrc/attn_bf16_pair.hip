@@ -74,6 +74,7 @@ constexpr int kRingChunks = 5;        // ring depth: look-back, two current, two
 constexpr int kBufferFlags = 0x00020000;   // word 3 of a raw buffer resource on gfx9: 32-bit data format
 typedef __attribute__((ext_vector_type(2))) short s16x2;
 constexpr int kBoostPhases = 3;       // phases that a later-arrived workgroup runs at raised priority
+constexpr float kMaskB = 2.0f;        // of the mask product (see run_step32): times -2^127 it is -inf
 constexpr int kLater = 2;             // descriptors, beyond the first step of a phase, that are fetched at
                                       // the start of the phase
 
@@ -448,7 +449,7 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
     const int nx = pw.nx_kq & 0xffff, ny = pw.sk_ny >> 16, dy = (n * pw.magic) >> 16, dx = n - dy * nx;
     const int i0 = (band ? n : dy) - 8 * hi, i1 = (band ? n : ny + dx) - 8 * hi;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) ps.b[e] = (__bf16)(((int)(i0 == e) | (int)(i1 == e)) ? 1.0f : 0.0f);
+    for (int e = 0; e < 8; ++e) ps.b[e] = (__bf16)(((int)(i0 == e) | (int)(i1 == e)) ? kMaskB : 0.0f);
     ps.O[0] = f32x16{}; ps.O[1] = f32x16{};
   } else {
     ps.thr = kFloor;
@@ -555,11 +556,12 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
 
   // One step of a wide patch: 32 keys against 32 queries.  The arithmetic is that of a 16-query step; what differs:
   //  * The mask is a matrix product too.  A window is a product of rows and columns: dimension i < ny of it stands for
-  //    query row i, dimension ny + j for query column j; the B operand has a one where the query lies in that
-  //    row or column, the A operand -2^127 or more where the key is not kept by it (else zero or nearly), from the
-  //    descriptor's sixteen bits per lane.  So the score tile starts at zero or at minus a number that no score
-  //    makes up for, with seven vector instructions, where sixteen selects took a scalar load of 128 bytes per
-  //    step on the wave's critical path.  Bands take two products with one dimension per query.
+  //    query row i, dimension ny + j for query column j; the B operand has a two where the query lies in that
+  //    row or column, the A operand -2^127 or more where the key is not kept by it (else zero or a subnormal), from the
+  //    descriptor's sixteen bits per lane.  Their products pass the range of fp32, so the score tile starts at -inf where
+  //    the key is not kept and below 2^-123 elsewhere, with seven vector instructions, where sixteen selects took a
+  //    scalar load of 128 bytes per step on the wave's critical path.  Bands take two products with one dimension per
+  //    query.  (With ones for the twos a raw product of 2^127, or a softmax scale of 1e-37, let masked keys through.)
   //  * The row sums are the lane's own (v_dot2 on the rounded probabilities; a product with ones would need
   //    sixteen more registers).
   //  * No maximum is formed.  The softmax reference starts at zero and moves only when a query's sum leaves
@@ -594,7 +596,7 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
       asm volatile("" : "+v"(i));
       bf16x8 upper;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) upper[e] = (__bf16)(i == e ? 1.0f : 0.0f);
+      for (int e = 0; e < 8; ++e) upper[e] = (__bf16)(i == e ? kMaskB : 0.0f);
       S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mask_operand(4), upper, S, 0, 0, 0);
     }
     asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
@@ -632,7 +634,7 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
       for (int e = 1; e < 16; ++e) mx = fmaxf(mx, S[e]);
       mx = fmaxf(mx, other_half(mx));                    // over both lanes of the query
       const float now = sum + other_half(sum), before = ps.L + other_half(ps.L);
-      float to = mx > -1.0e30f ? __builtin_fmaf(mx, c, ps.negm) : kFloor;      // (masked scores lie far below)
+      float to = mx > -INFINITY ? __builtin_fmaf(mx, c, ps.negm) : kFloor;
       if (before > 0.f) to = fmaxf(to, __builtin_amdgcn_logf(before));         // (base 2)
       const float shift = (now > kMostSum || now < kLeastSum) && to > kFloor ? rintf(to) : 0.f;
       const float alpha = before > 0.f ? __builtin_amdgcn_exp2f(-shift) : 1.f;

@@ -1,0 +1,40 @@
+"""Finite operands at the ends of their range through the 32-query kernel and the dense kernel, against the fp64
+oracle.  Inputs are chosen so that scores are exact in fp32; outputs are compared relative to the largest value
+(2e-2: P and O are rounded to bf16)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+
+pytestmark = pytest.mark.gpu
+WIDE = (16, 0, 0, -1, 2)
+
+
+def _compare(scales, radii, q, k, v, sm_scale=0.125, q_scales=None, band=False, tol=2e-2, **build):
+    import paper_2411_17178_amd as lv
+    plan = lv.litevar_mask_build(scales, 0, radii, 0, q_scales, mask_mode=int(band), **build)
+    o = lv.litevar_windowed_attn_fwd(plan, q.cuda(), k.cuda(), v.cuda(), sm_scale)
+    torch.cuda.synchronize()
+    lv.litevar_plan_check(plan)
+    o = o.double().cpu().numpy()
+    ref = oracle.attn(scales, radii, *[workloads.to_oracle_array(t) for t in (q, k, v)], float(np.float32(sm_scale)), 0, q_scales,
+                      mode=int(band))
+    assert np.isfinite(o).all()
+    assert np.abs(o - ref).max() <= tol * max(1e-38, float(v.double().abs().max()))
+
+
+@pytest.mark.parametrize("band", [False, True])
+@pytest.mark.parametrize("case", ["product", "scale"])
+def test_masked_pairs_stay_masked(case, band):
+    """Raw products close to 2^128 with keys that few queries keep; a softmax scale of 9e-39."""
+    scales, radii = (2, 5, 18), [2, 2, 2]
+    q, k, v = workloads.make_qkv(scales, 1, 2, 64, "bf16", 51)
+    q[..., 0], k[..., 0] = 2.0 ** 61, 0.0
+    if case == "product":
+        for tok in (3, 17, 29 + 8 * 18 + 9, 29 + 200):
+            k[:, :, tok, 0] = 1.9375 * 2.0 ** 66
+    else:
+        q[..., 0] = 0.0
+    _compare(scales, radii, q, k, v, 0.125 if case == "product" else 9e-39, None, band, waves_per_group=WIDE)
