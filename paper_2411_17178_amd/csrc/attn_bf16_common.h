@@ -107,6 +107,12 @@ __device__ inline int checked_index([[maybe_unused]] Header* hdr, int value, [[m
   return value;
 }
 
+// A softmax reference that is subtracted from scaled scores is a multiple of its own rounding, so that the largest
+// probability is off by up to 2^(2^-25 m): nothing below 2^24, everything from 2^31 on.  Queries whose reference
+// gets there are formed again by attend_row, which subtracts the largest score before it scales.
+constexpr float kFarReference = 0x1p24f;
+__device__ inline uint64_t is_far(float negm) { return __builtin_amdgcn_ballot_w64(!(fabsf(negm) < kFarReference)); }
+
 // (counted anew, where threadIdx.x would hold a register from the kernel's start)
 __device__ inline int lane_of_wave() { return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
 

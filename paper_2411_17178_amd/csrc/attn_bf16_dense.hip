@@ -34,6 +34,12 @@ constexpr int kChunk = 64;                     // keys per LDS buffer
 constexpr int kRow = 128;                      // bytes of a K or V row
 constexpr int kBufBytes = 2 * kChunk * kRow;   // K rows, V rows
 
+// the keys [0, n) for attend_row
+struct AllKeys {
+  int n, n_blocks;
+  __device__ bool key(int block, int i, int& tok) const { tok = min(32 * block + i, n - 1); return 32 * block + i < n; }
+};
+
 struct DenseArgs {
   AttnArgs a;
   uint32_t bh_magic;                           // floor(2^32 / (B H)), see divmod_by
@@ -169,6 +175,7 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
   float L[2] = {0.f, 0.f}, negm = 0.f;         // this lane's part of the row sum, one chain per slice; minus the softmax reference (base 2)
   const uint64_t queries = __builtin_amdgcn_ballot_w64(row_ok);
   uint64_t unset = queries;                    // lanes whose query has no reference yet
+  uint64_t far = 0;                            // lanes whose reference was beyond kFarReference at some time
 
   // S^T of a block whose K rows have been requested
   auto scores = [&](u32x4 (&kr)[4]) -> f32x16 {
@@ -206,6 +213,7 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
       const bool set = __builtin_amdgcn_inverse_ballot_w64(unset) && mx > kFloor;
       negm = set ? -mx * c : negm;
       unset &= ~__builtin_amdgcn_ballot_w64(set);
+      far |= is_far(negm);
     }
     bf16x8 pb[2];
     float sum[2];
@@ -231,6 +239,7 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
       const float shift = now > kMostSum && to > kFloor ? rintf(to) : 0.f;
       const float alpha = before > 0.f ? __builtin_amdgcn_exp2f(-shift) : 1.f;
       negm -= shift; L[0] *= alpha; L[1] *= alpha;
+      far |= is_far(negm);
 #pragma unroll
       for (int e = 0; e < 16; ++e) { O[0][e] *= alpha; O[1][e] *= alpha; }
       exponentials();
@@ -314,21 +323,26 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
 #pragma unroll
     for (int e = 0; e < 16; e += 2)
       r[dt][e / 2] = __builtin_bit_cast(unsigned, bf16x2{(__bf16)(O[dt][e] * inv), (__bf16)(O[dt][e + 1] * inv)});
-  if (!row_ok) return;
   const bool shared = is_shared(un.k);
-  if (shared && partner) return;               // the conditional workgroup writes this row
-  __bf16* op = (__bf16*)a.o + b * a.os[0] + h * a.os[1] + checked_index(a.hdr, row, a.q_len) * a.os[2] + 8 * hh;
+  if (unit < 0 || (shared && partner)) return;           // (the conditional workgroup writes this row)
+  if (row_ok) {
+    __bf16* op = (__bf16*)a.o + b * a.os[0] + h * a.os[1] + checked_index(a.hdr, row, a.q_len) * a.os[2] + 8 * hh;
 #pragma unroll
-  for (int dt = 0; dt < 2; ++dt)
+    for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      // dims 32 dt + 16 j .. + 15 of the query: its lanes hold 4 of each 8; exchanged, 8 in a row
-      const auto x0 = __builtin_amdgcn_permlane32_swap(r[dt][4 * j], r[dt][4 * j + 2], false, false);
-      const auto x1 = __builtin_amdgcn_permlane32_swap(r[dt][4 * j + 1], r[dt][4 * j + 3], false, false);
-      const u32x4 piece = {x0[0], x1[0], x0[1], x1[1]};
-      *(u32x4*)(op + 32 * dt + 16 * j) = piece;
-      if (shared) *(u32x4*)(op + (a.B / 2) * a.os[0] + 32 * dt + 16 * j) = piece;
-    }
+      for (int j = 0; j < 2; ++j) {
+        // dims 32 dt + 16 j .. + 15 of the query: its lanes hold 4 of each 8; exchanged, 8 in a row
+        const auto x0 = __builtin_amdgcn_permlane32_swap(r[dt][4 * j], r[dt][4 * j + 2], false, false);
+        const auto x1 = __builtin_amdgcn_permlane32_swap(r[dt][4 * j + 1], r[dt][4 * j + 3], false, false);
+        const u32x4 piece = {x0[0], x1[0], x0[1], x1[1]};
+        *(u32x4*)(op + 32 * dt + 16 * j) = piece;
+        if (shared) *(u32x4*)(op + (a.B / 2) * a.os[0] + 32 * dt + 16 * j) = piece;
+      }
+  }
+  for (unsigned rest = (unsigned)(far & queries); __builtin_expect(rest != 0, 0); rest &= rest - 1) {
+    wait_vmcnt<0>();                                     // (the row is stored to once more)
+    attend_row<false>(a, c, b, h, __builtin_amdgcn_readlane(row, __builtin_ctz(rest)), shared, true, AllKeys{wave_keys, (wave_keys + 31) / 32});
+  }
 }
 
 // Plans that keep every pair of the block-causal map, however their radii say so, go to the kernel

@@ -138,6 +138,7 @@ struct WidePatchState {   // a wave's 32 queries
   f32x16 O[2];            // O^T accumulators: dims 32 dt + 8 (e / 4) + 4 h + e % 4 of query n
   float L, negm;          // this lane's part of the row sum, minus the softmax reference m (base 2, whole numbers)
   uint64_t unset;         // lanes whose query's sum is still below kLeastSum
+  uint64_t far;           // lanes whose reference was beyond kFarReference at some time
   bf16x8 b;               // B operand of the mask product, see run_step32
 };
 
@@ -445,7 +446,7 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
   [[maybe_unused]] bf16x8 ones;
   ps.negm = 0.f;
   if constexpr (WIDE) {
-    ps.L = 0.f; ps.unset = queries;
+    ps.L = 0.f; ps.unset = queries; ps.far = 0;
     const int nx = pw.nx_kq & 0xffff, ny = pw.sk_ny >> 16, dy = (n * pw.magic) >> 16, dx = n - dy * nx;
     const int i0 = (band ? n : dy) - 8 * hi, i1 = (band ? n : ny + dx) - 8 * hi;
 #pragma unroll
@@ -639,6 +640,7 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
       const float shift = (now > kMostSum || now < kLeastSum) && to > kFloor ? rintf(to) : 0.f;
       const float alpha = before > 0.f ? __builtin_amdgcn_exp2f(-shift) : 1.f;
       ps.negm -= shift; ps.L *= alpha;
+      ps.far |= is_far(ps.negm);
 #pragma unroll
       for (int e = 0; e < 16; ++e) { ps.O[0][e] *= alpha; ps.O[1][e] *= alpha; }
       exponentials();
@@ -734,9 +736,10 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
     // A matrix product multiplies the rows of a step with the probability 0 of the queries that do not keep them, so a
     // value that is not finite makes all queries of its step NaN: in every dimension where it is K's, in its own where
     // it is V's.  Those dimensions (bit e of r's 32 values of the lane) are formed once more behind the store, query by
-    // query, from the kept pairs alone.
+    // query, from the kept pairs alone; rows whose reference went too far in all dimensions.
     const float rest_of_row = other_half(any);
-    const bool bad = qrow >= 0 && (not_finite(any) || not_finite(rest_of_row));
+    const bool far = __builtin_amdgcn_inverse_ballot_w64(ps.far);
+    const bool bad = qrow >= 0 && (not_finite(any) || not_finite(rest_of_row) || far);
     unsigned rows_again = (unsigned)__builtin_amdgcn_ballot_w64(bad), bad_dims = 0;
     if (__builtin_expect(rows_again != 0, 0)) {
 #pragma unroll
@@ -744,7 +747,7 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
         const unsigned half = (r[e >> 4][(e & 15) >> 1] >> (16 * (e & 1))) & 0x7f80u;
         bad_dims |= (unsigned)(half == 0x7f80u) << e;
       }
-      if (not_finite(sum)) bad_dims = ~0u;
+      if (far || not_finite(sum)) bad_dims = ~0u;
     }
     if (qrow >= 0) {
       const int to = checked_index(a.hdr, qrow, a.q_len);

@@ -38,3 +38,22 @@ def test_masked_pairs_stay_masked(case, band):
     else:
         q[..., 0] = 0.0
     _compare(scales, radii, q, k, v, 0.125 if case == "product" else 9e-39, None, band, waves_per_group=WIDE)
+
+
+@pytest.mark.parametrize("sign", [1, -1])
+@pytest.mark.parametrize("form", ["dense", "wide", "band"])
+def test_scores_beyond_the_reference(form, sign):
+    """All of a query's scores equal and beyond 2^24 in base 2, where a reference in whole numbers, or rounded, is off
+    by many powers of two: every head at a magnitude of its own, from 2^24 to 2^38; and a last scale that lies above or
+    below the others by a part of it."""
+    scales, H = (3, 6, 18), 36
+    q, k, v = workloads.make_qkv(scales, 1, H, 64, "bf16", 54)
+    q[..., 1:], k[..., 1:] = 0.0, 0.0
+    for h in range(H):
+        x = 2.0 ** (14 + h % 12) * (1 + h / 64)
+        q[:, h, :, 0] = x
+        k[:, h, :, 0] = sign * 2.0 ** 14
+        if h >= 24:
+            k[:, h, 9:45, 0] = sign * 2.0 ** 13
+    build = {} if form == "dense" else {"waves_per_group": WIDE}
+    _compare(scales, [-1 if form == "dense" else 3] * 3, q, k, v, band=form == "band", **build)
