@@ -23,7 +23,9 @@ typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
 
 constexpr float kFloor = -1.0e30f;   // initial softmax reference: keeps exp2 arguments finite
 constexpr float kSlack = 6.0f;       // base-2 exponent by which a score may exceed the reference
-constexpr float kMostSum = 0x1p40f, kLeastSum = 0x1p-40f;   // row sums outside move the reference of the 32-query kernels
+// Row sums outside move the reference of the windowed 32-query kernel.  Below 1 the products with V would lose bits of values
+// near the smallest normal ones; above, they may overflow, which ends in attend_row.
+constexpr float kMostSum = 0x1p40f, kLeastSum = 1.f;
 
 __device__ inline bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -112,6 +114,12 @@ __device__ inline int checked_index([[maybe_unused]] Header* hdr, int value, [[m
 // gets there are formed again by attend_row, which subtracts the largest score before it scales.
 constexpr float kFarReference = 0x1p24f;
 __device__ inline uint64_t is_far(float negm) { return __builtin_amdgcn_ballot_w64(!(fabsf(negm) < kFarReference)); }
+
+template <int N> __device__ inline void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
+  // gfx9 encoding: vmcnt[3:0] in bits 3:0, vmcnt[5:4] in bits 15:14; expcnt/lgkmcnt left at max
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
+}
 
 // (counted anew, where threadIdx.x would hold a register from the kernel's start)
 __device__ inline int lane_of_wave() { return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
@@ -208,6 +216,30 @@ __device__ inline void attend_row(const AttnArgs& a, float c, int b, int h, int 
   if (shared) op[(a.B / 2) * a.os[0]] = r;
 }
 
+// Which of a query's 32 values in this lane (r: pairs of bf16, dims 32 dt + 8 j + 4 (lane / 32) .. + 3 of a 32 x 32 tile's
+// column, in that order) are not finite.
+__device__ inline unsigned not_finite_dims(const unsigned (&r)[2][8]) {
+  unsigned bits = 0;
+#pragma unroll
+  for (int e = 0; e < 32; ++e)
+    bits |= (unsigned)(((r[e >> 4][(e & 15) >> 1] >> (16 * (e & 1))) & 0x7f80u) == 0x7f80u) << e;
+  return bits;
+}
+
+// attend_row for the rows of the lanes in `rows` (their row: `row`), behind the store of the wave's results: the
+// dimensions dims of a lane and of the one 32 above it are stored again.
+template <bool Q8, class KeysOf>
+__device__ inline void attend_rows(const AttnArgs& a, float c, int b, int h, bool shared, unsigned rows, int row, unsigned dims, KeysOf keys_of) {
+  for (; __builtin_expect(rows != 0, 0); rows &= rows - 1) {
+    wait_vmcnt<0>();                           // (what is stored next goes to places that were just stored to)
+    const int at = __builtin_ctz(rows), r = __builtin_amdgcn_readlane(row, at), l = lane_of_wave();
+    // lane d for dimension d: value 16 (d / 32) + 4 (d / 8 % 4) + d % 4 of the query's lane half d / 4 % 2
+    const unsigned lo = __builtin_amdgcn_readlane(dims, at), up = __builtin_amdgcn_readlane(dims, at + 32);
+    const bool mine = ((l & 4 ? up : lo) >> (16 * (l >> 5) + 4 * ((l >> 3) & 3) + (l & 3))) & 1u;
+    attend_row<Q8>(a, c, b, h, r, shared, mine, keys_of(r));
+  }
+}
+
 // x = q n + r for a divisor n whose magic = floor(2^32 / n) came with the kernel arguments
 // (n = 1: magic = 2^32 - 1): the estimate floor(x magic / 2^32) is the quotient or one below it
 // for every x < 2^32, so one correction step makes it exact.
@@ -229,12 +261,6 @@ __device__ inline bool xcd_item(const AttnArgs& a, int items, int& me, int& bh, 
   bh = me * (8 >> a.spread_log) + (xcd >> a.spread_log);
   item = (in_part << a.spread_log) + (xcd & ((1 << a.spread_log) - 1));
   return bh < a.B * a.H && item < items;
-}
-
-template <int N> __device__ inline void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
-  // gfx9 encoding: vmcnt[3:0] in bits 3:0, vmcnt[5:4] in bits 15:14; expcnt/lgkmcnt left at max
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
 }
 
 // N consecutive-stride LDS words (stride 32 bytes) written by earlier LDS-DMA loads of this

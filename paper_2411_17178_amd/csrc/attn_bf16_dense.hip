@@ -175,6 +175,7 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
   float L[2] = {0.f, 0.f}, negm = 0.f;         // this lane's part of the row sum, one chain per slice; minus the softmax reference (base 2)
   const uint64_t queries = __builtin_amdgcn_ballot_w64(row_ok);
   uint64_t unset = queries;                    // lanes whose query has no reference yet
+  uint64_t moved = 0;                          // lanes whose reference has moved
   uint64_t far = 0;                            // lanes whose reference was beyond kFarReference at some time
 
   // S^T of a block whose K rows have been requested
@@ -240,6 +241,7 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
       const float alpha = before > 0.f ? __builtin_amdgcn_exp2f(-shift) : 1.f;
       negm -= shift; L[0] *= alpha; L[1] *= alpha;
       far |= is_far(negm);
+      moved |= __builtin_amdgcn_ballot_w64(shift != 0.f);
 #pragma unroll
       for (int e = 0; e < 16; ++e) { O[0][e] *= alpha; O[1][e] *= alpha; }
       exponentials();
@@ -316,7 +318,7 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
     }
   }
 
-  const float l = L[0] + L[1], inv = 1.f / (l + other_half(l));
+  const float part = L[0] + L[1], l = part + other_half(part), inv = 1.f / l;
   unsigned r[2][8];
 #pragma unroll
   for (int dt = 0; dt < 2; ++dt)
@@ -339,9 +341,20 @@ void k_attn_bf16_dense(DenseArgs d, float c) {
         if (shared) *(u32x4*)(op + (a.B / 2) * a.os[0] + 32 * dt + 16 * j) = piece;
       }
   }
-  for (unsigned rest = (unsigned)(far & queries); __builtin_expect(rest != 0, 0); rest &= rest - 1) {
-    wait_vmcnt<0>();                                     // (the row is stored to once more)
-    attend_row<false>(a, c, b, h, __builtin_amdgcn_readlane(row, __builtin_ctz(rest)), shared, true, AllKeys{wave_keys, (wave_keys + 31) / 32});
+  // Rows whose reference went too far, and rows whose products with V may have overflowed although V and the result are
+  // in range -- not finite, and formed under sums that a reference which follows each score would not have let grow --
+  // are formed once more, the latter in the dimensions that are not finite.
+  far &= queries;
+  moved = (moved | __builtin_amdgcn_ballot_w64(l > 64.f * (float)wave_keys)) & queries;
+  if (__builtin_expect((far | moved) != 0, 0)) {
+    float any = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) any = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, r[e >> 3][e & 7]), kOnes, any, false);
+    const uint64_t bad = (__builtin_amdgcn_ballot_w64(not_finite(any)) & moved) | far;
+    if (bad != 0)
+      attend_rows<false>(a, c, b, h, shared, (unsigned)(bad | (bad >> 32)), row,
+                         __builtin_amdgcn_inverse_ballot_w64(far) ? ~0u : not_finite_dims(r),
+                         [&](int) { return AllKeys{wave_keys, (wave_keys + 31) / 32}; });
   }
 }
 

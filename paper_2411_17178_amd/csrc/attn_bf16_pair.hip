@@ -566,9 +566,9 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
   //  * The row sums are the lane's own (v_dot2 on the rounded probabilities; a product with ones would need
   //    sixteen more registers).
   //  * No maximum is formed.  The softmax reference starts at zero and moves only when a query's sum leaves
-  //    [2^-40, 2^40] (the lower end is looked at until every query has passed it), which costs one comparison
+  //    [1, 2^40] (the lower end is looked at until every query has passed it), which costs one comparison
   //    where the maximum of sixteen scores costs eight.  Probabilities and sums keep their relative precision
-  //    under any common factor, and the factors are powers of two.
+  //    under any common factor, and the factors are powers of two; the products with V do from sums of 1 on.
   [[maybe_unused]] auto run_step32 = [&](auto& ps, const u32x4 cur) {
     constexpr int kRingBytes = R * kRingRowBytes;
     u32x4 kr[4];
@@ -735,20 +735,14 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
       }
     // A matrix product multiplies the rows of a step with the probability 0 of the queries that do not keep them, so a
     // value that is not finite makes all queries of its step NaN: in every dimension where it is K's, in its own where
-    // it is V's.  Those dimensions (bit e of r's 32 values of the lane) are formed once more behind the store, query by
-    // query, from the kept pairs alone; rows whose reference went too far in all dimensions.
+    // it is V's.  Those dimensions are formed once more behind the store, query by query, from the kept pairs alone;
+    // rows whose reference went too far in all dimensions.
     const float rest_of_row = other_half(any);
     const bool far = __builtin_amdgcn_inverse_ballot_w64(ps.far);
     const bool bad = qrow >= 0 && (not_finite(any) || not_finite(rest_of_row) || far);
-    unsigned rows_again = (unsigned)__builtin_amdgcn_ballot_w64(bad), bad_dims = 0;
-    if (__builtin_expect(rows_again != 0, 0)) {
-#pragma unroll
-      for (int e = 0; e < 32; ++e) {
-        const unsigned half = (r[e >> 4][(e & 15) >> 1] >> (16 * (e & 1))) & 0x7f80u;
-        bad_dims |= (unsigned)(half == 0x7f80u) << e;
-      }
-      if (far || not_finite(sum)) bad_dims = ~0u;
-    }
+    const unsigned rows_again = (unsigned)__builtin_amdgcn_ballot_w64(bad);
+    unsigned bad_dims = 0;
+    if (__builtin_expect(rows_again != 0, 0)) bad_dims = far || not_finite(sum) ? ~0u : not_finite_dims(r);
     if (qrow >= 0) {
       const int to = checked_index(a.hdr, qrow, a.q_len);
       __bf16* op = (__bf16*)a.o + b * a.os[0] + h * a.os[1] + to * a.os[2] + 8 * hi;
@@ -764,15 +758,8 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
           if (shared) *(u32x4*)(op + (a.B / 2) * a.os[0] + 32 * dt + 16 * j) = piece;
         }
     }
-    for (; __builtin_expect(rows_again != 0, 0); rows_again &= rows_again - 1) {
-      wait_vmcnt<0>();                         // (what is stored next goes to places that were just stored to)
-      const int at = __builtin_ctz(rows_again), row = __builtin_amdgcn_readlane(qrow, at);
-      // lane d for dimension d: value 16 (d / 32) + 4 (d / 8 % 4) + d % 4 of the query's lane half d / 4 % 2
-      const unsigned lo = __builtin_amdgcn_readlane(bad_dims, at), up = __builtin_amdgcn_readlane(bad_dims, at + 32);
-      const int l = lane_of_wave();
-      const bool mine = ((l & 4 ? up : lo) >> (16 * (l >> 5) + 4 * ((l >> 3) & 3) + (l & 3))) & 1u;
-      attend_row<Q8>(a, c, b, h, row, shared, mine, StepKeys(a, a.waves + (size_t)grp_g * kGroupPatches, row));
-    }
+    attend_rows<Q8>(a, c, b, h, shared, rows_again, qrow, bad_dims,
+                    [&](int row) { return StepKeys(a, a.waves + (size_t)grp_g * kGroupPatches, row); });
   } else {
     if (qrow < 0) return;
     qrow = checked_index(a.hdr, qrow, a.q_len);

@@ -57,3 +57,33 @@ def test_scores_beyond_the_reference(form, sign):
             k[:, h, 9:45, 0] = sign * 2.0 ** 13
     build = {} if form == "dense" else {"waves_per_group": WIDE}
     _compare(scales, [-1 if form == "dense" else 3] * 3, q, k, v, band=form == "band", **build)
+
+
+def _rising(scales, step):
+    """K's component 0 grows by `step` from scale to scale (q's is 8, the softmax scale 1/8): scores rise by that much."""
+    q, k, v = workloads.make_qkv(scales, 1, 2, 64, "bf16", 52)
+    q[..., 0] = 8.0
+    at = 0
+    for j, s in enumerate(scales):
+        k[:, :, at:at + s * s, 0] = step * j
+        at += s * s
+    return q, k, v
+
+
+@pytest.mark.parametrize("form", ["dense", "wide"])
+def test_large_values_under_rising_scores(form):
+    """Scores that rise by 24 (2^35 in the probabilities) over values of 2^105: sums of 2^35 would overflow in the products."""
+    scales = (6, 7, 9, 11)
+    q, k, v = _rising(scales, 8.0)
+    v = (v.float().sign() * 2.0 ** 105 + 0.0).to(torch.bfloat16)
+    _compare(scales, [-1 if form == "dense" else 3] * 4, q, k, v, **({"waves_per_group": WIDE} if form == "wide" else {}))
+
+
+@pytest.mark.parametrize("level", [-26.0, -20.0, -3.0])
+def test_small_values_under_low_scores(level):
+    """Values of about 2^-115 under probabilities of 2^-37 would lose their bits in the products."""
+    scales = (3, 5, 20)
+    q, k, v = workloads.make_qkv(scales, 1, 2, 64, "bf16", 53)
+    q[..., 0], k[..., 0] = 8.0, level
+    v = (v.float() * 2.0 ** -115).to(torch.bfloat16)
+    _compare(scales, [3] * 3, q, k, v, waves_per_group=WIDE)
