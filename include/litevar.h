@@ -137,7 +137,8 @@ typedef struct litevar_plan {
   int32_t scales[LITEVAR_MAX_SCALES];
   int32_t radii[LITEVAR_MAX_SCALES];   /* per key scale: the widest radius over the plan's query scales */
   int32_t n_sink_scales;
-  int32_t patches_per_wave; /* 16 patches per group only: as the options asked, 0, 1 or 2 */
+  int32_t patches_per_wave; /* 16 patches per group only: as the options asked, 0, 1 or 2; 1 also where eight
+                               waves cannot serve the plan (32 queries that need more than 65 535 steps) */
   int32_t spin_limit;       /* bound of the kernels' LDS-flag waits, in polls */
   int32_t mask_mode;
   int32_t n_heads;          /* 0, or the number of heads the plan holds radius tables for */
@@ -163,8 +164,8 @@ typedef struct litevar_plan_opts {
                                Supported (chunk, prefetch, spare) for 4 and 8 patches per group:
                                (32,2,2) and (64,2,1).  16 patches per group take (128,2,0) only:
                                phases of 128 keys, ring and prefetch depth counted in 64-key chunks */
-  int32_t patches_per_wave; /* 16 patches per group only: 0 = choose (two), 1 = sixteen waves per
-                               workgroup with 16 queries each, 2 = eight waves with 32 queries each */
+  int32_t patches_per_wave; /* 16 patches per group only: 1 = sixteen waves per workgroup with 16 queries
+                               each, 0 and 2 = eight waves with 32 queries each, where they can (see the handle) */
   int32_t batch_heads_hint; /* 0 = unknown, else the B * H of the launches this plan is for: when
                                waves_per_group is left to the library, few (batch, head) pairs get
                                smaller groups, so that the launch still fills the GPU */

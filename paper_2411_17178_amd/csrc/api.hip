@@ -94,7 +94,7 @@ static void fill_handle(const PlanSpec& sp, const PlanSizes& z, const litevar_pl
   plan->n_heads = sp.n_heads; plan->n_head_groups = g.n_hg;
   memcpy(plan->head_group, sp.head_group, sizeof plan->head_group);
   for (int i = 0; i < g.n_hg && i < kMaxHeads; ++i) plan->retained_pairs_of_group[i] = z.pairs_of_group[i];
-  plan->patches_per_wave = (opts && g.NW == 16) ? opts->patches_per_wave : 0;
+  plan->patches_per_wave = g.NW != 16 ? 0 : !g.n_wide ? 1 : opts ? opts->patches_per_wave : 0;
   plan->blob_bytes = z.bytes;
   plan->n_scales = g.K;
   plan->q_scale_begin = g.qb; plan->q_scale_end = g.qe;

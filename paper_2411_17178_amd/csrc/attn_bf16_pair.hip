@@ -782,22 +782,22 @@ litevar_status launch_attn_bf16_pair(const litevar_plan* pl, const AttnArgs& arg
   AttnArgs a = args;
   const int64_t blocks = spread_over_xcds(a, a.n_groups, a.k_sz ? 72 : 128);
   if (blocks > 0x7fffffff) return fail(LITEVAR_E_UNSUPPORTED, "grid too large");
-  // Sixteen waves with a 16-query patch each where the plan asks for them, or has no wide patches.  They are nowhere
+  // Sixteen waves with a 16-query patch each where the plan asks for them, or can have no wide patches.  They are nowhere
   // quicker, on a CU of their own either: 256 queries on 680 keys, 60 / 240 pairs 14.0 / 17.0 us, wide 13.4 / 16.4; 169
   // queries 10.5 / 11.6, wide 10.4 / 11.6; 1024 on 2240 keys, 60 pairs 22.8, wide 21.2; 680 tokens, 8 pairs 12.7, wide 12.1.
-  // (A blob laid out before there were wide patches has none of their descriptors.  Its section of patches says so
-  // without doubt: a group's 16 descriptors are 512 bytes and its eight wide ones 256, so it has no padding.)
   const int64_t groups = (int64_t)pl->n_groups * pl->n_head_groups;
+  // (A plan has wide patches where its section of patches holds theirs: a group's 16 descriptors are 512 bytes and its
+  // eight wide ones 256, so the section has no padding.)
   const bool has_wide = pl->off[kSecPhaseEnd] - pl->off[kSecWaves] == (uint64_t)groups * (16 + kWidePatches) * sizeof(WaveDesc);
-  const int pw = has_wide && pl->patches_per_wave != 1 ? 2 : 1;
+  if (has_wide && pl->patches_per_wave == 1) return fail(LITEVAR_E_PLAN_CORRUPT, "a plan of sixteen waves with wide patches");
+  const int pw = has_wide ? 2 : 1;
   WideArgs w{};
-  if (has_wide) {
+  if (pw == 2) {
     w.waves = a.waves + groups * 16;
     w.phase_end = a.phase_end + pl->n_union_keys / pl->chunk_keys * 16;
     w.union_tok = a.union_tok + pl->n_union_keys;
-    // (the wide steps come first in their section, which has no padding either)
+    // (the wide steps come first in their section)
     w.step_addr = (const unsigned char*)a.step_addr;
-    a.step_addr = (const uint2*)((const char*)pl->d_blob + pl->off[kSecStepMask]) - pl->n_steps * 64;
   }
   // all workgroups are resident at once (two per CU): see later_arrival
   static thread_local int n_cu[64] = {0};

@@ -15,7 +15,8 @@ litevar_status hip_check(hipError_t e, const char* what);
 
 struct PlanSizes {
   int64_t n_steps, n_union, n_phase_entries, retained_pairs;   // summed over the head groups
-  int64_t n_wide_steps;                                        // of the wide patches (16 patches per group), else 0
+  int64_t n_wide_steps;                                        // of the wide patches
+  int n_wide;                                                  // wide patches per group, 0: the plan has none
   int64_t pairs_of_group[kMaxHeads];                           // kept pairs per (batch, head) of each head group
   uint64_t off[kNumSections];
   uint64_t bytes;

@@ -20,7 +20,9 @@
 //           carry a second work-list over the same key list: up to eight wide patches (4 x 8
 //           queries, or what covers the group's queries with the fewest key rows; band mode: 32
 //           consecutive queries) with steps of 32 keys of their own.  The 16-patch kernel's eight-wave form
-//           walks it; the exports and the other kernels walk the patches of 16.
+//           walks it; the exports and the other kernels walk the patches of 16.  Plans that ask for the sixteen-wave
+//           form (patches_per_wave = 1) have none, nor have plans one of whose wide patches would need more
+//           than 65535 steps: their box can be larger than those of its two patches of 16.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -48,6 +50,7 @@ struct Geom {
   int K, qb, qe, n_sink;
   int L, Lq, q0, smax;
   int NW;               // patches per group
+  int n_wide;           // wide patches per group: kWidePatches, or 0 where the plan has none
   short grh[kMaxScales], grw[kMaxScales];   // window mode: group shape in patches (grh x grw <= NW) of every query scale
   short wph[kMaxScales], wpw[kMaxScales];   // window mode, NW = 16: queries of a wide patch of every query scale
   int C, NR, A, D;      // chunk keys (a power of two), ring depth in chunks, look-back and
@@ -110,7 +113,7 @@ struct Header {      // first 256 bytes of the blob
                        // kErrBounds: a kernel of the bounds-checking build found a token, a query
                        // row or an LDS offset out of range (it used index 0 instead)
   int32_t pad0;
-  int64_t n_wide_steps;  // steps of the wide patches (16 patches per group), else 0
+  int64_t n_wide_steps;  // steps of the wide patches, 0 without them
   uint64_t pad[23];
 };
 static_assert(sizeof(Header) == 256, "header size");

@@ -142,6 +142,7 @@ litevar_status make_spec(const litevar_mask_desc* d, const litevar_plan_opts* op
     return fail(LITEVAR_E_INVALID_ARG, "unsupported (chunk_keys, prefetch_chunks, spare_chunks) = (%d, %d, %d)",
                 chunk, depth, spare);
   choose_tiling(g, waves, chunk, depth, spare);
+  g.n_wide = waves == 16 && !(opts && opts->patches_per_wave == 1) ? kWidePatches : 0;
 
   int64_t ng = 0, np = 0;
   for (int i = 0; i < g.qe - g.qb; ++i) {
@@ -174,14 +175,21 @@ static bool same_spec(const PlanSpec& a, const PlanSpec& b) {
 }
 
 litevar_status size_plan(PlanSpec& sp, PlanSizes& z) {
+  const int asked_wide = sp.g.n_wide;
   if (g_last_sizing.valid && same_spec(g_last_sizing.sp, sp)) {
     z = g_last_sizing.z;
+    sp.g.n_wide = z.n_wide;
     sp.group_phases = g_last_sizing.sp.group_phases; sp.patch_steps = g_last_sizing.sp.patch_steps;
     return LITEVAR_OK;
   }
-  const litevar_status rc = size_plan_uncached(sp, z);
+  litevar_status rc = size_plan_uncached(sp, z);
+  if (rc == LITEVAR_OK && sp.g.n_wide != asked_wide) rc = size_plan_uncached(sp, z);      // (without wide patches)
   sp.load_head_group(0);
-  if (rc == LITEVAR_OK) { g_last_sizing.sp = sp; g_last_sizing.z = z; g_last_sizing.valid = true; }
+  z.n_wide = sp.g.n_wide;
+  if (rc == LITEVAR_OK) {
+    g_last_sizing.sp = sp; g_last_sizing.z = z; g_last_sizing.valid = true;
+    g_last_sizing.sp.g.n_wide = asked_wide;             // (what the next one is compared with)
+  }
   return rc;
 }
 
@@ -226,6 +234,10 @@ static void add_dealt_box(StepCounter& steps, const AxisSpan& rows, const AxisSp
   }
 }
 
+constexpr int kMostPatchSteps = 65535;                  // (counts travel in 16 bits)
+constexpr int64_t kMostSteps = (int64_t)1 << 26;
+
+// clears sp.g.n_wide and stops where the wide patches would pass the limits
 static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
   HostGeom& g = sp.g;
   const bool keep_places = (int64_t)g.n_groups * g.n_hg <= kMostPlacedGroups;
@@ -247,7 +259,7 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
       for (int c = 0; c < g.s[k]; ++c) centres.push_back((int16_t)window_interval(g.s[k], g.s[j], c, 0).lo);
   }
   ListBox boxes[kMaxScales];
-  std::vector<int16_t> orders((size_t)(g.NW == 16 ? g.K : 0) * g.smax);
+  std::vector<int16_t> orders((size_t)(g.n_wide ? g.K : 0) * g.smax);
   for (int hg = 0; hg < g.n_hg; ++hg) {
     sp.load_head_group(hg);
     const ArithRad rad{g};
@@ -255,7 +267,7 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
     for (int k = g.qe - 1; k >= g.qb; --k) {
       const int pps = patches_per_side(g, k), nk = g.s[k] * g.s[k];
       const int ngy = groups_y(g, k), ngx = groups_x(g, k);
-      const bool wide = g.NW == 16;
+      const bool wide = g.n_wide > 0;
       // wide patch rows of a group, and columns (window mode)
       int wny = 0, wnx = 0;
       if (g.mode == kModeWindow) {
@@ -334,11 +346,11 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
             }
           }
           const int ns = steps.finish();
-          if (ns > 65535) return fail(LITEVAR_E_UNSUPPORTED, "a query patch needs more than 65535 steps");
+          if (ns > kMostPatchSteps) return fail(LITEVAR_E_UNSUPPORTED, "a query patch needs more than 65535 steps");
           z.n_steps += ns;
           if (keep_places) sp.patch_steps.push_back((uint16_t)ns);
         }
-        for (int w = 0; wide && w < kWidePatches; ++w) {
+        for (int w = 0; w < g.n_wide; ++w) {
           const PatchExtent p = wide_extent(g, k, gy, gx, w);
           if (p.ny == 0) { if (keep_places) sp.patch_steps.push_back(0); continue; }
           StepCounter steps{g};
@@ -360,8 +372,8 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
             }
           }
           const int ns = steps.finish();
-          if (ns > 65535) return fail(LITEVAR_E_UNSUPPORTED, "a query patch needs more than 65535 steps");
           z.n_wide_steps += ns;
+          if (ns > kMostPatchSteps || z.n_wide_steps > kMostSteps) { g.n_wide = 0; return LITEVAR_OK; }
           if (keep_places) sp.patch_steps.push_back((uint16_t)ns);
         }
       }
@@ -369,10 +381,10 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
     z.retained_pairs += pairs_hg;
     if (hg < kMaxHeads) z.pairs_of_group[hg] = pairs_hg;
   }
-  if (z.n_steps > (int64_t)1 << 26 || z.n_wide_steps > (int64_t)1 << 26 || z.n_union > (int64_t)1 << 30)
+  if (z.n_steps > kMostSteps || z.n_union > (int64_t)1 << 30)
     return fail(LITEVAR_E_UNSUPPORTED, "work-list too large (%lld steps)", (long long)z.n_steps);
   const uint64_t ngt = (uint64_t)g.n_groups * g.n_hg;
-  const bool wide = g.NW == 16;        // (the wide patches' entries follow the others in their sections; their steps' descriptors come first)
+  const bool wide = g.n_wide > 0;      // (the wide patches' entries follow the others in their sections; their steps' descriptors come first)
   uint64_t o = 0;
   z.off[kSecHeader] = o; o += sizeof(Header);
   z.off[kSecWin] = o;
@@ -380,7 +392,7 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
   z.off[kSecRad] = o; o = align256(o + (uint64_t)g.n_hg * g.K * g.K * sizeof(int16_t));
   z.off[kSecHeadMap] = o; o = align256(o + (uint64_t)kMaxHeads * sizeof(int32_t));
   z.off[kSecGroups] = o; o = align256(o + ngt * sizeof(GroupDesc));
-  z.off[kSecWaves] = o; o = align256(o + ngt * (g.NW + (wide ? kWidePatches : 0)) * sizeof(WaveDesc));
+  z.off[kSecWaves] = o; o = align256(o + ngt * (g.NW + g.n_wide) * sizeof(WaveDesc));
   z.off[kSecPhaseEnd] = o; o = align256(o + (uint64_t)(z.n_phase_entries + (wide ? z.n_phase_entries / 2 : 0)) * sizeof(int32_t));
   z.off[kSecUnion] = o; o = align256(o + (uint64_t)z.n_union * (wide ? 2 : 1) * sizeof(int32_t));
   z.off[kSecStepAddr] = o; o = align256(o + (uint64_t)z.n_steps * 64 * sizeof(uint2) + (uint64_t)z.n_wide_steps * 64 * kWideDesc);
@@ -423,7 +435,7 @@ static_assert(sizeof(Places) + sizeof(Geom) + sizeof(BlobPtrs) + sizeof(Caps) + 
 
 // false: they don't fit
 static bool place(const PlanSpec& sp, Places& s) {
-  const int n = (int)sp.group_phases.size(), per = sp.g.NW + (sp.g.NW == 16 ? kWidePatches : 0);
+  const int n = (int)sp.group_phases.size(), per = sp.g.NW + sp.g.n_wide;
   if (n == 0 || n != sp.g.n_groups * sp.g.n_hg || 3 * n + 1 + (n * per + 1) / 2 > kPlaceWords) return false;
   uint32_t at[2] = {0, 0}, phases = 0;
   uint16_t* ends = (uint16_t*)(s.w + 3 * n + 1);
@@ -793,7 +805,7 @@ __global__ __launch_bounds__(64) void k_count(Geom g, BlobPtrs p, int n_waves) {
 __global__ __launch_bounds__(1024) void k_scan(Geom g, BlobPtrs p, Caps caps, int n_waves) {
   constexpr int kSums = 5;
   __shared__ int64_t wave_total[kSums][16];
-  const int n_wide = g.NW == 16 ? kWidePatches : 0;     // per group
+  const int n_wide = g.n_wide;                          // per group
   WaveDesc* const wide = p.waves + n_waves;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int n_all = g.n_groups * g.n_hg;
@@ -855,7 +867,7 @@ __global__ __launch_bounds__(1024) void k_scan(Geom g, BlobPtrs p, Caps caps, in
 __device__ void fill_union(const Geom& g, const BlobPtrs& p, const Caps& caps, const GroupTables& t, const GroupDesc& gd) {
   const GroupExtent e = group_extent(g, gd.k, gd.gy, gd.gx);
   int32_t* out = p.union_tok + gd.union_base;
-  int32_t* wide = g.NW == 16 ? out + caps.n_union : nullptr;   // the wide patches' list, some of whose boxes are dealt
+  int32_t* wide = g.n_wide ? out + caps.n_union : nullptr;   // the wide patches' list, some of whose boxes are dealt
   if ((int64_t)gd.union_base + (int64_t)gd.n_phases * g.C > caps.n_union) return;
   int ubase = 0, last_tok = 0;
   if (g.mode == kModeBand) {
@@ -997,7 +1009,7 @@ __global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int 
   __shared__ StepBuf buf;
   const int lane = threadIdx.x;
   if (!PLACED && p.hdr->error) return;
-  const int n_wide = g.NW == 16 ? caps.n_groups * kWidePatches : 0;
+  const int n_wide = caps.n_groups * g.n_wide;
   const bool wide = (int)blockIdx.x >= n_waves, lists = (int)blockIdx.x >= n_waves + n_wide;
   const int idx = lists ? blockIdx.x - n_waves - n_wide : wide ? blockIdx.x - n_waves : blockIdx.x;
   const int per = lists ? 1 : wide ? kWidePatches : g.NW;
@@ -1042,7 +1054,7 @@ __global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int 
   WaveDesc wd;
   if (PLACED) {
     wd = wide ? wide_desc(g, gd.k, pe) : patch_desc(g, gd.k, pe);
-    const uint16_t* ends = (const uint16_t*)(s.w + 3 * caps.n_groups + 1) + G * (g.NW + (g.NW == 16 ? kWidePatches : 0)) + (wide ? g.NW : 0);
+    const uint16_t* ends = (const uint16_t*)(s.w + 3 * caps.n_groups + 1) + G * (g.NW + g.n_wide) + (wide ? g.NW : 0);
     const int begin = w > 0 ? ends[w - 1] : 0;
     wd.step_begin = (int)s.w[3 * G + (wide ? 1 : 0)] + begin;
     wd.n_steps = ends[w] - begin;
@@ -1110,7 +1122,7 @@ litevar_status build_plan(PlanSpec& sp, const PlanSizes& z, void* d_blob, hipStr
   }
   const int n_all = g.n_groups * g.n_hg;
   const int nw = n_all * g.NW;
-  const int n_wide = g.NW == 16 ? n_all * kWidePatches : 0;
+  const int n_wide = n_all * g.n_wide;
   Places s;
   if (place(sp, s)) {
     hipLaunchKernelGGL(k_fill<Places>, dim3(nw + n_wide + n_all), dim3(64), 0, st, g, p, caps, nw, s);
