@@ -33,10 +33,11 @@ struct PlanSpec {
   int n_heads = 0;                      // 0: one table for all heads
   std::vector<int16_t> rad_all;         // [n_hg][K][K]
   uint8_t head_group[kMaxHeads] = {};   // head -> head group
-  // set by size_plan, for plans of at most kMostPlacedGroups groups: the phases of every group, and the steps of
-  // every patch of every group (the wide ones after the others)
+  // set by size_plan, for plans of at most kMostPlacedGroups groups: the phases of every group, and the steps and kept
+  // pairs of every patch of every group (the wide ones after the others)
+  struct PatchCount { uint16_t steps, pairs; };         // (pairs: of their number, the low 16 bits)
   std::vector<int32_t> group_phases;
-  std::vector<uint16_t> patch_steps;
+  std::vector<PatchCount> patch_counts;
   void load_head_group(int hg) {
     for (int k = 0; k < g.K; ++k)
       for (int j = 0; j < g.K; ++j) g.rad[k][j] = rad_all[((size_t)hg * g.K + k) * g.K + j];

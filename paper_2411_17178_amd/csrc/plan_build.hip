@@ -179,7 +179,7 @@ litevar_status size_plan(PlanSpec& sp, PlanSizes& z) {
   if (g_last_sizing.valid && same_spec(g_last_sizing.sp, sp)) {
     z = g_last_sizing.z;
     sp.g.n_wide = z.n_wide;
-    sp.group_phases = g_last_sizing.sp.group_phases; sp.patch_steps = g_last_sizing.sp.patch_steps;
+    sp.group_phases = g_last_sizing.sp.group_phases; sp.patch_counts = g_last_sizing.sp.patch_counts;
     return LITEVAR_OK;
   }
   litevar_status rc = size_plan_uncached(sp, z);
@@ -241,7 +241,10 @@ constexpr int64_t kMostSteps = (int64_t)1 << 26;
 static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
   HostGeom& g = sp.g;
   const bool keep_places = (int64_t)g.n_groups * g.n_hg <= kMostPlacedGroups;
-  sp.group_phases.clear(); sp.patch_steps.clear();
+  sp.group_phases.clear(); sp.patch_counts.clear();
+  auto keep_count = [&](int steps, int64_t pairs) {
+    if (keep_places) sp.patch_counts.push_back({(uint16_t)steps, (uint16_t)pairs});
+  };
   memset(&z, 0, sizeof z);
   std::vector<AxisSpan> ax;            // window mode: [key scale][patch row or column of the query scale]
   std::vector<AxisSpan> wide_rows, wide_cols;   // the same of the wide patches: [key scale][group row, patch row in it]
@@ -325,8 +328,9 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
         if (keep_places) sp.group_phases.push_back(nph);
         for (int w = 0; w < g.NW; ++w) {
           const PatchExtent p = patch_extent(g, k, gy, gx, w);
-          if (p.ny == 0) { if (keep_places) sp.patch_steps.push_back(0); continue; }
+          if (p.ny == 0) { keep_count(0, 0); continue; }
           StepCounter steps{g};
+          int64_t pairs = 0;
           if (g.mode == kModeBand) {
             int ubase = 0;
             for (int pt = 0; pt < band_parts(k); ++pt) {
@@ -335,25 +339,26 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
               AxisSpan a;
               for (int n = 0; n < p.nx; ++n) a.add(band_interval(b, nk, p.y0 + n));
               for (int i = 0; i < a.n_runs; ++i) steps.run(ubase + a.run[i].lo - glo, a.run[i].hi - a.run[i].lo + 1);
-              pairs_hg += a.kept;
+              pairs += a.kept;
               ubase += ghi - glo + 1;
             }
           } else {
             const AxisSpan *rows = &ax[p.y0 / kPatch], *cols = &ax[p.x0 / kPatch];
             for (int j = 0; j <= k; ++j, rows += pps, cols += pps) {
               add_box(steps, *rows, *cols, boxes[j]);
-              pairs_hg += (int64_t)rows->kept * cols->kept;
+              pairs += (int64_t)rows->kept * cols->kept;
             }
           }
           const int ns = steps.finish();
           if (ns > kMostPatchSteps) return fail(LITEVAR_E_UNSUPPORTED, "a query patch needs more than 65535 steps");
-          z.n_steps += ns;
-          if (keep_places) sp.patch_steps.push_back((uint16_t)ns);
+          z.n_steps += ns; pairs_hg += pairs;
+          keep_count(ns, pairs);
         }
         for (int w = 0; w < g.n_wide; ++w) {
           const PatchExtent p = wide_extent(g, k, gy, gx, w);
-          if (p.ny == 0) { if (keep_places) sp.patch_steps.push_back(0); continue; }
+          if (p.ny == 0) { keep_count(0, 0); continue; }
           StepCounter steps{g};
+          int64_t pairs = 0;
           if (g.mode == kModeBand) {
             int ubase = 0;
             for (int pt = 0; pt < band_parts(k); ++pt) {
@@ -362,6 +367,7 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
               AxisSpan a;
               for (int n = 0; n < p.nx; ++n) a.add(band_interval(b, nk, p.y0 + n));
               for (int i = 0; i < a.n_runs; ++i) steps.run(ubase + a.run[i].lo - glo, a.run[i].hi - a.run[i].lo + 1);
+              pairs += a.kept;
               ubase += ghi - glo + 1;
             }
           } else {
@@ -369,12 +375,13 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
             for (int j = 0; j <= k; ++j, rows += ngy * wny, cols += ngx * wnx) {
               if (dealt_box(g.mode, boxes[j].base)) add_dealt_box(steps, *rows, *cols, boxes[j]);
               else add_box(steps, *rows, *cols, boxes[j]);
+              pairs += (int64_t)rows->kept * cols->kept;
             }
           }
           const int ns = steps.finish();
           z.n_wide_steps += ns;
           if (ns > kMostPatchSteps || z.n_wide_steps > kMostSteps) { g.n_wide = 0; return LITEVAR_OK; }
-          if (keep_places) sp.patch_steps.push_back((uint16_t)ns);
+          keep_count(ns, pairs);
         }
       }
     }
@@ -427,8 +434,10 @@ struct Caps { int64_t n_steps, n_union, n_phase_entries, retained_pairs, n_wide_
 // Where the patches and groups of a smaller plan go: the host counts the steps of every patch anyway, so as many as
 // fit the 4 KiB argument block travel with k_fill, which then needs no count and no scan ahead of it.  (30 tables
 // of 13 x 13 queries, 60 groups: k_count and k_scan took 16 + 6 of the 52 us that the builder's launches took.)
-// Words: first step, first wide step and first phase of every group; then the phases of all; then, two to a word,
-// for every patch the steps of its group up to it, itself included (the wide patches after the others).
+// Words: first step, first wide step and first phase of every group; then the phases of all; then for every patch the
+// steps of its group up to it, itself included, and the low half of its kept pairs' number << 16 (the wide patches after
+// the others).  A walk that ends at other steps or pairs than the host's marks the plan; pairs that differ by a multiple of
+// 65536 at the same steps of at most 1024 pairs would take 64 steps of wrong masks.
 struct Places { uint32_t w[kPlaceWords]; };
 struct NoPlaces { uint32_t w[1]; };
 static_assert(sizeof(Places) + sizeof(Geom) + sizeof(BlobPtrs) + sizeof(Caps) + 16 <= 4096, "kernel argument block");
@@ -436,19 +445,19 @@ static_assert(sizeof(Places) + sizeof(Geom) + sizeof(BlobPtrs) + sizeof(Caps) + 
 // false: they don't fit
 static bool place(const PlanSpec& sp, Places& s) {
   const int n = (int)sp.group_phases.size(), per = sp.g.NW + sp.g.n_wide;
-  if (n == 0 || n != sp.g.n_groups * sp.g.n_hg || 3 * n + 1 + (n * per + 1) / 2 > kPlaceWords) return false;
+  if (n == 0 || n != sp.g.n_groups * sp.g.n_hg || 3 * n + 1 + n * per > kPlaceWords) return false;
   uint32_t at[2] = {0, 0}, phases = 0;
-  uint16_t* ends = (uint16_t*)(s.w + 3 * n + 1);
-  const uint16_t* steps = sp.patch_steps.data();
+  uint32_t* ends = s.w + 3 * n + 1;
+  const PlanSpec::PatchCount* count = sp.patch_counts.data();
   for (int G = 0; G < n; ++G) {
     s.w[3 * G] = at[0]; s.w[3 * G + 1] = at[1]; s.w[3 * G + 2] = phases;
     phases += (uint32_t)sp.group_phases[G];
     uint32_t in[2] = {0, 0};
-    for (int w = 0; w < per; ++w) {
+    for (int w = 0; w < per; ++w, ++count) {
       uint32_t& sum = in[w >= sp.g.NW];
-      sum += *steps++;
+      sum += count->steps;
       if (sum > 65535) return false;
-      *ends++ = (uint16_t)sum;
+      *ends++ = sum | (uint32_t)count->pairs << 16;
     }
     at[0] += in[0]; at[1] += in[1];
   }
@@ -927,6 +936,7 @@ struct FillSink {
   int n_steps, n_phases;               // what the plan has room for (the counts agree with the walk, or nothing beyond is written)
   int chunk = 0;                       // chunk of the last closed step: phase_end is written up to it
   int pairs = 0;                       // this lane's share of the kept pairs
+  int ny = 0;                          // WIDE: of the patch (window mode), else 0
   int end0 = 0, end2 = 0;              // steps that end in chunk 0, in chunks 0 to 2
   // steps close in the order of their chunks, so the cumulative counts of the chunks that a step
   // skips are final when it closes: no counter is read back
@@ -945,7 +955,7 @@ struct FillSink {
     return slot * kRingRowBytes + 8u * half + 16u * ((b ^ sw) & 1u) + ((sw >> 1) << 5);
   }
   __device__ void keys(int, int idx, int upos, int t, unsigned qmask, bool take) {
-    if (take) pairs += __builtin_popcount(qmask);
+    if (take) pairs += WIDE && ny > 0 ? __builtin_popcount(qmask & ((1u << ny) - 1u)) * __builtin_popcount(qmask >> ny) : __builtin_popcount(qmask);
     if (take) { buf->slot[idx] = (uint32_t)(upos % R); buf->tok[idx] = t; buf->qmask[idx] = qmask; }
   }
   __device__ void close(int step, int n_keys, int last_upos) {
@@ -1002,7 +1012,7 @@ struct FillSink {
 // 480 patches of 30 head groups: 27 us, 35 us as two launches with counters that were read back; 30 us with the
 // places in its arguments, where k_count, k_scan and it took 50 and the launches' gaps.
 // With Places the places come with the arguments, and the descriptors and the header are written here; a patch whose
-// walk ends at another count than the host's marks the header, as k_scan does.
+// walk ends at other counts than the host's marks the header, as k_scan does.
 template <class PlacesArg>
 __global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int n_waves, PlacesArg s) {
   constexpr bool PLACED = sizeof(PlacesArg) > sizeof(NoPlaces);
@@ -1052,12 +1062,14 @@ __global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int 
   const PatchExtent pe = wide ? wide_extent(g, gd.k, gd.gy, gd.gx, w) : patch_extent(g, gd.k, gd.gy, gd.gx, w);
   WaveDesc* const out = p.waves + blockIdx.x;
   WaveDesc wd;
+  uint32_t host_pairs = 0;
   if (PLACED) {
     wd = wide ? wide_desc(g, gd.k, pe) : patch_desc(g, gd.k, pe);
-    const uint16_t* ends = (const uint16_t*)(s.w + 3 * caps.n_groups + 1) + G * (g.NW + g.n_wide) + (wide ? g.NW : 0);
-    const int begin = w > 0 ? ends[w - 1] : 0;
+    const uint32_t* ends = s.w + 3 * caps.n_groups + 1 + G * (g.NW + g.n_wide) + (wide ? g.NW : 0);
+    const int begin = w > 0 ? (int)(ends[w - 1] & 0xffffu) : 0;
     wd.step_begin = (int)s.w[3 * G + (wide ? 1 : 0)] + begin;
-    wd.n_steps = ends[w] - begin;
+    wd.n_steps = (int)(ends[w] & 0xffffu) - begin;
+    host_pairs = ends[w] >> 16;
   } else {
     wd = *out;
   }
@@ -1077,10 +1089,11 @@ __global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int 
     FillSink<true> sink;
     fill(sink, true);
     sink.addr = (uint2*)((char*)p.step_addr + (int64_t)wd.step_begin * 64 * kWideDesc);
-    sink.mask = nullptr; sink.toks = nullptr;
+    sink.mask = nullptr; sink.toks = nullptr; sink.ny = g.mode == kModeBand ? 0 : pe.ny;
     ns = wave_walk_patch<true>(g, t.win, t.rad, e, pe, sink, lane);
     sink.fill_ends(sink.chunk, gd.n_phases, ns);
     first_ends = (uint32_t)sink.end0 | ((uint32_t)sink.end2 << 16);   // (a patch has at most 65535 steps)
+    if (PLACED) pairs = sum_of_lanes(sink.pairs);
   } else {
     FillSink<false> sink;
     fill(sink, false);
@@ -1093,7 +1106,7 @@ __global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int 
     if (PLACED) pairs = sum_of_lanes(sink.pairs);
   }
   if (PLACED) {
-    if (ns != wd.n_steps) { p.hdr->error = kErrBuilder; return; }
+    if (ns != wd.n_steps || ((uint32_t)pairs & 0xffffu) != host_pairs) { p.hdr->error = kErrBuilder; return; }
     if (!wide) wd.pairs = pairs;
     wd.first_ends = first_ends;
     if (lane == 0) *out = wd;
