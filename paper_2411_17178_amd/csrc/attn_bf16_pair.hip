@@ -128,8 +128,8 @@ __device__ inline void lds_read_v_wide(const unsigned (&v)[4], const unsigned (&
                : "v"(v[0]), "v"(x[0]), "v"(v[1]), "v"(x[1]), "v"(v[2]), "v"(x[2]), "v"(v[3]), "v"(x[3]),
                  "i"(VOFF) : "memory");
 }
-struct WideArgs {         // the wide patches' entries in the blob, where the plan has them
-  const WaveDesc* waves; const int32_t* phase_end; const unsigned char* step_addr; const int32_t* union_tok;
+struct WideArgs {
+  const WaveDesc* waves;  // the wide patches
   int boost;              // all workgroups of the launch are resident at once
 };
 
@@ -240,7 +240,7 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
   const unsigned char* Kp = (const unsigned char*)a.k + (b * a.ks[0] + h * a.ks[1]) * kElem;
   const unsigned char* Vp = (const unsigned char*)a.v + (b * a.ks[0] + h * a.ks[1]) * kElem;
   const unsigned row_bytes = (unsigned)a.ks[2] * kElem;   // a (batch, head) slab spans < 2 GiB (checked by the API)
-  const int32_t* utok = (WIDE ? wide.union_tok : a.union_tok) + gd.union_base;
+  const int32_t* utok = a.union_tok + gd.union_base;
   // bf16: eight lanes per 128-byte row; Q8: four lanes per 64-byte row of codes
   const int row = Q8 ? 8 * (wave & 7) + ((lane >> 2) & 7) : 8 * (wave & 7) + (lane >> 3);
   // A lane's row of chunk t goes to slot (t % 5) * 64 + row.  Chunks start at multiples of 64
@@ -309,7 +309,7 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
   const WaveDesc* const patches = (WIDE ? wide.waves : a.waves) + grp_g * kPerGroup;
   const const_i32_ptr wA = (const_i32_ptr)(patches + wave);
   const const_i32_ptr wF = (const_i32_ptr)patches, wL = (const_i32_ptr)(patches + kPerGroup - 1);
-  const const_i32_ptr pe = (const_i32_ptr)((WIDE ? wide.phase_end + gd.phase_base / 2 : a.phase_end + gd.phase_base) + wave * NC);
+  const const_i32_ptr pe = (const_i32_ptr)(a.phase_end + gd.phase_base + wave * NC);
   auto last_chunk = [&](int ph) -> int { return min(2 * ph, NC - 1); };   // of phase ph (clamped)
   struct PatchWords { int step_begin, q_base, sk_ny, nx_kq, magic, valid; };   // (the wide patches' band has sk = 0)
   const PatchWords pw = {wA[0], wA[2], wA[3], WIDE ? wA[4] : 0, WIDE ? wA[5] : 0, wA[6]};
@@ -342,9 +342,9 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
   // Step descriptors: 8 bytes per lane; wide patches 16, the mask included.
   using Desc = std::conditional_t<WIDE, u32x4, uint2>;
   constexpr int kDescLane = WIDE ? kWideDesc : 8, kDescBytes = 64 * kDescLane;
-  const unsigned char* const step_desc = WIDE ? wide.step_addr : (const unsigned char*)a.step_addr;
+  const unsigned char* const step_desc = (const unsigned char*)a.step_addr;
   const __amdgpu_buffer_rsrc_t desc_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(step_desc + (int64_t)pw.step_begin * kDescBytes), 0, (last + 1) * kDescBytes, kBufferFlags);
+      (void*)(step_desc + (int64_t)pw.step_begin * kDescBytes), 0, wA[1] * kDescBytes, kBufferFlags);   // (an idle patch's reads give zeros)
   const int lane_desc = lane * kDescLane;
   auto load_desc = [&](int s) -> Desc {
     if constexpr (WIDE) {
@@ -789,16 +789,11 @@ litevar_status launch_attn_bf16_pair(const litevar_plan* pl, const AttnArgs& arg
   // (A plan has wide patches where its section of patches holds theirs: a group's 16 descriptors are 512 bytes and its
   // eight wide ones 256, so the section has no padding.)
   const bool has_wide = pl->off[kSecPhaseEnd] - pl->off[kSecWaves] == (uint64_t)groups * (16 + kWidePatches) * sizeof(WaveDesc);
-  if (has_wide && pl->patches_per_wave == 1) return fail(LITEVAR_E_PLAN_CORRUPT, "a plan of sixteen waves with wide patches");
+  if ((has_wide && pl->patches_per_wave == 1) || pl->off[kSecStepAddr] - pl->off[kSecUnion] != (uint64_t)pl->n_union_keys * sizeof(int32_t))
+    return fail(LITEVAR_E_PLAN_CORRUPT, "the plan's sections are not those of this library");
   const int pw = has_wide ? 2 : 1;
   WideArgs w{};
-  if (pw == 2) {
-    w.waves = a.waves + groups * 16;
-    w.phase_end = a.phase_end + pl->n_union_keys / pl->chunk_keys * 16;
-    w.union_tok = a.union_tok + pl->n_union_keys;
-    // (the wide steps come first in their section)
-    w.step_addr = (const unsigned char*)a.step_addr;
-  }
+  w.waves = a.waves + groups * 16;
   // all workgroups are resident at once (two per CU): see later_arrival
   static thread_local int n_cu[64] = {0};
   int dev = 0;

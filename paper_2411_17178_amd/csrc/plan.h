@@ -20,7 +20,8 @@
 //           carry a second work-list over the same key list: up to eight wide patches (4 x 8
 //           queries, or what covers the group's queries with the fewest key rows; band mode: 32
 //           consecutive queries) with steps of 32 keys of their own.  The 16-patch kernel's eight-wave form
-//           walks it; the exports and the other kernels walk the patches of 16.  Plans that ask for the sixteen-wave
+//           walks it, and the list's order, the phase tables and the ring offsets of the steps are theirs; of the patches of
+//           16 such plans hold tokens and masks only, which the exports, the fp32 kernel and attend_row read.  Plans that ask for the sixteen-wave
 //           form (patches_per_wave = 1) have none, nor have plans one of whose wide patches would need more
 //           than 65535 steps: their box can be larger than those of its two patches of 16.
 #pragma once
@@ -80,7 +81,7 @@ struct GroupDesc {   // 32 bytes
   int32_t n_phases;    // ceil(n_union / C), >= 1
   int32_t k;           // query scale
   int32_t gy, gx;      // group position in units of groups (band mode: gy = index in the scale, gx = 0)
-  int32_t phase_base;  // first entry in phase_end (NW * n_phases int32 entries, wave-major)
+  int32_t phase_base;  // first entry in phase_end (walked_patches * n_phases int32 entries, wave-major)
   int32_t ident;       // union entries [0, ident) hold token i at position i
 };
 
@@ -237,6 +238,9 @@ LV_HD int dealt_row(int i, int rows) {     // row of the box at place i
   const int a = rows >> 2, b = rows & 3, strip = i < 4 * a ? i & 3 : i - 4 * a, round = i < 4 * a ? i >> 2 : a;
   return strip * a + (strip < b ? strip : b) + round;
 }
+
+// patches of a group whose steps walk the key list: phase tables, ring offsets and the list's order are theirs
+LV_HD int walked_patches(const Geom& g) { return g.n_wide ? g.n_wide : g.NW; }
 
 LV_HD int patches_per_side(const Geom& g, int k) { return (g.s[k] + kPatch - 1) / kPatch; }
 LV_HD int scale_patches(const Geom& g, int k) {

@@ -324,7 +324,7 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
         }
         const int nph = (nu + g.C - 1) / g.C;
         z.n_union += (int64_t)nph * g.C;
-        z.n_phase_entries += (int64_t)nph * g.NW;
+        z.n_phase_entries += (int64_t)nph * walked_patches(g);
         if (keep_places) sp.group_phases.push_back(nph);
         for (int w = 0; w < g.NW; ++w) {
           const PatchExtent p = patch_extent(g, k, gy, gx, w);
@@ -391,7 +391,6 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
   if (z.n_steps > kMostSteps || z.n_union > (int64_t)1 << 30)
     return fail(LITEVAR_E_UNSUPPORTED, "work-list too large (%lld steps)", (long long)z.n_steps);
   const uint64_t ngt = (uint64_t)g.n_groups * g.n_hg;
-  const bool wide = g.n_wide > 0;      // (the wide patches' entries follow the others in their sections; their steps' descriptors come first)
   uint64_t o = 0;
   z.off[kSecHeader] = o; o += sizeof(Header);
   z.off[kSecWin] = o;
@@ -400,9 +399,9 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
   z.off[kSecHeadMap] = o; o = align256(o + (uint64_t)kMaxHeads * sizeof(int32_t));
   z.off[kSecGroups] = o; o = align256(o + ngt * sizeof(GroupDesc));
   z.off[kSecWaves] = o; o = align256(o + ngt * (g.NW + g.n_wide) * sizeof(WaveDesc));
-  z.off[kSecPhaseEnd] = o; o = align256(o + (uint64_t)(z.n_phase_entries + (wide ? z.n_phase_entries / 2 : 0)) * sizeof(int32_t));
-  z.off[kSecUnion] = o; o = align256(o + (uint64_t)z.n_union * (wide ? 2 : 1) * sizeof(int32_t));
-  z.off[kSecStepAddr] = o; o = align256(o + (uint64_t)z.n_steps * 64 * sizeof(uint2) + (uint64_t)z.n_wide_steps * 64 * kWideDesc);
+  z.off[kSecPhaseEnd] = o; o = align256(o + (uint64_t)z.n_phase_entries * sizeof(int32_t));
+  z.off[kSecUnion] = o; o = align256(o + (uint64_t)z.n_union * sizeof(int32_t));
+  z.off[kSecStepAddr] = o; o = align256(o + (uint64_t)(g.n_wide ? z.n_wide_steps * kWideDesc : z.n_steps * (int64_t)sizeof(uint2)) * 64);
   z.off[kSecStepMask] = o; o = align256(o + (uint64_t)z.n_steps * 8 * sizeof(uint64_t));
   z.off[kSecStepTok] = o; o = align256(o + (uint64_t)z.n_steps * kStepKeys * sizeof(int32_t));
   z.off[kSecEnd] = o;
@@ -823,7 +822,7 @@ __global__ __launch_bounds__(1024) void k_scan(Geom g, BlobPtrs p, Caps caps, in
   const int g1 = g0 + per < n_all ? g0 + per : n_all;
   int64_t v[kSums] = {0, 0, 0, 0, 0};                   // steps, union keys, phase entries, pairs, wide patches' steps
   for (int grp = g0; grp < g1; ++grp) {
-    v[1] += (int64_t)p.groups[grp].n_phases * g.C; v[2] += (int64_t)p.groups[grp].n_phases * g.NW;
+    v[1] += (int64_t)p.groups[grp].n_phases * g.C; v[2] += (int64_t)p.groups[grp].n_phases * walked_patches(g);
 #pragma unroll 4
     for (int w = 0; w < g.NW; ++w) { v[0] += p.waves[grp * g.NW + w].n_steps; v[3] += p.waves[grp * g.NW + w].pairs; }
 #pragma unroll 4
@@ -848,7 +847,7 @@ __global__ __launch_bounds__(1024) void k_scan(Geom g, BlobPtrs p, Caps caps, in
   for (int grp = g0; grp < g1; ++grp) {
     GroupDesc& gd = p.groups[grp];
     gd.union_base = (int32_t)uni; gd.phase_base = (int32_t)phe;
-    uni += (int64_t)gd.n_phases * g.C; phe += (int64_t)gd.n_phases * g.NW;
+    uni += (int64_t)gd.n_phases * g.C; phe += (int64_t)gd.n_phases * walked_patches(g);
     for (int w = 0; w < g.NW; ++w) {
       WaveDesc& wd = p.waves[grp * g.NW + w];
       wd.step_begin = (int32_t)steps; steps += wd.n_steps;
@@ -876,7 +875,6 @@ __global__ __launch_bounds__(1024) void k_scan(Geom g, BlobPtrs p, Caps caps, in
 __device__ void fill_union(const Geom& g, const BlobPtrs& p, const Caps& caps, const GroupTables& t, const GroupDesc& gd) {
   const GroupExtent e = group_extent(g, gd.k, gd.gy, gd.gx);
   int32_t* out = p.union_tok + gd.union_base;
-  int32_t* wide = g.n_wide ? out + caps.n_union : nullptr;   // the wide patches' list, some of whose boxes are dealt
   if ((int64_t)gd.union_base + (int64_t)gd.n_phases * g.C > caps.n_union) return;
   int ubase = 0, last_tok = 0;
   if (g.mode == kModeBand) {
@@ -885,10 +883,7 @@ __device__ void fill_union(const Geom& g, const BlobPtrs& p, const Caps& caps, c
       const BandPart b = band_part(g, t.rad, e.k, pt);
       const int glo = band_interval(b, nk, e.qy0).lo, ghi = band_interval(b, nk, e.qy1).hi;
       const int n = ghi - glo + 1;
-      for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        out[ubase + i] = b.tok0 + glo + i;
-        if (wide) wide[ubase + i] = b.tok0 + glo + i;
-      }
+      for (int i = threadIdx.x; i < n; i += blockDim.x) out[ubase + i] = b.tok0 + glo + i;
       ubase += n;
       last_tok = b.tok0 + ghi;
     }
@@ -899,20 +894,16 @@ __device__ void fill_union(const Geom& g, const BlobPtrs& p, const Caps& caps, c
     for (int j = 0; j <= e.k; ++j) {
       const Box b = boxes[j];
       const int gw = b.xhi - b.xlo + 1, n = (b.yhi - b.ylo + 1) * gw;
-      const bool dealt = dealt_box(g.mode, ubase);
+      const bool dealt = g.n_wide > 0 && dealt_box(g.mode, ubase);
       for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        const int row = i / gw, first = g.off[j] + b.xlo + i - row * gw;
-        out[ubase + i] = first + (b.ylo + row) * g.s[j];
-        if (wide) wide[ubase + i] = first + (b.ylo + (dealt ? dealt_row(row, b.yhi - b.ylo + 1) : row)) * g.s[j];
+        const int row = i / gw;
+        out[ubase + i] = g.off[j] + (b.ylo + (dealt ? dealt_row(row, b.yhi - b.ylo + 1) : row)) * g.s[j] + b.xlo + i - row * gw;
       }
       ubase += n;
       last_tok = g.off[j] + b.yhi * g.s[j] + b.xhi;
     }
   }
-  for (int i = gd.n_union + threadIdx.x; i < gd.n_phases * g.C; i += blockDim.x) {
-    out[i] = last_tok;
-    if (wide) wide[i] = last_tok;
-  }
+  for (int i = gd.n_union + threadIdx.x; i < gd.n_phases * g.C; i += blockDim.x) out[i] = last_tok;
 }
 
 // Step under construction: the wave's lanes deposit the keys they place (ring slot, token,
@@ -982,9 +973,11 @@ struct FillSink {
       end_step(step, last_upos);
       return;
     }
-    const uint32_t k0 = k_off(slot_of(n), g4), k1 = k_off(slot_of(16 + n), g4);
-    const uint32_t v0 = v_off(slot_of(4 * g4 + (n >> 2)), n), v1 = v_off(slot_of(16 + 4 * g4 + (n >> 2)), n);
-    addr[(int64_t)step * 64 + lane] = make_uint2(k0 | (k1 << 16), v0 | (v1 << 16));
+    if (addr) {
+      const uint32_t k0 = k_off(slot_of(n), g4), k1 = k_off(slot_of(16 + n), g4);
+      const uint32_t v0 = v_off(slot_of(4 * g4 + (n >> 2)), n), v1 = v_off(slot_of(16 + 4 * g4 + (n >> 2)), n);
+      addr[(int64_t)step * 64 + lane] = make_uint2(k0 | (k1 << 16), v0 | (v1 << 16));
+    }
     uint64_t mine = 0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -995,7 +988,7 @@ struct FillSink {
     }
     if (lane < 8) mask[(int64_t)step * 8 + lane] = mine;
     if (lane < kStepKeys) toks[(int64_t)step * kStepKeys + lane] = lane < n_keys ? buf->tok[lane] : -1;
-    end_step(step, last_upos);
+    if (addr) end_step(step, last_upos);
   }
   __device__ void end_step(int step, int last_upos) {
     const int c = last_upos >> logC;
@@ -1030,7 +1023,7 @@ __global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int 
     group_coords(g, t.grp, gd.k, gd.gy, gd.gx);
     const int phase0 = (int)s.w[3 * G + 2];
     gd.n_phases = (int)s.w[G + 1 < caps.n_groups ? 3 * G + 5 : 3 * caps.n_groups] - phase0;
-    gd.union_base = phase0 * g.C; gd.phase_base = phase0 * g.NW;
+    gd.union_base = phase0 * g.C; gd.phase_base = phase0 * walked_patches(g);
   } else {
     gd = p.groups[G];
   }
@@ -1074,20 +1067,20 @@ __global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int 
     wd = *out;
   }
   if ((int64_t)wd.step_begin + wd.n_steps > (wide ? caps.n_wide_steps : caps.n_steps) ||
-      (int64_t)gd.phase_base + (int64_t)gd.n_phases * g.NW > caps.n_phase_entries) {
+      (int64_t)gd.phase_base + (int64_t)gd.n_phases * walked_patches(g) > caps.n_phase_entries) {
     if (PLACED) p.hdr->error = kErrBuilder;
     return;
   }
   int ns, pairs = 0;
   uint32_t first_ends;
-  auto fill = [&](auto& sink, bool is_wide) {
+  auto fill = [&](auto& sink) {
     sink.buf = &buf; sink.R = g.R; sink.logC = g.logC; sink.lane = lane;
     sink.n_steps = wd.n_steps; sink.n_phases = gd.n_phases;
-    sink.phase_end = p.phase_end + (is_wide ? caps.n_phase_entries + gd.phase_base / 2 : (int64_t)gd.phase_base) + (int64_t)w * gd.n_phases;
+    sink.phase_end = p.phase_end + gd.phase_base + (int64_t)w * gd.n_phases;
   };
   if (wide) {
     FillSink<true> sink;
-    fill(sink, true);
+    fill(sink);
     sink.addr = (uint2*)((char*)p.step_addr + (int64_t)wd.step_begin * 64 * kWideDesc);
     sink.mask = nullptr; sink.toks = nullptr; sink.ny = g.mode == kModeBand ? 0 : pe.ny;
     ns = wave_walk_patch<true>(g, t.win, t.rad, e, pe, sink, lane);
@@ -1096,12 +1089,12 @@ __global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int 
     if (PLACED) pairs = sum_of_lanes(sink.pairs);
   } else {
     FillSink<false> sink;
-    fill(sink, false);
-    sink.addr = p.step_addr + (caps.n_wide_steps * (64 * kWideDesc) / (int64_t)sizeof(uint2)) + (int64_t)wd.step_begin * 64;
+    fill(sink);
+    sink.addr = g.n_wide ? nullptr : p.step_addr + (int64_t)wd.step_begin * 64;      // (wide patches: nobody walks the list in these steps)
     sink.mask = p.step_mask + (int64_t)wd.step_begin * 8;
     sink.toks = p.step_tok + (int64_t)wd.step_begin * kStepKeys;
     ns = wave_walk_patch<false>(g, t.win, t.rad, e, pe, sink, lane);
-    sink.fill_ends(sink.chunk, gd.n_phases, ns);
+    if (sink.addr) sink.fill_ends(sink.chunk, gd.n_phases, ns);
     first_ends = (uint32_t)sink.end0 | ((uint32_t)sink.end2 << 16);
     if (PLACED) pairs = sum_of_lanes(sink.pairs);
   }

@@ -28,8 +28,8 @@ def _decode(plan, band, head):
     groups = _words(blob, off[SEC_GROUPS], n_all, 8)
     waves = _words(blob, off[SEC_WAVES] + n_all * 16 * 32, n_all * 8, 8)
     n_phases = int(plan.n_union_keys) // 64
-    phases = _words(blob, off[SEC_PHASES] + PHASES_BEFORE * n_phases * 4, 1, 8 * n_phases)[0]
-    union = _words(blob, off[SEC_UNION] + LISTS_BEFORE * int(plan.n_union_keys) * 4, 1, int(plan.n_union_keys))[0]
+    phases = _words(blob, off[SEC_PHASES], 1, 8 * n_phases)[0]
+    union = _words(blob, off[SEC_UNION], 1, int(plan.n_union_keys))[0]
     rows, toks = [], []
     for G in range(hg * plan.n_groups, (hg + 1) * plan.n_groups):
         union_base, n_union, nph = int(groups[G, 0]), int(groups[G, 1]), int(groups[G, 2])
@@ -75,7 +75,6 @@ def _decode(plan, band, head):
     return np.concatenate(rows), np.concatenate(toks)
 
 
-PHASES_BEFORE, LISTS_BEFORE = 16, 1              # what precedes the wide patches' entries in their sections
 LISTS = [((1, 2, 3, 4, 5, 6, 7, 8), 1, None), ((9, 10, 11), 2, None), ((3, 13, 14), 0, (1, 3)), ((2, 17), 3, None), ((5, 19, 21), 2, (2, 3)),
          ((33, 7), 4, None), ((1, 3, 30), 40, None), ((12, 25), -1, (1, 2)), ((4, 9, 16), [2, 0, 5], None), ((20, 24), 5, (1, 2)),
          (workloads.configs.VAR256, 3, (9, 10)), (workloads.configs.VAR512, 4, (8, 10))]
