@@ -13,6 +13,8 @@ namespace lv {
 litevar_status fail(litevar_status code, const char* fmt, ...);
 litevar_status hip_check(hipError_t e, const char* what);
 
+constexpr int kPairsModulus = 251;
+
 struct PlanSizes {
   int64_t n_steps, n_union, n_phase_entries, retained_pairs;   // summed over the head groups
   int64_t n_wide_steps;                                        // of the wide patches
@@ -22,9 +24,6 @@ struct PlanSizes {
   uint64_t bytes;
 };
 
-constexpr int kPlaceWords = 768;                        // (of k_fill's arguments)
-constexpr int kMostPlacedGroups = kPlaceWords / 3;
-
 // What a mask descriptor asks for: the geometry, and one radius table per head group
 // (heads with equal tables share a group).  g.rad holds the table of the group that was
 // loaded last; make_spec and size_plan leave group 0 loaded.
@@ -33,9 +32,9 @@ struct PlanSpec {
   int n_heads = 0;                      // 0: one table for all heads
   std::vector<int16_t> rad_all;         // [n_hg][K][K]
   uint8_t head_group[kMaxHeads] = {};   // head -> head group
-  // set by size_plan, for plans of at most kMostPlacedGroups groups: the phases of every group, and the steps and kept
-  // pairs of every patch of every group (the wide ones after the others)
-  struct PatchCount { uint16_t steps, pairs; };         // (pairs: of their number, the low 16 bits)
+  // set by size_plan: the phases of every group, and the steps and kept pairs of every patch of every group (the wide
+  // ones after the others)
+  struct PatchCount { uint16_t steps; uint8_t pairs; };      // (pairs: modulo kPairsModulus)
   std::vector<int32_t> group_phases;
   std::vector<PatchCount> patch_counts;
   void load_head_group(int hg) {

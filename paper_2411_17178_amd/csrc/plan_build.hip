@@ -1,10 +1,11 @@
 // Plan construction: host-side validation and sizing, device-side builder kernels
-// (tables, work-list count -> scan -> fill) and the parity exports.
+// (tables, places, fill) and the parity exports.
 #include "internal.h"
 
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 namespace lv {
@@ -240,11 +241,10 @@ constexpr int64_t kMostSteps = (int64_t)1 << 26;
 // clears sp.g.n_wide and stops where the wide patches would pass the limits
 static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
   HostGeom& g = sp.g;
-  const bool keep_places = (int64_t)g.n_groups * g.n_hg <= kMostPlacedGroups;
   sp.group_phases.clear(); sp.patch_counts.clear();
-  auto keep_count = [&](int steps, int64_t pairs) {
-    if (keep_places) sp.patch_counts.push_back({(uint16_t)steps, (uint16_t)pairs});
-  };
+  auto keep_count = [&](int steps, int64_t pairs) { sp.patch_counts.push_back({(uint16_t)steps, (uint8_t)(pairs % kPairsModulus)}); };
+  sp.group_phases.reserve((size_t)g.n_groups * g.n_hg);
+  sp.patch_counts.reserve((size_t)g.n_groups * g.n_hg * (g.NW + g.n_wide));
   memset(&z, 0, sizeof z);
   std::vector<AxisSpan> ax;            // window mode: [key scale][patch row or column of the query scale]
   std::vector<AxisSpan> wide_rows, wide_cols;   // the same of the wide patches: [key scale][group row, patch row in it]
@@ -325,7 +325,7 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
         const int nph = (nu + g.C - 1) / g.C;
         z.n_union += (int64_t)nph * g.C;
         z.n_phase_entries += (int64_t)nph * walked_patches(g);
-        if (keep_places) sp.group_phases.push_back(nph);
+        sp.group_phases.push_back(nph);
         for (int w = 0; w < g.NW; ++w) {
           const PatchExtent p = patch_extent(g, k, gy, gx, w);
           if (p.ny == 0) { keep_count(0, 0); continue; }
@@ -430,38 +430,70 @@ static BlobPtrs blob_ptrs(void* blob, const uint64_t* off) {
 
 struct Caps { int64_t n_steps, n_union, n_phase_entries, retained_pairs, n_wide_steps; uint64_t bytes; int n_groups; };
 
-// Where the patches and groups of a smaller plan go: the host counts the steps of every patch anyway, so as many as
-// fit the 4 KiB argument block travel with k_fill, which then needs no count and no scan ahead of it.  (30 tables
-// of 13 x 13 queries, 60 groups: k_count and k_scan took 16 + 6 of the 52 us that the builder's launches took.)
-// Words: first step, first wide step and first phase of every group; then the phases of all; then for every patch the
-// steps of its group up to it, itself included, and the low half of its kept pairs' number << 16 (the wide patches after
-// the others).  A walk that ends at other steps or pairs than the host's marks the plan; pairs that differ by a multiple of
-// 65536 at the same steps of at most 1024 pairs would take 64 steps of wrong masks.
-struct Places { uint32_t w[kPlaceWords]; };
-struct NoPlaces { uint32_t w[1]; };
+// Where the patches and groups of a plan go.  The host counts the steps of every patch anyway, so the counts travel with
+// the builder's launches and nothing is counted on the device: with k_fill's own arguments where all of them
+// fit, else ahead of it with k_place's, as many groups to a launch as the 4 KiB argument block takes: 66 of 16 patches.
+// All launches of a build, with counting walks and a scan on the device / like this (and before there were wide patches):
+// 34 240 tokens 174 / 82 us (103), 36 tables of 2240 tokens 252 / 143 (154).  A launch of k_place takes 3.3.
+// A list's words: first step, first wide step and first phase of every group, the phases up to its end, and for every patch
+// a Count of its steps and its kept pairs modulo 251 (the wide patches after the others): 16 bits where no patch has
+// more than 255 steps, else 32.  A walk that ends at other steps or pairs than the host's marks the plan (a wrong mask
+// bit is a wrong pair; a difference of a multiple of 251 in every patch that it touches passes).
+struct SmallCount {
+  uint16_t v;
+  static constexpr int kMost = 255;
+  __host__ __device__ static SmallCount of(int steps, int pairs) { return {(uint16_t)(steps | pairs << 8)}; }
+  __host__ __device__ int steps() const { return v & 0xff; }
+  __host__ __device__ int pairs() const { return v >> 8; }
+};
+struct LargeCount {
+  uint32_t v;
+  __host__ __device__ static LargeCount of(int steps, int pairs) { return {(uint32_t)steps | (uint32_t)pairs << 16}; }
+  __host__ __device__ int steps() const { return (int)(v & 0xffff); }
+  __host__ __device__ int pairs() const { return (int)(v >> 16); }
+};
+template <int N> struct PlaceList {
+  int first_group, n_groups;
+  uint32_t w[N];
+  template <class Count> __host__ __device__ const Count* counts() const { return (const Count*)(w + 3 * n_groups + 1); }
+  __host__ __device__ int phases_of(int i) const { return (int)(w[i + 1 < n_groups ? 3 * i + 5 : 3 * n_groups] - w[3 * i + 2]); }
+};
+constexpr int kInlineWords = (4096 - sizeof(Geom) - sizeof(BlobPtrs) - sizeof(Caps) - 40) / 4;
+constexpr int kLaunchWords = (4096 - sizeof(BlobPtrs) - 40) / 4;
+using Places = PlaceList<kInlineWords>;
+struct NoPlaces {};
 static_assert(sizeof(Places) + sizeof(Geom) + sizeof(BlobPtrs) + sizeof(Caps) + 16 <= 4096, "kernel argument block");
+static_assert(sizeof(PlaceList<kLaunchWords>) + sizeof(BlobPtrs) + 24 <= 4096, "kernel argument block");
 
-// false: they don't fit
-static bool place(const PlanSpec& sp, Places& s) {
-  const int n = (int)sp.group_phases.size(), per = sp.g.NW + sp.g.n_wide;
-  if (n == 0 || n != sp.g.n_groups * sp.g.n_hg || 3 * n + 1 + n * per > kPlaceWords) return false;
-  uint32_t at[2] = {0, 0}, phases = 0;
-  uint32_t* ends = s.w + 3 * n + 1;
-  const PlanSpec::PatchCount* count = sp.patch_counts.data();
-  for (int G = 0; G < n; ++G) {
-    s.w[3 * G] = at[0]; s.w[3 * G + 1] = at[1]; s.w[3 * G + 2] = phases;
-    phases += (uint32_t)sp.group_phases[G];
-    uint32_t in[2] = {0, 0};
-    for (int w = 0; w < per; ++w, ++count) {
-      uint32_t& sum = in[w >= sp.g.NW];
-      sum += count->steps;
-      if (sum > 65535) return false;
-      *ends++ = sum | (uint32_t)count->pairs << 16;
+// groups that fit into `words` words, with `per` patches each
+template <class Count> static int groups_in(int words, int per) { return (int)((4 * words - 8) / (12 + per * sizeof(Count))); }
+
+// Where the next group's steps, wide steps and phases begin
+struct PlaceAt { uint32_t step[2] = {0, 0}, phase = 0; };
+
+// the groups from `first` on, as many as there are and fit; `at` moves behind them
+template <class Count, int N> static void fill_list(const PlanSpec& sp, int first, PlaceAt& at, PlaceList<N>& list) {
+  const int per = sp.g.NW + sp.g.n_wide, n_all = (int)sp.group_phases.size();
+  list.first_group = first;
+  list.n_groups = std::min(n_all - first, groups_in<Count>(N, per));
+  uint32_t* w = list.w;
+  Count* c = (Count*)(w + 3 * list.n_groups + 1);
+  const PlanSpec::PatchCount* count = sp.patch_counts.data() + (size_t)first * per;
+  for (int i = 0; i < list.n_groups; ++i) {
+    *w++ = at.step[0]; *w++ = at.step[1]; *w++ = at.phase;
+    at.phase += (uint32_t)sp.group_phases[first + i];
+    for (int j = 0; j < per; ++j, ++count) {
+      at.step[j >= sp.g.NW] += count->steps;
+      *c++ = Count::of(count->steps, count->pairs);
     }
-    at[0] += in[0]; at[1] += in[1];
   }
-  s.w[3 * n] = phases;
-  return true;
+  *w = at.phase;
+}
+
+__device__ inline int sum_of_lanes(int v) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d);
+  return v;
 }
 
 // K1: the radius tables rad[hg][k][j] (-1: dense part), in window mode the window tables
@@ -551,6 +583,8 @@ struct WavePacker {
 
 // One key scale of the walk over a wide patch (window mode): ny + nx <= 12 lanes from l0 on hold the windows of its
 // query rows and columns, the last four of the sixteen those of the group's first and last row and column.
+// The rows of the box that some query keeps are closed up in lanes, each with the queries that keep it; a lane's column
+// is the same in every pass, so its queries are found once.
 template <class Sink>
 __device__ int wave_walk_wide_box(const PatchExtent& p, const Interval& mine, int l0, int sj, int offj, int ubase,
                                   WavePacker<Sink>& pack, int lane) {
@@ -560,20 +594,33 @@ __device__ int wave_walk_wide_box(const PatchExtent& p, const Interval& mine, in
   const int xlo = lane_value(mine.lo, l0 + p.ny), xhi = lane_value(mine.hi, l0 + p.ny + p.nx - 1);
   const int W = xhi - xlo + 1, WL = W < 64 ? W : 64, RP = 64 / WL;
   const int ry = lane / WL, xx = lane - ry * WL;
+  auto keeping = [&](int c, int from, int n) {          // the queries of lanes [from, from + n) whose windows hold c
+    unsigned bits = 0;
+    for (int d = 0; d < n; ++d) bits |= (unsigned)(c >= lane_value(mine.lo, from + d) && c <= lane_value(mine.hi, from + d)) << d;
+    return bits;
+  };
+  unsigned cb = keeping(xlo + xx, l0 + p.ny, p.nx);
   // places of the box's rows in the list: the patch's own rows, or all of them where they are dealt
   const bool dealt = dealt_box(kModeWindow, ubase);
   const int n_rows = gyhi - gylo + 1, i_lo = dealt ? 0 : ylo - gylo, i_hi = dealt ? n_rows - 1 : yhi - gylo;
-  for (int i0 = i_lo; i0 <= i_hi; i0 += RP) {
-    const int i = i0 + ry, y = gylo + (dealt ? dealt_row(i, n_rows) : i);
-    const bool in_box = ry < RP && i <= i_hi && y >= ylo && y <= yhi;
-    const int urow = ubase + i * gw - gxlo, trow = offj + y * sj;
-    for (int x0 = xlo; x0 <= xhi; x0 += WL) {
-      const int x = x0 + xx;
-      unsigned rb = 0, cb = 0;                          // the query rows and columns that keep the key
-      for (int d = 0; d < p.ny; ++d) rb |= (unsigned)(y >= lane_value(mine.lo, l0 + d) && y <= lane_value(mine.hi, l0 + d)) << d;
-      for (int d = 0; d < p.nx; ++d)
-        cb |= (unsigned)(x >= lane_value(mine.lo, l0 + p.ny + d) && x <= lane_value(mine.hi, l0 + p.ny + d)) << d;
-      pack.pass(in_box && x <= xhi && rb && cb, urow + x, trow + x, rb | (cb << p.ny));
+  for (int i0 = i_lo; i0 <= i_hi; i0 += 64) {
+    const int at = min(i0 + lane, i_hi), y_at = gylo + (dealt ? dealt_row(at, n_rows) : at);
+    const unsigned rb_at = i0 + lane <= i_hi ? keeping(y_at, l0, p.ny) : 0;
+    const uint64_t kept = __ballot(rb_at != 0);
+    const int n_kept = __builtin_popcountll(kept), rank = __builtin_popcountll(kept & ((1ull << lane) - 1));
+    static_assert(kMaxSide <= 1024, "a row's place and coordinate in ten bits each");
+    // (lanes without a kept row all write to lane 63, which then is beyond the kept ones)
+    const unsigned rows = (unsigned)__builtin_amdgcn_ds_permute(4 * (rb_at ? rank : 63), (int)(at | y_at << 10 | rb_at << 20));
+    for (int r0 = 0; r0 < n_kept; r0 += RP) {
+      const unsigned row = (unsigned)__shfl((int)rows, (r0 + ry) & 63);
+      const bool in_box = ry < RP && r0 + ry < n_kept;
+      const unsigned rb = row >> 20;
+      const int urow = ubase + (int)(row & 1023) * gw - gxlo, trow = offj + (int)((row >> 10) & 1023) * sj;
+      for (int x0 = xlo; x0 <= xhi; x0 += WL) {
+        const int x = x0 + xx;
+        if (W > 64) cb = keeping(x, l0 + p.ny, p.nx);
+        pack.pass(in_box && x <= xhi && cb, urow + x, trow + x, rb | (cb << p.ny));
+      }
     }
   }
   return n_rows * gw;
@@ -595,20 +642,22 @@ __device__ int wave_walk_patch(const Geom& g, const TableWin& win, const TableRa
     for (int pt = 0; pt < band_parts(e.k); ++pt) {
       const BandPart b = band_part(g, rad, e.k, pt);
       const int glo = band_interval(b, nk, e.qy0).lo, ghi = band_interval(b, nk, e.qy1).hi;
-      // the queries' intervals: one lane each (a 64-bit division), handed round
-      Interval mine = {1, 0};
+      // the queries' intervals: one lane each (a 64-bit division).  Neither end ever falls from one query to the next,
+      // so the queries that keep a column are those from the first whose end reaches it to the last that has begun.
+      constexpr int kNone = 0x7fffffff;
+      Interval mine = {kNone, kNone};
       if (lane < p.nx) mine = band_interval(b, nk, p.y0 + lane);
-      Interval iv[kQ];
+      const int clo = lane_value(mine.lo, 0), chi = lane_value(mine.hi, p.nx - 1);
+      auto up_to = [&](int v, int c) {                  // lanes of the first kQ, in ascending order, with a value of at most c
+        int n = 0;
 #pragma unroll
-      for (int n = 0; n < kQ; ++n) { iv[n].lo = lane_value(mine.lo, n); iv[n].hi = lane_value(mine.hi, n); }
-      const int clo = iv[0].lo, chi = lane_value(mine.hi, p.nx - 1);
+        for (int d = kQ / 2; d > 0; d >>= 1) n += __shfl(v, n + d - 1) <= c ? d : 0;
+        return n + (int)(__shfl(v, n) <= c);
+      };
       for (int c0 = clo; c0 <= chi; c0 += 64) {
         const int c = c0 + lane;
-        unsigned qmask = 0;
-        if (c <= chi) {
-#pragma unroll
-          for (int n = 0; n < kQ; ++n) qmask |= (unsigned)(c >= iv[n].lo && c <= iv[n].hi) << n;
-        }
+        const unsigned begun = (unsigned)((1ull << up_to(mine.lo, c)) - 1), ended = (unsigned)((1ull << up_to(mine.hi, c - 1)) - 1);
+        const unsigned qmask = c <= chi ? begun & ~ended : 0;
         pack.pass(qmask != 0, ubase + c - glo, b.tok0 + c, qmask);
       }
       ubase += ghi - glo + 1;
@@ -694,12 +743,6 @@ __device__ int wave_walk_patch(const Geom& g, const TableWin& win, const TableRa
   return pack.finish();
 }
 
-struct WaveCountSink {
-  int pairs = 0;                                         // this lane's share
-  __device__ void keys(int, int, int, int, unsigned qmask, bool take) { if (take) pairs += __builtin_popcount(qmask); }
-  __device__ void close(int, int, int) {}
-};
-
 // the tables of the head group that global group G belongs to
 struct GroupTables { TableWin win; TableRad rad; int grp; };
 __device__ inline GroupTables group_tables(const Geom& g, const BlobPtrs& p, int G) {
@@ -709,12 +752,6 @@ __device__ inline GroupTables group_tables(const Geom& g, const BlobPtrs& p, int
   t.rad = TableRad{p.rad + (size_t)hg * g.K * g.K, g.K};
   t.grp = G - hg * g.n_groups;
   return t;
-}
-
-__device__ inline int sum_of_lanes(int v) {
-#pragma unroll
-  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d);
-  return v;
 }
 
 // a patch's descriptor without what its walk and its place in the plan say
@@ -777,98 +814,27 @@ __device__ GroupDesc group_desc(const Geom& g, const GroupTables& t, int k, int 
   return gd;
 }
 
-// K2a: one wave per (group, patch): number of steps and kept pairs; patch 0 also
-// sizes the group's union list.  Waves from n_waves on: the wide patches.
-__global__ __launch_bounds__(64) void k_count(Geom g, BlobPtrs p, int n_waves) {
-  const int idx = blockIdx.x, lane = threadIdx.x;
-  const bool wide = idx >= n_waves;
-  const int G = wide ? (idx - n_waves) / kWidePatches : idx / g.NW, w = wide ? (idx - n_waves) % kWidePatches : idx % g.NW;
-  const GroupTables t = group_tables(g, p, G);
-  int k, gy, gx;
-  group_coords(g, t.grp, k, gy, gx);
-  const GroupExtent e = group_extent(g, k, gy, gx);
-  WaveCountSink sink;
-  if (wide) {
-    const PatchExtent pe = wide_extent(g, k, gy, gx, w);
-    WaveDesc wd = wide_desc(g, k, pe);
-    wd.n_steps = wave_walk_patch<true>(g, t.win, t.rad, e, pe, sink, lane);
-    if (lane == 0) p.waves[idx] = wd;
-    return;
+// K2: one wave per group of the list: the places of its patches, its key list and its phase tables, into their
+// descriptors.  (first_ends carries the kept pairs to k_fill.)
+template <class Count>
+__global__ __launch_bounds__(64) void k_place(BlobPtrs p, PlaceList<kLaunchWords> s, int NW, int n_wide, int n_waves, int C) {
+  const int lane = threadIdx.x, i = blockIdx.x, G = s.first_group + i, per = NW + n_wide;
+  if (lane == 0) {
+    GroupDesc& gd = p.groups[G];
+    const int phase0 = (int)s.w[3 * i + 2];
+    gd.union_base = phase0 * C; gd.n_phases = s.phases_of(i); gd.phase_base = phase0 * (n_wide ? n_wide : NW);
   }
-  const PatchExtent pe = patch_extent(g, k, gy, gx, w);
-  WaveDesc wd = patch_desc(g, k, pe);
-  wd.n_steps = wave_walk_patch<false>(g, t.win, t.rad, e, pe, sink, lane);
-  wd.pairs = sum_of_lanes(sink.pairs);
-  if (lane == 0) p.waves[idx] = wd;
-  if (w == 0) {
-    const GroupDesc gd = group_desc(g, t, k, gy, gx, lane);
-    if (lane == 0) p.groups[G] = gd;
-  }
-}
-
-// K2b: exclusive scans over groups (union keys, phase entries) and patches (steps) by one
-// 1024-thread block: per-thread partial sums over a contiguous slice of groups, a scan of the
-// partials inside each wave, then over the waves' totals, then the slice is revisited.
-// (60 groups of 8 patches: 5.5 us; 8.1 us with ten rounds through LDS)
-__global__ __launch_bounds__(1024) void k_scan(Geom g, BlobPtrs p, Caps caps, int n_waves) {
-  constexpr int kSums = 5;
-  __shared__ int64_t wave_total[kSums][16];
-  const int n_wide = g.n_wide;                          // per group
-  WaveDesc* const wide = p.waves + n_waves;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int n_all = g.n_groups * g.n_hg;
-  const int per = (n_all + 1023) / 1024;
-  const int g0 = t * per < n_all ? t * per : n_all;
-  const int g1 = g0 + per < n_all ? g0 + per : n_all;
-  int64_t v[kSums] = {0, 0, 0, 0, 0};                   // steps, union keys, phase entries, pairs, wide patches' steps
-  for (int grp = g0; grp < g1; ++grp) {
-    v[1] += (int64_t)p.groups[grp].n_phases * g.C; v[2] += (int64_t)p.groups[grp].n_phases * walked_patches(g);
-#pragma unroll 4
-    for (int w = 0; w < g.NW; ++w) { v[0] += p.waves[grp * g.NW + w].n_steps; v[3] += p.waves[grp * g.NW + w].pairs; }
-#pragma unroll 4
-    for (int w = 0; w < n_wide; ++w) v[4] += wide[grp * n_wide + w].n_steps;
-  }
-  int64_t sum[kSums];                                   // inclusive
+  const Count own = lane < per ? s.template counts<Count>()[i * per + lane] : Count{0};
+  int upto = own.steps();                               // steps of the patches up to the lane's
 #pragma unroll
-  for (int i = 0; i < kSums; ++i) {
-    sum[i] = v[i];
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int64_t below = __shfl_up(sum[i], d);
-      if (lane >= d) sum[i] += below;
-    }
-    if (lane == 63) wave_total[i][wave] = sum[i];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < kSums; ++i)
-    for (int w = 0; w < wave; ++w) sum[i] += wave_total[i][w];
-  int64_t steps = sum[0] - v[0], uni = sum[1] - v[1], phe = sum[2] - v[2], wide_steps = sum[4] - v[4];
-  for (int grp = g0; grp < g1; ++grp) {
-    GroupDesc& gd = p.groups[grp];
-    gd.union_base = (int32_t)uni; gd.phase_base = (int32_t)phe;
-    uni += (int64_t)gd.n_phases * g.C; phe += (int64_t)gd.n_phases * walked_patches(g);
-    for (int w = 0; w < g.NW; ++w) {
-      WaveDesc& wd = p.waves[grp * g.NW + w];
-      wd.step_begin = (int32_t)steps; steps += wd.n_steps;
-    }
-    for (int w = 0; w < n_wide; ++w) {
-      WaveDesc& wd = wide[grp * n_wide + w];
-      wd.step_begin = (int32_t)wide_steps; wide_steps += wd.n_steps;
-    }
-  }
-  if (t == 1023) {
-    Header h;
-    memset(&h, 0, sizeof h);
-    h.magic = kMagic; h.blob_bytes = caps.bytes;
-    h.n_groups = n_all; h.n_waves = n_all * g.NW;
-    h.n_steps = sum[0]; h.n_union = sum[1]; h.n_phase_entries = sum[2];
-    h.retained_pairs = sum[3]; h.n_wide_steps = sum[4];
-    h.error = (h.n_steps != caps.n_steps || h.n_union != caps.n_union ||
-               h.n_phase_entries != caps.n_phase_entries || h.retained_pairs != caps.retained_pairs ||
-               h.n_wide_steps != caps.n_wide_steps) ? kErrBuilder : kErrNone;
-    *p.hdr = h;
-  }
+  for (int d = 1; d < 32; d <<= 1) { const int x = __shfl_up(upto, d); if (lane >= d) upto += x; }
+  const int narrow = lane_value(upto, NW - 1);
+  if (lane >= per) return;
+  const bool wide = lane >= NW;
+  WaveDesc& wd = p.waves[wide ? n_waves + G * n_wide + lane - NW : G * NW + lane];
+  wd.step_begin = (int)s.w[3 * i + wide] + upto - own.steps() - (wide ? narrow : 0);
+  wd.n_steps = own.steps();
+  wd.first_ends = (uint32_t)own.pairs();
 }
 
 // the group's key list (token indices), padded to whole chunks with its last key; one wave
@@ -999,54 +965,57 @@ struct FillSink {
   }
 };
 
-// K2c: one wave per (group, patch) and (group, wide patch): steps (ring addresses, lane masks, tokens) and the
+// K3: one wave per (group, patch) and (group, wide patch): steps (ring addresses, lane masks, tokens) and the
 // cumulative number of steps that are runnable after each phase; then one wave per group: its
-// key list (in the same launch: neither needs the other).  Bound: the serial walk of one wave.
+// key list and descriptor (in the same launch: neither needs the other).  Bound: the serial walk of one wave.
 // 480 patches of 30 head groups: 27 us, 35 us as two launches with counters that were read back; 30 us with the
-// places in its arguments, where k_count, k_scan and it took 50 and the launches' gaps.
-// With Places the places come with the arguments, and the descriptors and the header are written here; a patch whose
-// walk ends at other counts than the host's marks the header, as k_scan does.
-template <class PlacesArg>
+// places in its arguments, where a count, a scan and it took 50 and the launches' gaps.  With the queries of a box's rows and
+// columns found once per box, those of a band by bisection, and no wide patches in the kernel of plans without: 34 240 tokens
+// 88 -> 68 us, a band over 2240 tokens 26 -> 20 (16 patches of 16 queries and 8 of 32 in a group).
+// The descriptors and the header are written here.  With Places the places come with the arguments, else k_place has
+// left them in the descriptors.  A patch whose walk ends at other counts than the host's, or a group of another number of
+// phases, marks the header.
+template <class PlacesArg, bool WIDE_PLAN>
 __global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int n_waves, PlacesArg s) {
-  constexpr bool PLACED = sizeof(PlacesArg) > sizeof(NoPlaces);
+  constexpr bool PLACED = std::is_same_v<PlacesArg, Places>;
   __shared__ StepBuf buf;
   const int lane = threadIdx.x;
-  if (!PLACED && p.hdr->error) return;
-  const int n_wide = caps.n_groups * g.n_wide;
-  const bool wide = (int)blockIdx.x >= n_waves, lists = (int)blockIdx.x >= n_waves + n_wide;
+  const int n_wide = WIDE_PLAN ? caps.n_groups * kWidePatches : 0;
+  const bool wide = WIDE_PLAN && (int)blockIdx.x >= n_waves, lists = (int)blockIdx.x >= n_waves + n_wide;
   const int idx = lists ? blockIdx.x - n_waves - n_wide : wide ? blockIdx.x - n_waves : blockIdx.x;
   const int per = lists ? 1 : wide ? kWidePatches : g.NW;
   const int G = idx / per, w = idx - G * per;
   const GroupTables t = group_tables(g, p, G);
   GroupDesc gd;
-  if (PLACED) {
-    group_coords(g, t.grp, gd.k, gd.gy, gd.gx);
+  int k, gy, gx;
+  group_coords(g, t.grp, k, gy, gx);
+  if constexpr (PLACED) {
     const int phase0 = (int)s.w[3 * G + 2];
-    gd.n_phases = (int)s.w[G + 1 < caps.n_groups ? 3 * G + 5 : 3 * caps.n_groups] - phase0;
+    gd.n_phases = s.phases_of(G);
     gd.union_base = phase0 * g.C; gd.phase_base = phase0 * walked_patches(g);
   } else {
-    gd = p.groups[G];
+    const GroupDesc& placed = p.groups[G];
+    gd.n_phases = placed.n_phases; gd.union_base = placed.union_base; gd.phase_base = placed.phase_base;
   }
+  gd.k = k; gd.gy = gy; gd.gx = gx;
   if (lists) {
-    if (PLACED) {
-      GroupDesc own = group_desc(g, t, gd.k, gd.gy, gd.gx, lane);
-      if (own.n_phases != gd.n_phases) { p.hdr->error = kErrBuilder; return; }
-      own.union_base = gd.union_base; own.phase_base = gd.phase_base;
-      gd = own;
-      if (lane == 0) p.groups[G] = gd;
-      if (G == 0) {                                     // the header, but for the error that others may be marking
-        Header h;
-        memset(&h, 0, sizeof h);
-        h.magic = kMagic; h.blob_bytes = caps.bytes;
-        h.n_groups = caps.n_groups; h.n_waves = n_waves;
-        h.n_steps = caps.n_steps; h.n_union = caps.n_union; h.n_phase_entries = caps.n_phase_entries;
-        h.retained_pairs = caps.retained_pairs; h.n_wide_steps = caps.n_wide_steps;
-        constexpr int kUsed = offsetof(Header, pad) / 4, kError = offsetof(Header, error) / 4;
+    GroupDesc own = group_desc(g, t, k, gy, gx, lane);
+    if (own.n_phases != gd.n_phases) { p.hdr->error = kErrBuilder; return; }
+    own.union_base = gd.union_base; own.phase_base = gd.phase_base;
+    gd = own;
+    if (lane == 0) p.groups[G] = gd;
+    if (G == 0) {                                       // the header, but for the error that others may be marking
+      Header h;
+      memset(&h, 0, sizeof h);
+      h.magic = kMagic; h.blob_bytes = caps.bytes;
+      h.n_groups = caps.n_groups; h.n_waves = n_waves;
+      h.n_steps = caps.n_steps; h.n_union = caps.n_union; h.n_phase_entries = caps.n_phase_entries;
+      h.retained_pairs = caps.retained_pairs; h.n_wide_steps = caps.n_wide_steps;
+      constexpr int kUsed = offsetof(Header, pad) / 4, kError = offsetof(Header, error) / 4;
 #pragma unroll
-        for (int i = 0; i < kUsed; ++i)
-          if (i != kError && lane == 0) ((uint32_t*)p.hdr)[i] = ((const uint32_t*)&h)[i];
-        if (lane >= kUsed) ((uint32_t*)p.hdr)[lane] = 0;
-      }
+      for (int i = 0; i < kUsed; ++i)
+        if (i != kError && lane == 0) ((uint32_t*)p.hdr)[i] = ((const uint32_t*)&h)[i];
+      if (lane >= kUsed) ((uint32_t*)p.hdr)[lane] = 0;
     }
     fill_union(g, p, caps, t, gd);
     return;
@@ -1054,21 +1023,20 @@ __global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int 
   const GroupExtent e = group_extent(g, gd.k, gd.gy, gd.gx);
   const PatchExtent pe = wide ? wide_extent(g, gd.k, gd.gy, gd.gx, w) : patch_extent(g, gd.k, gd.gy, gd.gx, w);
   WaveDesc* const out = p.waves + blockIdx.x;
-  WaveDesc wd;
-  uint32_t host_pairs = 0;
-  if (PLACED) {
-    wd = wide ? wide_desc(g, gd.k, pe) : patch_desc(g, gd.k, pe);
-    const uint32_t* ends = s.w + 3 * caps.n_groups + 1 + G * (g.NW + g.n_wide) + (wide ? g.NW : 0);
-    const int begin = w > 0 ? (int)(ends[w - 1] & 0xffffu) : 0;
-    wd.step_begin = (int)s.w[3 * G + (wide ? 1 : 0)] + begin;
-    wd.n_steps = (int)(ends[w] & 0xffffu) - begin;
-    host_pairs = ends[w] >> 16;
+  WaveDesc wd = wide ? wide_desc(g, gd.k, pe) : patch_desc(g, gd.k, pe);
+  int host_pairs;
+  if constexpr (PLACED) {
+    const int first = wide ? g.NW : 0;
+    const SmallCount* counts = s.template counts<SmallCount>() + G * (g.NW + g.n_wide) + first;
+    const SmallCount mine = counts[min(lane, w)], own = {(uint16_t)lane_value(mine.v, w)};
+    wd.step_begin = (int)s.w[3 * G + wide] + sum_of_lanes(lane < w ? mine.steps() : 0);
+    wd.n_steps = own.steps(); host_pairs = own.pairs();
   } else {
-    wd = *out;
+    wd.step_begin = out->step_begin; wd.n_steps = out->n_steps; host_pairs = (int)out->first_ends;
   }
   if ((int64_t)wd.step_begin + wd.n_steps > (wide ? caps.n_wide_steps : caps.n_steps) ||
       (int64_t)gd.phase_base + (int64_t)gd.n_phases * walked_patches(g) > caps.n_phase_entries) {
-    if (PLACED) p.hdr->error = kErrBuilder;
+    p.hdr->error = kErrBuilder;
     return;
   }
   int ns, pairs = 0;
@@ -1078,7 +1046,7 @@ __global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int 
     sink.n_steps = wd.n_steps; sink.n_phases = gd.n_phases;
     sink.phase_end = p.phase_end + gd.phase_base + (int64_t)w * gd.n_phases;
   };
-  if (wide) {
+  if constexpr (WIDE_PLAN) if (wide) {
     FillSink<true> sink;
     fill(sink);
     sink.addr = (uint2*)((char*)p.step_addr + (int64_t)wd.step_begin * 64 * kWideDesc);
@@ -1086,26 +1054,23 @@ __global__ __launch_bounds__(64) void k_fill(Geom g, BlobPtrs p, Caps caps, int 
     ns = wave_walk_patch<true>(g, t.win, t.rad, e, pe, sink, lane);
     sink.fill_ends(sink.chunk, gd.n_phases, ns);
     first_ends = (uint32_t)sink.end0 | ((uint32_t)sink.end2 << 16);   // (a patch has at most 65535 steps)
-    if (PLACED) pairs = sum_of_lanes(sink.pairs);
-  } else {
+    pairs = sum_of_lanes(sink.pairs);
+  }
+  if (!wide) {
     FillSink<false> sink;
     fill(sink);
-    sink.addr = g.n_wide ? nullptr : p.step_addr + (int64_t)wd.step_begin * 64;      // (wide patches: nobody walks the list in these steps)
+    sink.addr = WIDE_PLAN ? nullptr : p.step_addr + (int64_t)wd.step_begin * 64;      // (wide patches: nobody walks the list in these steps)
     sink.mask = p.step_mask + (int64_t)wd.step_begin * 8;
     sink.toks = p.step_tok + (int64_t)wd.step_begin * kStepKeys;
     ns = wave_walk_patch<false>(g, t.win, t.rad, e, pe, sink, lane);
     if (sink.addr) sink.fill_ends(sink.chunk, gd.n_phases, ns);
     first_ends = (uint32_t)sink.end0 | ((uint32_t)sink.end2 << 16);
-    if (PLACED) pairs = sum_of_lanes(sink.pairs);
+    pairs = sum_of_lanes(sink.pairs);
   }
-  if (PLACED) {
-    if (ns != wd.n_steps || ((uint32_t)pairs & 0xffffu) != host_pairs) { p.hdr->error = kErrBuilder; return; }
-    if (!wide) wd.pairs = pairs;
-    wd.first_ends = first_ends;
-    if (lane == 0) *out = wd;
-  } else if (lane == 0) {
-    out->first_ends = first_ends;
-  }
+  if (ns != wd.n_steps || pairs % kPairsModulus != host_pairs) { p.hdr->error = kErrBuilder; return; }
+  if (!wide) wd.pairs = pairs;
+  wd.first_ends = first_ends;
+  if (lane == 0) *out = wd;
 }
 
 litevar_status build_plan(PlanSpec& sp, const PlanSizes& z, void* d_blob, hipStream_t st) {
@@ -1129,13 +1094,25 @@ litevar_status build_plan(PlanSpec& sp, const PlanSizes& z, void* d_blob, hipStr
   const int n_all = g.n_groups * g.n_hg;
   const int nw = n_all * g.NW;
   const int n_wide = n_all * g.n_wide;
-  Places s;
-  if (place(sp, s)) {
-    hipLaunchKernelGGL(k_fill<Places>, dim3(nw + n_wide + n_all), dim3(64), 0, st, g, p, caps, nw, s);
+  const dim3 waves(nw + n_wide + n_all);
+  bool small = true;
+  for (const PlanSpec::PatchCount& c : sp.patch_counts) small = small && c.steps <= SmallCount::kMost;
+  PlaceAt at;
+  if (small && n_all <= groups_in<SmallCount>(kInlineWords, g.NW + g.n_wide)) {
+    Places s;
+    fill_list<SmallCount>(sp, 0, at, s);
+    if (g.n_wide) hipLaunchKernelGGL((k_fill<Places, true>), waves, dim3(64), 0, st, g, p, caps, nw, s);
+    else hipLaunchKernelGGL((k_fill<Places, false>), waves, dim3(64), 0, st, g, p, caps, nw, s);
   } else {
-    hipLaunchKernelGGL(k_count, dim3(nw + n_wide), dim3(64), 0, st, g, p, nw);
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, st, g, p, caps, nw);
-    hipLaunchKernelGGL(k_fill<NoPlaces>, dim3(nw + n_wide + n_all), dim3(64), 0, st, g, p, caps, nw, NoPlaces{});
+    PlaceList<kLaunchWords> s;
+    for (int first = 0; first < n_all; first += s.n_groups) {
+      if (small) fill_list<SmallCount>(sp, first, at, s);
+      else fill_list<LargeCount>(sp, first, at, s);
+      hipLaunchKernelGGL(small ? k_place<SmallCount> : k_place<LargeCount>, dim3(s.n_groups), dim3(64), 0, st, p, s, g.NW,
+                         g.n_wide, nw, g.C);
+    }
+    if (g.n_wide) hipLaunchKernelGGL((k_fill<NoPlaces, true>), waves, dim3(64), 0, st, g, p, caps, nw, NoPlaces{});
+    else hipLaunchKernelGGL((k_fill<NoPlaces, false>), waves, dim3(64), 0, st, g, p, caps, nw, NoPlaces{});
   }
   return hip_check(hipGetLastError(), "plan builder launch");
 }

@@ -122,3 +122,17 @@ def test_pairs_of_every_head_group(heads):
     lv.litevar_plan_check(plan)
     for h in sorted({0, 1, heads // 2, heads - 1}):
         _compare(plan, oracle.mask_dense(scales, tables[h], 0, (2, 4)), False, h)
+
+
+@pytest.mark.parametrize("waves", [4, 8, 16])
+def test_patches_of_many_steps(waves):
+    """More than 255 steps in a patch, whose counts travel in 32 bits."""
+    import paper_2411_17178_amd as lv
+    scales, tables = (96, 9), [[[-1, -1], [-1, h]] for h in range(5)]
+    plan = lv.litevar_mask_build(scales, 0, tables, 0, (1, 2), waves_per_group=waves)
+    lv.litevar_plan_check(plan)
+    for h in (0, 4):
+        want = oracle.mask_dense(scales, tables[h], 0, (1, 2))
+        if waves == 16:
+            _compare(plan, want, False, h)
+        assert (lv.litevar_mask_export_dense(plan, head=h)[0].cpu().numpy() == want).all()
