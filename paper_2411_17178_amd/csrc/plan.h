@@ -27,6 +27,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <vector>
 
 #define LV_HD __host__ __device__ inline
 
@@ -370,58 +371,55 @@ LV_HD int band_union_keys(const Geom& g, const Rad& rad, const GroupExtent& e) {
 // ---- host sizing: the same steps as the device's walk, counted run by run ---------------
 // A step is closed when it holds 32 keys or when the next key's 2^logS-key block lies more
 // than A blocks after the block of the step's first key (LDS ring constraint).
+// Only the number of keys in each block matters for that, so the counter is fed block by block.
 struct StepCounter {
   const int logS, A;
   explicit StepCounter(const Geom& g) : logS(g.logS), A(g.A) {}
   int steps = 0, cnt = 0, first_block = 0;
-  void run(int upos, int n) {              // n consecutive keys of the union list, all kept by some query
-    while (n > 0) {
-      const int blk = upos >> logS;
-      if (cnt == kStepKeys || (cnt > 0 && blk - first_block > A)) { ++steps; cnt = 0; }
-      if (cnt == 0) first_block = blk;
-      const int room = ((first_block + A + 1) << logS) - upos;
-      int take = kStepKeys - cnt < room ? kStepKeys - cnt : room;
-      if (take > n) take = n;
-      cnt += take; upos += take; n -= take;
-    }
+  // n more keys, all in block blk (a block's keys may come in several parts)
+  void block(int blk, int n) {
+    if (n <= 0) return;
+    if (cnt > 0 && blk - first_block > A) { ++steps; cnt = 0; }
+    if (cnt == 0) first_block = blk;
+    const int full = (cnt + n - 1) / kStepKeys;          // steps that a further key of the block finds full
+    if (full > 0) { first_block = blk; steps += full; cnt -= full * kStepKeys; }
+    cnt += n;
   }
-  // n_rows runs of w keys each, `pitch` entries apart: the same as run() for each of them, but the rows that end
-  // ahead of the open step's last block are counted together (no step that starts in them is cut by its span)
-  void rows(int upos, int w, int pitch, int n_rows) {
-    while (n_rows > 0) {
-      const int blk = upos >> logS;
-      if (cnt == kStepKeys || (cnt > 0 && blk - first_block > A)) { ++steps; cnt = 0; }
-      if (cnt == 0) first_block = blk;
-      const int room = ((first_block + A + 1) << logS) - upos;
-      if (room < w) { run(upos, w); upos += pitch; --n_rows; continue; }
-      int m = n_rows;
-      if ((int64_t)(n_rows - 1) * pitch > room - w) m = 1 + (unsigned)(room - w) / (unsigned)pitch;
-      const int n = m * w, full = (cnt + n - 1) / kStepKeys;
-      if (full > 0) {
-        const unsigned first = (unsigned)(full * kStepKeys - cnt);      // of these keys, the open step's first one
-        first_block = (upos + (int)(first / (unsigned)w) * (pitch - w) + (int)first) >> logS;
-        steps += full;
-      }
-      cnt += n - full * kStepKeys;
-      upos += m * pitch; n_rows -= m;
+  void run(int upos, int n) {              // n consecutive keys of the union list, all kept by some query
+    if (n <= 0) return;
+    const int end = upos + n, last = (end - 1) >> logS;
+    int blk = upos >> logS;
+    if (blk == last) { block(blk, n); return; }
+    block(blk, ((blk + 1) << logS) - upos);
+    // (behind one whole block, a multiple of the step's 32 keys, the next ones leave the count as it is)
+    if (++blk < last) {
+      block(blk, 1 << logS);
+      steps += (last - blk - 1) << (logS - 5); first_block = last - 1;
     }
+    block(last, end - (last << logS));
   }
   int finish() { if (cnt > 0) { ++steps; cnt = 0; } return steps; }
 };
+static_assert(kStepKeys == 32, "whole blocks of 2^logS keys");
 
 // What a patch keeps of one axis of a part: its queries' intervals (both ends grow with the
-// query) merged into runs, and their summed length.
-struct AxisSpan {
-  int n_runs = 0, kept = 0;
-  Interval run[kWideQueries];
-  void clear() { n_runs = kept = 0; }
-  void add(const Interval& iv) {
-    kept += iv.hi - iv.lo + 1;
-    if (n_runs > 0 && iv.lo <= run[n_runs - 1].hi + 1) { if (iv.hi > run[n_runs - 1].hi) run[n_runs - 1].hi = iv.hi; }
-    else run[n_runs++] = iv;
+// query) merged into runs, and their summed length.  One run is [lo, hi]; several stand in a pool, from `first` on.
+struct AxisSpan { int lo, hi, kept, n_runs, first; };
+
+// iv(c) for c in [from, to]
+template <class Iv>
+inline AxisSpan span_of(std::vector<Interval>& pool, int from, int to, Iv iv) {
+  Interval run = iv(from);
+  AxisSpan a = {run.lo, run.hi, run.hi - run.lo + 1, 1, (int)pool.size()};
+  for (int c = from + 1; c <= to; ++c) {
+    const Interval x = iv(c);
+    a.kept += x.hi - x.lo + 1;
+    if (x.lo > run.hi + 1) { pool.push_back(run); run = x; ++a.n_runs; }
+    else if (x.hi > run.hi) run.hi = x.hi;
   }
-  int lo() const { return run[0].lo; }
-  int hi() const { return run[n_runs - 1].hi; }
-};
+  a.hi = run.hi;
+  if (a.n_runs > 1) pool.push_back(run);
+  return a;
+}
 
 }  // namespace lv

@@ -160,8 +160,7 @@ litevar_status make_spec(const litevar_mask_desc* d, const litevar_plan_opts* op
 
 static uint64_t align256(uint64_t x) { return (x + 255) & ~(uint64_t)255; }
 
-// The sizing walk visits every patch's box in every key scale on the host, rows at a time (30 tables of 13 x 13
-// queries: 36 us, 48 row by row with the windows' centres divided anew for every table; 540 key by key).
+// The sizing walk visits every block of every group's list on the host (30 tables of 13 x 13 queries: 29 us, 540 key by key).
 // Callers size and then build with the same descriptor, often repeatedly,
 // so the last result is remembered per thread, keyed by the whole specification.
 static thread_local struct { bool valid; PlanSpec sp; PlanSizes z; } g_last_sizing = {false, {}, {}};
@@ -195,45 +194,137 @@ litevar_status size_plan(PlanSpec& sp, PlanSizes& z) {
 }
 
 // a group's box in a key scale: its rows and columns and its first entry in the group's list
-struct ListBox { int base, ylo, n_rows, xlo, w; const int16_t* order; };   // order: the rows of a dealt box, from place 0 on
+struct ListBox { int base, ylo, n_rows, xlo, w; };
 
-// a patch's keys of one key scale: rows x columns of the group's box
-static void add_box(StepCounter& steps, const AxisSpan& rows, const AxisSpan& cols, const ListBox& b) {
-  for (int r = 0; r < rows.n_runs; ++r) {
-    const int at = b.base + (rows.run[r].lo - b.ylo) * b.w - b.xlo, n = rows.run[r].hi - rows.run[r].lo + 1;
-    if (cols.n_runs == 1) {
-      const int w = cols.run[0].hi - cols.run[0].lo + 1;
-      steps.rows(at + cols.run[0].lo, w, b.w, n);
-      continue;
-    }
-    for (int y = 0; y < n; ++y)
-      for (int i = 0; i < cols.n_runs; ++i)
-        steps.run(at + y * b.w + cols.run[i].lo, cols.run[i].hi - cols.run[i].lo + 1);
-  }
-}
+// The host's walk over one patch, run by run: bands, and windows with gaps between neighbouring queries
+struct PatchWalk {
+  StepCounter steps;
+  const std::vector<Interval>& pool;
+  int64_t pairs = 0;
 
-// the same with the box's rows dealt (see dealt_row)
-static void add_dealt_box(StepCounter& steps, const AxisSpan& rows, const AxisSpan& cols, const ListBox& b) {
-  auto kept = [&](int i) {
-    for (int r = 0; r < rows.n_runs; ++r)
-      if (b.order[i] >= rows.run[r].lo && b.order[i] <= rows.run[r].hi) return true;
-    return false;
-  };
-  for (int i = 0; i < b.n_rows;) {
-    int n = 0;
-    while (i + n < b.n_rows && kept(i + n)) ++n;
-    if (n == 0) { ++i; continue; }
-    const int at = b.base + i * b.w - b.xlo;
-    if (cols.n_runs == 1) {
-      steps.rows(at + cols.run[0].lo, cols.run[0].hi - cols.run[0].lo + 1, b.w, n);
-    } else {
-      for (int y = 0; y < n; ++y)
-        for (int c = 0; c < cols.n_runs; ++c)
-          steps.run(at + y * b.w + cols.run[c].lo, cols.run[c].hi - cols.run[c].lo + 1);
-    }
-    i += n + 1;                                                       // (the row after the run is not kept)
+  // an axis' keys; `from` is the entry of coordinate 0
+  void runs(const AxisSpan& a, int from) {
+    each_run(a, [&](int lo, int hi) { steps.run(from + lo, hi - lo + 1); });
   }
-}
+  template <class F> void each_run(const AxisSpan& a, F f) const {
+    if (a.n_runs == 1) f(a.lo, a.hi);
+    else for (int i = a.first; i < a.first + a.n_runs; ++i) f(pool[i].lo, pool[i].hi);
+  }
+  // its keys of one key scale: rows x columns of the group's box, whose rows may be dealt (see dealt_row)
+  void box(const AxisSpan& rows, const AxisSpan& cols, const ListBox& b, bool dealt) {
+    pairs += (int64_t)rows.kept * cols.kept;
+    auto row = [&](int place) { runs(cols, b.base + place * b.w - b.xlo); };
+    if (!dealt) { each_run(rows, [&](int lo, int hi) { for (int y = lo; y <= hi; ++y) row(y - b.ylo); }); return; }
+    const int per = b.n_rows >> 2, extra = b.n_rows & 3;      // rows of a strip, and how many have one more
+    for (int i0 = 0; i0 < b.n_rows; i0 += 64) {
+      const int round0 = i0 >> 2;
+      uint64_t places = 0;                                    // bit i: place i0 + i holds a row of the patch
+      each_run(rows, [&](int lo, int hi) {
+        for (int strip = 0; strip < 4; ++strip) {             // place 4 round + strip holds row strip start + round
+          const int start = b.ylo + strip * per + std::min(strip, extra), n = per + (strip < extra);
+          const int from = std::max(std::max(lo - start, 0), round0), to = std::min(std::min(hi - start, n - 1), round0 + 15);
+          if (from > to) continue;
+          const uint64_t upto = to - round0 == 15 ? ~0ull : (1ull << (4 * (to - round0) + 4)) - 1;
+          places |= (0x1111111111111111ull << strip) & upto & ~((1ull << (4 * (from - round0))) - 1);
+        }
+      });
+      for (; places; places &= places - 1) row(i0 + __builtin_ctzll(places));
+    }
+  }
+};
+
+// The host's walk over all patches of a group whose windows have no gaps, eight patches in the lanes of a vector: how many keys
+// of a box's first entries a patch keeps is a product of rows and columns, formed once for every block of the list, and
+// the steps follow from the keys in each block as in StepCounter.  (Sizing with a patch at a time, several rows together: 34 240
+// tokens 618 us, 30 tables of 16 x 16 queries 76, all pairs of 34 240 tokens 3791; like this 169, 40 and 574.)
+// All values are exact modulo 2^16: a block holds at most 64 keys, and a patch keeps some of every box, so that the
+// blocks between two of its keys number less than 2^16.
+typedef short v8s __attribute__((ext_vector_type(8)));
+typedef unsigned short v8u __attribute__((ext_vector_type(8)));
+struct GroupWalk {
+  static constexpr int kMost = (16 + kWidePatches) / 8;
+  const int logS, n_vec, first_wide;                     // vectors in use, and the first that holds wide patches
+  const short A;
+  v8s n[kMost], cnt[kMost], first[kMost];                // keys of the block at hand, keys and first block of the open step
+  v8u closed[kMost];                                     // steps since `steps` was brought up to date
+  v8s row_lo[kMost], row_n[kMost], col_lo[kMost], col_w[kMost], before[kMost];
+  int steps[8 * kMost]; int64_t pairs[8 * kMost];
+  const AxisSpan *rows[8 * kMost], *cols[8 * kMost];     // of key scale 0; the next scales' are a stride away
+  int row_stride[8 * kMost], col_stride[8 * kMost];
+  std::vector<v8s> dealt_rows;                           // by place: the wide patches' rows before it, and whether its row is theirs
+  int pending = -1;                                      // block whose keys are in n
+
+  GroupWalk(const Geom& g) : logS(g.logS), n_vec((g.NW + g.n_wide + 7) / 8), first_wide(g.n_wide ? g.NW / 8 : kMost), A((short)g.A) {}
+  void start() {
+    static const AxisSpan none = {0, -1, 0, 1, 0};
+    for (int v = 0; v < kMost; ++v) { n[v] = cnt[v] = first[v] = v8s{}; closed[v] = v8u{}; }
+    for (int l = 0; l < 8 * kMost; ++l) { steps[l] = 0; pairs[l] = 0; rows[l] = cols[l] = &none; row_stride[l] = col_stride[l] = 0; }
+    pending = -1;
+  }
+  static v8s sel(v8s mask, v8s a, v8s b) { return (mask & a) | (~mask & b); }
+  static v8s clamp(v8s x, v8s hi) { return __builtin_elementwise_min(__builtin_elementwise_max(x, v8s{}), hi); }
+  void end_block() {
+    const v8s blk = (short)pending;
+    for (int v = 0; v < n_vec; ++v) {
+      const v8s has = n[v] > (short)0, far = __builtin_bit_cast(v8s, __builtin_bit_cast(v8u, blk - first[v]) > (unsigned short)A);
+      const v8s cut = has & (cnt[v] > (short)0) & far;
+      cnt[v] &= ~cut;
+      const v8s open = cnt[v] + n[v], full = ((open - (short)1) >> (short)5) & has;
+      first[v] = sel(has & ((cnt[v] == (short)0) | (full > (short)0)), blk, first[v]);
+      cnt[v] = open - (full << (short)5);
+      closed[v] += __builtin_bit_cast(v8u, full - cut);
+      n[v] = v8s{};
+    }
+  }
+  // the group's box in the next key scale
+  void box(const ListBox& b, bool dealt) {
+    for (int l = 0; l < 8 * n_vec; ++l) {
+      const AxisSpan &r = *rows[l], &c = *cols[l];
+      row_lo[l >> 3][l & 7] = (short)(r.lo - b.ylo); row_n[l >> 3][l & 7] = (short)(r.hi - r.lo + 1);
+      col_lo[l >> 3][l & 7] = (short)(c.lo - b.xlo); col_w[l >> 3][l & 7] = (short)(c.hi - c.lo + 1);
+      pairs[l] += (int64_t)r.kept * c.kept;
+      rows[l] += row_stride[l]; cols[l] += col_stride[l];
+    }
+    if (dealt) {
+      const int v = first_wide;
+      dealt_rows.resize(2 * (b.n_rows + 1));
+      v8s sum = {};
+      for (int i = 0; i < b.n_rows; ++i) {
+        const v8s at = (v8s)(short)dealt_row(i, b.n_rows) - row_lo[v], its = (at >= (short)0) & (at < row_n[v]);
+        dealt_rows[2 * i] = sum; dealt_rows[2 * i + 1] = its;
+        sum -= its;
+      }
+      dealt_rows[2 * b.n_rows] = sum; dealt_rows[2 * b.n_rows + 1] = v8s{};
+    }
+    for (int v = 0; v < n_vec; ++v) before[v] = v8s{};
+    const int end = b.base + b.n_rows * b.w;
+    const uint64_t inv = (((uint64_t)1 << 40) + b.w - 1) / b.w;          // i / w = i inv >> 40, exact for i w < 2^40
+    static_assert((uint64_t)kMaxSide * kMaxSide * kMaxSide < (uint64_t)1 << 40, "sides");
+    for (int blk = b.base >> logS;; ++blk) {
+      if (blk != pending) { if (pending >= 0) end_block(); pending = blk; }
+      const int stop = std::min((blk + 1) << logS, end), r = (int)((uint64_t)(stop - b.base) * inv >> 40);
+      const v8s place = (short)r, x = (short)(stop - b.base - r * b.w);
+      for (int v = 0; v < n_vec; ++v) {
+        const v8s at = place - row_lo[v];
+        v8s whole = clamp(at, row_n[v]), part = (at >= (short)0) & (at < row_n[v]);
+        if (dealt && v == first_wide) { whole = dealt_rows[2 * r]; part = dealt_rows[2 * r + 1]; }
+        const v8s now = whole * col_w[v] + (part & clamp(x - col_lo[v], col_w[v]));
+        n[v] += now - before[v];
+        before[v] = now;
+      }
+      if (stop == end) break;
+    }
+    for (int v = 0; v < n_vec; ++v) {
+      for (int i = 0; i < 8; ++i) steps[8 * v + i] += closed[v][i];
+      closed[v] = v8u{};
+    }
+  }
+  void close() {                                         // behind the last box
+    if (pending >= 0) end_block();
+    for (int v = 0; v < n_vec; ++v)
+      for (int i = 0; i < 8; ++i) steps[8 * v + i] += closed[v][i] + (cnt[v][i] > 0);
+  }
+};
 
 constexpr int kMostPatchSteps = 65535;                  // (counts travel in 16 bits)
 constexpr int64_t kMostSteps = (int64_t)1 << 26;
@@ -242,17 +333,16 @@ constexpr int64_t kMostSteps = (int64_t)1 << 26;
 static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
   HostGeom& g = sp.g;
   sp.group_phases.clear(); sp.patch_counts.clear();
-  auto keep_count = [&](int steps, int64_t pairs) { sp.patch_counts.push_back({(uint16_t)steps, (uint8_t)(pairs % kPairsModulus)}); };
   sp.group_phases.reserve((size_t)g.n_groups * g.n_hg);
   sp.patch_counts.reserve((size_t)g.n_groups * g.n_hg * (g.NW + g.n_wide));
   memset(&z, 0, sizeof z);
+  std::vector<Interval> pool;
   std::vector<AxisSpan> ax;            // window mode: [key scale][patch row or column of the query scale]
   std::vector<AxisSpan> wide_rows, wide_cols;   // the same of the wide patches: [key scale][group row, patch row in it]
-  // (entries are cleared and not assigned: one holds the runs of 32 queries)
-  auto cleared = [](std::vector<AxisSpan>& v, size_t n) {
-    if (v.size() < n) v.resize(n);
-    for (size_t i = 0; i < n; ++i) v[i].clear();
-  };
+  std::vector<int64_t> kept_before;    // kept keys of the coordinates (queries of a group) before c, in the part at hand
+  std::vector<Interval> of_query;      // band mode: intervals of a group's queries, in the part at hand
+  std::vector<PatchWalk> walks;
+  GroupWalk together(g);
   // window mode: the windows' centres, which are the same for every head group: [query scale][key scale][coordinate]
   std::vector<int16_t> centres;
   size_t centre_of[kMaxScales] = {};
@@ -262,7 +352,6 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
       for (int c = 0; c < g.s[k]; ++c) centres.push_back((int16_t)window_interval(g.s[k], g.s[j], c, 0).lo);
   }
   ListBox boxes[kMaxScales];
-  std::vector<int16_t> orders((size_t)(g.n_wide ? g.K : 0) * g.smax);
   for (int hg = 0; hg < g.n_hg; ++hg) {
     sp.load_head_group(hg);
     const ArithRad rad{g};
@@ -273,32 +362,46 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
       const bool wide = g.n_wide > 0;
       // wide patch rows of a group, and columns (window mode)
       int wny = 0, wnx = 0;
+      bool gaps = true;
       if (g.mode == kModeWindow) {
         const int gh = g.grh[k] * kPatch, gw = g.grw[k] * kPatch, ph = g.wph[k], pw = g.wpw[k], sk = g.s[k];
-        cleared(ax, (size_t)(k + 1) * pps);
+        ax.resize((size_t)(k + 1) * pps);
         if (wide) {
           wny = ((gh < sk ? gh : sk) + ph - 1) / ph; wnx = ((gw < sk ? gw : sk) + pw - 1) / pw;
-          cleared(wide_rows, (size_t)(k + 1) * ngy * wny);
-          cleared(wide_cols, (size_t)(k + 1) * ngx * wnx);
+          wide_rows.resize((size_t)(k + 1) * ngy * wny);
+          wide_cols.resize((size_t)(k + 1) * ngx * wnx);
         }
+        pool.clear();
+        gaps = false;
+        kept_before.resize(sk + 1);
         const int16_t* ctr = &centres[centre_of[k]];
         for (int j = 0; j <= k; ++j, ctr += sk) {
-          const int last = g.s[j] - 1, r = j < g.n_sink ? -1 : g.rad[k][j];
+          const int sj = g.s[j], last = sj - 1, r = j < g.n_sink ? -1 : g.rad[k][j];
           auto window = [&](int c) {
             if (r < 0) return Interval{0, last};
             return Interval{ctr[c] - r < 0 ? 0 : ctr[c] - r, ctr[c] + r > last ? last : ctr[c] + r};
           };
-          AxisSpan* a = &ax[(size_t)j * pps];
-          for (int c = 0; c < sk; ++c) a[c / kPatch].add(window(c));
+          // (neighbouring centres are ceil(sj / sk) apart at most: windows as wide as that leave no gaps)
+          const bool joined = r < 0 || sj <= (int64_t)(2 * r + 1) * sk;
+          gaps = gaps || !joined;
+          if (joined) {
+            int64_t n = 0;
+            for (int c = 0; c < sk; ++c) { kept_before[c] = n; const Interval iv = window(c); n += iv.hi - iv.lo + 1; }
+            kept_before[sk] = n;
+          }
+          auto span = [&](int from, int to) {
+            if (joined) return AxisSpan{window(from).lo, window(to).hi, (int)(kept_before[to + 1] - kept_before[from]), 1, 0};
+            return span_of(pool, from, to, window);
+          };
+          // patches of `side` coordinates, in groups of `group`
+          auto cut = [&](AxisSpan* a, int group, int per_group, int side) {
+            for (int y = 0; y < sk; y += group, a += per_group)
+              for (int p = 0, c = y, end = std::min(sk, y + group); c < end; ++p, c += side) a[p] = span(c, std::min(end, c + side) - 1);
+          };
+          cut(&ax[(size_t)j * pps], sk, pps, kPatch);
           if (!wide) continue;
-          a = &wide_rows[(size_t)j * ngy * wny];
-          for (int y = 0; y < sk; y += gh, a += wny)
-            for (int p = 0, c = y, end = std::min(sk, y + gh); c < end; ++p)
-              for (int to = std::min(end, c + ph); c < to; ++c) a[p].add(window(c));
-          a = &wide_cols[(size_t)j * ngx * wnx];
-          for (int x = 0; x < sk; x += gw, a += wnx)
-            for (int p = 0, c = x, end = std::min(sk, x + gw); c < end; ++p)
-              for (int to = std::min(end, c + pw); c < to; ++c) a[p].add(window(c));
+          cut(&wide_rows[(size_t)j * ngy * wny], gh, wny, ph);
+          cut(&wide_cols[(size_t)j * ngx * wnx], gw, wnx, pw);
         }
       }
       for (int gi = 0; gi < ngy * ngx; ++gi) {
@@ -312,13 +415,8 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
             const AxisSpan* a = &ax[(size_t)j * pps];
             ListBox& b = boxes[j];
             b.base = nu;
-            b.ylo = a[e.qy0 / kPatch].lo(); b.n_rows = a[e.qy1 / kPatch].hi() - b.ylo + 1;
-            b.xlo = a[e.qx0 / kPatch].lo(); b.w = a[e.qx1 / kPatch].hi() - b.xlo + 1;
-            if (wide && dealt_box(g.mode, nu)) {
-              int16_t* order = &orders[(size_t)j * g.smax];
-              for (int i = 0; i < b.n_rows; ++i) order[i] = (int16_t)(b.ylo + dealt_row(i, b.n_rows));
-              b.order = order;
-            }
+            b.ylo = a[e.qy0 / kPatch].lo; b.n_rows = a[e.qy1 / kPatch].hi - b.ylo + 1;
+            b.xlo = a[e.qx0 / kPatch].lo; b.w = a[e.qx1 / kPatch].hi - b.xlo + 1;
             nu += b.n_rows * b.w;
           }
         }
@@ -326,62 +424,76 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
         z.n_union += (int64_t)nph * g.C;
         z.n_phase_entries += (int64_t)nph * walked_patches(g);
         sp.group_phases.push_back(nph);
-        for (int w = 0; w < g.NW; ++w) {
-          const PatchExtent p = patch_extent(g, k, gy, gx, w);
-          if (p.ny == 0) { keep_count(0, 0); continue; }
-          StepCounter steps{g};
-          int64_t pairs = 0;
-          if (g.mode == kModeBand) {
-            int ubase = 0;
-            for (int pt = 0; pt < band_parts(k); ++pt) {
-              const BandPart b = band_part(g, rad, k, pt);
-              const int glo = band_interval(b, nk, e.qy0).lo, ghi = band_interval(b, nk, e.qy1).hi;
-              AxisSpan a;
-              for (int n = 0; n < p.nx; ++n) a.add(band_interval(b, nk, p.y0 + n));
-              for (int i = 0; i < a.n_runs; ++i) steps.run(ubase + a.run[i].lo - glo, a.run[i].hi - a.run[i].lo + 1);
-              pairs += a.kept;
-              ubase += ghi - glo + 1;
-            }
-          } else {
-            const AxisSpan *rows = &ax[p.y0 / kPatch], *cols = &ax[p.x0 / kPatch];
-            for (int j = 0; j <= k; ++j, rows += pps, cols += pps) {
-              add_box(steps, *rows, *cols, boxes[j]);
-              pairs += (int64_t)rows->kept * cols->kept;
-            }
-          }
-          const int ns = steps.finish();
-          if (ns > kMostPatchSteps) return fail(LITEVAR_E_UNSUPPORTED, "a query patch needs more than 65535 steps");
-          z.n_steps += ns; pairs_hg += pairs;
-          keep_count(ns, pairs);
+        const int n_walks = g.NW + g.n_wide;
+        auto extent = [&](int w) { return w < g.NW ? patch_extent(g, k, gy, gx, w) : wide_extent(g, k, gy, gx, w - g.NW); };
+        if (gaps) {
+          walks.clear();
+          for (int w = 0; w < n_walks; ++w) walks.push_back(PatchWalk{StepCounter(g), pool});
         }
-        for (int w = 0; w < g.n_wide; ++w) {
-          const PatchExtent p = wide_extent(g, k, gy, gx, w);
-          if (p.ny == 0) { keep_count(0, 0); continue; }
-          StepCounter steps{g};
-          int64_t pairs = 0;
-          if (g.mode == kModeBand) {
-            int ubase = 0;
-            for (int pt = 0; pt < band_parts(k); ++pt) {
-              const BandPart b = band_part(g, rad, k, pt);
-              const int glo = band_interval(b, nk, e.qy0).lo, ghi = band_interval(b, nk, e.qy1).hi;
-              AxisSpan a;
-              for (int n = 0; n < p.nx; ++n) a.add(band_interval(b, nk, p.y0 + n));
-              for (int i = 0; i < a.n_runs; ++i) steps.run(ubase + a.run[i].lo - glo, a.run[i].hi - a.run[i].lo + 1);
-              pairs += a.kept;
-              ubase += ghi - glo + 1;
+        if (g.mode == kModeBand) {
+          int ubase = 0;
+          for (int pt = 0; pt < band_parts(k); ++pt) {
+            const BandPart b = band_part(g, rad, k, pt);
+            const int n = e.qy1 - e.qy0 + 1;
+            of_query.resize(n); kept_before.resize(n + 1);
+            kept_before[0] = 0;
+            // band_interval of every query; the centre moves by 2 cols / 2 nk, the remainder kept
+            const int64_t den = 2 * (int64_t)nk, num = (2 * (int64_t)e.qy0 + 1) * b.cols, by = 2 * (int64_t)b.cols;
+            int64_t ctr = num / den, rem = num % den;
+            const int64_t ctr_by = by / den, rem_by = by % den;
+            for (int i = 0; i < n; ++i) {
+              Interval& iv = of_query[i];
+              if (b.rad < 0) iv = {0, b.cols - 1};
+              else iv = {(int)std::max<int64_t>(ctr - b.rad, 0), (int)std::min<int64_t>(ctr + b.rad, b.cols - 1)};
+              kept_before[i + 1] = kept_before[i] + iv.hi - iv.lo + 1;
+              ctr += ctr_by; rem += rem_by;
+              if (rem >= den) { rem -= den; ++ctr; }
             }
-          } else {
-            const AxisSpan *rows = &wide_rows[gy * wny + w / wnx], *cols = &wide_cols[gx * wnx + w % wnx];
-            for (int j = 0; j <= k; ++j, rows += ngy * wny, cols += ngx * wnx) {
-              if (dealt_box(g.mode, boxes[j].base)) add_dealt_box(steps, *rows, *cols, boxes[j]);
-              else add_box(steps, *rows, *cols, boxes[j]);
-              pairs += (int64_t)rows->kept * cols->kept;
+            const int glo = of_query.front().lo, ghi = of_query.back().hi;
+            pool.clear();
+            const bool joined = b.rad < 0 || b.cols <= (2 * (int64_t)b.rad + 1) * nk;       // (as in window mode)
+            for (int w = 0; w < n_walks; ++w) {
+              const PatchExtent p = extent(w);
+              if (p.ny == 0) continue;
+              const int from = p.y0 - e.qy0, to = from + p.nx - 1;
+              walks[w].runs(joined ? AxisSpan{of_query[from].lo, of_query[to].hi, 0, 1, 0}
+                                   : span_of(pool, from, to, [&](int i) { return of_query[i]; }), ubase - glo);
+              walks[w].pairs += kept_before[to + 1] - kept_before[from];
             }
+            ubase += ghi - glo + 1;
           }
-          const int ns = steps.finish();
-          z.n_wide_steps += ns;
-          if (ns > kMostPatchSteps || z.n_wide_steps > kMostSteps) { g.n_wide = 0; return LITEVAR_OK; }
-          keep_count(ns, pairs);
+        } else {
+          if (!gaps) together.start();
+          for (int w = 0; w < n_walks; ++w) {
+            const PatchExtent p = extent(w);
+            if (p.ny == 0) continue;
+            const int v = w - g.NW, row_stride = v < 0 ? pps : ngy * wny, col_stride = v < 0 ? pps : ngx * wnx;
+            const AxisSpan* rows = v < 0 ? &ax[p.y0 / kPatch] : &wide_rows[gy * wny + v / wnx];
+            const AxisSpan* cols = v < 0 ? &ax[p.x0 / kPatch] : &wide_cols[gx * wnx + v % wnx];
+            if (!gaps) {
+              together.rows[w] = rows; together.row_stride[w] = row_stride;
+              together.cols[w] = cols; together.col_stride[w] = col_stride;
+              continue;
+            }
+            for (int j = 0; j <= k; ++j, rows += row_stride, cols += col_stride)
+              walks[w].box(*rows, *cols, boxes[j], v >= 0 && dealt_box(g.mode, boxes[j].base));
+          }
+          if (!gaps) {
+            for (int j = 0; j <= k; ++j) together.box(boxes[j], wide && dealt_box(g.mode, boxes[j].base));
+            together.close();
+          }
+        }
+        for (int w = 0; w < n_walks; ++w) {
+          const int ns = gaps ? walks[w].steps.finish() : together.steps[w];
+          const int64_t pairs = gaps ? walks[w].pairs : together.pairs[w];
+          if (w < g.NW) {
+            if (ns > kMostPatchSteps) return fail(LITEVAR_E_UNSUPPORTED, "a query patch needs more than 65535 steps");
+            z.n_steps += ns; pairs_hg += pairs;
+          } else {
+            z.n_wide_steps += ns;
+            if (ns > kMostPatchSteps || z.n_wide_steps > kMostSteps) { g.n_wide = 0; return LITEVAR_OK; }
+          }
+          sp.patch_counts.push_back({(uint16_t)ns, (uint8_t)(pairs % kPairsModulus)});
         }
       }
     }

@@ -95,3 +95,93 @@ def test_radius_tables_of_every_number_type(lv):
         assert int(lv.litevar_mask_plan_stats(scales, 0, other).retained_pairs) == want
     with pytest.raises(Exception):
         lv.litevar_mask_plan_stats(scales, 0, [[[-2, 0, 0], [1, 2, 0], [2, 1, 3]]])
+
+
+def _wide_shape(side, h, w):
+    """Rows and columns of a 32-query patch in groups of h x w patches of 16: the least sum of (rows + 6) (columns + 6)."""
+    H, W = min(4 * h, side), min(4 * w, side)
+    best = None
+    for ph in range(1, min(H, 11) + 1):
+        for pw in range(1, min(W, 32 // ph, 12 - ph) + 1):
+            if -(-H // ph) * -(-W // pw) > 8:
+                continue
+            ny = side // H * -(-H // ph) + -(-(side % H) // ph)
+            nx = side // W * -(-W // pw) + -(-(side % W) // pw)
+            key = (ny * nx * (ph + 6) * (pw + 6) * 16 - pw, ph, pw)
+            best = min(best or key, key)
+    return best[1:]
+
+
+def _dealt(lo, hi):
+    """Rows lo .. hi dealt from four strips, the first of which are a row longer."""
+    n = hi - lo + 1
+    strips, at = [], lo
+    for t in range(4):
+        size = n // 4 + (t < n % 4)
+        strips.append(range(at, at + size))
+        at += size
+    return [s[r] for r in range(n // 4 + 1) for s in strips if r < len(s)]
+
+
+def _count_wide(scales, radius, qb, qe, band):
+    steps = 0
+    for k in range(qb, qe):
+        sk = scales[k]
+        parts = ([(0, min(k, 2))] + [(j, j) for j in range(3, k + 1)]) if band else [(j, j) for j in range(k + 1)]
+        pps = (sk + 3) // 4
+        gh = min(((-(-pps // h)) * (-(-pps // min(16 // h, pps))), h + min(16 // h, pps), -h, h) for h in range(1, min(16, pps) + 1))[3]
+        gw = min(16 // gh, pps)
+        if band:
+            groups = [(list(range(a, min(sk * sk, a + 256))), None) for a in range(0, sk * sk, 256)]
+            groups = [(q, [q[i:i + 32] for i in range(0, len(q), 32)]) for q, _ in groups]
+        else:
+            ph, pw = _wide_shape(sk, gh, gw)
+            groups = []
+            for y0 in range(0, sk, 4 * gh):
+                for x0 in range(0, sk, 4 * gw):
+                    ys, xs = list(range(y0, min(sk, y0 + 4 * gh))), list(range(x0, min(sk, x0 + 4 * gw)))
+                    groups.append(([(y, x) for y in ys for x in xs],
+                                   [(ys[a:a + ph], xs[b:b + pw]) for a in range(0, len(ys), ph) for b in range(0, len(xs), pw)]))
+        for queries, patches in groups:
+            keys, keep = [], {}
+            for p, (a, b) in enumerate(parts):
+                n = sum(scales[j] ** 2 for j in range(a, b + 1)) if band else scales[b]
+                iv = {c: _interval(sk * sk if band else sk, n, c, radius) for c in (queries if band else range(sk))}
+                keep[p] = iv
+                if band:
+                    keys += [(p, c) for c in range(iv[queries[0]][0], iv[queries[-1]][1] + 1)]
+                    continue
+                (ya, xa), (yb, xb) = queries[0], queries[-1]
+                rows = (iv[ya][0], iv[yb][1])
+                for y in (_dealt(*rows) if len(keys) >= 192 else range(rows[0], rows[1] + 1)):
+                    keys += [(p, y, x) for x in range(iv[xa][0], iv[xb][1] + 1)]
+            for patch in patches:
+                cnt, first = 0, 0
+                for pos, key in enumerate(keys):
+                    iv = keep[key[0]]
+                    if band:
+                        kept = any(iv[q][0] <= key[1] <= iv[q][1] for q in patch)
+                    else:
+                        kept = any(iv[y][0] <= key[1] <= iv[y][1] for y in patch[0]) and any(iv[x][0] <= key[2] <= iv[x][1] for x in patch[1])
+                    if not kept:
+                        continue
+                    if cnt == 32 or (cnt and pos // 64 - first > 1):
+                        steps, cnt = steps + 1, 0
+                    if cnt == 0:
+                        first = pos // 64
+                    cnt += 1
+                steps += cnt > 0
+    return steps
+
+
+STEP_ADDR, STEP_MASK = 8, 9                      # sections of the blob
+
+
+@pytest.mark.parametrize("band", [False, True])
+@pytest.mark.parametrize("scales,radius,qs", [
+    ((1, 2, 3, 4, 6, 9), 1, (0, 6)), ((2, 17), 0, (0, 2)), ((21, 3, 5), 0, (1, 3)), ((7, 2, 9, 4), -1, (0, 4)), ((1, 2, 13), 40, (2, 3)),
+    ((5, 18), 2, (1, 2)), ((20, 12, 9), 0, (1, 3)), ((6, 10, 16, 23), 4, (2, 4)), ((30, 26), 3, (1, 2))])
+def test_steps_of_the_wide_patches_equal_the_key_by_key_count(lv, scales, radius, qs, band):
+    st = lv.litevar_mask_plan_stats(scales, radius, None, 0, qs, waves_per_group=16, mask_mode=int(band))
+    want = _count_wide(scales, radius, *qs, band)
+    assert int(st.off[STEP_MASK]) - int(st.off[STEP_ADDR]) == 1024 * want
