@@ -43,7 +43,7 @@ def test_waves(scales, H):
 
 @pytest.mark.parametrize("shift", [-76.0, 32.0, 256.0])
 def test_reference_follows_the_scores(shift):
-    """One amount on all scores of a scale (exact in bf16), growing over the scales: sums start far below 2^-40 or pass 2^40."""
+    """One amount on all scores of a scale (exact in bf16), growing over the scales: the first block lies far below zero, or sums pass 2^40."""
     scales = (6, 7, 9, 11)
 
     def tune(q, k):

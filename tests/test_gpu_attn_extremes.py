@@ -87,3 +87,27 @@ def test_small_values_under_low_scores(level):
     q[..., 0], k[..., 0] = 8.0, level
     v = (v.float() * 2.0 ** -115).to(torch.bfloat16)
     _compare(scales, [3] * 3, q, k, v, waves_per_group=WIDE)
+
+
+@pytest.mark.parametrize("first,step", [(-44.0, 4.0), (-44.0, -4.0), (-100.0, 12.0)])
+def test_low_scores_that_rise_or_fall(first, step):
+    """Scores at -63 (-144) in base 2 from the first step on, higher or lower from scale to scale."""
+    scales = (1, 2, 3, 4, 6, 9, 13, 18)
+    q, k, v = workloads.make_qkv(scales, 1, 2, 64, "bf16", 56)
+    q[..., 0] = 8.0
+    at = 0
+    for j, s in enumerate(scales):
+        k[:, :, at:at + s * s, 0] = first + step * j
+        at += s * s
+    _compare(scales, [2] * 8, q, k, v, waves_per_group=WIDE)
+
+
+@pytest.mark.parametrize("band", [False, True])
+@pytest.mark.parametrize("level", [-76.0, -28.0, 60.0])
+def test_queries_that_keep_nothing_in_the_first_step(level, band):
+    """The first key scale has the queries' own side: the queries of a patch's last rows keep none of the first step's 32 keys,
+    while those of its first rows have their reference already."""
+    scales = (20, 20)
+    q, k, v = workloads.make_qkv(scales, 1, 2, 64, "bf16", 57)
+    q[..., 0], k[..., 0] = 8.0, level
+    _compare(scales, [8, 8] if band else [1, 1], q[:, :, 400:].contiguous(), k, v, 0.125, (1, 2), band, waves_per_group=WIDE)
