@@ -97,6 +97,14 @@ def kernel_name(plan, w):
     return "k_attn_f32"
 
 
+def tile_density(plan):
+    """Kept pairs over the pairs that the tiles of the plan's bf16 kernel cover: 32 x 32 for eight waves with 32 queries
+    each, whose steps fill a section of the plan with a kilobyte each, else 32 x 16."""
+    wide = plan.waves_per_group == 16 and plan.patches_per_wave != 1
+    covered = int(plan.off[9]) - int(plan.off[8]) if wide else plan.computed_pairs
+    return round(plan.retained_pairs / covered, 4)
+
+
 def run_workload(name, dense, steps, warmup, layers, tiling, keep_layer0=False):
     """Times `steps` steps (plan build + one attention launch per layer) of one workload;
     returns (result dict, context for the oracle leg)."""
@@ -197,7 +205,7 @@ def run_workload(name, dense, steps, warmup, layers, tiling, keep_layer0=False):
         "bound": "hbm" if t_hbm_us >= t_mfma_us else "mfma",
         "floor_us": round(max(t_hbm_us, t_mfma_us), 2),
         "binding_roofline_frac": round(max(t_hbm_us, t_mfma_us) / kernel_us, 4),
-        "tile_density": round(plan.retained_pairs / plan.computed_pairs, 4),
+        "tile_density": tile_density(plan),
         "retained_pairs_per_bh": int(plan.retained_pairs), "layers": layers, "steps": steps,
         "bytes_per_launch": bytes_layer,
     }
@@ -285,7 +293,7 @@ def run_variants(steps=8, layers=8):
     out.append({"variant": "band_1d_radius_24", "section": "Section 2 step (2)",
                 "attn_us_per_layer": round(t_band, 2), "retained_pairs_per_bh": int(band.retained_pairs),
                 "kernel_tflops_retained": round(256.0 * band.retained_pairs * BH / (t_band * 1e-6) / 1e12, 1),
-                "tile_density": round(band.retained_pairs / band.computed_pairs, 4)})
+                "tile_density": tile_density(band)})
 
     # ---- one radius table per head (Section 2, step (3)): thirty heads, radii 2..4 per part
     rng = np.random.default_rng(7)

@@ -129,10 +129,11 @@ typedef struct litevar_plan {
   int32_t n_groups;         /* workgroup tiles per (batch, head) */
   int32_t n_patches;        /* 4x4 query patches per (batch, head) */
   int32_t tiling_chosen;    /* 1: the options asked for waves_per_group, chunk_keys or prefetch_chunks */
-  int64_t n_steps;          /* 32-key MFMA steps per (batch, head) */
+  int64_t n_steps;          /* steps of 32 keys and 16 queries per (batch, head); a bf16 launch of eight waves with
+                               32 queries each has a list of its own over the same pairs */
   int64_t n_union_keys;     /* keys staged through LDS per (batch, head), padded */
   int64_t retained_pairs;   /* allowed (query, key) pairs per (batch, head) */
-  int64_t computed_pairs;   /* 16 * 32 * n_steps: pairs the MFMA tiles cover */
+  int64_t computed_pairs;   /* 16 * 32 * n_steps: pairs that the tiles of these steps cover */
   uint64_t off[12];         /* byte offsets of the blob's sections (private) */
   int32_t scales[LITEVAR_MAX_SCALES];
   int32_t radii[LITEVAR_MAX_SCALES];   /* per key scale: the widest radius over the plan's query scales */
@@ -233,8 +234,9 @@ litevar_status litevar_window_table_export(const litevar_plan* plan, int32_t hea
 
 /*
  * What the work-list encodes (Section 2: the kept pairs of every part), as a dense byte mask
- * of head `head`: d_mask is DEVICE uint8 [q_len][kv_len], 1 = kept pair.  Written from the per-wave steps the attention
- * kernel consumes (not from the window table).  d_pair_count: optional DEVICE
+ * of head `head`: d_mask is DEVICE uint8 [q_len][kv_len], 1 = kept pair.  Written from the plan's steps of 16 queries
+ * (not from the window table), which are what every kernel walks but the bf16 kernel of eight waves with 32 queries
+ * each: its own list holds the same pairs, as the builder checks patch by patch.  d_pair_count: optional DEVICE
  * uint64[1], receives the number of (query, key) entries in the work-list, which
  * equals the mask's popcount iff no pair is listed twice.
  */

@@ -303,7 +303,6 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
   // vector memory operation: behind the burst of first chunks of all workgroups a scalar
   // miss would take microseconds, and the vector loads below depend on these values.
   // Patch descriptor words: {step_begin, n_steps, q_base, sk | ny << 16, nx | kq << 16, pairs, valid, first_ends}
-  // (two patches per wave: p and its partner two patch rows below, columns swapped)
   // (wide patches: {.., nx | kq << 16, ceil(65536 / nx), ..})
   constexpr int kPerGroup = kGroupPatches / PW;          // patches of the list that this form walks
   const WaveDesc* const patches = (WIDE ? wide.waves : a.waves) + grp_g * kPerGroup;
