@@ -249,7 +249,7 @@ struct GroupWalk {
   v8u closed[kMost];                                     // steps since `steps` was brought up to date
   v8s row_lo[kMost], row_n[kMost], col_lo[kMost], col_w[kMost], before[kMost];
   int steps[8 * kMost]; int64_t pairs[8 * kMost];
-  const AxisSpan *rows[8 * kMost], *cols[8 * kMost];     // of key scale 0; the next scales' are a stride away
+  const AxisSpan *rows[8 * kMost], *cols[8 * kMost];     // of key scale 0; scale j's are j strides away
   int row_stride[8 * kMost], col_stride[8 * kMost];
   std::vector<v8s> dealt_rows;                           // by place: the wide patches' rows before it, and whether its row is theirs
   int pending = -1;                                      // block whose keys are in n
@@ -276,14 +276,13 @@ struct GroupWalk {
       n[v] = v8s{};
     }
   }
-  // the group's box in the next key scale
-  void box(const ListBox& b, bool dealt) {
+  // the group's box in key scale j
+  void box(int j, const ListBox& b, bool dealt) {
     for (int l = 0; l < 8 * n_vec; ++l) {
-      const AxisSpan &r = *rows[l], &c = *cols[l];
+      const AxisSpan &r = rows[l][j * row_stride[l]], &c = cols[l][j * col_stride[l]];
       row_lo[l >> 3][l & 7] = (short)(r.lo - b.ylo); row_n[l >> 3][l & 7] = (short)(r.hi - r.lo + 1);
       col_lo[l >> 3][l & 7] = (short)(c.lo - b.xlo); col_w[l >> 3][l & 7] = (short)(c.hi - c.lo + 1);
       pairs[l] += (int64_t)r.kept * c.kept;
-      rows[l] += row_stride[l]; cols[l] += col_stride[l];
     }
     if (dealt) {
       const int v = first_wide;
@@ -479,7 +478,7 @@ static litevar_status size_plan_uncached(PlanSpec& sp, PlanSizes& z) {
               walks[w].box(*rows, *cols, boxes[j], v >= 0 && dealt_box(g.mode, boxes[j].base));
           }
           if (!gaps) {
-            for (int j = 0; j <= k; ++j) together.box(boxes[j], wide && dealt_box(g.mode, boxes[j].base));
+            for (int j = 0; j <= k; ++j) together.box(j, boxes[j], wide && dealt_box(g.mode, boxes[j].base));
             together.close();
           }
         }
