@@ -1,6 +1,6 @@
 """The 16-patch kernel's wide patches (32 queries per wave): shapes that tile sides of every remainder, both mask
 modes, the order in which boxes are dealt, the moving softmax reference and operands that are not finite, against the
-fp64 oracle (tolerance 2e-2: P and O are rounded to bf16) and against the sixteen-wave form on the same plan."""
+fp64 oracle (tolerance 2e-2: P and O are rounded to bf16) and against the sixteen-wave form of the same mask."""
 import numpy as np
 import pytest
 import torch

@@ -1,5 +1,6 @@
-"""Plans around the size up to which the places of patches and groups travel with the builder's launch: every head's
-work-list against the oracle's mask, for the largest plan that fits and the smallest that is counted on the device."""
+"""Plans around the sizes up to which the places of patches and groups travel with the filling launch (158, 113 and 52
+groups of 4, 8 and 16 patches) and with one launch ahead of it (66 of 16): every head's work-list against the oracle's
+mask, for the largest plan that fits and the smallest that does not."""
 import numpy as np
 import pytest
 import torch
@@ -8,7 +9,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("waves,side,tables", [(4, 13, 38), (4, 13, 39), (8, 13, 54), (8, 13, 55), (16, 16, 51), (16, 16, 52),
-                                               (16, 1, 1), (4, 1, 153), (4, 1, 154)])
+                                               (16, 1, 1), (4, 1, 153), (4, 1, 154), (4, 13, 40), (4, 1, 158), (4, 1, 159),
+                                               (8, 13, 56), (8, 13, 57), (16, 16, 53), (16, 16, 66), (16, 16, 67)])
 def test_places(waves, side, tables):
     import oracle
     import paper_2411_17178_amd as lv
