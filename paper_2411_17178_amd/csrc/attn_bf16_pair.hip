@@ -4,7 +4,7 @@
 //
 // One workgroup = eight waves = one group of up to 16 x 16 queries of one scale of one (batch, head), which its
 // wide patches tile: every wave owns 32 queries (4 x 8, or whatever covers the group best) and one eighth of the
-// loading.  (A second form, sixteen waves with a patch of 16 queries each, serves plans that ask for it.)
+// loading.  (A second form, sixteen waves with a patch of 16 queries each, serves plans without wide patches.)
 //
 // Why 32 queries per wave: what bounds a step is the vector issue of its SIMD, four waves of which run steps at the same
 // time, and its own chain of latencies.  A step of 32 keys costs 69 vector and 9 matrix instructions for 32 queries
@@ -176,8 +176,9 @@ struct StepKeys {
 }  // namespace
 
 // PW = 2: a wide patch, 32 queries, per wave (8 waves per workgroup, two workgroups per CU); PW = 1: a patch of 16
-// queries per wave (16 waves per workgroup, one workgroup per CU).  Same plan, same phases, each its own steps and, where
-// boxes are dealt, its own order of the key list; with 16 waves the loading duty of a chunk is one K or one V transfer per wave.
+// queries per wave (16 waves per workgroup, one workgroup per CU).  A plan is laid out for one of them: the
+// steps and the order of the key list are that form's; with 16 waves the loading duty of a chunk is one K or one V transfer
+// per wave.
 //
 // Q8 (Section 4, 8-bit Q, K, V): the operands are int8 codes with one (scale, zero point) per
 // token row.  A wave's share of a chunk then comes through registers instead of LDS-DMA: one
