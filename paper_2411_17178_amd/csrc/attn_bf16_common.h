@@ -23,9 +23,11 @@ typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
 
 constexpr float kFloor = -1.0e30f;   // initial softmax reference: keeps exp2 arguments finite
 constexpr float kSlack = 6.0f;       // base-2 exponent by which a score may exceed the reference
-// Row sums outside move the reference of the windowed 32-query kernel.  Below 1 the products with V would lose bits of values
-// near the smallest normal ones; above, they may overflow, which ends in attend_row.
-constexpr float kMostSum = 0x1p40f, kLeastSum = 1.f;
+// Row sums outside move the reference of the windowed 32-query kernel.  From 2^-10 on, products with the smallest normal V
+// keep 13 bits above fp32's smallest subnormal; above 2^40 they may overflow, which ends in attend_row.  (A move leaves a sum
+// of at least 2^-0.5.  At 1 as the lower end, rows of one large probability moved in every step: 2240 tokens, 288 pairs,
+// scores of mean -24 and standard deviation 6 159 -> 218 us; 164 with a reference that moves once.)
+constexpr float kMostSum = 0x1p40f, kLeastSum = 0x1p-10f;
 
 __device__ inline bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 

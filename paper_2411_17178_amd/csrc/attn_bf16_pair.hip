@@ -566,9 +566,9 @@ void k_attn_bf16_pair(AttnArgs a, WideArgs wide, float c) {
   //  * The row sums are the lane's own (v_dot2 on the rounded probabilities; a product with ones would need
   //    sixteen more registers).
   //  * No maximum is formed.  The softmax reference starts at zero and moves only when a query's sum leaves
-  //    [1, 2^40] (the lower end is looked at until every query has passed it), which costs one comparison
+  //    [2^-10, 2^40] (the lower end is looked at until every query has passed it), which costs one comparison
   //    where the maximum of sixteen scores costs eight.  Probabilities and sums keep their relative precision
-  //    under any common factor, and the factors are powers of two; the products with V do from sums of 1 on.
+  //    under any common factor, and the factors are powers of two; the products with V do from sums of 2^-10 on.
   [[maybe_unused]] auto run_step32 = [&](auto& ps, const u32x4 cur) {
     constexpr int kRingBytes = R * kRingRowBytes;
     u32x4 kr[4];

@@ -79,13 +79,14 @@ def test_large_values_under_rising_scores(form):
     _compare(scales, [-1 if form == "dense" else 3] * 4, q, k, v, **({"waves_per_group": WIDE} if form == "wide" else {}))
 
 
-@pytest.mark.parametrize("level", [-26.0, -20.0, -3.0])
-def test_small_values_under_low_scores(level):
+@pytest.mark.parametrize("level", [-26.0, -20.0, -10.0, -3.0])
+@pytest.mark.parametrize("exponent", [-115, -122])
+def test_small_values_under_low_scores(exponent, level):
     """Values of about 2^-115 under probabilities of 2^-37 would lose their bits in the products."""
     scales = (3, 5, 20)
     q, k, v = workloads.make_qkv(scales, 1, 2, 64, "bf16", 53)
     q[..., 0], k[..., 0] = 8.0, level
-    v = (v.float() * 2.0 ** -115).to(torch.bfloat16)
+    v = (v.float() * 2.0 ** exponent).to(torch.bfloat16)
     _compare(scales, [3] * 3, q, k, v, waves_per_group=WIDE)
 
 

@@ -55,7 +55,7 @@ def test_every_patch_shape(lv, scales, rad, band):
 @pytest.mark.parametrize("shift", [-90.0, 0.0, 300.0])
 def test_reference_follows_the_scores(lv, shift):
     """All scores of a query moved by one amount (in units of the exponent): the result does not change, although sums
-    start below 1, at 2^-11, or leave 2^40 on the way.  The amount grows over the scales, so that it keeps moving.
+    start below 2^-10, at 2^-11, or leave 2^40 on the way.  The amount grows over the scales, so that it keeps moving.
     Bound: the score is a sum of products of about |shift|, so the softmax weights carry 2^-9 |shift| / 8 of K's
     rounding at most; K's component is a power of two here, exact in bf16, and the bound is the usual one."""
     scales = (1, 2, 3, 4, 6, 9, 13, 18)
