@@ -34,3 +34,39 @@ def test_places(waves, side, tables):
         total += int(mask.sum())
     header = plan.blob[:256].cpu().numpy().view(np.int64)
     assert total == int(plan.retained_pairs) == int(header[6]) and int(header[3]) == plan.n_steps
+
+
+@pytest.mark.parametrize("tables", [3, 70])                    # places with the filling launch, and in two launches ahead of it
+def test_builds_replay(tables):
+    """A captured build and call: every replay lays the plan out anew over what the eager work between left in its buffer."""
+    import paper_2411_17178_amd as lv
+    scales, K = (2, 5, 16), 3
+    rad = [[[h % 3, h // 3 % 5, h // 15]] * K for h in range(tables)]
+    n = lv.litevar_mask_plan_bytes(scales, 1, rad, 0, (2, 3), waves_per_group=16)
+    blob = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    q, k, v = (torch.randn((1, tables, m, 64), device="cuda", dtype=torch.bfloat16) for m in (256, 285, 285))
+    out = torch.zeros_like(q)
+
+    def work(stream=None):
+        plan = lv.litevar_mask_build(scales, 1, rad, 0, (2, 3), waves_per_group=16, blob=blob, stream=stream)
+        lv.litevar_windowed_attn_fwd(plan, q, k, v, 0.125, out=out, stream=stream)
+        return plan
+    plan = work()
+    lv.litevar_plan_check(plan)
+    eager, laid_out = out.clone(), blob.clone()
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        plan = work(side)
+    for rep in range(3):
+        out.fill_(float(rep))
+        blob.fill_(0xff)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        lv.litevar_plan_check(plan)
+        assert torch.equal(out, eager)
+        used = torch.zeros(n, dtype=torch.bool, device="cuda")
+        for i in range(4, 11):                                 # the sections that a plan fills whole, but for their padding
+            used[int(plan.off[i]):int(plan.off[i + 1]) // 256 * 256 - 255] = True
+        assert int(used.sum()) > n // 2 and torch.equal(blob[used], laid_out[used])
